@@ -67,7 +67,8 @@ enum {
 /* Execution parameters (the part of the layer-wise representation that the paper leaves to tuning,
  * section 2.3.1).  A zero field means "let the library choose". */
 typedef struct {
-    int32_t variant;        /* 0 auto; 1 generic kernel (any layer); 2 tiled pattern-specialised kernel (3x3, stride 1, no
+    int32_t variant;        /* 0 auto; 1 generic (any layer: binary32 as a dense product on the binary32 matrix
+                               cores, otherwise one lane per output); 2 tiled pattern-specialised kernel (3x3, stride 1, no
                                fused pool; masks outside its sixteen run as covers of those with zero weights); 3 matrix-core kernel (binary16 storage only: the pruned
                                weights zero-filled to a dense matrix and multiplied on the MFMA units -- the measured
                                alternative to pattern-specialised vector code; any pattern table, kernel size, stride) */

@@ -9,6 +9,7 @@
 #include "k1_tiled.hpp"
 #include "k2_mfma.hpp"
 #include "k3_mfma_direct.hpp"
+#include "k5_f32.hpp"
 #include "block_plan.hpp"
 #include "plan.hpp"
 #include "pp_block_gemm.h"
@@ -65,8 +66,8 @@ k1_launch_fn k1_lookup(int dtype, int np, int r, int f, int lw, bool direct) {
 // Generic kernel: any pattern table, kernel size, stride, with or without the fused 2x2 max-pool.
 // One lane per stored output, one filter per blockIdx.y; walks the filter's reordered kernel list
 // (same-pattern kernels consecutive) with wave-uniform indices and reads the input straight from
-// global memory with bounds checks.  It is the correctness path for layers the fast kernels do not
-// take, not a fast path.
+// global memory with bounds checks.  It serves binary16 plans that ask for it and binary32 images
+// beyond the matrix-core kernel's 31-bit offsets.
 struct K0Args {
     const void* x;
     void* y;
@@ -193,6 +194,9 @@ struct pp_conv_plan {
     float* d_ws3 = nullptr;                   // their workspace: [ksplit][n_hint][c_out][h][w] binary32
     pp_block_gemm_plan_t* pointwise = nullptr; // a 1x1 stride-1 layer in binary16 runs as a batch of matrix products (one per image)
     _Float16* d_xpad = nullptr;               // x with zero channels appended up to whole chunks of 16: [n_hint][cpad][h][w]
+    // binary32 matrix-core kernel
+    float* d_w32 = nullptr;
+    float* d_bias32 = nullptr;
     // generic kernel
     int32_t* d_filt_off = nullptr;
     int32_t* d_kidx = nullptr;
@@ -217,7 +221,7 @@ bool upload(T** dst, const void* src, size_t bytes) {
 }
 
 void free_device(pp_conv_plan_t* p) {
-    void* bufs[] = {p->d_xpad, p->d_ws3, p->d_stream, p->d_wave_off, p->d_chan_map, p->d_ws, p->d_counters, p->d_perm_pad, p->d_bias_pad, p->d_wpk, p->d_bias_mfma, p->d_filt_off, p->d_kidx,
+    void* bufs[] = {p->d_w32, p->d_bias32, p->d_xpad, p->d_ws3, p->d_stream, p->d_wave_off, p->d_chan_map, p->d_ws, p->d_counters, p->d_perm_pad, p->d_bias_pad, p->d_wpk, p->d_bias_mfma, p->d_filt_off, p->d_kidx,
                     p->d_kpat,   p->d_w,        p->d_tap,      p->d_perm,     p->d_bias};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -461,6 +465,9 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
                  hipMemset(p->d_xpad, 0, (size_t)std::max(1, hp.n_hint) * hp.ml.cpad * hp.h * hp.w * 2) == hipSuccess;
         if (hp.ml.direct && hp.ml.ksplit > 1)   // the shares' partial sums, for up to n_hint images
             ok = ok && upload(&p->d_ws3, nullptr, (size_t)hp.ml.ksplit * std::max(1, hp.n_hint) * hp.c_out * hp.h * hp.w * 4);
+    } else if (hp.dense32) {
+        ok = ok && upload(&p->d_w32, hp.fl.wpk.data(), hp.fl.wpk.size() * 4);
+        ok = ok && upload(&p->d_bias32, hp.fl.bias_pad.data(), hp.fl.bias_pad.size() * 4);
     } else {
         const Canonical& cn = hp.canon;
         std::vector<float> w = cn.wpacked;
@@ -562,6 +569,35 @@ static pp_status_t check_run_args(const pp_conv_plan_t* plan, const void* x_dev,
     if (xa < ye && ya < xe) return PP_ERR_ALIGN;
     if (!plan->on_device) return PP_ERR_UNSUPPORTED;
     return PP_OK;
+}
+
+// One launch of the binary32 matrix-core kernel.
+static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream) {
+    const HostPlan& hp = plan->hp;
+    const F32Layout& fl = hp.fl;
+    K5ConvArgs a{};
+    a.x = static_cast<const float*>(x_dev);
+    a.y = static_cast<float*>(y_dev);
+    a.wpk = plan->d_w32;
+    a.bias = plan->d_bias32;
+    a.n = n, a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w = hp.w, a.ho = hp.ho, a.wo = hp.wo, a.out_h = hp.out_h, a.out_w = hp.out_w;
+    a.ks = hp.ks, a.stride = hp.stride, a.pool = hp.pool ? 1 : 0, a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
+    a.groups = fl.groups, a.units = fl.units;
+    const int64_t pix = (int64_t)n * hp.ho * hp.wo;
+    const int rows32 = (hp.c_out + 31) / 32;
+    const K5Shape sh = k5_pick_conv(rows32, pix, fl.units);
+    const int64_t per_wg = (int64_t)32 * sh.nt * sh.wp;
+    const int64_t ptiles = (pix + per_wg - 1) / per_wg;
+    a.ftiles = (rows32 + sh.mt - 1) / sh.mt;
+    // pixel indices past the last one are formed in 32 bits
+    if (pix + per_wg >= ((int64_t)1 << 31) || ptiles * a.ftiles >= ((int64_t)1 << 28)) return PP_ERR_SHAPE;
+    a.pix = (int32_t)pix, a.ptiles = (int32_t)ptiles, a.items = (int32_t)(ptiles * a.ftiles), a.per_xcd = (a.items + 7) / 8;
+    a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 4;
+    const k5_conv_fn fn = k5_conv_lookup(sh);
+    if (!fn) return PP_ERR_UNSUPPORTED;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(fn, dim3((unsigned)(a.per_xcd * 8)), dim3((unsigned)(64 * sh.wk * sh.wp)), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
 static pp_status_t launch_generic(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream) {
@@ -754,6 +790,7 @@ pp_status_t pp_conv_run(const pp_conv_plan_t* plan, const void* x_dev, void* y_d
     const int64_t hw = (int64_t)hp.h * hp.w;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (hp.mfma) return launch_mfma(plan, x_dev, y_dev, n, stream);
+    if (hp.dense32) return launch_f32(plan, x_dev, y_dev, n, stream);
     if (!hp.tiled) return launch_generic(plan, x_dev, y_dev, n, stream);
     // A plan that splits channels across workgroups owns a workspace for n_hint images: larger
     // batches go through it n_hint images at a time.
@@ -776,6 +813,7 @@ pp_status_t pp_conv_run_static(const pp_conv_plan_t* plan, const void* x_dev, vo
     const HostPlan& hp = plan->hp;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (hp.mfma) return launch_mfma(plan, x_dev, y_dev, n, stream, false);      // no reduction split: that needs the plan's workspace
+    if (hp.dense32) return launch_f32(plan, x_dev, y_dev, n, stream);
     if (!hp.tiled) return launch_generic(plan, x_dev, y_dev, n, stream);
     const TiledLayout& tl = hp.tl;
     if (tl.sw <= 1) return launch_tiled(plan, x_dev, y_dev, n, stream, nullptr, nullptr);

@@ -95,16 +95,16 @@ uint16_t f32_to_f16_rne(float v) {
 }
 
 float f16_to_f32(uint16_t b) {
-    uint32_t sign = (uint32_t)(b & 0x8000u) << 16;
-    int e = (b >> 10) & 31;
-    uint32_t m = b & 1023u;
-    float v;
-    if (e == 0) v = std::ldexp((float)m, -24);
-    else if (e == 31) v = m ? NAN : INFINITY;
-    else v = std::ldexp(1.0f + (float)m / 1024.0f, e - 15);
+    const uint32_t sign = (uint32_t)(b & 0x8000u) << 16, e = (b >> 10) & 31u, m = b & 1023u;
     uint32_t u;
-    std::memcpy(&u, &v, 4);
+    if (e == 0) {
+        const float v = (float)m * 0x1p-24f;
+        std::memcpy(&u, &v, 4);
+    } else {
+        u = e == 31 ? 0x7F800000u | (m ? 0x400000u : 0u) : ((e + 112u) << 23) | (m << 13);
+    }
     u |= sign;
+    float v;
     std::memcpy(&v, &u, 4);
     return v;
 }
@@ -330,7 +330,17 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     hp.chosen.variant = variant;
     if (t.split_k < 0 || (t.split_k > 1 && variant != 3)) return PP_ERR_UNSUPPORTED;
     if (variant == 3) return build_mfma_layout(t, hp);
-    if (!hp.tiled) return PP_OK;
+    if (!hp.tiled) {
+        // The binary32 layers the tiled kernel has no code for run as dense products on the binary32 matrix cores: a
+        // bottleneck block (1x1, strided 3x3, 1x1; 256-128-512 channels, 56x56 maps, batch 8) took 1574 us with one lane per output.
+        // That kernel stays for binary16 storage on request and for images that a 31-bit byte offset does not span.
+        const int64_t images = 64 / ((int64_t)hp.ho * hp.wo) + 2;       // that the 64 pixels of a wavefront can touch
+        if (hp.dtype == PP_F32 && images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31)) {
+            hp.dense32 = true;
+            build_f32_layout(hp);
+        }
+        return PP_OK;
+    }
 
     TiledLayout& tl = hp.tl;
     tl.covered = covered;
@@ -850,6 +860,36 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         }
     }
     return PP_OK;
+}
+
+// Binary32 matrix-core operands: unit (tap, g) of a 32-filter tile multiplies channels 8 g .. 8 g + 7 at one tap with four
+// MFMAs, the p-th on the two channels from min(8 g + 2 p, c_in - 2) on.  A channel's weight sits in the first pair that holds
+// it; what the pairs past the end hold again is zero.
+void build_f32_layout(HostPlan& hp) {
+    F32Layout& fl = hp.fl;
+    const int KK = hp.ks * hp.ks;
+    fl.groups = (hp.c_in + 7) / 8;
+    fl.units = KK * fl.groups;
+    fl.tiles = (hp.c_out + 63) / 64 * 2;
+    fl.wpk.assign(((size_t)fl.tiles * fl.units + kF32Pad) * 256, 0.0f);
+    fl.bias_pad.assign((size_t)fl.tiles * 32, 0.0f);
+    std::copy(hp.bias.begin(), hp.bias.end(), fl.bias_pad.begin());
+    const Canonical& cn = hp.canon;
+    const int last_pair = std::max(hp.c_in - 2, 0);
+    std::vector<std::vector<int>> taps(hp.num_patterns);
+    for (int p = 0; p < hp.num_patterns; ++p)
+        for (int tp = 0; tp < KK; ++tp)
+            if ((hp.masks[p] >> tp) & 1u) taps[p].push_back(tp);
+    for (int pos = 0; pos < hp.c_out; ++pos) {
+        const int co = cn.perm[pos], row = co % 32;
+        for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
+            const int ci = cn.kidx[e], g = ci / 8, p = ci % 8 / 2, half = ci - std::min(ci / 2 * 2, last_pair);
+            const size_t at = (size_t)(row + 32 * half) * 4 + p;
+            const std::vector<int>& tl = taps[cn.kpat[e]];
+            for (int j = 0; j < hp.taps; ++j)
+                fl.wpk[((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at] = cn.wpacked[(size_t)e * hp.taps + j];
+        }
+    }
 }
 
 pp_status_t unpack_stream(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, float* w) {

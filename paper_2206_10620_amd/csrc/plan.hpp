@@ -68,6 +68,14 @@ struct MfmaLayout {
     std::vector<float> bias_pad;      // [fb*64]
 };
 
+constexpr int kF32Pad = 4;                  // units the kernel may load past the end
+// Binary32 matrix-core kernel: the zero-filled dense weights in operand order.
+struct F32Layout {
+    int groups = 0, units = 0, tiles = 0;   // groups of eight channels, ks * ks * groups, 32-filter tiles (rounded up to an even number)
+    std::vector<float> wpk;                 // [tiles][units][64][4], and kF32Pad units of zeros behind them
+    std::vector<float> bias_pad;            // [tiles * 32]
+};
+
 struct HostPlan {
     int32_t c_in = 0, c_out = 0, h = 0, w = 0, n_hint = 1, num_patterns = 0, taps = 4;
     int32_t ks = 3, stride = 1;         // kernel size, stride
@@ -84,6 +92,8 @@ struct HostPlan {
     TiledLayout tl;
     bool mfma = false;
     MfmaLayout ml;
+    bool dense32 = false;               // binary32 layer that runs on the matrix cores
+    F32Layout fl;
     // generic kernel tables
     std::vector<int32_t> filt_off;      // [c_out+1] prefix of kcount
     std::vector<int8_t> tap_dyx;        // [P*taps*2] (dy, dx) per tap
@@ -99,6 +109,8 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp);
 // Choose the matrix-core kernel's tile and pack its weights (hp.ml).  PP_ERR_UNSUPPORTED if the layer
 // or the tuning request does not fit.
 pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp);
+// Pack the weights of a binary32 layer for the matrix-core kernel (hp.fl).
+void build_f32_layout(HostPlan& hp);
 // Decode tl.stream back to canonical order.
 pp_status_t unpack_stream(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, float* w);
 
