@@ -47,7 +47,7 @@ typedef struct {
     const float *bias;         /* [m], or NULL */
     uint32_t flags;            /* PP_FLAG_RELU, PP_FLAG_HOST_ONLY */
     int32_t dtype;             /* pp_dtype_t: storage of x, y and the packed weights; products accumulate in fp32 */
-    int32_t variant;           /* 0 auto; 1 generic kernel (any dtype, any n); 2 matrix-core kernel (PP_F16) */
+    int32_t variant;           /* 0 auto; 1 any dtype, any n (PP_F32 on the binary32 matrix cores); 2 matrix-core kernel (PP_F16) */
 } pp_block_gemm_desc_t;
 
 /* Build a plan.  Validation comes before any device call; on error *out_plan is NULL.  Unless

@@ -6,16 +6,18 @@
 
 #include "block_plan.hpp"
 #include "k4_block_gemm.hpp"
+#include "k5_f32.hpp"
 
 struct pp_block_gemm_plan {
     ppc::BlockHostPlan hp;
     bool on_device = false;
     void* d_apk = nullptr;
-    float* d_wc = nullptr;
     float* d_bias = nullptr;
     int32_t* d_tile_off = nullptr;
     int32_t* d_tile_cols = nullptr;
-    int32_t* d_tile_len = nullptr;
+    float* d_wpk32 = nullptr;
+    int32_t* d_list32 = nullptr;
+    int32_t* d_group_off32 = nullptr;
 };
 
 namespace {
@@ -33,7 +35,7 @@ bool put(T** dst, const void* src, size_t bytes, size_t pad_bytes = 0) {
 }
 
 void release(pp_block_gemm_plan_t* p) {
-    void* bufs[] = {p->d_apk, p->d_wc, p->d_bias, p->d_tile_off, p->d_tile_cols, p->d_tile_len};
+    void* bufs[] = {p->d_apk, p->d_bias, p->d_tile_off, p->d_tile_cols, p->d_wpk32, p->d_list32, p->d_group_off32};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
 }
@@ -64,6 +66,28 @@ pp_status_t pp_block_gemm_launch_batched(const pp_block_gemm_plan_t* plan, const
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
+// Binary32 on the matrix cores.  PP_ERR_UNSUPPORTED if x does not fit 31-bit byte offsets.
+static pp_status_t launch_list_f32(const pp_block_gemm_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream) {
+    const BlockHostPlan& hp = plan->hp;
+    K5ListArgs a{};
+    a.x_bytes = (int64_t)hp.k * n * 4;
+    if (a.x_bytes >= ((int64_t)1 << 31)) return PP_ERR_UNSUPPORTED;
+    a.x = static_cast<const float*>(x_dev), a.y = static_cast<float*>(y_dev);
+    a.wpk = plan->d_wpk32, a.bias = plan->d_bias, a.list = plan->d_list32, a.group_off = plan->d_group_off32;
+    a.m = hp.m, a.n = n, a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
+    a.row_tiles = (hp.m + kBlockRow32 - 1) / kBlockRow32;
+    const K5Shape sh = k5_pick_list(a.row_tiles, n, hp.group_off32.back() / a.row_tiles);
+    a.col_tiles = (n + 32 * sh.nt - 1) / (32 * sh.nt);
+    const int64_t items = (int64_t)a.row_tiles * a.col_tiles;
+    if (items >= ((int64_t)1 << 28)) return PP_ERR_UNSUPPORTED;
+    a.items = (int32_t)items, a.per_xcd = (a.items + 7) / 8;
+    const k5_list_fn fn = k5_list_lookup(sh);
+    if (!fn) return PP_ERR_UNSUPPORTED;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(fn, dim3((unsigned)(a.per_xcd * 8)), dim3((unsigned)(64 * sh.wk)), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
+}
+
 extern "C" {
 
 pp_status_t pp_block_gemm_plan(const pp_block_gemm_desc_t* desc, pp_block_gemm_plan_t** out_plan) {
@@ -83,12 +107,15 @@ pp_status_t pp_block_gemm_plan(const pp_block_gemm_desc_t* desc, pp_block_gemm_p
     }
     if (!(desc->flags & PP_FLAG_HOST_ONLY)) {
         const BlockHostPlan& hp = p->hp;
-        bool ok = put(&p->d_wc, hp.wc.data(), hp.wc.size() * sizeof(float));
-        ok = ok && put(&p->d_apk, hp.apk.data(), hp.apk.size() * sizeof(uint16_t));
+        bool ok = put(&p->d_apk, hp.apk.data(), hp.apk.size() * sizeof(uint16_t));
         ok = ok && put(&p->d_bias, hp.bias.data(), hp.bias.size() * sizeof(float));
         ok = ok && put(&p->d_tile_off, hp.tile_off.data(), hp.tile_off.size() * sizeof(int32_t));
         ok = ok && put(&p->d_tile_cols, hp.tile_cols.data(), hp.tile_cols.size() * sizeof(int32_t), kBlockChunk * sizeof(int32_t));   // the kernel reads one chunk ahead
-        ok = ok && put(&p->d_tile_len, hp.tile_len.data(), hp.tile_len.size() * sizeof(int32_t));
+        if (!hp.wpk32.empty()) {
+            ok = ok && put(&p->d_wpk32, hp.wpk32.data(), hp.wpk32.size() * sizeof(float));
+            ok = ok && put(&p->d_list32, hp.list32.data(), hp.list32.size() * sizeof(int32_t));
+            ok = ok && put(&p->d_group_off32, hp.group_off32.data(), hp.group_off32.size() * sizeof(int32_t));
+        }
         if (!ok) {
             (void)hipGetLastError();
             release(p);
@@ -120,15 +147,20 @@ pp_status_t pp_block_gemm_run(const pp_block_gemm_plan_t* plan, const void* x_de
     const int relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
     (void)hipGetLastError();
     if (variant == 2) return pp_block_gemm_launch_batched(plan, x_dev, y_dev, n, 1, 0, 0, hip_stream);
+    if (hp.dtype == PP_F32) {
+        const pp_status_t st = launch_list_f32(plan, x_dev, y_dev, n, stream);
+        if (st != PP_ERR_UNSUPPORTED) return st;
+    }
     {
-        const dim3 grid((unsigned)((n + 63) / 64), (unsigned)hp.row_tiles), block(64, 4);
-        if (hp.row_tiles > 65535) return PP_ERR_SHAPE;
+        const int tiles = (hp.m + kBlockRow32 - 1) / kBlockRow32;
+        const dim3 grid((unsigned)((n + 63) / 64), (unsigned)tiles), block(64, 4);
+        if (tiles > 65535) return PP_ERR_SHAPE;
         if (hp.dtype == PP_F16)
             hipLaunchKernelGGL(k4_generic<_Float16>, grid, block, 0, stream, static_cast<const _Float16*>(x_dev), static_cast<_Float16*>(y_dev),
-                               plan->d_wc, plan->d_bias, plan->d_tile_off, plan->d_tile_cols, plan->d_tile_len, hp.m, n, relu);
+                               plan->d_wpk32, plan->d_bias, plan->d_group_off32, plan->d_list32, hp.m, n, relu);
         else
-            hipLaunchKernelGGL(k4_generic<float>, grid, block, 0, stream, static_cast<const float*>(x_dev), static_cast<float*>(y_dev), plan->d_wc,
-                               plan->d_bias, plan->d_tile_off, plan->d_tile_cols, plan->d_tile_len, hp.m, n, relu);
+            hipLaunchKernelGGL(k4_generic<float>, grid, block, 0, stream, static_cast<const float*>(x_dev), static_cast<float*>(y_dev), plan->d_wpk32,
+                               plan->d_bias, plan->d_group_off32, plan->d_list32, hp.m, n, relu);
     }
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }

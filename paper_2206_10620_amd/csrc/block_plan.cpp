@@ -62,28 +62,64 @@ pp_status_t build_block_plan(const pp_block_gemm_desc_t& d, BlockHostPlan& p) {
     p.executed_weights = (int64_t)p.tile_cols.size() * RT;
 
     const bool half = d.dtype == PP_F16;
-    auto value = [&](int r, int c) -> float {      // Wd[r][c], as the kernels will see it
-        if (r >= d.m || !row_kept(r, c / d.block_k) || !col_kept(r / d.block_m, c)) return 0.0f;
-        const float v = d.weights[(int64_t)r * d.k + c];
-        return half ? f16_to_f32(f32_to_f16_rne(v)) : v;
-    };
-    p.wc.assign(p.tile_cols.size() * (size_t)RT, 0.0f);
-    for (int t = 0; t < p.row_tiles; ++t)
-        for (int i = 0; i < p.tile_len[t]; ++i) {
-            const size_t at = (size_t)p.tile_off[t] + i;
-            for (int r = 0; r < RT; ++r) p.wc[at * RT + r] = value(t * RT + r, p.tile_cols[at]);
-        }
-    p.apk.clear();
-    if (half) {
-        p.apk.assign(p.tile_cols.size() * (size_t)RT, 0);
-        for (int t = 0; t < p.row_tiles; ++t)
-            for (int i = 0; i < p.tile_len[t]; ++i) {
-                const size_t at = (size_t)p.tile_off[t] + i, chunk = at / kBlockChunk, kk = at % kBlockChunk;
-                for (int r = 0; r < RT; ++r) {
-                    const int lane = (r % 32) + 32 * (int)(kk / 8);
-                    p.apk[((chunk * 2 + r / 32) * 64 + lane) * 8 + kk % 8] = f32_to_f16_rne(p.wc[at * RT + r]);
-                }
+    // Calls put(row, column, value) for every kept weight of rows r0 .. r1 - 1, block by block.
+    auto each_kept = [&](int r0, int r1, auto&& put) {
+        for (int r = r0; r < r1; ++r) {
+            const int bi = r / d.block_m;
+            const float* w = d.weights + (int64_t)r * d.k;
+            for (int bj = 0; bj < blocks_k; ++bj) {
+                if (!row_kept(r, bj)) continue;
+                const int c0 = bj * d.block_k, c1 = std::min(d.k, c0 + d.block_k);
+                const uint8_t* keep = d.col_keep ? d.col_keep + ((int64_t)bi * blocks_k + bj) * d.block_k : nullptr;
+                for (int c = c0; c < c1; ++c)
+                    if (!keep || keep[c - c0]) put(r, c, w[c]);
             }
+        }
+    };
+    std::vector<int32_t> place((size_t)d.k, 0);        // where a column sits in the current tile's list
+    p.apk.assign(half ? p.tile_cols.size() * (size_t)RT : 0, 0);
+    for (int t = 0; half && t < p.row_tiles; ++t) {
+        for (int i = 0; i < p.tile_len[t]; ++i) place[p.tile_cols[(size_t)p.tile_off[t] + i]] = p.tile_off[t] + i;
+        each_kept(t * RT, std::min(d.m, (t + 1) * RT), [&](int row, int c, float v) {
+            const size_t at = (size_t)place[c], chunk = at / kBlockChunk, kk = at % kBlockChunk;
+            const int r = row - t * RT;
+            p.apk[((chunk * 2 + r / 32) * 64 + (r % 32) + 32 * (kk / 8)) * 8 + kk % 8] = f32_to_f16_rne(v);
+        });
+    }
+    if (p.variant == 1 || !p.forced) {
+        // (a row group that a block prunes entirely takes none of the block's columns)
+        const int R = kBlockRow32, tiles = (d.m + R - 1) / R;
+        p.group_off32.assign(1, 0);
+        p.list32.clear();
+        std::vector<int32_t> cols;
+        for (int t = 0; t < tiles; ++t) {
+            const int r0 = t * R, r1 = std::min(d.m, r0 + R);
+            std::fill(used.begin(), used.end(), 0);
+            for (int bi = r0 / d.block_m; bi <= (r1 - 1) / d.block_m; ++bi)
+                for (int bj = 0; bj < blocks_k; ++bj) {
+                    bool any = false;
+                    for (int r = std::max(r0, bi * d.block_m); r < std::min(r1, (bi + 1) * d.block_m) && !any; ++r) any = row_kept(r, bj);
+                    if (!any) continue;
+                    for (int c = bj * d.block_k; c < std::min(d.k, (bj + 1) * d.block_k); ++c) used[c] |= col_kept(bi, c) ? 1 : 0;
+                }
+            cols.clear();
+            for (int c = 0; c < d.k; ++c)
+                if (used[c]) cols.push_back(c);
+            const size_t len = cols.size();
+            while (cols.size() % 8) cols.push_back(cols.back());
+            const size_t g0 = p.list32.size() / 8, ng = cols.size() / 8;
+            p.list32.resize((g0 + ng) * 8);
+            p.wpk32.resize((g0 + ng) * 256, 0.0f);
+            for (size_t e = 0; e < cols.size(); ++e) p.list32[(g0 + e / 8) * 8 + (e & 1) * 4 + (e % 8) / 2] = cols[e];
+            for (size_t e = 0; e < len; ++e) place[cols[e]] = (int32_t)e;
+            each_kept(r0, r1, [&](int r, int c, float v) {
+                const int e = place[c];
+                p.wpk32[((g0 + e / 8) * 64 + (r - r0) + 32 * (e & 1)) * 4 + (e % 8) / 2] = half ? f16_to_f32(f32_to_f16_rne(v)) : v;
+            });
+            p.group_off32.push_back((int32_t)(g0 + ng));
+        }
+        p.list32.resize(p.list32.size() + 2 * kF32Pad * 8, 0);
+        p.wpk32.resize(p.wpk32.size() + kF32Pad * 256, 0.0f);
     }
     p.bias.assign((size_t)p.row_tiles * RT, 0.0f);
     if (d.bias) std::memcpy(p.bias.data(), d.bias, (size_t)d.m * sizeof(float));
@@ -94,17 +130,22 @@ pp_status_t unpack_block_tile(const BlockHostPlan& p, int tile, float* w_out) {
     if (tile < 0 || tile >= p.row_tiles) return PP_ERR_SHAPE;
     const int RT = kBlockRowTile;
     std::fill(w_out, w_out + (size_t)RT * p.k, 0.0f);
+    if (p.variant == 1) {
+        for (int t = 2 * tile; t < 2 * tile + 2 && t + 1 < (int)p.group_off32.size(); ++t)
+            for (int64_t e = (int64_t)p.group_off32[t] * 8; e < (int64_t)p.group_off32[t + 1] * 8; ++e) {
+                const int64_t g = e / 8;
+                const int k8 = (int)(e % 8), c = p.list32[g * 8 + (k8 & 1) * 4 + k8 / 2];
+                for (int r = 0; r < kBlockRow32; ++r)      // (a repeated column carries zeros)
+                    w_out[(size_t)((t & 1) * kBlockRow32 + r) * p.k + c] += p.wpk32[(g * 64 + r + 32 * (k8 & 1)) * 4 + k8 / 2];
+            }
+        return PP_OK;
+    }
     for (int32_t at = p.tile_off[tile]; at < p.tile_off[tile + 1]; ++at) {
         const int c = p.tile_cols[at];
         const bool pad = at - p.tile_off[tile] >= p.tile_len[tile];
+        const size_t chunk = (size_t)at / kBlockChunk, kk = (size_t)at % kBlockChunk;
         for (int r = 0; r < RT; ++r) {
-            float v;
-            if (p.dtype == PP_F16) {
-                const size_t chunk = (size_t)at / kBlockChunk, kk = (size_t)at % kBlockChunk;
-                v = f16_to_f32(p.apk[((chunk * 2 + r / 32) * 64 + (r % 32) + 32 * (kk / 8)) * 8 + kk % 8]);
-            } else {
-                v = p.wc[(size_t)at * RT + r];
-            }
+            const float v = f16_to_f32(p.apk[((chunk * 2 + r / 32) * 64 + (r % 32) + 32 * (kk / 8)) * 8 + kk % 8]);
             if (pad) {
                 if (v != 0.0f) return PP_ERR_PATTERN;      // padding must carry zeros
             } else {

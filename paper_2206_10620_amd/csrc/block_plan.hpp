@@ -11,6 +11,7 @@ namespace ppc {
 
 constexpr int kBlockRowTile = 64;     // rows per tile: two 32-row MFMA operands
 constexpr int kBlockChunk = 16;       // columns of the compact list one MFMA consumes
+constexpr int kBlockRow32 = 32;       // rows per tile of the binary32 kernel
 constexpr int kBlockColTile = 512;    // columns of x and y per workgroup of the matrix-core kernel
 
 struct BlockHostPlan {
@@ -24,11 +25,14 @@ struct BlockHostPlan {
     std::vector<int32_t> tile_off;    // [row_tiles + 1] offsets into tile_cols (multiples of kBlockChunk)
     std::vector<int32_t> tile_cols;   // padded compact lists
     std::vector<int32_t> tile_len;    // [row_tiles] before padding
-    // generic kernel: wc[(tile_off[t] + i) * kBlockRowTile + r] = Wd[t * 64 + r][tile_cols[tile_off[t] + i]] (binary16-rounded for PP_F16)
-    std::vector<float> wc;
     // matrix-core kernel (PP_F16): per chunk of 16 list entries two operands of 64 lanes x 8 binary16:
     // apk[((chunk * 2 + half) * 64 + lane) * 8 + e] = Wd[t * 64 + half * 32 + lane % 32][list[chunk * 16 + 8 * (lane / 32) + e]]
     std::vector<uint16_t> apk;
+    // binary32 matrix-core kernel and the generic kernel (values rounded to binary16 for PP_F16): their own lists, one per 32 rows (16-row blocks at 50 % leave 75 % of the columns to 32
+    // rows and 94 % to 64), in groups of eight entries stored [half][4]: entry 2 p + half of the group at [half][p]; weights
+    // in operand order, [group][64 lanes][4]: lane l, value p: row l % 32, entry 2 p + l / 32
+    std::vector<int32_t> list32, group_off32;     // padding at the ends: the kernel loads ahead
+    std::vector<float> wpk32;
     std::vector<float> bias;          // [row_tiles * 64], zeros where there is no bias or no row
 };
 

@@ -234,19 +234,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
-// Generic kernel: one lane per output element, walking the tile's compact list (any dtype, any n).
+// Generic kernel: one lane per output element, walking the 32-row tile's compact list (any dtype, any size).  It serves
+// binary16 plans that ask for it and binary32 inputs of 2 GB and more.
 template <typename T>
-__global__ __launch_bounds__(256) void k4_generic(const T* __restrict__ x, T* __restrict__ y, const float* __restrict__ wc,
-                                                  const float* __restrict__ bias, const int32_t* __restrict__ tile_off,
-                                                  const int32_t* __restrict__ tile_cols, const int32_t* __restrict__ tile_len, int m, int n, int relu) {
+__global__ __launch_bounds__(256) void k4_generic(const T* __restrict__ x, T* __restrict__ y, const float* __restrict__ wpk, const float* __restrict__ bias,
+                                                  const int32_t* __restrict__ group_off, const int32_t* __restrict__ list, int m, int n, int relu) {
     const int t = (int)blockIdx.y, j = (int)(blockIdx.x * 64 + threadIdx.x);
     if (j >= n) return;
-    const int e0 = tile_off[t], len = tile_len[t];
-    for (int r = (int)threadIdx.y; r < kBlockRowTile; r += (int)blockDim.y) {
-        const int row = t * kBlockRowTile + r;
+    for (int r = (int)threadIdx.y; r < kBlockRow32; r += (int)blockDim.y) {
+        const int row = t * kBlockRow32 + r;
         if (row >= m) break;
         float acc = bias[row];
-        for (int i = 0; i < len; ++i) acc = __builtin_fmaf(wc[(int64_t)(e0 + i) * kBlockRowTile + r], (float)x[(int64_t)tile_cols[e0 + i] * n + j], acc);
+        for (int64_t g = group_off[t]; g < group_off[t + 1]; ++g)
+            for (int e = 0; e < 8; ++e) {
+                const int half = e & 1, p = e >> 1;
+                acc = __builtin_fmaf(wpk[(g * 64 + r + 32 * half) * 4 + p], (float)x[(int64_t)list[g * 8 + half * 4 + p] * n + j], acc);
+            }
         if (relu) acc = acc > 0.0f ? acc : 0.0f;
         y[(int64_t)row * n + j] = (T)acc;
     }
