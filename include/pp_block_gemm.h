@@ -59,9 +59,8 @@ pp_status_t pp_block_gemm_plan(const pp_block_gemm_desc_t *desc, pp_block_gemm_p
 /* Enqueue y = act(Wd x + bias) for n columns.
  *   x_dev : [k][n] row-major, plan dtype, 16-byte aligned, caller-owned
  *   y_dev : [m][n] row-major, plan dtype, 16-byte aligned, caller-owned, must not overlap x_dev
- * Asynchronous on hip_stream (a hipStream_t, NULL = default stream).  The matrix-core kernel needs n
- * to be a multiple of 8 (rows of x and y then start on 16-byte boundaries); an automatic plan runs
- * the generic kernel for any other n, a plan with variant 2 forced returns PP_ERR_UNSUPPORTED.
+ * Asynchronous on hip_stream (a hipStream_t, NULL = default stream).  An automatic plan takes any n; a plan
+ * with variant 2 forced returns PP_ERR_UNSUPPORTED for an n that is not a multiple of 8.
  * n < 1, or k * n or m * n beyond 2^31 - 1 elements: PP_ERR_SHAPE.  Misaligned or overlapping
  * buffers: PP_ERR_ALIGN. */
 pp_status_t pp_block_gemm_run(const pp_block_gemm_plan_t *plan, const void *x_dev, void *y_dev, int32_t n, void *hip_stream);
@@ -74,7 +73,7 @@ pp_status_t pp_block_gemm_destroy(pp_block_gemm_plan_t *plan);
  * column, with zero weights there; an empty list stays empty).  Pointers stay valid until destroy. */
 typedef struct {
     int32_t m, k, block_m, block_k;
-    int32_t variant;            /* the kernel an n that is a multiple of 8 runs with: 1 or 2 */
+    int32_t variant;            /* 1 or 2 */
     int32_t row_tile;           /* rows per tile (64) */
     int32_t row_tiles;          /* ceil(m / row_tile) */
     int64_t kept_weights;       /* number of (m, k) with Wd structurally kept */

@@ -1,6 +1,7 @@
 // C ABI of the block-pruned matrix product (include/pp_block_gemm.h): plan upload, launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <new>
 
@@ -40,29 +41,77 @@ void release(pp_block_gemm_plan_t* p) {
         if (b) (void)hipFree(b);
 }
 
+struct K4Shape {
+    int cols;                                                  // columns of a workgroup
+    void (*launch)(const K4Args& a, int blocks, hipStream_t stream);
+};
+
+template <bool RAGGED> void launch_wide_as(const K4Args& a, int blocks, hipStream_t stream) {
+    static const hipError_t lds_attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k4_block_gemm<RAGGED>), hipFuncAttributeMaxDynamicSharedMemorySize, kK4LdsBytes);
+    (void)lds_attr;
+    hipLaunchKernelGGL(k4_block_gemm<RAGGED>, dim3((unsigned)blocks), dim3(256), kK4LdsBytes, stream, a);
+}
+void launch_wide(const K4Args& a, int blocks, hipStream_t stream) {
+    if (a.ragged) launch_wide_as<true>(a, blocks, stream);
+    else launch_wide_as<false>(a, blocks, stream);
+}
+template <int NT, int WK> void launch_split(const K4Args& a, int blocks, hipStream_t stream) {
+    constexpr int lds = k4_split_lds_bytes(NT, WK);
+    static const hipError_t lds_attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k4_split<NT, WK>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    (void)lds_attr;
+    hipLaunchKernelGGL((k4_split<NT, WK>), dim3((unsigned)blocks), dim3(64 * WK), lds, stream, a);
+}
+
+// Which tile a launch runs with: the smallest modelled time.  A workgroup of the split kernel walks chunks / wk chunks per
+// wavefront, each worth 0.3 us of load latency or, with several wavefronts on a compute unit, nt + 2 KB through the vector
+// cache (0.012 us per KB); the 512-column tile takes 0.4 us per chunk alone on a compute unit and 0.52 with a neighbour.
+// Measured on 27 products (1 to 4096 columns, 4 to 64 row tiles, 8 to 106 chunks) the pick is 1.4 % from the best shape on
+// average, 16 % at worst; 4096 x 4096 at 0.41: at 2048 columns 4 x 4 takes 57 us against the wide tile's 61, at 3000 87 against 72.
+K4Shape k4_pick(const BlockHostPlan& hp, int n, int batch) {
+    struct Split { int nt, wk, resident; K4Shape shape; };
+    static const Split kSplits[] = {{1, 4, 4, {32, launch_split<1, 4>}}, {1, 8, 2, {32, launch_split<1, 8>}}, {2, 4, 3, {64, launch_split<2, 4>}},
+                                    {2, 8, 1, {64, launch_split<2, 8>}}, {4, 4, 2, {128, launch_split<4, 4>}}, {4, 8, 1, {128, launch_split<4, 8>}}};
+    const K4Shape wide{kBlockColTile, launch_wide};
+    if (hp.k >= (1 << 24) || n >= (1 << 23)) return wide;       // the split kernel multiplies in 24 bits
+    const double chunks = (double)hp.tile_cols.size() / kBlockChunk / hp.row_tiles;
+    auto per_cu = [&](int cols) { return ((int64_t)hp.row_tiles * ((n + cols - 1) / cols) * batch + 255) / 256; };
+    const int64_t pw = per_cu(kBlockColTile);
+    K4Shape best = wide;
+    double best_t = chunks * ((double)(pw / 2) * 0.52 + (double)(pw % 2) * 0.4);
+    for (const Split& s : kSplits) {
+        const double share = chunks / s.wk > 1.0 ? chunks / s.wk : 1.0;
+        auto round = [&](int64_t k) { return k == 0 ? 0.0 : std::max(share * 0.3, (double)k * s.wk * share * (s.nt + 2) * 0.012) + 0.7 * s.nt; };
+        const int64_t p = per_cu(s.shape.cols);
+        const double t = (double)(p / s.resident) * round(s.resident) + round(p % s.resident);
+        if (t < best_t) best_t = t, best = s.shape;
+    }
+    return best;
+}
+
 }  // namespace
 
 pp_status_t pp_block_gemm_launch_batched(const pp_block_gemm_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, int32_t batch, int64_t x_stride,
                                          int64_t y_stride, void* hip_stream) {
     if (!plan || !x_dev || !y_dev) return PP_ERR_NULL;
     const BlockHostPlan& hp = plan->hp;
-    if (n < 1 || batch < 1 || (n % 8) != 0 || hp.dtype != PP_F16 || !plan->on_device) return PP_ERR_UNSUPPORTED;
+    if (n < 1 || batch < 1 || hp.dtype != PP_F16 || !plan->on_device) return PP_ERR_UNSUPPORTED;
     if ((int64_t)hp.k * n >= ((int64_t)1 << 31) || (int64_t)hp.m * n >= ((int64_t)1 << 31)) return PP_ERR_SHAPE;
     K4Args a;
     a.x = x_dev, a.y = y_dev, a.apk = plan->d_apk, a.bias = plan->d_bias;
     a.tile_off = plan->d_tile_off, a.tile_cols = plan->d_tile_cols;
     a.m = hp.m, a.n = n, a.row_tiles = hp.row_tiles;
-    a.col_tiles = (n + kBlockColTile - 1) / kBlockColTile;
+    a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
+    a.ragged = (n % 8) != 0 ? 1 : 0;
+    a.x_bytes = (uint32_t)((int64_t)hp.k * n * 2);
+    a.x_stride = x_stride, a.y_stride = y_stride;
+    const K4Shape sh = k4_pick(hp, n, batch);
+    a.col_tiles = (n + sh.cols - 1) / sh.cols;
     const int64_t items = (int64_t)a.row_tiles * a.col_tiles * batch;
     if (items >= ((int64_t)1 << 28)) return PP_ERR_SHAPE;
     a.items = (int)items;
     a.per_xcd = (a.items + 7) / 8;
-    a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
-    a.x_stride = x_stride, a.y_stride = y_stride;
-    static const hipError_t lds_attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k4_block_gemm), hipFuncAttributeMaxDynamicSharedMemorySize, kK4LdsBytes);
-    (void)lds_attr;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k4_block_gemm, dim3((unsigned)(a.per_xcd * 8)), dim3(256), kK4LdsBytes, static_cast<hipStream_t>(hip_stream), a);
+    sh.launch(a, a.per_xcd * 8, static_cast<hipStream_t>(hip_stream));
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
@@ -110,8 +159,8 @@ pp_status_t pp_block_gemm_plan(const pp_block_gemm_desc_t* desc, pp_block_gemm_p
         bool ok = put(&p->d_apk, hp.apk.data(), hp.apk.size() * sizeof(uint16_t));
         ok = ok && put(&p->d_bias, hp.bias.data(), hp.bias.size() * sizeof(float));
         ok = ok && put(&p->d_tile_off, hp.tile_off.data(), hp.tile_off.size() * sizeof(int32_t));
-        ok = ok && put(&p->d_tile_cols, hp.tile_cols.data(), hp.tile_cols.size() * sizeof(int32_t), kBlockChunk * sizeof(int32_t));   // the kernel reads one chunk ahead
-        if (!hp.wpk32.empty()) {
+        ok = ok && put(&p->d_tile_cols, hp.tile_cols.data(), hp.tile_cols.size() * sizeof(int32_t), 256 * sizeof(int32_t));   // the kernels read ahead: a chunk, or two segments of 128
+        if (hp.variant == 1) {
             ok = ok && put(&p->d_wpk32, hp.wpk32.data(), hp.wpk32.size() * sizeof(float));
             ok = ok && put(&p->d_list32, hp.list32.data(), hp.list32.size() * sizeof(int32_t));
             ok = ok && put(&p->d_group_off32, hp.group_off32.data(), hp.group_off32.size() * sizeof(int32_t));
@@ -137,16 +186,12 @@ pp_status_t pp_block_gemm_run(const pp_block_gemm_plan_t* plan, const void* x_de
     if ((xa | ya) & 15u) return PP_ERR_ALIGN;
     const uintptr_t xe = xa + (uintptr_t)((int64_t)hp.k * n * eb), ye = ya + (uintptr_t)((int64_t)hp.m * n * eb);
     if (xa < ye && ya < xe) return PP_ERR_ALIGN;
-    int variant = hp.variant;
-    if (variant == 2 && (n % 8) != 0) {
-        if (hp.forced) return PP_ERR_UNSUPPORTED;
-        variant = 1;
-    }
+    if (hp.variant == 2 && hp.forced && (n % 8) != 0) return PP_ERR_UNSUPPORTED;        // what the header promises of a forced variant
     if (!plan->on_device) return PP_ERR_UNSUPPORTED;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
     (void)hipGetLastError();
-    if (variant == 2) return pp_block_gemm_launch_batched(plan, x_dev, y_dev, n, 1, 0, 0, hip_stream);
+    if (hp.variant == 2) return pp_block_gemm_launch_batched(plan, x_dev, y_dev, n, 1, 0, 0, hip_stream);
     if (hp.dtype == PP_F32) {
         const pp_status_t st = launch_list_f32(plan, x_dev, y_dev, n, stream);
         if (st != PP_ERR_UNSUPPORTED) return st;

@@ -86,7 +86,7 @@ pp_status_t build_block_plan(const pp_block_gemm_desc_t& d, BlockHostPlan& p) {
             p.apk[((chunk * 2 + r / 32) * 64 + (r % 32) + 32 * (kk / 8)) * 8 + kk % 8] = f32_to_f16_rne(v);
         });
     }
-    if (p.variant == 1 || !p.forced) {
+    if (p.variant == 1) {
         // (a row group that a block prunes entirely takes none of the block's columns)
         const int R = kBlockRow32, tiles = (d.m + R - 1) / R;
         p.group_off32.assign(1, 0);

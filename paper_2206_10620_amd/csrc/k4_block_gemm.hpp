@@ -30,6 +30,8 @@ struct K4Args {
     const int32_t* tile_off;    // [row_tiles + 1], multiples of 16
     const int32_t* tile_cols;   // compact lists
     int32_t m, n, row_tiles, col_tiles, items, per_xcd, relu;
+    int32_t ragged;             // n is not a multiple of 8: pieces of 8 columns straddle rows, the last one the end of x
+    uint32_t x_bytes;           // k * n * 2: one matrix of x
     // a batch of products with the same weights (the images of a 1x1 convolution): item = (image, column tile, row tile)
     int64_t x_stride, y_stride;  // elements between the x (y) matrices of consecutive images
 };
@@ -49,6 +51,7 @@ typedef _Float16 k4_h8 __attribute__((ext_vector_type(8)));
 typedef float k4_f2 __attribute__((ext_vector_type(2)));
 typedef float k4_f16 __attribute__((ext_vector_type(16)));
 typedef uint32_t k4_u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t k4_u4_any __attribute__((ext_vector_type(4), aligned(2)));      // rows of y start on 2-byte boundaries when n is odd
 
 template <typename P> __device__ __forceinline__ P* k4_uniform_ptr(P* p) {
     const uint64_t v = (uint64_t)(uintptr_t)p;
@@ -63,6 +66,22 @@ __device__ __forceinline__ void k4_dma16(uint32_t off, const void* base, uint32_
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_dst) : "memory", "m0");
 }
 
+// The last piece of the last row where n is not a multiple of 8 (or rows shorter than a piece): eight guarded element
+// loads instead of one that would end behind x.  Rare; kept out of line.
+__device__ __attribute__((noinline)) void k4_edge_piece(const unsigned char* x, uint32_t off, uint32_t x_bytes, unsigned char* lds_dst) {
+    const uint16_t* src = reinterpret_cast<const uint16_t*>(x);
+    uint32_t v[4];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t at = off + 2u * (uint32_t)e;
+        const uint32_t bits = at < x_bytes ? (uint32_t)src[at / 2] : 0u;
+        v[e >> 1] = (e & 1) ? (v[e >> 1] | (bits << 16)) : bits;
+    }
+    k4_u4 v4;
+    v4.x = v[0], v4.y = v[1], v4.z = v[2], v4.w = v[3];
+    *reinterpret_cast<k4_u4*>(lds_dst) = v4;
+}
+
 // s_waitcnt vmcnt(n) for a wave-uniform n in 0..15
 __device__ __forceinline__ void k4_wait_vm(int n) {
     switch (n) {
@@ -74,6 +93,8 @@ __device__ __forceinline__ void k4_wait_vm(int n) {
     }
 }
 
+// RAGGED: n is not a multiple of 8 (a variant of its own: the checks cost the aligned case 5 %, 66.5 -> 70 us on 4096 columns)
+template <bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k4_block_gemm(const K4Args a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char k4_smem[];
     constexpr int NS = kK4Stages, NT = 4;
@@ -94,11 +115,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     typedef const __attribute__((address_space(4))) int32_t* k4_const_i32;
     const k4_const_i32 list = (k4_const_i32)(uintptr_t)k4_uniform_ptr(a.tile_cols + e0);
     const unsigned char* wsrc = k4_uniform_ptr(static_cast<const unsigned char*>(a.apk) + (int64_t)(e0 / kBlockChunk) * 2048 + wave * 1024);
-    const unsigned char* xsrc = k4_uniform_ptr(static_cast<const unsigned char*>(a.x) + ((int64_t)img * a.x_stride + col0) * 2);
+    const unsigned char* xsrc = k4_uniform_ptr(static_cast<const unsigned char*>(a.x) + ((int64_t)img * a.x_stride + (RAGGED ? 0 : col0)) * 2);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)k4_smem;
     const uint32_t lane16 = (uint32_t)lane * 16u;
-    const bool piece_ok = col0 + lane * 8 < a.n;            // n is a multiple of 8: a 16-byte piece is inside a row or outside
     const uint32_t row_bytes = (uint32_t)a.n * 2u;          // x is smaller than 4 GB: byte offsets fit 32 bits
+    const uint32_t piece_off = RAGGED ? lane16 + (uint32_t)col0 * 2u : lane16;
+    const bool piece_ok = col0 + lane * 8 < a.n;            // (columns of a piece past the row's end reach outputs that are not stored only)
+    const uint32_t edge_from = a.x_bytes > row_bytes + 14u ? a.x_bytes - row_bytes - 14u : 0u;
+    bool drain = false;                                     // an instruction was skipped: the wait counts no longer hold, wait for everything
     const bool wload = wave < 2;                            // wavefronts 0 and 1 also fetch the two weight operands
 
     // chunks are issued in order, so the four list entries of the next chunk to issue are fetched one
@@ -114,8 +138,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const uint32_t st = lds0 + (uint32_t)(stage * kK4StageBytes);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t off = (uint32_t)rows[i] * row_bytes + lane16;
-            if (piece_ok) k4_dma16(off, xsrc, st + (uint32_t)((wave + 4 * i) * kK4RowPitch));
+            const uint32_t off = (uint32_t)rows[i] * row_bytes + piece_off;
+            const uint32_t dst = (uint32_t)((wave + 4 * i) * kK4RowPitch);
+            if (RAGGED && (uint32_t)rows[i] * row_bytes >= edge_from) {               // a row whose last piece may end behind x
+                const bool edge = piece_ok && off > a.x_bytes - 16u;
+                const bool mine = piece_ok && !edge;
+                if (__builtin_amdgcn_ballot_w64(mine) == 0) drain = true;
+                if (mine) k4_dma16(off, xsrc, st + dst);
+                if (edge) k4_edge_piece(xsrc, off, a.x_bytes, k4_smem + stage * kK4StageBytes + dst + lane16);
+            } else if (piece_ok) {
+                k4_dma16(off, xsrc, st + dst);
+            }
         }
         if (wload) k4_dma16(lane16, wsrc + (int64_t)c * 2048, st + (uint32_t)(kBlockChunk * kK4RowPitch + wave * 1024));
         fetch_rows();
@@ -161,7 +194,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
     // waits until this wavefront's direct loads of a chunk have landed, given how many younger chunks it has issued
     auto wait_chunk = [&](int younger) {
-        if (younger >= 2) {
+        if (younger >= 2 && !(RAGGED && drain)) {
             if (wload) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
             else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
         } else {
@@ -188,7 +221,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int c = 0; c < NS; ++c)
             if (c < nch) issue(c, c);
-        k4_wait_vm((nch > NS ? NS - 1 : nch - 1) * (wload ? 5 : 4));
+        k4_wait_vm(RAGGED && drain ? 0 : (nch > NS ? NS - 1 : nch - 1) * (wload ? 5 : 4));
         __syncthreads();
         read_frags(0, 0);
 #pragma unroll 1
@@ -207,7 +240,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const k4_h2 floor2 = a.relu ? k4_h2((_Float16)0.0f) : k4_h2((_Float16)-65504.0f);
     const int srow = lane >> 4, scol = (lane & 15) * 8;                  // store side: 16 lanes hold one row's 128 columns
     const int ycol = col0 + wave * 128 + scol;
-    const bool col_ok = ycol < a.n;
+    const bool col_ok = ycol + 8 <= a.n;
     unsigned char* ybase = static_cast<unsigned char*>(a.y) + (int64_t)img * a.y_stride * 2;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
@@ -229,7 +262,199 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int row = j * 4 + srow;
             const k4_u4 v = *reinterpret_cast<const k4_u4*>(corner + row * kK4CornerPitch + scol * 2);
             const int yrow = rt * kBlockRowTile + mt * 32 + row;
-            if (col_ok && yrow < a.m) *reinterpret_cast<k4_u4*>(ybase + ((int64_t)yrow * a.n + ycol) * 2) = v;
+            if (yrow < a.m) {
+                unsigned char* dst = ybase + ((int64_t)yrow * a.n + ycol) * 2;
+                if (col_ok) {
+                    if constexpr (RAGGED) *reinterpret_cast<k4_u4_any*>(dst) = v;
+                    else *reinterpret_cast<k4_u4*>(dst) = v;
+                } else if (RAGGED && ycol < a.n) {                      // the last piece of a row, n not a multiple of 8
+#pragma unroll
+                    for (int e = 0; e < 7; ++e)
+                        if (ycol + e < a.n) *reinterpret_cast<uint16_t*>(dst + 2 * e) = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+                }
+            }
+        }
+    }
+}
+
+// ---- few columns: the reduction split over the wavefronts of a workgroup ----
+// A product with few columns has few 64 x 512 tiles, each a long serial walk: 4096 x 4096 on one column is 64 of them.  Here
+// a workgroup owns 64 rows x 32 NT columns and its WK wavefronts take consecutive shares of the list; each stages its own
+// chunks (a ring in its own part of LDS, so the loop has no barrier) and the shares are summed through LDS in order.
+// Bound by the latency of its loads (0.3 us per chunk and wavefront); 4096 x 4096 in 64 x 64 blocks at 0.41: one column 2834 us
+// (one lane per output) -> 9 us, 8 columns 44.7 (the 512-column tile) -> 7.5, 512 columns 57 -> 19, 1024 columns 59 -> 30.
+// A row of x in the stage is 64 NT bytes, so one direct load moves 16 / NT rows: lane i of load q brings list entry
+// (i / (4 NT)) NT + q, whose columns sit at slot piece ^ (q << 1) of LDS row q (16 / NT) + i / (4 NT) -- the exchange puts
+// the four rows a transposing read touches into different banks.
+constexpr int kK4SplitStages = 3;
+constexpr int k4_split_stage_bytes(int nt) { return kBlockChunk * 64 * nt + 2048; }
+constexpr int k4_split_wave_bytes(int nt) { return kK4SplitStages * k4_split_stage_bytes(nt) + 2 * 512; }      // + two list segments of 128 entries
+constexpr int k4_split_lds_bytes(int nt, int wk) {
+    const int ring = wk * k4_split_wave_bytes(nt), sum = wk * 8192;      // the epilogue sums a 64 x 32 tile of every wavefront
+    return ring > sum ? ring : sum;
+}
+
+template <int NT, int WK>
+__global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(2))) void k4_split(const K4Args a) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char k4_smem[];
+    constexpr int NS = kK4SplitStages, PPR = 4 * NT, RPI = 16 / NT, SB = k4_split_stage_bytes(NT), CI = NT + 2;
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int item = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
+    if (item >= a.items) return;
+    const int per_image = a.row_tiles * a.col_tiles;
+    const int img = item / per_image, in_image = item - img * per_image;
+    const int ct = in_image / a.row_tiles, rt = in_image - ct * a.row_tiles;
+    const int col0 = ct * 32 * NT;
+    const int e0 = __builtin_amdgcn_readfirstlane(a.tile_off[rt]), e1 = __builtin_amdgcn_readfirstlane(a.tile_off[rt + 1]);
+    const int all = (e1 - e0) / kBlockChunk;
+    const int c0 = all * wave / WK, nch = all * (wave + 1) / WK - c0;      // this wavefront's chunks
+    const unsigned char* lsrc = k4_uniform_ptr(reinterpret_cast<const unsigned char*>(a.tile_cols + e0 + c0 * kBlockChunk));
+    const unsigned char* wsrc = k4_uniform_ptr(static_cast<const unsigned char*>(a.apk) + (int64_t)(e0 / kBlockChunk + c0) * 2048);
+    const unsigned char* xsrc = k4_uniform_ptr(static_cast<const unsigned char*>(a.x) + (int64_t)img * a.x_stride * 2);
+    unsigned char* mine_lds = k4_smem + wave * k4_split_wave_bytes(NT);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)mine_lds;
+    const uint32_t lists = (uint32_t)(NS * SB);
+    const uint32_t lane16 = (uint32_t)lane * 16u;
+    const uint32_t row_bytes = (uint32_t)a.n * 2u;
+    const int b = lane / PPR, slot = lane % PPR;
+    uint32_t piece_off[NT];                                  // byte offset in a row of the piece the lane brings with load q
+    bool piece_ok[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        const int c = col0 + (slot ^ (q << 1)) * 8;
+        piece_off[q] = (uint32_t)c * 2u;
+        piece_ok[q] = c < a.n;
+    }
+    // (x of less than 16 bytes: every piece takes the guarded path)
+    const uint32_t last_off = a.x_bytes >= 16u ? a.x_bytes - 16u : 0u;
+    bool drain = false;
+    auto issue_list = [&](int seg) {                         // 128 entries: eight chunks
+        if (lane < 32) k4_dma16(lane16, lsrc + (int64_t)seg * 512, lds0 + lists + (uint32_t)((seg & 1) * 512));
+    };
+    auto issue = [&](int c, int stage) {
+        const uint32_t st = lds0 + (uint32_t)(stage * SB);
+        const int32_t* lp = reinterpret_cast<const int32_t*>(mine_lds + lists + ((c >> 3) & 1) * 512 + (c & 7) * 64) + b * NT;
+        uint32_t entry[NT];
+        if constexpr (NT == 4) {
+            const k4_u4 v = *reinterpret_cast<const k4_u4*>(lp);
+            entry[0] = v.x, entry[1] = v.y, entry[2] = v.z, entry[3] = v.w;
+        } else {
+#pragma unroll
+            for (int q = 0; q < NT; ++q) entry[q] = (uint32_t)lp[q];
+        }
+        uint32_t off[NT];
+        bool end = false;                                    // a piece of mine ends behind x
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            off[q] = __umul24(entry[q], row_bytes) + piece_off[q];                      // the launcher sees to it that both fit 24 bits
+            end = end || (piece_ok[q] && (off[q] > last_off || a.x_bytes < 16u));
+        }
+        if (a.ragged && __builtin_amdgcn_ballot_w64(end) != 0) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                const bool edge = piece_ok[q] && (off[q] > last_off || a.x_bytes < 16u), mine = piece_ok[q] && !edge;
+                if (__builtin_amdgcn_ballot_w64(mine) == 0) drain = true;
+                if (mine) k4_dma16(off[q], xsrc, st + (uint32_t)(q * 1024));
+                if (edge) k4_edge_piece(xsrc, off[q], a.x_bytes, mine_lds + stage * SB + q * 1024 + lane16);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+                if (piece_ok[q]) k4_dma16(off[q], xsrc, st + (uint32_t)(q * 1024));
+        }
+        k4_dma16(lane16, wsrc + (int64_t)c * 2048, st + (uint32_t)(NT * 1024));
+        k4_dma16(lane16, wsrc + (int64_t)c * 2048 + 1024, st + (uint32_t)(NT * 1024 + 1024));
+    };
+    k4_f16 acc[2][NT];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = k4_f16(0.0f);
+
+    // the transposing reads: block of 16 lanes, lane 4 j + q' reads four columns of entry 8 (blk / 2) + 4 h + j
+    const int blk = lane >> 4, jj = (lane & 15) >> 2, qq = lane & 3;
+    uint32_t baddr[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int e = 8 * (blk >> 1) + 4 * h + jj, q = e % NT, row = q * RPI + e / NT;
+        const int s = 2 * (blk & 1) + (qq >> 1);             // slot of the columns inside a 32-column tile; tile nt adds 4 nt
+        baddr[h] = (uint32_t)(row * 64 * NT + (s ^ ((q << 1) & 3)) * 16 + (qq & 1) * 8);
+    }
+    const int ex = NT == 4 ? ((jj << 1) & 4) : 0;            // what the exchange does to the slot's bit 2 (tiles of four swap in pairs)
+    k4_h8 af[2][2], bf[2][NT];
+    auto read_frags = [&](int stage, int set) {
+        const uint32_t st = lds0 + (uint32_t)(stage * SB);
+        const unsigned char* wst = mine_lds + stage * SB + NT * 1024 + lane16;
+        af[set][0] = *reinterpret_cast<const k4_h8*>(wst);
+        af[set][1] = *reinterpret_cast<const k4_h8*>(wst + 1024);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const uint32_t t = (uint32_t)(((nt * 4) ^ ex) * 16);
+            const k4_hh4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4f16(reinterpret_cast<__attribute__((address_space(3))) k4_hh4*>(st + baddr[0] + t));
+            const k4_hh4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4f16(reinterpret_cast<__attribute__((address_space(3))) k4_hh4*>(st + baddr[1] + t));
+            bf[set][nt] = __builtin_shufflevector(__builtin_bit_cast(k4_h4, lo), __builtin_bit_cast(k4_h4, hi), 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
+    if (nch > 0) {
+        issue_list(0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int c = 0; c < NS; ++c)
+            if (c < nch) issue(c, c);
+        if (nch > 8) issue_list(1);                          // segment s + 1 is fetched eight chunks ahead of its first use
+        k4_wait_vm(drain ? 0 : (nch > NS ? NS - 1 : nch - 1) * CI);
+        read_frags(0, 0);
+        int stage = 0;
+#pragma unroll 1
+        for (int c = 0; c < nch; c += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (c + u < nch) {
+                    const int nxt = stage + 1 == NS ? 0 : stage + 1;
+                    if (c + u + 1 < nch) {
+                        if (nch - 2 - (c + u) >= NS - 2 && !drain) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * CI) : "memory");
+                        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the reads of this chunk have left its stage
+                        const int ahead = c + u + NS;
+                        if (ahead < nch) {
+                            issue(ahead, stage);
+                            if ((ahead & 7) == 0 && ahead + 8 < nch) issue_list((ahead >> 3) + 1);
+                        }
+                        read_frags(nxt, u ^ 1);
+                    }
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[u][mt], bf[u][nt], acc[mt][nt], 0, 0, 0);
+                    stage = nxt;
+                }
+            }
+        }
+    }
+    // ---- epilogue: tile by tile of 32 columns, the wavefronts' sums in order, bias, ReLU, binary16 ----
+    constexpr int R = 32 / WK;                               // accumulator registers of a 64 x 32 tile that a wavefront finishes
+    float* red = reinterpret_cast<float*>(k4_smem);
+    _Float16* y = static_cast<_Float16*>(a.y) + (int64_t)img * a.y_stride;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        if (col0 + nt * 32 >= a.n) break;                    // uniform
+        __syncthreads();
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[((wave * 2 + mt) * 16 + i) * 64 + lane] = acc[mt][nt][i];
+        __syncthreads();
+        const int col = col0 + nt * 32 + (lane & 31);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int reg = wave * R + i, mt = reg >> 4, ri = reg & 15;
+            const int row = rt * kBlockRowTile + mt * 32 + (ri >> 2) * 8 + (lane >> 5) * 4 + (ri & 3);
+            float v = a.bias[row];
+#pragma unroll
+            for (int w = 0; w < WK; ++w) v += red[(w * 32 + reg) * 64 + lane];
+            if (a.relu) v = v > 0.0f ? v : 0.0f;
+            if (row < a.m && col < a.n) y[(int64_t)row * a.n + col] = (_Float16)v;
         }
     }
 }
