@@ -1,0 +1,48 @@
+"""Deep reuse on its tiled path (neuron vectors and outputs in multiples of 4) against the CPU checker: signatures and
+representatives bit-exact, outputs within the binary32 gate; sizes around the 64- and 128-row tiles, the 512-row rounds, the
+2048-row padding, the 64-column blocks; every vector length; segments with more clusters than fit in LDS."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from oracle.compare import TOL, error_report
+import paper_2206_10620_amd as pp
+from test_gpu_reuse import check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L", [4, 8, 12, 16, 20, 24, 28, 32])
+@pytest.mark.parametrize("n", [1, 127, 513])
+def test_vector_lengths(L, n):
+    check(synth.random_reuse_layer("L", n, 5 * L, 12, L, 7, seed=L + n, prototypes=9, noise=0.02))
+
+
+@pytest.mark.parametrize("m", [4, 60, 64, 68, 132])
+@pytest.mark.parametrize("n", [64, 1025, 4100])
+def test_output_blocks_and_row_counts(m, n):
+    check(synth.random_reuse_layer("m", n, 48, m, 16, 9, seed=m + n, prototypes=20, noise=0.02, relu=bool(n & 1)))
+
+
+@pytest.mark.parametrize("hash_bits", [1, 6, 12])
+def test_many_clusters(hash_bits):
+    # unrelated vectors: up to 4096 clusters in a segment, read from memory instead of LDS
+    check(synth.random_reuse_layer("c", 6000, 64, 64, 16, hash_bits, seed=3, prototypes=6000, noise=0.0))
+
+
+def test_runs_of_different_lengths_in_turn():
+    lay = synth.random_reuse_layer("t", 5000, 96, 32, 8, 10, seed=6, prototypes=40)
+    plan = pp.reuse_plan_from_layer(lay)
+    try:
+        for n in (5000, 70, 2049, 5000):          # each run finds the tables as the one before left them
+            x = lay.make_input(n)
+            y = plan.run(torch.from_numpy(x).cuda())
+            torch.cuda.synchronize()
+            sig, rep = plan.clusters(n)
+            ref, pre, sc, rsig, rrep = oracle.reuse_layer(x, lay.weights, lay.hyperplanes, lay.seg_len, lay.hash_bits, lay.bias, lay.relu)
+            assert np.array_equal(sig, rsig) and np.array_equal(rep, rrep), n
+            assert error_report(y.cpu().numpy(), ref, pre, sc)["E"] <= TOL["f32"]
+    finally:
+        plan.close()
