@@ -69,7 +69,9 @@ enum {
 typedef struct {
     int32_t variant;        /* 0 auto; 1 generic (any layer: binary32 as a dense product on the binary32 matrix
                                cores, otherwise one lane per output); 2 tiled pattern-specialised kernel (3x3, stride 1, no
-                               fused pool; masks outside its sixteen run as covers of those with zero weights); 3 matrix-core kernel (binary16 storage only: the pruned
+                               fused pool; masks outside its sixteen run as covers of those with zero weights; a binary32
+                               plan whose other fields are zero too, and that was left to the library, reports this
+                               variant and its layout and runs the same layer on the binary32 matrix cores); 3 matrix-core kernel (binary16 storage only: the pruned
                                weights zero-filled to a dense matrix and multiplied on the MFMA units -- the measured
                                alternative to pattern-specialised vector code; any pattern table, kernel size, stride) */
     int32_t filters_per_wave; /* F: output filters whose accumulators one wavefront holds (4, 8 or 16) */

@@ -10,6 +10,7 @@
 #include "k2_mfma.hpp"
 #include "k3_mfma_direct.hpp"
 #include "k5_f32.hpp"
+#include "k6_f32_3x3.hpp"
 #include "block_plan.hpp"
 #include "plan.hpp"
 #include "pp_block_gemm.h"
@@ -197,6 +198,10 @@ struct pp_conv_plan {
     // binary32 matrix-core kernel
     float* d_w32 = nullptr;
     float* d_bias32 = nullptr;
+    // binary32 3x3 kernel on the small matrix instruction
+    float* d_wquad = nullptr;
+    uint32_t* d_used = nullptr;
+    float* d_bias_quad = nullptr;
     // generic kernel
     int32_t* d_filt_off = nullptr;
     int32_t* d_kidx = nullptr;
@@ -221,7 +226,7 @@ bool upload(T** dst, const void* src, size_t bytes) {
 }
 
 void free_device(pp_conv_plan_t* p) {
-    void* bufs[] = {p->d_w32, p->d_bias32, p->d_xpad, p->d_ws3, p->d_stream, p->d_wave_off, p->d_chan_map, p->d_ws, p->d_counters, p->d_perm_pad, p->d_bias_pad, p->d_wpk, p->d_bias_mfma, p->d_filt_off, p->d_kidx,
+    void* bufs[] = {p->d_wquad, p->d_used, p->d_bias_quad, p->d_w32, p->d_bias32, p->d_xpad, p->d_ws3, p->d_stream, p->d_wave_off, p->d_chan_map, p->d_ws, p->d_counters, p->d_perm_pad, p->d_bias_pad, p->d_wpk, p->d_bias_mfma, p->d_filt_off, p->d_kidx,
                     p->d_kpat,   p->d_w,        p->d_tap,      p->d_perm,     p->d_bias};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -439,7 +444,11 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
         return PP_OK;
     }
     bool ok = true;
-    if (hp.tiled) {
+    if (hp.quads) {
+        ok = ok && upload(&p->d_wquad, hp.ql.wpk.data(), hp.ql.wpk.size() * 4);
+        ok = ok && upload(&p->d_used, hp.ql.used.data(), hp.ql.used.size() * 4);
+        ok = ok && upload(&p->d_bias_quad, hp.ql.bias_pad.data(), hp.ql.bias_pad.size() * 4);
+    } else if (hp.tiled && !hp.dense32) {
         const TiledLayout& tl = hp.tl;
         ok = ok && upload(&p->d_stream, tl.stream.data(), tl.stream.size() * 4);
         ok = ok && upload(&p->d_wave_off, tl.wave_off.data(), tl.wave_off.size() * 4);
@@ -597,6 +606,29 @@ static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, voi
     if (!fn) return PP_ERR_UNSUPPORTED;
     (void)hipGetLastError();
     hipLaunchKernelGGL(fn, dim3((unsigned)(a.per_xcd * 8)), dim3((unsigned)(64 * sh.wk * sh.wp)), 0, stream, a);
+    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
+}
+
+// One launch of the binary32 3x3 kernel.
+static pp_status_t launch_quads(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream) {
+    const HostPlan& hp = plan->hp;
+    K6Args a{};
+    a.x = static_cast<const float*>(x_dev);
+    a.y = static_cast<float*>(y_dev);
+    a.wpk = plan->d_wquad, a.used = plan->d_used, a.bias = plan->d_bias_quad;
+    a.n = n, a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w = hp.w, a.mc = (hp.w + 3) / 4;
+    a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
+    const int64_t pieces = (int64_t)n * hp.h * a.mc, ptiles = (pieces + 63) / 64;
+    int wk = 0;
+    (void)k6_model(hp.ql.groups, ptiles, hp.c_in, hp.ql.taps_used, &wk);
+    a.fgroups = hp.ql.groups;
+    if (pieces + 64 >= ((int64_t)1 << 31) || ptiles * a.fgroups >= ((int64_t)1 << 28)) return PP_ERR_SHAPE;
+    a.pieces = (int32_t)pieces, a.items = (int32_t)(ptiles * a.fgroups), a.per_xcd = (a.items + 7) / 8;
+    a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 4;
+    const k6_fn fn = k6_lookup(wk, 64 % a.mc != 0, hp.w % 4 != 0);
+    if (!fn) return PP_ERR_UNSUPPORTED;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(fn, dim3((unsigned)(a.per_xcd * 8)), dim3((unsigned)(64 * wk)), 0, stream, a);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
@@ -791,6 +823,7 @@ pp_status_t pp_conv_run(const pp_conv_plan_t* plan, const void* x_dev, void* y_d
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (hp.mfma) return launch_mfma(plan, x_dev, y_dev, n, stream);
     if (hp.dense32) return launch_f32(plan, x_dev, y_dev, n, stream);
+    if (hp.quads) return launch_quads(plan, x_dev, y_dev, n, stream);
     if (!hp.tiled) return launch_generic(plan, x_dev, y_dev, n, stream);
     // A plan that splits channels across workgroups owns a workspace for n_hint images: larger
     // batches go through it n_hint images at a time.
@@ -814,6 +847,7 @@ pp_status_t pp_conv_run_static(const pp_conv_plan_t* plan, const void* x_dev, vo
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (hp.mfma) return launch_mfma(plan, x_dev, y_dev, n, stream, false);      // no reduction split: that needs the plan's workspace
     if (hp.dense32) return launch_f32(plan, x_dev, y_dev, n, stream);
+    if (hp.quads) return launch_quads(plan, x_dev, y_dev, n, stream);
     if (!hp.tiled) return launch_generic(plan, x_dev, y_dev, n, stream);
     const TiledLayout& tl = hp.tl;
     if (tl.sw <= 1) return launch_tiled(plan, x_dev, y_dev, n, stream, nullptr, nullptr);

@@ -19,6 +19,8 @@
 
 #include <cstdint>
 
+#include "f32_rules.hpp"
+
 namespace ppc {
 
 struct K5ConvArgs {
@@ -354,17 +356,9 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 1
     }
 }
 
-// How a launch deals its work: wavefront tiles of 32 mt filters x 32 nt pixels (columns), wk wavefronts of a workgroup on
-// one tile's reduction, wp on different pixels.
-struct K5Shape {
-    int mt = 1, nt = 1, wk = 1, wp = 1;
-};
 typedef void (*k5_conv_fn)(K5ConvArgs);
 typedef void (*k5_list_fn)(K5ListArgs);
 k5_conv_fn k5_conv_lookup(const K5Shape& s);
 k5_list_fn k5_list_lookup(const K5Shape& s);
-// The shape for a layer of `rows32` 32-filter tiles, `cols` pixels and `units` reduction units per tile.
-K5Shape k5_pick_conv(int rows32, int64_t cols, int units);
-K5Shape k5_pick_list(int rows32, int64_t cols, int units);
 
 }  // namespace ppc

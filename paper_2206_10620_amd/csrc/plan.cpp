@@ -3,6 +3,8 @@
 // in which kernels are visited, and the code that visits them, is fixed ahead of time.
 #include "plan.hpp"
 
+#include "f32_rules.hpp"
+
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -342,6 +344,28 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
         return PP_OK;
     }
 
+    // A binary32 layer whose tuning is left to the library runs on the matrix cores: on the small instruction, which profits
+    // from the sparsity, or as a dense product where that is modelled to be faster (few pixels: it splits the work finer).
+    // The tiled kernel's layout is built all the same: it is what pp_conv_plan_query and pp_conv_plan_unpack describe.
+    // Measured, tiled / dense / small instruction: 256 channels 56x56 batch 1 at 0.3: 41 / 39 / 28 us; 256 channels 14x14 batch
+    // 32 at 0.5: 78 / 73 / 56; 64 channels 56x56 batch 32: 56 / 76 / 50; 64 channels 56x56 batch 1: 26 / 7 / 12.
+    {
+        const pp_conv_tuning_t none{};
+        pp_conv_tuning_t asked = t;
+        asked.autotune = 0;
+        const int mc = (hp.w + 3) / 4;
+        const int64_t images = 64 / ((int64_t)hp.h * std::min(mc, hp.w)) + 2;         // that the 64 pieces or pixels of a wavefront can touch
+        if (hp.dtype == PP_F32 && std::memcmp(&asked, &none, sizeof none) == 0 && images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31)) {
+            mark_quad_taps(hp);
+            int wk = 0;
+            const int64_t rows = (int64_t)hp.n_hint * hp.h;
+            hp.quads = k6_model(hp.ql.groups, (rows * mc + 63) / 64, hp.c_in, hp.ql.taps_used, &wk) <
+                       k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 7) / 8));
+            hp.dense32 = !hp.quads;
+            if (hp.quads) pack_quads(hp);
+            else build_f32_layout(hp);
+        }
+    }
     TiledLayout& tl = hp.tl;
     tl.covered = covered;
     const int eb = hp.dtype == PP_F16 ? 2 : 4;
@@ -558,10 +582,11 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     // ---- weight stream: one sequence of entries per (filter group, channel split) wavefront ----
     struct Item { int32_t ci; int32_t fl; int32_t slot; int64_t src; int32_t part; };
     tl.stream.clear();
+    tl.stream.reserve(((size_t)cn.k_kept + (size_t)G * KS * Q + Q + 2) * EW);      // more where patterns are covered in parts
     const int SW = tl.sw;
     tl.wave_off.assign((size_t)G * KS * SW, 0);
-    std::vector<Item> items;
-    std::vector<size_t> first(C + 1);
+    std::vector<Item> items, by_chan;
+    std::vector<size_t> first(C + 1), next;
     const int chan_word = hp.dtype == PP_F16 ? 3 : 1;      // where the channel word sits in an entry
     const uint32_t chan_stride_bytes = (uint32_t)(tg.chs * eb);
     auto push_entry = [&](uint32_t code, uint32_t chan, const float* w4) {
@@ -590,15 +615,13 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
                 for (int part = 0; part < (int)parts.size(); ++part) items.push_back(Item{cn.kidx[e], fl, parts[part].slot, e, part});
             }
         }
-        std::sort(items.begin(), items.end(), [](const Item& a, const Item& b) {
-            if (a.ci != b.ci) return a.ci < b.ci;
-            if (a.fl != b.fl) return a.fl < b.fl;
-            return a.part < b.part;
-        });
-        // first[ci] .. first[ci+1]: the group's kernels on channel ci
+        // by channel, the order of filters and parts kept; first[ci] .. first[ci+1]: the group's kernels on channel ci
         std::fill(first.begin(), first.end(), (size_t)0);
         for (const Item& k : items) ++first[k.ci + 1];
         for (int ci = 0; ci < C; ++ci) first[ci + 1] += first[ci];
+        next.assign(first.begin(), first.end() - 1);
+        by_chan.resize(items.size());
+        for (const Item& k : items) by_chan[next[k.ci]++] = k;
         for (int s = 0; s < KS; ++s) {
             for (int q = 0; q < Q; ++q) {
                 for (int sh = 0; sh < SW; ++sh)       // a share starts here
@@ -607,7 +630,7 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
                     const int ci = cmap[q * CC + cl];
                     if (ci < 0) continue;
                     for (size_t j = first[ci]; j < first[ci + 1]; ++j) {
-                        const Item& k = items[j];
+                        const Item& k = by_chan[j];
                         const uint32_t code = (uint32_t)(k.fl * tl.np + k.slot);
                         const uint32_t chan = j == first[ci] ? (uint32_t)cl * chan_stride_bytes : kSameChannel;
                         const CoverPart& part = tl.cover[cn.kpat[k.src]][k.part];
@@ -888,6 +911,43 @@ void build_f32_layout(HostPlan& hp) {
             const std::vector<int>& tl = taps[cn.kpat[e]];
             for (int j = 0; j < hp.taps; ++j)
                 fl.wpk[((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at] = cn.wpacked[(size_t)e * hp.taps + j];
+        }
+    }
+}
+
+// Which taps any filter of a quad uses, per channel.
+void mark_quad_taps(HostPlan& hp) {
+    QuadLayout& ql = hp.ql;
+    ql.groups = (hp.c_out + 15) / 16;
+    ql.used.assign((size_t)ql.groups * hp.c_in * 2, 0u);
+    const Canonical& cn = hp.canon;
+    for (int pos = 0; pos < hp.c_out; ++pos) {
+        const int co = cn.perm[pos], q = co % 16 / 4, shift = 9 * (q & 1);
+        uint32_t* used = ql.used.data() + (size_t)(co / 16) * hp.c_in * 2 + q / 2;
+        for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) used[2 * cn.kidx[e]] |= (uint32_t)hp.masks[cn.kpat[e]] << shift;
+    }
+    int64_t taps = 0;
+    for (uint32_t u : ql.used) taps += popcount64(u);
+    ql.taps_used = (double)taps / ((double)ql.groups * hp.c_in * 4);
+}
+
+// Weights of one (16-filter group, channel): the value of filter 4 q + i at tap t sits in lane 4 b + i, value v, where 9 q + t = 16 v + b.
+void pack_quads(HostPlan& hp) {
+    QuadLayout& ql = hp.ql;
+    ql.wpk.assign((size_t)ql.groups * hp.c_in * 256, 0.0f);
+    ql.bias_pad.assign((size_t)ql.groups * 16, 0.0f);
+    std::copy(hp.bias.begin(), hp.bias.end(), ql.bias_pad.begin());
+    const Canonical& cn = hp.canon;
+    for (int pos = 0; pos < hp.c_out; ++pos) {
+        const int co = cn.perm[pos], q = co % 16 / 4, i = co % 4;
+        float* group = ql.wpk.data() + (size_t)(co / 16) * hp.c_in * 256 + i * 4;
+        const float* src = cn.wpacked.data() + hp.filt_off[pos] * hp.taps;
+        for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
+            float* dst = group + (size_t)cn.kidx[e] * 256;
+            for (uint64_t mask = hp.masks[cn.kpat[e]]; mask; mask &= mask - 1) {
+                const int kr = 9 * q + __builtin_ctzll(mask);
+                dst[kr % 16 * 16 + kr / 16] = *src++;
+            }
         }
     }
 }

@@ -76,6 +76,15 @@ struct F32Layout {
     std::vector<float> bias_pad;            // [tiles * 32]
 };
 
+// Binary32 3x3 kernel on the small matrix instruction: weights by 16-filter group and channel.
+struct QuadLayout {
+    int groups = 0;                         // of 16 filters
+    std::vector<float> wpk;                 // [groups][c_in][64][4]
+    std::vector<uint32_t> used;             // [groups][c_in][2] taps that any filter of a quad uses
+    std::vector<float> bias_pad;            // [groups * 16]
+    double taps_used = 0.0;                 // mean over quads and channels
+};
+
 struct HostPlan {
     int32_t c_in = 0, c_out = 0, h = 0, w = 0, n_hint = 1, num_patterns = 0, taps = 4;
     int32_t ks = 3, stride = 1;         // kernel size, stride
@@ -92,8 +101,10 @@ struct HostPlan {
     TiledLayout tl;
     bool mfma = false;
     MfmaLayout ml;
-    bool dense32 = false;               // binary32 layer that runs on the matrix cores
+    bool dense32 = false;               // binary32 layer that runs as a dense product on the matrix cores
     F32Layout fl;
+    bool quads = false;                 // binary32 3x3, stride 1 layer that runs on the small matrix instruction
+    QuadLayout ql;
     // generic kernel tables
     std::vector<int32_t> filt_off;      // [c_out+1] prefix of kcount
     std::vector<int8_t> tap_dyx;        // [P*taps*2] (dy, dx) per tap
@@ -111,6 +122,9 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp);
 pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp);
 // Pack the weights of a binary32 layer for the matrix-core kernel (hp.fl).
 void build_f32_layout(HostPlan& hp);
+// Pack the weights of a binary32 3x3, stride 1 layer for the small matrix instruction (hp.ql).
+void mark_quad_taps(HostPlan& hp);
+void pack_quads(HostPlan& hp);
 // Decode tl.stream back to canonical order.
 pp_status_t unpack_stream(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, float* w);
 
