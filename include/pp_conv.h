@@ -92,7 +92,7 @@ typedef struct {
     /* matrix-core kernel (variant 3) */
     int32_t tile_rows;      /* TR: rows of convolution outputs per workgroup tile (rows of the batch laid out as one tall image) */
     int32_t tile_cols;      /* TC: columns per workgroup tile; TR * TC <= 32 * tiles_per_wave * wg_waves */
-    int32_t tiles_per_wave; /* NTW: 32-pixel MFMA column tiles per wavefront (2 or 4) */
+    int32_t tiles_per_wave; /* NTW: 32-pixel MFMA column tiles per wavefront (1, 2 or 4) */
     int32_t wg_waves;       /* wavefronts per workgroup (4 or 8), all on the same 64 filters; 8 only with NTW = 4 */
     int32_t autotune;       /* 1: pp_conv_plan times candidate variants and parameters on the device (the rules' own
                                choice, the other kernels that take the layer, other workgroup sizes and tile shapes;

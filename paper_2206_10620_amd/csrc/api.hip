@@ -31,17 +31,17 @@ k1_launch_fn k1_lookup_f16_p16_r1(int f, int lw, bool direct);
 k1_launch_fn k1_lookup_f16_p16_r2(int f, int lw, bool direct);
 k1_launch_fn k1_lookup_f16_p16_r4(int f, int lw, bool direct);
 
-k2_launch_fn k2_lookup_k1(int stride, int ntw, int waves, bool pairs);
-k2_launch_fn k2_lookup_k3(int stride, int ntw, int waves, bool pairs);
-k2_launch_fn k2_lookup_k5(int stride, int ntw, int waves, bool pairs);
-k2_launch_fn k2_lookup_k7(int stride, int ntw, int waves, bool pairs);
+k2_launch_fn k2_lookup_k1(int stride, int ntw, int waves, int units, bool pairs);
+k2_launch_fn k2_lookup_k3(int stride, int ntw, int waves, int units, bool pairs);
+k2_launch_fn k2_lookup_k5(int stride, int ntw, int waves, int units, bool pairs);
+k2_launch_fn k2_lookup_k7(int stride, int ntw, int waves, int units, bool pairs);
 
-k2_launch_fn k2_lookup(int ks, int stride, int ntw, int waves, bool pairs) {
+k2_launch_fn k2_lookup(int ks, int stride, int ntw, int waves, int units, bool pairs) {
     switch (ks) {
-        case 1: return k2_lookup_k1(stride, ntw, waves, pairs);
-        case 3: return k2_lookup_k3(stride, ntw, waves, pairs);
-        case 5: return k2_lookup_k5(stride, ntw, waves, pairs);
-        case 7: return k2_lookup_k7(stride, ntw, waves, pairs);
+        case 1: return k2_lookup_k1(stride, ntw, waves, units, pairs);
+        case 3: return k2_lookup_k3(stride, ntw, waves, units, pairs);
+        case 5: return k2_lookup_k5(stride, ntw, waves, units, pairs);
+        case 7: return k2_lookup_k7(stride, ntw, waves, units, pairs);
         default: return nullptr;
     }
 }
@@ -402,7 +402,7 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
             p->launch3 = k3_lookup(hp.ml.g3.sw, hp.ml.g3.waves, false, hp.pool);
             if (hp.ml.ksplit > 1) p->launch3_split = k3_lookup(hp.ml.g3.sw, hp.ml.g3.waves, true, false);
         }
-        else p->launch2 = k2_lookup(hp.ks, hp.stride, hp.ml.ntw, hp.ml.waves, hp.ml.pairs);
+        else p->launch2 = k2_lookup(hp.ks, hp.stride, hp.ml.ntw, hp.ml.waves, hp.ml.units, hp.ml.pairs);
         if (!p->launch2 && !p->launch3) {
             delete p;
             return PP_ERR_UNSUPPORTED;

@@ -774,17 +774,18 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         if (hp.pool && (ml.po & 1)) ++ml.po;
         const int64_t vrows = (int64_t)hp.n_hint * ml.po - (ml.po - hp.ho);
         const int step = hp.pool ? 2 : 1;
-        ml.pairs = (hp.w & 1) == 0;
+        ml.pairs = hp.w > 1;
         auto staged_cols = [&](int tc) { return ((tc - 1) * S + KS + 2) & ~1; };
         auto pair_groups = [&](int tr, int tc) { return (((tr - 1) * S + KS) * (staged_cols(tc) / 2) + 15) / 16; };
-        auto lds_need = [&](int tr, int tc) -> int64_t {
+        // (a request for a tile is held to a limit that leaves `spare` bytes)
+        auto lds_need = [&](int tr, int tc, int64_t spare) -> int64_t {
             const int64_t xbuf = (int64_t)pair_groups(tr, tc) * 32 * kMfmaPixelBytes;
-            const int64_t main = 2 * xbuf + 2 * ml.wbuf_bytes;
+            const int64_t main = 2 * xbuf + spare;
             const int64_t out = (int64_t)kMfmaFilters * ((tr * tc + 7) / 8 * 8) * 2;
             return std::max(main, out) + kMfmaFilters * 4;      // + the workgroup's bias values
         };
         auto fits = [&](int tr, int tc, int waves, int ntw) {
-            return lds_need(tr, tc) <= kMfmaMaxDynamicLds && (pair_groups(tr, tc) + waves / 2 - 1) / (waves / 2) <= mfma_max_units(waves, ntw);
+            return lds_need(tr, tc, 2 * ml.wbuf_bytes) <= kMfmaMaxDynamicLds && (pair_groups(tr, tc) + waves / 2 - 1) / (waves / 2) <= mfma_max_units(waves, ntw);
         };
         auto evaluate = [&](int waves, int ntw, int& btr, int& btc, int64_t& bwgs) {
             const int slots = 32 * ntw * waves;
@@ -810,25 +811,41 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
                 }
             }
         };
-        if (t.tiles_per_wave != 0 && t.tiles_per_wave != 2 && t.tiles_per_wave != 4) return PP_ERR_UNSUPPORTED;
+        if (t.tiles_per_wave != 0 && t.tiles_per_wave != 1 && t.tiles_per_wave != 2 && t.tiles_per_wave != 4) return PP_ERR_UNSUPPORTED;
         if (t.wg_waves != 0 && t.wg_waves != 4 && t.wg_waves != 8) return PP_ERR_UNSUPPORTED;
-        // Larger tiles re-read less (weights once per tile, a thinner halo) and eight wavefronts hide each
-        // other's LDS and barrier latency, but the layer needs enough workgroups to fill 256 compute units.
-        static const int kShapes[3][2] = {{8, 4}, {4, 4}, {4, 2}};
         int btr = 0, btc = 0;
         ml.waves = 0;
-        for (int k = 0; k < 3; ++k) {
+        auto take = [&](int waves, int ntw, int tr, int tc) { ml.waves = waves, ml.ntw = ntw, btr = tr, btc = tc; };
+        if (!t.tiles_per_wave && t.wg_waves != 8 && !t.tile_rows && !t.tile_cols) {
+            // One or two column tiles per wavefront: a workgroup of the larger shape takes 1.4 times as long (measured 1.35
+            // alone on a compute unit, 1.47 with neighbours) and covers up to twice the pixels, less where its tile is cut
+            // short by the staging registers.  5x5, 64 -> 64 channels, batch 8: 56x56 maps 15.3 us against 18.8, 150x150 maps
+            // 62 against 47.  More column tiles or wavefronts were slower on all 18 layers tried (3x3 to 7x7, batch 1 to 32:
+            // 28 to 124 us against 7 to 47) and are taken on request only.
+            double best = 1e300;
+            for (int ntw : {1, 2}) {
+                int tr = 0, tc = 0;
+                int64_t wgs = 0;
+                evaluate(4, ntw, tr, tc, wgs);
+                const double rounds = (double)((wgs + 255) / 256) * (ntw == 1 ? 1.0 : 1.4);
+                if (tr != 0 && rounds < best) {
+                    best = rounds;
+                    take(4, ntw, tr, tc);
+                }
+            }
+        }
+        // A request for some of the shape's or the tile's sizes: the largest workgroup of which the layer has enough to fill
+        // 256 compute units twice.
+        static const int kShapes[4][2] = {{8, 4}, {4, 4}, {4, 2}, {4, 1}};
+        for (int k = 0; ml.waves == 0 && k < 4; ++k) {
             const int waves = kShapes[k][0], ntw = kShapes[k][1];
-            if ((t.wg_waves && t.wg_waves != waves) || (t.tiles_per_wave && t.tiles_per_wave != ntw)) continue;
+            if ((t.wg_waves && t.wg_waves != waves) || (t.tiles_per_wave ? t.tiles_per_wave != ntw : ntw == 1)) continue;
             int tr = 0, tc = 0;
             int64_t wgs = 0;
             evaluate(waves, ntw, tr, tc, wgs);
-            if (tr == 0) continue;
-            ml.waves = waves;
-            ml.ntw = ntw;
-            btr = tr;
-            btc = tc;
-            if (wgs >= 480) break;          // otherwise try the next smaller shape (the last one stands)
+            const bool smaller = (!t.wg_waves || t.wg_waves == 4) && (!t.tiles_per_wave ? k < 2 : t.tiles_per_wave == 4 && k == 0);       // shapes left to try
+            if (tr == 0 || (wgs < 480 && smaller)) continue;
+            take(waves, ntw, tr, tc);
         }
         if (ml.waves == 0) return PP_ERR_UNSUPPORTED;
         ml.tr = btr;
@@ -843,7 +860,8 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         ml.twpa = staged_cols(ml.tc);
         ml.xbuf_bytes = pair_groups(ml.tr, ml.tc) * 32 * kMfmaPixelBytes;
         ml.out_pitch = (ml.tr * ml.tc + 7) / 8 * 8;
-        ml.lds_bytes = lds_need(ml.tr, ml.tc);
+        ml.lds_bytes = lds_need(ml.tr, ml.tc, 0);
+        ml.units = (pair_groups(ml.tr, ml.tc) + ml.waves / 2 - 1) / (ml.waves / 2);
         const int ow = hp.out_w, otc = hp.pool ? ml.tc / 2 : ml.tc;
         ml.gw = 1;
         for (int g = 8; g > 1; g /= 2)

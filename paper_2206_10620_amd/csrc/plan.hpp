@@ -56,7 +56,8 @@ struct MfmaLayout {
     K3Geom g3;                        // ... with this geometry
     int cpad = 0;                     // ... on this many input channels: c_in rounded up to whole chunks (a larger value than c_in means x is copied into a zero-padded buffer first)
     int ksplit = 1;                   // ... and this many workgroups sharing a tile's reduction (partial sums to a workspace)
-    bool pairs = true;                // even image width: input staged as aligned 32-bit pixel pairs
+    bool pairs = true;                // images more than one pixel wide: input loaded as 32-bit pixel pairs
+    int units = 0;                    // staging units (16 pixel pairs x 8 channels) of a wavefront
     int po = 0;                       // rows per image in the tall virtual output image (ho + separator rows)
     int trp = 0, twpa = 0;            // staged input rows per tile: (tr-1)*stride + K; staged columns: (tc-1)*stride + K + 2, rounded down to even
     int fb = 0, q = 0;                // filter blocks of 64, channel chunks of 16
