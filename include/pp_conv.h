@@ -101,7 +101,8 @@ typedef struct {
                                section 2.3.1 decided by measurement.  Takes some milliseconds per candidate and
                                synchronises with its own stream only.  Ignored with PP_FLAG_HOST_ONLY.  The plan
                                reports chosen.autotune = 1 */
-    int32_t mfma_kind;      /* which matrix-core kernel: 0 auto; 3 the product kernel of pp_block_gemm.h for 1x1 layers
+    int32_t mfma_kind;      /* which matrix-core kernel: 0 auto (a layer that 2 takes, with every field here zero, reports 2
+                               and its parameters, and runs on 1 where that is modelled to be faster); 3 the product kernel of pp_block_gemm.h for 1x1 layers
                                (stride 1, no pool, h * w a multiple of 8: one matrix product per image, connectivity
                                pruning as its column pruning); 1 the general one (tiles transposed in registers on
                                their way into LDS; any kernel size, stride, channel count, fused pool); 2 the

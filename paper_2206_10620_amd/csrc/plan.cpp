@@ -679,6 +679,7 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
     if (t.mfma_kind < 0 || t.mfma_kind > 3 || (t.mfma_kind == 2 && !direct_ok)) return PP_ERR_UNSUPPORTED;
     // A request for a tile the direct kernel has no geometry for goes to the general kernel, unless the
     // direct one was asked for by name.
+    double direct_us = 0.0;
     auto direct_layout = [&]() -> bool {
         // Segment width: the one that computes the fewest columns per image row (a segment of sw computed
         // columns yields sw - 2 outputs).  Segments per tile row: the divisor of the workgroup's units
@@ -761,11 +762,29 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         ml.ksplit = ks;
         hp.chosen.split_k = ks;
         ml.cpad = ml.q * kMfmaChunk;
+        // Modelled microseconds: two four-wavefront workgroups (one of eight) to a compute unit, each a fixed part and one
+        // per chunk; the copy that pads the channels is a launch of its own.
+        const double load = std::max(1.0, tiles * (waves == 8 ? 2 : 1) / 512.0);
+        const bool ragged = hp.h * hp.w % 8 != 0;
+        direct_us = 1.2 + load * (5.6 + 1.3 * ml.q + (ragged ? 0.5 : 0.0));
+        if (ml.cpad != hp.c_in) direct_us += 1.5 + 2e-6 * hp.n_hint * hp.c_in * hp.h * hp.w * (ragged ? 1.1 : 0.5);
         return true;
     };
     ml.direct = direct_ok && t.mfma_kind != 1 && t.mfma_kind != 3 && direct_layout();
     if (t.mfma_kind == 2 && !ml.direct) return PP_ERR_UNSUPPORTED;
     if (t.split_k > 1 && !ml.direct) return PP_ERR_UNSUPPORTED;      // only the direct-load kernel splits the reduction
+    // A layer left to the library that does not split its reduction runs on whichever of the two is modelled faster; the plan
+    // reports the direct kernel's parameters either way.  Small maps, widths off the segments and padded channels favour the
+    // general kernel (no padding launch, tiles of any shape), large pooled or whole-chunk layers the direct one.  Both models
+    // were fitted to 160 layers (batch 1 to 32, 16 to 512 channels, 7x7 to 880x764, pooled and not): 15 and 9 % rms; of the
+    // 102 layers the rule moves none loses more than 3 %, the mean gain over all 160 is 1.24.  97 -> 33 channels, 64x53:
+    // 20.5 -> 11.9 us; 256 -> 256, 14x14, batch 32: 27.2 -> 23.1; it leaves 64 -> 128, 112x112, batch 8 (25 us) alone.
+    const bool left_to_us = t.variant == 0 && !t.mfma_kind && !t.split_k && !t.wg_waves && !t.tiles_per_wave && !t.tile_rows && !t.tile_cols;
+    const bool either = ml.direct && left_to_us && ml.ksplit == 1 && hp.h < 65000;      // (rows of a tile past that count overflow the general kernel's 16-bit division)
+    const MfmaLayout direct_ml = ml;
+    const pp_conv_tuning_t direct_chosen = hp.chosen;
+    double general_us = 0.0;
+    if (either) ml.direct = false;
     // The batch is one tall virtual image: image n's output row oy is virtual row n*po + oy, and the
     // matching input rows start at virtual input row n*po*S, so that a tile may straddle images; the
     // rows between images read as zeros (they are the padding) and their outputs are not stored.
@@ -831,6 +850,8 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
                 if (tr != 0 && rounds < best) {
                     best = rounds;
                     take(4, ntw, tr, tc);
+                    const double load = std::max(1.0, wgs / 256.0);
+                    general_us = 6.1 + load * (ntw == 1 ? 0.88 * ml.q + (hp.pool ? 0.3 : 0.0) : 3.2 + 1.23 * ml.q + (hp.pool ? 1.4 : 0.0));      // of a 3x3, stride-1 layer
                 }
             }
         }
@@ -874,6 +895,11 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         hp.chosen.tile_cols = ml.tc;
         hp.chosen.tiles_per_wave = ml.ntw;
         hp.chosen.mfma_kind = 1;
+    }
+    if (either) {
+        if (general_us == 0.0 || general_us >= 0.95 * direct_us) ml = direct_ml;
+        else ml.ksplit = 1, ml.cpad = hp.c_in;
+        hp.chosen = direct_chosen;
     }
 
     // weights: scatter the kept kernels into zero-filled operand fragments

@@ -2,11 +2,12 @@
 pixels wide, odd widths whose last column is loaded one column early, single-pixel images, one to four chunks of channels
 (whole and partial), tiles at both ends of the staging registers, both workgroup shapes.  Tolerance: the binary16 gate of
 2e-3, four units in the last place of the stored type."""
+import numpy as np
 import pytest
 
 import synth
 import paper_2206_10620_amd as pp
-from gpu_util import check_layer
+from gpu_util import check_layer, run_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +36,21 @@ def test_the_rule_takes_both_shapes():
         rep, _ = check_layer(lay, tuning=pp.Tuning(variant=3, mfma_kind=1), label=f"shape{hw}")
         return rep["chosen"]["tiles_per_wave"]
     assert chosen(1, 20) == 1 and chosen(3, 120) == 2
+
+
+# n, c_in, c_out, h, w, pool, whether the general kernel runs it: small and odd maps, padded channels, pools; and large whole-chunk layers
+AUTO = [(1, 1, 1, 2, 2, False, True), (1, 97, 33, 64, 53, False, True), (4, 40, 20, 7, 7, False, True), (2, 64, 96, 33, 29, False, True), (3, 30, 70, 20, 24, True, True),
+        (9, 64, 256, 14, 14, False, True), (2, 20, 64, 113, 111, False, True), (8, 16, 64, 112, 112, True, False), (2, 64, 64, 224, 224, False, False)]
+
+
+@pytest.mark.parametrize("layer", AUTO, ids=lambda v: "x".join(str(int(i)) for i in v))
+def test_the_rule_between_the_matrix_core_kernels(layer):
+    n, c_in, c_out, h, w, pool, general = layer
+    print(f"mfma auto {layer}", flush=True)
+    lay = synth.random_pruned_layer_k("auto", n, c_in, c_out, h, w, "f16", 3, synth.PSET8, 0.5, 0.1, seed=n + c_in, pool=pool)
+    for hint in (n, 1):
+        rep, y = check_layer(lay, n_hint=hint, label=f"auto{layer}")
+        assert rep["chosen"]["mfma_kind"] == 2
+    _, y = check_layer(lay, label=f"auto{layer}")
+    same, _ = run_layer(lay, lay.make_input(), tuning=pp.Tuning(variant=3, mfma_kind=1 if general else 2))
+    assert np.array_equal(y, same)               # the kernel it is said to run: the two sum in different orders
