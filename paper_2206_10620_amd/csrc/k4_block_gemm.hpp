@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "block_plan.hpp"
+#include "block_rules.hpp"
 
 namespace ppc {
 
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const uint32_t row_bytes = (uint32_t)a.n * 2u;          // x is smaller than 4 GB: byte offsets fit 32 bits
     const uint32_t piece_off = RAGGED ? lane16 + (uint32_t)col0 * 2u : lane16;
     const bool piece_ok = col0 + lane * 8 < a.n;            // (columns of a piece past the row's end reach outputs that are not stored only)
-    const uint32_t edge_from = a.x_bytes > row_bytes + 14u ? a.x_bytes - row_bytes - 14u : 0u;
+    const uint32_t edge_from = k4_edge_from(a.x_bytes, row_bytes);
     bool drain = false;                                     // an instruction was skipped: the wait counts no longer hold, wait for everything
     const bool wload = wave < 2;                            // wavefronts 0 and 1 also fetch the two weight operands
 
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const uint32_t off = (uint32_t)rows[i] * row_bytes + piece_off;
             const uint32_t dst = (uint32_t)((wave + 4 * i) * kK4RowPitch);
             if (RAGGED && (uint32_t)rows[i] * row_bytes >= edge_from) {               // a row whose last piece may end behind x
-                const bool edge = piece_ok && off > a.x_bytes - 16u;
+                const bool edge = piece_ok && k4_piece_ends_behind(off, a.x_bytes);
                 const bool mine = piece_ok && !edge;
                 if (__builtin_amdgcn_ballot_w64(mine) == 0) drain = true;
                 if (mine) k4_dma16(off, xsrc, st + dst);
@@ -326,8 +327,6 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(2))) vo
         piece_off[q] = (uint32_t)c * 2u;
         piece_ok[q] = c < a.n;
     }
-    // (x of less than 16 bytes: every piece takes the guarded path)
-    const uint32_t last_off = a.x_bytes >= 16u ? a.x_bytes - 16u : 0u;
     bool drain = false;
     auto issue_list = [&](int seg) {                         // 128 entries: eight chunks
         if (lane < 32) k4_dma16(lane16, lsrc + (int64_t)seg * 512, lds0 + lists + (uint32_t)((seg & 1) * 512));
@@ -348,12 +347,12 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
         for (int q = 0; q < NT; ++q) {
             off[q] = __umul24(entry[q], row_bytes) + piece_off[q];                      // the launcher sees to it that both fit 24 bits
-            end = end || (piece_ok[q] && (off[q] > last_off || a.x_bytes < 16u));
+            end = end || (piece_ok[q] && k4_piece_ends_behind(off[q], a.x_bytes));
         }
         if (a.ragged && __builtin_amdgcn_ballot_w64(end) != 0) {
 #pragma unroll
             for (int q = 0; q < NT; ++q) {
-                const bool edge = piece_ok[q] && (off[q] > last_off || a.x_bytes < 16u), mine = piece_ok[q] && !edge;
+                const bool edge = piece_ok[q] && k4_piece_ends_behind(off[q], a.x_bytes), mine = piece_ok[q] && !edge;
                 if (__builtin_amdgcn_ballot_w64(mine) == 0) drain = true;
                 if (mine) k4_dma16(off[q], xsrc, st + (uint32_t)(q * 1024));
                 if (edge) k4_edge_piece(xsrc, off[q], a.x_bytes, mine_lds + stage * SB + q * 1024 + lane16);
