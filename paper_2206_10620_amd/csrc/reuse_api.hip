@@ -21,6 +21,9 @@
 #include <vector>
 
 #include "pp_deep_reuse.h"
+#include "reuse_rules.hpp"
+
+using namespace ppc;
 
 namespace {
 
@@ -152,7 +155,6 @@ __global__ __launch_bounds__(256) void reuse_gather(const uint16_t* __restrict__
 // ---- the tiled path ----
 
 constexpr int kTileWaves = 4;
-constexpr int kGatherMaxRows = 2048;                                       // rows of a workgroup of the gather, at most
 constexpr int reuse_rows_per_lane(int L) { return L <= 16 ? 2 : 1; }      // a wavefront's tile: 64 or 128 rows of one segment, at most 8 KB
 
 typedef uint32_t reuse_u4 __attribute__((ext_vector_type(4)));
@@ -263,7 +265,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void reuse_hash_tiled(const float*
 template <int L>
 __global__ __launch_bounds__(256) void reuse_products_packed(const float* __restrict__ x, const float* __restrict__ w, const int32_t* __restrict__ rep,
                                                              const uint16_t* __restrict__ sig, float* __restrict__ P, uint16_t* __restrict__ ids,
-                                                             int32_t* __restrict__ used, int32_t* __restrict__ rep_out, int n, int row_pitch, int k, int m, int G) {
+                                                             int32_t* __restrict__ used, int32_t* __restrict__ rep_out, int n, int numbered, int row_pitch, int k, int m, int G) {
     __shared__ int wave_sum[4];
     __shared__ int list_n;
     __shared__ int list_rep[512];
@@ -311,8 +313,7 @@ __global__ __launch_bounds__(256) void reuse_products_packed(const float* __rest
     __syncthreads();
     // Eight rows per thread and turn: 16-byte words of both tables.  Rows from n to the end of the gather's last workgroup
     // are numbered 0, so that their (unused) sums read inside the tables.
-    const int n_pad = (n + kGatherMaxRows - 1) / kGatherMaxRows * kGatherMaxRows;
-    for (int i = ((int)blockIdx.y * 256 + tid) * 8; i < n_pad; i += parts * 256 * 8) {
+    for (int i = ((int)blockIdx.y * 256 + tid) * 8; i < numbered; i += parts * 256 * 8) {
         const reuse_u4 v = *reinterpret_cast<const reuse_u4*>(sig + (int64_t)s * row_pitch + i);
         reuse_u4 o;
 #pragma unroll
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(256) void reuse_products_packed(const float* __rest
 // 64 columns, is read from memory instead): the rows' reads are then LDS reads, 128 bytes per clock and compute unit
 // instead of what L2 delivers (925 MB of reads for 100 352 rows of 36 segments: 55 us out of L2).  The kernel also empties
 // the election table for the next pass.
-constexpr int kGatherThreads = 512, kGatherSlots = 4, kGatherProducts = 12 * 1024;
+constexpr int kGatherSlots = 4, kGatherProducts = 12 * 1024;
 template <int RPT>
 __global__ __launch_bounds__(kGatherThreads) void reuse_gather_packed(const uint16_t* __restrict__ ids, const float* __restrict__ P,
                                                                       const int32_t* __restrict__ used, const float* __restrict__ bias, float* __restrict__ y,
@@ -448,7 +449,7 @@ template <int L> hash_tiled_fn pick_hash_tiled(int seg_len) {
     if constexpr (L == 0) return nullptr;
     else return seg_len == L ? reuse_hash_tiled<L> : pick_hash_tiled<L - 4>(seg_len);
 }
-typedef void (*products_fn)(const float*, const float*, const int32_t*, const uint16_t*, float*, uint16_t*, int32_t*, int32_t*, int, int, int, int, int);
+typedef void (*products_fn)(const float*, const float*, const int32_t*, const uint16_t*, float*, uint16_t*, int32_t*, int32_t*, int, int, int, int, int, int);
 template <int L> products_fn pick_products(int seg_len) {
     if constexpr (L == 0) return nullptr;
     else return seg_len == L ? reuse_products_packed<L> : pick_products<L - 4>(seg_len);
@@ -475,7 +476,7 @@ struct pp_reuse_plan {
     bool tiled = false;                 // L and m multiples of 4: the tiled path
     int32_t* d_rep_out = nullptr;       // ... representatives of the last run (d_rep, the election table, is left empty by each run)
     uint16_t* d_ids = nullptr;          // ... [S][row_pitch] number of a row's cluster in the segment (d_sig has the same layout then)
-    int row_pitch = 0;                  // ... n_max rounded up to kGatherMaxRows
+    int row_pitch = 0;                  // ... room for the rows of the gather's last workgroup
     int32_t* d_used = nullptr;          // ... [S] clusters of a segment
 };
 
@@ -522,7 +523,7 @@ pp_status_t pp_reuse_plan(const pp_reuse_desc_t* d, pp_reuse_plan_t** out_plan) 
             bias = zero_bias.data();
         }
         p->tiled = d->seg_len % 4 == 0 && d->m % 4 == 0;
-        p->row_pitch = p->tiled ? (d->n_max + kGatherMaxRows - 1) / kGatherMaxRows * kGatherMaxRows : d->n_max;
+        p->row_pitch = p->tiled ? reuse_row_pitch(d->n_max) : d->n_max;
         bool ok = put(&p->d_w, d->weights, (size_t)d->k * d->m * 4) && put(&p->d_bias, bias, (size_t)d->m * 4) &&
                   put(&p->d_hyper, d->hyperplanes, (size_t)S * d->hash_bits * d->seg_len * 4, 256) &&
                   put(&p->d_sig, nullptr, (size_t)S * p->row_pitch * 2) && put(&p->d_rep, nullptr, (size_t)S * G * 4) &&
@@ -571,18 +572,12 @@ pp_status_t pp_reuse_run(const pp_reuse_plan_t* p, const void* x_dev, void* y_de
                            items, per_xcd);
         // enough workgroups per segment for four in all on every other compute unit, and for lists of 512 clusters
         const int parts = std::max(std::max(1, G / 512), std::min(16, 512 / S));
+        const ReuseGather gs = reuse_gather_shape(n, p->m);
         hipLaunchKernelGGL(pick_products<kMaxSeg>(p->L), dim3((unsigned)S, (unsigned)parts), dim3(256), 0, stream, x, p->d_w, p->d_rep, p->d_sig, p->d_P, p->d_ids, p->d_used, p->d_rep_out, n,
-                           p->row_pitch, p->k, p->m, G);
-        // rows per lane: the fewest rounds of workgroups, each worth its rows and about four more for the work per segment
-        const int groups = kGatherThreads / (std::min(p->m, 64) / 4), blocks_y = (p->m + 63) / 64;
-        auto wgs = [&](int rpt) { return (int64_t)((n + groups * rpt - 1) / (groups * rpt)) * blocks_y; };
-        auto cost = [&](int rpt) { return groups * rpt > kGatherMaxRows ? INT64_MAX : ((wgs(rpt) + 255) / 256) * (rpt + 4); };
-        int rpt = 4;
-        if (cost(8) < cost(rpt)) rpt = 8;
-        if (cost(16) < cost(rpt)) rpt = 16;
-        const dim3 grid((unsigned)(wgs(rpt) / blocks_y), (unsigned)blocks_y);
-        const size_t gather_lds = (size_t)kGatherSlots * (kGatherProducts + (groups * rpt * 2 + 1023) / 1024 * 1024);
-        hipLaunchKernelGGL(rpt == 16 ? reuse_gather_packed<16> : rpt == 8 ? reuse_gather_packed<8> : reuse_gather_packed<4>, grid, dim3(kGatherThreads), gather_lds, stream, p->d_ids,
+                           reuse_numbered_rows(gs), p->row_pitch, p->k, p->m, G);
+        const dim3 grid((unsigned)gs.wgs_x, (unsigned)gs.blocks_y);
+        const size_t gather_lds = (size_t)kGatherSlots * (kGatherProducts + (gs.rows * 2 + 1023) / 1024 * 1024);
+        hipLaunchKernelGGL(gs.rpt == 16 ? reuse_gather_packed<16> : gs.rpt == 8 ? reuse_gather_packed<8> : reuse_gather_packed<4>, grid, dim3(kGatherThreads), gather_lds, stream, p->d_ids,
                            p->d_P, p->d_used, p->d_bias, y, p->d_rep, n, p->row_pitch, p->m, S, G, relu);
         return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
     }

@@ -3,6 +3,7 @@
 #include <cstdio>
 
 #include "block_rules.hpp"
+#include "reuse_rules.hpp"
 
 using namespace ppc;
 
@@ -29,8 +30,21 @@ static int block_pieces() {
     return 0;
 }
 
+// Every row whose number the gather's lanes read has one, and the tables hold it, whatever n_max the plan was made for.
+static int gather_rows() {
+    for (int m = 4; m <= 132; m += 4)
+        for (int n = 1; n < 140000; n = n < 9000 ? n + 1 : n * 17 / 16 + 1) {
+            const ReuseGather g = reuse_gather_shape(n, m);
+            if (g.rows < 1 || g.rows > kGatherMaxRows || g.wgs_x * g.rows < n) return fail("gather does not cover the rows", m, n, g.rows);
+            if (reuse_numbered_rows(g) < g.wgs_x * g.rows) return fail("gather reads a row without a number", m, n, g.rows);
+            if (reuse_numbered_rows(g) % 8 || reuse_numbered_rows(g) > reuse_row_pitch(n)) return fail("numbered rows outside the tables", m, n, g.rows);
+            if (reuse_row_pitch(n) % 8) return fail("segments off the 16-byte words", m, n, 0);
+        }
+    return 0;
+}
+
 int main() {
-    if (block_pieces()) return 1;
+    if (block_pieces() || gather_rows()) return 1;
     std::printf("ok\n");
     return 0;
 }

@@ -26,6 +26,13 @@ def test_output_blocks_and_row_counts(m, n):
     check(synth.random_reuse_layer("m", n, 48, m, 16, 9, seed=m + n, prototypes=20, noise=0.02, relu=bool(n & 1)))
 
 
+@pytest.mark.parametrize("m", [12, 28, 60])
+@pytest.mark.parametrize("n", [2041, 2048, 6144])
+def test_workgroups_that_end_behind_the_last_whole_2048_rows(m, n):
+    # 680, 292 and 544 rows a workgroup; the table of numbers is as short as the plan makes it, and a longer run came before
+    check(synth.random_reuse_layer("end", n, 48, m, 16, 9, seed=m + n, prototypes=20, noise=0.02))
+
+
 @pytest.mark.parametrize("hash_bits", [1, 6, 12])
 def test_many_clusters(hash_bits):
     # unrelated vectors: up to 4096 clusters in a segment, read from memory instead of LDS
