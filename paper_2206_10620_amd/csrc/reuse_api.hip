@@ -1,11 +1,12 @@
 // Deep reuse (paper, section 2.3.2): kernels and C ABI (include/pp_deep_reuse.h).
 //
-// Neuron vectors whose length is a multiple of 4 and outputs whose number is a multiple of 4 (three launches per pass):
+// Both paths are four launches per pass and begin with an empty election table, whatever the pass before left:
+//   reuse_clear           representatives <- "none"
+// Neuron vectors whose length is a multiple of 4 and outputs whose number is a multiple of 4:
 //   reuse_hash_tiled      signatures, segment by segment for tiles of rows staged in LDS; elects each cluster's lowest row
 //   reuse_products_packed numbers a segment's clusters in ascending signature order and computes their products
 //   reuse_gather_packed   y[i][:] = act(bias + sum_s P[s][cluster(i, s)][:]) with a segment's products in LDS
-// Anything else (four launches per pass):
-//   reuse_clear           representatives <- "none"
+// Anything else:
 //   reuse_hash            one lane per neuron vector, segments fastest (a wavefront reads one contiguous stretch of x),
 //                         hyperplanes in LDS; the lowest row of every cluster is elected with integer minimum atomics
 //   reuse_products        P[s][g][:] = x[rep(s,g)][segment s] . W[segment s][:]
@@ -31,9 +32,10 @@ constexpr int kMaxSeg = 32;
 
 typedef const __attribute__((address_space(4))) float* const_f32;
 
+// count is rounded up to whole 16-byte words (the table has room for them)
 __global__ __launch_bounds__(256) void reuse_clear(int32_t* rep, int count) {
-    const int e = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (e < count) rep[e] = INT_MAX;
+    const int e = (int)(blockIdx.x * 256 + threadIdx.x) * 4;
+    if (e < count) *reinterpret_cast<int4*>(rep + e) = int4{INT_MAX, INT_MAX, INT_MAX, INT_MAX};
 }
 
 // One lane per neuron vector, segments fastest: consecutive lanes read consecutive runs of L floats of x, so a
@@ -265,7 +267,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void reuse_hash_tiled(const float*
 template <int L>
 __global__ __launch_bounds__(256) void reuse_products_packed(const float* __restrict__ x, const float* __restrict__ w, const int32_t* __restrict__ rep,
                                                              const uint16_t* __restrict__ sig, float* __restrict__ P, uint16_t* __restrict__ ids,
-                                                             int32_t* __restrict__ used, int32_t* __restrict__ rep_out, int n, int numbered, int row_pitch, int k, int m, int G) {
+                                                             int32_t* __restrict__ used, int n, int numbered, int row_pitch, int k, int m, int G) {
     __shared__ int wave_sum[4];
     __shared__ int list_n;
     __shared__ int list_rep[512];
@@ -297,7 +299,6 @@ __global__ __launch_bounds__(256) void reuse_products_packed(const float* __rest
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int g = tid * per + q;
-        if (blockIdx.y == 0 && q < per && g < G) rep_out[(int64_t)s * G + g] = rv[q];      // kept for reading: the gather empties the table
         if (rv[q] == INT_MAX) {
             if (q < per && g < G) number[g] = 0;
             continue;
@@ -348,13 +349,12 @@ __global__ __launch_bounds__(256) void reuse_products_packed(const float* __rest
 // products and the rows' cluster numbers come in by direct loads to a ring of four places in LDS, three segments ahead of
 // the one being summed (always 12 KB of products, so that the wait counts are constants; a segment of more, 48 clusters of
 // 64 columns, is read from memory instead): the rows' reads are then LDS reads, 128 bytes per clock and compute unit
-// instead of what L2 delivers (925 MB of reads for 100 352 rows of 36 segments: 55 us out of L2).  The kernel also empties
-// the election table for the next pass.
+// instead of what L2 delivers (925 MB of reads for 100 352 rows of 36 segments: 55 us out of L2).
 constexpr int kGatherSlots = 4, kGatherProducts = 12 * 1024;
 template <int RPT>
 __global__ __launch_bounds__(kGatherThreads) void reuse_gather_packed(const uint16_t* __restrict__ ids, const float* __restrict__ P,
                                                                       const int32_t* __restrict__ used, const float* __restrict__ bias, float* __restrict__ y,
-                                                                      int32_t* __restrict__ rep, int n, int row_pitch, int m, int S, int G, int relu) {
+                                                                      int n, int row_pitch, int m, int S, int G, int relu) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char reuse_smem[];      // kGatherSlots x (products, rows x 2 bytes rounded up to 1 KB)
     constexpr int WAVES = kGatherThreads / 64, AHEAD = kGatherSlots - 1, PI = kGatherProducts / 1024;
     static_assert(RPT % 4 == 0 && PI + kGatherMaxRows * 2 / 1024 <= 2 * WAVES, "a row group's numbers are whole 8-byte words; at most two loads per wavefront and segment");
@@ -365,9 +365,6 @@ __global__ __launch_bounds__(kGatherThreads) void reuse_gather_packed(const uint
     const bool on = rl < rpp && cl < width;
     const int rows = rpp * RPT, row0 = (int)blockIdx.x * rows;
     const int id_loads = (rows * 2 + 1023) / 1024, slot_bytes = kGatherProducts + id_loads * 1024;
-    // (the table is padded to whole 16-byte words)
-    for (int e = (((int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x) * kGatherThreads + tid) * 4; e < S * G; e += (int)(gridDim.x * gridDim.y) * kGatherThreads * 4)
-        *reinterpret_cast<int4*>(rep + e) = int4{INT_MAX, INT_MAX, INT_MAX, INT_MAX};
     reuse_f4 acc[RPT];
     const reuse_f4 b4 = on ? *reinterpret_cast<const reuse_f4*>(bias + cb * 64 + cl) : reuse_f4(0.0f);
 #pragma unroll
@@ -449,7 +446,7 @@ template <int L> hash_tiled_fn pick_hash_tiled(int seg_len) {
     if constexpr (L == 0) return nullptr;
     else return seg_len == L ? reuse_hash_tiled<L> : pick_hash_tiled<L - 4>(seg_len);
 }
-typedef void (*products_fn)(const float*, const float*, const int32_t*, const uint16_t*, float*, uint16_t*, int32_t*, int32_t*, int, int, int, int, int, int);
+typedef void (*products_fn)(const float*, const float*, const int32_t*, const uint16_t*, float*, uint16_t*, int32_t*, int, int, int, int, int, int);
 template <int L> products_fn pick_products(int seg_len) {
     if constexpr (L == 0) return nullptr;
     else return seg_len == L ? reuse_products_packed<L> : pick_products<L - 4>(seg_len);
@@ -474,7 +471,6 @@ struct pp_reuse_plan {
     int32_t* d_rep = nullptr;
     float* d_P = nullptr;
     bool tiled = false;                 // L and m multiples of 4: the tiled path
-    int32_t* d_rep_out = nullptr;       // ... representatives of the last run (d_rep, the election table, is left empty by each run)
     uint16_t* d_ids = nullptr;          // ... [S][row_pitch] number of a row's cluster in the segment (d_sig has the same layout then)
     int row_pitch = 0;                  // ... room for the rows of the gather's last workgroup
     int32_t* d_used = nullptr;          // ... [S] clusters of a segment
@@ -483,7 +479,7 @@ struct pp_reuse_plan {
 namespace {
 
 void release(pp_reuse_plan_t* p) {
-    void* bufs[] = {p->d_w, p->d_bias, p->d_hyper, p->d_sig, p->d_rep, p->d_P, p->d_rep_out, p->d_ids, p->d_used};
+    void* bufs[] = {p->d_w, p->d_bias, p->d_hyper, p->d_sig, p->d_rep, p->d_P, p->d_ids, p->d_used};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
 }
@@ -529,9 +525,7 @@ pp_status_t pp_reuse_plan(const pp_reuse_desc_t* d, pp_reuse_plan_t** out_plan) 
                   put(&p->d_sig, nullptr, (size_t)S * p->row_pitch * 2) && put(&p->d_rep, nullptr, (size_t)S * G * 4) &&
                   put(&p->d_P, nullptr, (size_t)S * G * d->m * 4, kGatherProducts);
         if (ok && p->tiled) {
-            const std::vector<int32_t> none((size_t)S * G, INT_MAX);
-            ok = hipMemcpy(p->d_rep, none.data(), none.size() * 4, hipMemcpyHostToDevice) == hipSuccess && put(&p->d_rep_out, none.data(), none.size() * 4) &&
-                 put(&p->d_ids, nullptr, (size_t)S * p->row_pitch * 2, kGatherMaxRows * 2) && put(&p->d_used, nullptr, (size_t)S * 4);
+            ok = put(&p->d_ids, nullptr, (size_t)S * p->row_pitch * 2, kGatherMaxRows * 2) && put(&p->d_used, nullptr, (size_t)S * 4);
         }
         if (!ok) {
             (void)hipGetLastError();
@@ -558,33 +552,31 @@ pp_status_t pp_reuse_run(const pp_reuse_plan_t* p, const void* x_dev, void* y_de
     const float* x = static_cast<const float*>(x_dev);
     float* y = static_cast<float*>(y_dev);
     const int relu = (p->flags & PP_FLAG_RELU) ? 1 : 0;
+    const hash_tiled_fn hash_tiled = p->tiled ? pick_hash_tiled<kMaxSeg>(p->L) : nullptr;
+    const hash_fn hash = p->tiled ? nullptr : pick_hash<kMaxSeg>(p->L);
+    if (!hash_tiled && !hash) return PP_ERR_UNSUPPORTED;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(reuse_clear, dim3((unsigned)((S * G + 1023) / 1024)), dim3(256), 0, stream, p->d_rep, S * G);
     if (p->tiled) {
-        const hash_tiled_fn fn = pick_hash_tiled<kMaxSeg>(p->L);
-        if (!fn) return PP_ERR_UNSUPPORTED;
         // rows per workgroup: whole rounds of its wavefronts' tiles, as many as leave three workgroups per compute unit
         const int round = kTileWaves * 64 * reuse_rows_per_lane(p->L);
         const int64_t rounds = (n + round - 1) / round;
         const int per_wg = (int)std::max<int64_t>(1, (rounds * S + 767) / 768);
         const int chunk = per_wg * round, chunks = (int)((rounds + per_wg - 1) / per_wg);
         const int items = chunks * S, per_xcd = (items + 7) / 8;
-        (void)hipGetLastError();
-        hipLaunchKernelGGL(fn, dim3((unsigned)(per_xcd * 8)), dim3(64 * kTileWaves), (size_t)G * 4, stream, x, p->d_hyper, p->d_sig, p->d_rep, n, p->row_pitch, p->k, p->H, chunk,
+        hipLaunchKernelGGL(hash_tiled, dim3((unsigned)(per_xcd * 8)), dim3(64 * kTileWaves), (size_t)G * 4, stream, x, p->d_hyper, p->d_sig, p->d_rep, n, p->row_pitch, p->k, p->H, chunk,
                            items, per_xcd);
         // enough workgroups per segment for four in all on every other compute unit, and for lists of 512 clusters
         const int parts = std::max(std::max(1, G / 512), std::min(16, 512 / S));
         const ReuseGather gs = reuse_gather_shape(n, p->m);
-        hipLaunchKernelGGL(pick_products<kMaxSeg>(p->L), dim3((unsigned)S, (unsigned)parts), dim3(256), 0, stream, x, p->d_w, p->d_rep, p->d_sig, p->d_P, p->d_ids, p->d_used, p->d_rep_out, n,
+        hipLaunchKernelGGL(pick_products<kMaxSeg>(p->L), dim3((unsigned)S, (unsigned)parts), dim3(256), 0, stream, x, p->d_w, p->d_rep, p->d_sig, p->d_P, p->d_ids, p->d_used, n,
                            reuse_numbered_rows(gs), p->row_pitch, p->k, p->m, G);
         const dim3 grid((unsigned)gs.wgs_x, (unsigned)gs.blocks_y);
         const size_t gather_lds = (size_t)kGatherSlots * (kGatherProducts + (gs.rows * 2 + 1023) / 1024 * 1024);
         hipLaunchKernelGGL(gs.rpt == 16 ? reuse_gather_packed<16> : gs.rpt == 8 ? reuse_gather_packed<8> : reuse_gather_packed<4>, grid, dim3(kGatherThreads), gather_lds, stream, p->d_ids,
-                           p->d_P, p->d_used, p->d_bias, y, p->d_rep, n, p->row_pitch, p->m, S, G, relu);
+                           p->d_P, p->d_used, p->d_bias, y, n, p->row_pitch, p->m, S, G, relu);
         return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
     }
-    const hash_fn hash = pick_hash<kMaxSeg>(p->L);
-    if (!hash) return PP_ERR_UNSUPPORTED;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(reuse_clear, dim3((unsigned)((S * G + 255) / 256)), dim3(256), 0, stream, p->d_rep, S * G);
     const size_t lds = (size_t)S * (p->H * p->L + 1) * 4;
     const int64_t hash_blocks = std::min<int64_t>(((int64_t)((n + 3) / 4) * S + 255) / 256, 256 * 8);      // at most eight workgroups per compute unit
     hipLaunchKernelGGL(hash, dim3((unsigned)hash_blocks), dim3(256), lds, stream, x, p->d_hyper, p->d_sig, p->d_rep, n, p->k, p->H);
@@ -615,7 +607,7 @@ pp_status_t pp_reuse_read_clusters(const pp_reuse_plan_t* p, int32_t n, uint16_t
                     for (int i = 0; i < n; ++i) sig_out[(size_t)i * S + s] = by_segment[(size_t)s * p->row_pitch + i];
         }
         if (rep_out) {
-            if (hipMemcpy(rep_out, p->tiled ? p->d_rep_out : p->d_rep, (size_t)S * G * 4, hipMemcpyDeviceToHost) != hipSuccess) return PP_ERR_DEVICE;
+            if (hipMemcpy(rep_out, p->d_rep, (size_t)S * G * 4, hipMemcpyDeviceToHost) != hipSuccess) return PP_ERR_DEVICE;
             for (size_t e = 0; e < (size_t)S * G; ++e)
                 if (rep_out[e] == INT_MAX) rep_out[e] = -1;
         }

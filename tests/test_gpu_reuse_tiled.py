@@ -53,3 +53,45 @@ def test_runs_of_different_lengths_in_turn():
             assert error_report(y.cpu().numpy(), ref, pre, sc)["E"] <= TOL["f32"]
     finally:
         plan.close()
+
+
+def test_a_pass_that_stopped_behind_its_hash_leaves_nothing_to_the_next():
+    """A pass recorded into a graph from which the last two kernels are taken (what a failed launch leaves: the
+    representatives elected, nothing after that), then an ordinary pass on other rows."""
+    import ctypes as C
+    lay = synth.random_reuse_layer("stop", 3000, 96, 32, 8, 10, seed=6, prototypes=40)
+    plan = pp.reuse_plan_from_layer(lay)
+    hip = pp.lib()                                  # the HIP runtime the library itself is linked to
+    try:
+        x0, x1 = lay.make_input(3000), np.ascontiguousarray(lay.make_input(3000)[::-1])
+        d0, d1 = torch.from_numpy(x0).cuda(), torch.from_numpy(x1).cuda()
+        y = torch.empty((3000, 32), device="cuda")
+        side = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        graph, execg, count = C.c_void_p(), C.c_void_p(), C.c_size_t()
+        s = C.c_void_p(side.cuda_stream)
+        assert hip.hipStreamBeginCapture(s, C.c_int(2)) == 0
+        st = pp.pp_reuse_run(plan.handle, d0.data_ptr(), y.data_ptr(), 3000, side.cuda_stream)
+        assert hip.hipStreamEndCapture(s, C.byref(graph)) == 0 and st == pp.PP_OK
+        chain, node, one = [], C.c_void_p(), C.c_size_t(1)
+        assert hip.hipGraphGetRootNodes(graph, C.byref(node), C.byref(one)) == 0 and one.value == 1
+        while one.value:
+            chain.append(C.c_void_p(node.value))
+            assert hip.hipGraphNodeGetDependentNodes(chain[-1], None, C.byref(count)) == 0 and count.value <= 1
+            one = C.c_size_t(count.value)
+            if one.value:
+                assert hip.hipGraphNodeGetDependentNodes(chain[-1], C.byref(node), C.byref(one)) == 0
+        for last in chain[:-3:-1]:
+            assert hip.hipGraphDestroyNode(last) == 0
+        assert hip.hipGraphInstantiate(C.byref(execg), graph, None, None, C.c_size_t(0)) == 0
+        assert hip.hipGraphLaunch(execg, s) == 0
+        torch.cuda.synchronize()
+        plan.run(d1, y)
+        torch.cuda.synchronize()
+        sig, rep = plan.clusters(3000)
+        ref, pre, sc, rsig, rrep = oracle.reuse_layer(x1, lay.weights, lay.hyperplanes, lay.seg_len, lay.hash_bits, lay.bias, lay.relu)
+        assert np.array_equal(sig, rsig) and np.array_equal(rep, rrep)
+        assert error_report(y.cpu().numpy(), ref, pre, sc)["E"] <= TOL["f32"]
+        assert hip.hipGraphExecDestroy(execg) == 0 and hip.hipGraphDestroy(graph) == 0
+    finally:
+        plan.close()
