@@ -197,9 +197,8 @@ pp_status_t pp_block_gemm_run(const pp_block_gemm_plan_t* plan, const void* x_de
         if (st != PP_ERR_UNSUPPORTED) return st;
     }
     {
-        const int tiles = (hp.m + kBlockRow32 - 1) / kBlockRow32;
-        const dim3 grid((unsigned)((n + 63) / 64), (unsigned)tiles), block(64, 4);
-        if (tiles > 65535) return PP_ERR_SHAPE;
+        const dim3 grid((unsigned)((n + 63) / 64), (unsigned)hp.row_tiles), block(64, 4);
+        if (hp.row_tiles > 65535) return PP_ERR_SHAPE;
         if (hp.dtype == PP_F16)
             hipLaunchKernelGGL(k4_generic<_Float16>, grid, block, 0, stream, static_cast<const _Float16*>(x_dev), static_cast<_Float16*>(y_dev),
                                plan->d_wpk32, plan->d_bias, plan->d_group_off32, plan->d_list32, hp.m, n, relu);

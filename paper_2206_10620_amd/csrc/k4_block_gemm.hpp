@@ -463,10 +463,10 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(2))) vo
 template <typename T>
 __global__ __launch_bounds__(256) void k4_generic(const T* __restrict__ x, T* __restrict__ y, const float* __restrict__ wpk, const float* __restrict__ bias,
                                                   const int32_t* __restrict__ group_off, const int32_t* __restrict__ list, int m, int n, int relu) {
-    const int t = (int)blockIdx.y, j = (int)(blockIdx.x * 64 + threadIdx.x);
+    const int j = (int)(blockIdx.x * 64 + threadIdx.x);
     if (j >= n) return;
-    for (int r = (int)threadIdx.y; r < kBlockRow32; r += (int)blockDim.y) {
-        const int row = t * kBlockRow32 + r;
+    for (int i = (int)threadIdx.y; i < kBlockRowTile; i += (int)blockDim.y) {       // two lists: the grid's rows are limited to 65 535
+        const int row = (int)blockIdx.y * kBlockRowTile + i, t = row / kBlockRow32, r = row % kBlockRow32;
         if (row >= m) break;
         float acc = bias[row];
         for (int64_t g = group_off[t]; g < group_off[t + 1]; ++g)

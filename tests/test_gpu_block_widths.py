@@ -25,3 +25,8 @@ def test_wide_tiles_with_ragged_rows(n):
 def test_empty_and_uneven_lists():
     check(synth.random_block_layer("empty", 128, 256, 5, 64, 64, "f16", 0.5, 0.0, seed=1))
     check(synth.random_block_layer("uneven", 192, 400, 13, 64, 400, "f16", 0.02, 0.5, seed=2))
+
+
+def test_the_generic_kernel_takes_more_rows_than_its_lists_have_in_one_grid():
+    # 65 536 lists of 32 rows, one more than a grid has rows
+    check(synth.random_block_layer("tall", 65535 * 32 + 1, 1, 2, 64, 1, "f16", 0.6, 1.0, seed=3), variant=1)
