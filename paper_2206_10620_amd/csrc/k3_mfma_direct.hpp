@@ -550,7 +550,7 @@ void k3_mfma(const K3Args a) {
             stores_behind = 0;
             store_credit = NS - 1;
             if (full && __builtin_amdgcn_ballot_w64(ok) != 0) stores_behind += 16;
-            const float floor1 = a.relu ? 0.0f : -65504.0f;
+            const float floor1 = a.relu ? 0.0f : -__builtin_inff();
             clear_outside(0, fix, kill0, kill2);
             clear_outside(1, fix, kill0, kill2);
 #pragma unroll
@@ -635,7 +635,7 @@ void k3_mfma(const K3Args a) {
         }
         unsigned char* ybase = static_cast<unsigned char*>(a.y);
         const uint32_t fstride = (uint32_t)(a.h * a.w * 2);              // bytes between filters
-        const k3_h2 floor2 = a.relu ? k3_h2((_Float16)0.0f) : k3_h2((_Float16)-65504.0f);
+        const k3_h2 floor2 = a.relu ? k3_h2((_Float16)0.0f) : k3_h2((_Float16)-__builtin_inff());
         stores_behind = 0;
         store_credit = NS - 1;
 #pragma unroll
@@ -681,7 +681,7 @@ void k3_mfma(const K3Args a) {
                     for (int i = 0; i < 2; ++i)
                         pr[i] = acc[0][mt][nt][r + i] + k3_shl1(acc[1][mt][nt][r + i] + k3_shl1(acc[2][mt][nt][r + i]));
                     k3_h2 hv = __builtin_convertvector(pr, k3_h2);                // (filter, filter + 1) of this column, rounded to nearest even
-                    hv = __builtin_elementwise_max(hv, floor2);                   // ReLU (or nothing: the floor is then the lowest finite value)
+                    hv = __builtin_elementwise_max(hv, floor2);                   // ReLU (or nothing: the floor is then minus infinity)
                     const int frow = (r >> 2) * 8 + (r & 3);                      // + kb * 4: the filter's row in the corner
                     *reinterpret_cast<_Float16*>(tb + tb_w + frow * 64) = hv.x;
                     *reinterpret_cast<_Float16*>(tb + tb_w + (frow + 1) * 64) = hv.y;

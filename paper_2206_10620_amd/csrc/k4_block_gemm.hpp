@@ -238,7 +238,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // ---- epilogue: ReLU, binary16, transpose through LDS, 16-byte stores in 256-byte runs ----
     unsigned char* corner = k4_smem + wave * 32 * kK4CornerPitch;
     const int p = lane & 31, kb = lane >> 5;
-    const k4_h2 floor2 = a.relu ? k4_h2((_Float16)0.0f) : k4_h2((_Float16)-65504.0f);
     const int srow = lane >> 4, scol = (lane & 15) * 8;                  // store side: 16 lanes hold one row's 128 columns
     const int ycol = col0 + wave * 128 + scol;
     const bool col_ok = ycol + 8 <= a.n;
@@ -252,7 +251,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 k4_f2 pr;
                 pr.x = acc[mt][nt][r], pr.y = acc[mt][nt][r + 1];
                 k4_h2 hv = __builtin_convertvector(pr, k4_h2);          // rows (row, row + 1) of this column, rounded to nearest even
-                hv = __builtin_elementwise_max(hv, floor2);             // ReLU, or nothing (the floor is then the lowest finite value)
+                if (a.relu) hv = __builtin_elementwise_max(hv, k4_h2((_Float16)0.0f));
                 const int row = (r >> 2) * 8 + kb * 4 + (r & 3);
                 *reinterpret_cast<_Float16*>(corner + row * kK4CornerPitch + (nt * 32 + p) * 2) = hv.x;
                 *reinterpret_cast<_Float16*>(corner + (row + 1) * kK4CornerPitch + (nt * 32 + p) * 2) = hv.y;
