@@ -106,7 +106,7 @@ pp_status_t build_block_plan(const pp_block_gemm_desc_t& d, BlockHostPlan& p) {
             for (int c = 0; c < d.k; ++c)
                 if (used[c]) cols.push_back(c);
             const size_t len = cols.size();
-            while (cols.size() % 8) cols.push_back(cols.back());
+            while (cols.size() % 8) cols.push_back(-1);        // no column: the kernels read 0 there
             const size_t g0 = p.list32.size() / 8, ng = cols.size() / 8;
             p.list32.resize((g0 + ng) * 8);
             p.wpk32.resize((g0 + ng) * 256, 0.0f);
@@ -135,8 +135,11 @@ pp_status_t unpack_block_tile(const BlockHostPlan& p, int tile, float* w_out) {
             for (int64_t e = (int64_t)p.group_off32[t] * 8; e < (int64_t)p.group_off32[t + 1] * 8; ++e) {
                 const int64_t g = e / 8;
                 const int k8 = (int)(e % 8), c = p.list32[g * 8 + (k8 & 1) * 4 + k8 / 2];
-                for (int r = 0; r < kBlockRow32; ++r)      // (a repeated column carries zeros)
-                    w_out[(size_t)((t & 1) * kBlockRow32 + r) * p.k + c] += p.wpk32[(g * 64 + r + 32 * (k8 & 1)) * 4 + k8 / 2];
+                for (int r = 0; r < kBlockRow32; ++r) {
+                    const float v = p.wpk32[(g * 64 + r + 32 * (k8 & 1)) * 4 + k8 / 2];
+                    if (c >= 0) w_out[(size_t)((t & 1) * kBlockRow32 + r) * p.k + c] = v;
+                    else if (v != 0.0f) return PP_ERR_PATTERN;      // padding must carry zeros
+                }
             }
         return PP_OK;
     }

@@ -18,7 +18,7 @@ struct BlockHostPlan {
     int m = 0, k = 0, bm = 0, bk = 0;
     uint32_t flags = 0;
     int dtype = PP_F32;
-    int variant = 1;                  // kernel for n % 8 == 0
+    int variant = 1;                  // 1 or 2, for every n
     bool forced = false;              // the description named the variant
     int row_tiles = 0;
     int64_t kept_weights = 0, executed_weights = 0;
@@ -29,7 +29,7 @@ struct BlockHostPlan {
     // apk[((chunk * 2 + half) * 64 + lane) * 8 + e] = Wd[t * 64 + half * 32 + lane % 32][list[chunk * 16 + 8 * (lane / 32) + e]]
     std::vector<uint16_t> apk;
     // binary32 matrix-core kernel and the generic kernel (values rounded to binary16 for PP_F16): their own lists, one per 32 rows (16-row blocks at 50 % leave 75 % of the columns to 32
-    // rows and 94 % to 64), in groups of eight entries stored [half][4]: entry 2 p + half of the group at [half][p]; weights
+    // rows and 94 % to 64), in groups of eight entries (the last group filled up with -1: no column) stored [half][4]: entry 2 p + half of the group at [half][p]; weights
     // in operand order, [group][64 lanes][4]: lane l, value p: row l % 32, entry 2 p + l / 32
     std::vector<int32_t> list32, group_off32;     // padding at the ends: the kernel loads ahead
     std::vector<float> wpk32;

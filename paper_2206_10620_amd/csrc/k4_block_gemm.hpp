@@ -470,8 +470,9 @@ __global__ __launch_bounds__(256) void k4_generic(const T* __restrict__ x, T* __
         float acc = bias[row];
         for (int64_t g = group_off[t]; g < group_off[t + 1]; ++g)
             for (int e = 0; e < 8; ++e) {
-                const int half = e & 1, p = e >> 1;
-                acc = __builtin_fmaf(wpk[(g * 64 + r + 32 * half) * 4 + p], (float)x[(int64_t)list[g * 8 + half * 4 + p] * n + j], acc);
+                const int half = e & 1, p = e >> 1, c = list[g * 8 + half * 4 + p];
+                if (c < 0) continue;
+                acc = __builtin_fmaf(wpk[(g * 64 + r + 32 * half) * 4 + p], (float)x[(int64_t)c * n + j], acc);
             }
         if (relu) acc = acc > 0.0f ? acc : 0.0f;
         y[(int64_t)row * n + j] = (T)acc;

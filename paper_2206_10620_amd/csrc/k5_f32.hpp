@@ -247,7 +247,9 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
 
 // Block-pruned product, binary32: a 32-row tile of the weight matrix with its own compact column list.  The B operand
 // gathers rows of x: lane (column lane % 32, half lane / 32) of MFMA p of a group of eight list entries reads entry
-// 2 p + half.  The list is stored so that a lane fetches its four entries of a group with one 16-byte load.
+// 2 p + half.  The list is stored so that a lane fetches its four entries of a group with one 16-byte load.  Entry -1 is no
+// column: its row offset is 2^32 less a row, with the lane's column in [2^32 - row, 2^32), beyond any buffer, so it reads 0
+// and an infinite or NaN x does not meet the padding's zero weights.
 struct K5ListArgs {
     const float* x;             // [k][n]
     const float* wpk;           // [group][64 lanes][4]

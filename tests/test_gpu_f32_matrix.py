@@ -3,6 +3,7 @@ block-pruned products) against the CPU checker.  Tolerance: the binary32 gate of
 errs by at most about sqrt(K) * 2^-24 of its rms, 2e-6 for the 1152 terms of the longest one here."""
 import numpy as np
 import pytest
+import torch
 
 import synth
 import paper_2206_10620_amd as pp
@@ -44,3 +45,17 @@ def test_block_product(product):
     m, k, n, b, rk, ck = product
     lay = synth.random_block_layer("f32mc", m, k, n, b, b, "f32", rk, ck, seed=m + n, relu=bool(n & 1))
     check_block(lay)
+
+
+@pytest.mark.parametrize("dtype,variant", [("f32", 0), ("f16", 1)])
+@pytest.mark.parametrize("k", [1, 8, 9, 15])
+def test_block_product_with_an_infinite_last_column(k, dtype, variant):
+    # the list's padding is no column: an infinity in its last one meets each row's own weight there and nothing else
+    lay = synth.random_block_layer("inf", 64, k, 37, 16, 16, dtype, 1.0, 1.0, seed=k, relu=False)
+    x = lay.make_input()
+    x[k - 1, 5] = np.inf
+    plan = pp.block_plan_from_layer(lay, variant=variant)
+    y = plan.run(torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    plan.close()
+    assert np.all(y[:, 5] == np.sign(lay.weights[:, k - 1]) * np.inf)
+    assert np.all(np.isfinite(np.delete(y, 5, axis=1)))
