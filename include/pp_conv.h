@@ -68,10 +68,10 @@ enum {
  * section 2.3.1).  A zero field means "let the library choose". */
 typedef struct {
     int32_t variant;        /* 0 auto; 1 generic (any layer: binary32 as a dense product on the binary32 matrix
-                               cores, otherwise one lane per output); 2 tiled pattern-specialised kernel (3x3, stride 1, no
-                               fused pool; masks outside its sixteen run as covers of those with zero weights; a binary32
-                               plan whose other fields are zero too, and that was left to the library, reports this
-                               variant and its layout and runs the same layer on the binary32 matrix cores); 3 matrix-core kernel (binary16 storage only: the pruned
+                               cores (mfma_kind 5), otherwise one lane per output); 2 the 3x3, stride 1 kernels without a
+                               fused pool that profit from the patterns: by itself the tiled pattern-specialised vector kernel
+                               (masks outside its sixteen run as covers of those with zero weights), with mfma_kind 4 or 5
+                               the binary32 matrix cores (an automatic binary32 plan reports 2 and one of these); 3 matrix-core kernel (binary16 storage only: the pruned
                                weights zero-filled to a dense matrix and multiplied on the MFMA units -- the measured
                                alternative to pattern-specialised vector code; any pattern table, kernel size, stride) */
     int32_t filters_per_wave; /* F: output filters whose accumulators one wavefront holds (4, 8 or 16) */
@@ -101,8 +101,7 @@ typedef struct {
                                section 2.3.1 decided by measurement.  Takes some milliseconds per candidate and
                                synchronises with its own stream only.  Ignored with PP_FLAG_HOST_ONLY.  The plan
                                reports chosen.autotune = 1 */
-    int32_t mfma_kind;      /* which matrix-core kernel: 0 auto (a layer that 2 takes, with every field here zero, reports 2
-                               and its parameters, and runs on 1 where that is modelled to be faster); 3 the product kernel of pp_block_gemm.h for 1x1 layers
+    int32_t mfma_kind;      /* which matrix-core kernel: 0 auto; 3 the product kernel of pp_block_gemm.h for 1x1 layers
                                (stride 1, no pool, h * w a multiple of 8: one matrix product per image, connectivity
                                pruning as its column pruning); 1 the general one (tiles transposed in registers on
                                their way into LDS; any kernel size, stride, channel count, fused pool); 2 the
@@ -112,7 +111,9 @@ typedef struct {
                                memory-to-LDS as they are and transposed by the LDS read; tile_cols is then a multiple
                                of 30 or of 14: segments of 30 or 14 outputs, of which a workgroup of wg_waves
                                wavefronts holds 2 * wg_waves or 4 * wg_waves; tile_rows = that count divided by
-                               the segments per row, tile_cols / 30 or tile_cols / 14) */
+                               the segments per row, tile_cols / 30 or tile_cols / 14); for binary32 storage: 4 the 3x3, stride 1 one on the small
+                               matrix instruction, which skips taps that no filter of four uses, 5 the dense product
+                               (variant 2 or 1) */
     int32_t split_k;        /* direct-load matrix-core kernel only: workgroups that share one output tile, each on its
                                own run of channel chunks (0 auto, 1 none, 2, 4 or 8; must divide the number of
                                16-channel chunks and leave each share at least 2).  Layers with few tiles fill the
@@ -202,12 +203,13 @@ typedef struct {
     const int32_t *kidx;     /* [k_kept] input channel of each kernel, filters concatenated in the new order */
     const uint8_t *kpat;     /* [k_kept] pattern id of each kernel */
     const float *wpacked;    /* [k_kept*taps] weights in the same order (fp32, before any binary16 rounding) */
-    pp_conv_tuning_t chosen; /* the parameters the plan will run with */
+    pp_conv_tuning_t chosen; /* the kernel and the parameters the plan will run with: a plan of the same layer made with
+                                these as its tuning runs the same */
 } pp_plan_info_t;
 pp_status_t pp_conv_plan_query(const pp_conv_plan_t *plan, pp_plan_info_t *out);
 
-/* Decode the device-format weight stream of a tiled plan back into the canonical order
- * (a round-trip check of the packing).  kidx_out/kpat_out [k_kept], w_out [k_kept*4] (fp32; for
+/* Decode the device-format weight stream of a tiled plan, or the packed operands of a binary32 3x3 plan, back into the
+ * canonical order (a round-trip check of the packing).  kidx_out/kpat_out [k_kept], w_out [k_kept*4] (fp32; for
  * a PP_F16 plan the binary16-rounded values).  PP_ERR_UNSUPPORTED if the plan has no stream. */
 pp_status_t pp_conv_plan_unpack(const pp_conv_plan_t *plan, int32_t *kidx_out, uint8_t *kpat_out, float *w_out);
 

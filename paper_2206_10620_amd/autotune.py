@@ -3,7 +3,7 @@
 The layer-wise representation of the paper has a part that is left to tuning (section 2.3.1); the
 plan's own rules choose those parameters from the layer's shape alone.  This helper times a small grid of
 alternatives on the device -- rows per lane, channel split inside a workgroup, channel split across
-workgroups -- and returns the fastest.  It only builds plans and launches them through the same
+workgroups, the kernels a layer can run on -- and returns the fastest.  It only builds plans and launches them through the same
 entry points as everything else; no arithmetic happens here.
 
     tuning, report = autotune(layer, x_dev, y_dev)
@@ -19,10 +19,12 @@ from .pp_conv import PPError, Tuning, plan_from_layer
 
 def default_candidates() -> List[dict]:
     """The automatic choice first; then, for the tiled vector kernel, rows per lane x (split inside, split
-    across workgroups); then, for the matrix-core kernel (binary16 layers only), both wavefront tile counts."""
+    across workgroups); then the matrix-core kernels: two for binary32 layers, two and both wavefront tile counts for
+    binary16 ones."""
     cands: List[dict] = [dict()]
     for r, (ks, sw) in itertools.product((1, 2), ((1, 1), (2, 1), (4, 1), (1, 2), (2, 2))):
         cands.append(dict(variant=2, filters_per_wave=4, rows_per_lane=r, split_c=ks, split_wg=sw))
+    cands += [dict(variant=2, mfma_kind=4), dict(variant=2, mfma_kind=5), dict(variant=3, mfma_kind=1), dict(variant=3, mfma_kind=2)]
     cands.append(dict(variant=3, tiles_per_wave=2))
     cands.append(dict(variant=3, tiles_per_wave=4))
     return cands

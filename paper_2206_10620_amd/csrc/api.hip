@@ -286,7 +286,9 @@ static pp_status_t plan_autotuned(const pp_conv_desc_t* desc, pp_conv_plan_t** o
         if (base.mfma_kind == 0) add([&](pp_conv_tuning_t& t) { t.variant = 3, t.mfma_kind = 1; });
     }
     if (base.variant == 0 || base.variant == 2) {
-        if (f16 && base.variant == 0) add([&](pp_conv_tuning_t& t) { t.variant = 2; });
+        if (base.variant == 0) add([&](pp_conv_tuning_t& t) { t.variant = 2; });
+        if (!f16 && !base.mfma_kind)
+            for (int kind : {4, 5}) add([&](pp_conv_tuning_t& t) { t.variant = 2, t.mfma_kind = kind; });
         if (!f16 || base.variant == 2)
             for (int r : {1, 2})
                 for (int ks : {1, 2, 4})
@@ -407,7 +409,7 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
             delete p;
             return PP_ERR_UNSUPPORTED;
         }
-    } else if (hp.c_out > 65535) {
+    } else if (hp.chosen.variant == 1 && hp.c_out > 65535) {
         delete p;
         return PP_ERR_UNSUPPORTED;
     }
@@ -448,7 +450,7 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
         ok = ok && upload(&p->d_wquad, hp.ql.wpk.data(), hp.ql.wpk.size() * 4);
         ok = ok && upload(&p->d_used, hp.ql.used.data(), hp.ql.used.size() * 4);
         ok = ok && upload(&p->d_bias_quad, hp.ql.bias_pad.data(), hp.ql.bias_pad.size() * 4);
-    } else if (hp.tiled && !hp.dense32) {
+    } else if (hp.tiled) {
         const TiledLayout& tl = hp.tl;
         ok = ok && upload(&p->d_stream, tl.stream.data(), tl.stream.size() * 4);
         ok = ok && upload(&p->d_wave_off, tl.wave_off.data(), tl.wave_off.size() * 4);

@@ -326,6 +326,8 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     if (t.variant == 3 && !mfma_ok) return PP_ERR_UNSUPPORTED;
     int variant = t.variant;
     if (variant == 0) variant = mfma_ok ? 3 : (builtin ? 2 : 1);
+    const bool quads_asked = t.mfma_kind == 4, dense_asked = t.mfma_kind == 5;      // the binary32 kernels by name
+    if ((quads_asked && (hp.dtype != PP_F32 || variant != 2)) || (dense_asked && hp.dtype != PP_F32)) return PP_ERR_UNSUPPORTED;
     hp.tiled = variant == 2;
     hp.mfma = variant == 3;
     hp.chosen = pp_conv_tuning_t{};
@@ -339,35 +341,45 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
         const int64_t images = 64 / ((int64_t)hp.ho * hp.wo) + 2;       // that the 64 pixels of a wavefront can touch
         if (hp.dtype == PP_F32 && images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31)) {
             hp.dense32 = true;
+            hp.chosen.mfma_kind = 5;
             build_f32_layout(hp);
         }
-        return PP_OK;
+        return dense_asked && !hp.dense32 ? PP_ERR_UNSUPPORTED : PP_OK;
     }
+    TiledLayout& tl = hp.tl;
+    tl.covered = covered;
 
     // A binary32 layer whose tuning is left to the library runs on the matrix cores: on the small instruction, which profits
     // from the sparsity, or as a dense product where that is modelled to be faster (few pixels: it splits the work finer).
-    // The tiled kernel's layout is built all the same: it is what pp_conv_plan_query and pp_conv_plan_unpack describe.
     // Measured, tiled / dense / small instruction: 256 channels 56x56 batch 1 at 0.3: 41 / 39 / 28 us; 256 channels 14x14 batch
     // 32 at 0.5: 78 / 73 / 56; 64 channels 56x56 batch 32: 56 / 76 / 50; 64 channels 56x56 batch 1: 26 / 7 / 12.
     {
         const pp_conv_tuning_t none{};
         pp_conv_tuning_t asked = t;
         asked.autotune = 0;
+        const bool left_to_us = std::memcmp(&asked, &none, sizeof none) == 0;
         const int mc = (hp.w + 3) / 4;
         const int64_t images = 64 / ((int64_t)hp.h * std::min(mc, hp.w)) + 2;         // that the 64 pieces or pixels of a wavefront can touch
-        if (hp.dtype == PP_F32 && std::memcmp(&asked, &none, sizeof none) == 0 && images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31)) {
-            mark_quad_taps(hp);
-            int wk = 0;
-            const int64_t rows = (int64_t)hp.n_hint * hp.h;
-            hp.quads = k6_model(hp.ql.groups, (rows * mc + 63) / 64, hp.c_in, hp.ql.taps_used, &wk) <
-                       k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 7) / 8));
-            hp.dense32 = !hp.quads;
-            if (hp.quads) pack_quads(hp);
-            else build_f32_layout(hp);
+        if (hp.dtype == PP_F32 && (left_to_us || quads_asked || dense_asked)) {
+            if (images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31)) {
+                hp.quads = quads_asked;
+                if (!dense_asked) mark_quad_taps(hp);
+                if (left_to_us) {
+                    int wk = 0;
+                    const int64_t rows = (int64_t)hp.n_hint * hp.h;
+                    hp.quads = k6_model(hp.ql.groups, (rows * mc + 63) / 64, hp.c_in, hp.ql.taps_used, &wk) <
+                               k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 7) / 8));
+                }
+                hp.tiled = false;
+                hp.dense32 = !hp.quads;
+                hp.chosen.mfma_kind = hp.quads ? 4 : 5;
+                if (hp.quads) pack_quads(hp);
+                else build_f32_layout(hp);
+                return PP_OK;
+            }
+            if (!left_to_us) return PP_ERR_UNSUPPORTED;
         }
     }
-    TiledLayout& tl = hp.tl;
-    tl.covered = covered;
     const int eb = hp.dtype == PP_F16 ? 2 : 4;
     tl.np = max_slot < 8 ? 8 : 16;
     tl.entry_words = hp.dtype == PP_F16 ? 4 : 8;   // header + two words of binary16 pairs, or header + 3 spare + 4 fp32
@@ -773,8 +785,7 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
     ml.direct = direct_ok && t.mfma_kind != 1 && t.mfma_kind != 3 && direct_layout();
     if (t.mfma_kind == 2 && !ml.direct) return PP_ERR_UNSUPPORTED;
     if (t.split_k > 1 && !ml.direct) return PP_ERR_UNSUPPORTED;      // only the direct-load kernel splits the reduction
-    // A layer left to the library that does not split its reduction runs on whichever of the two is modelled faster; the plan
-    // reports the direct kernel's parameters either way.  Small maps, widths off the segments and padded channels favour the
+    // A layer left to the library that does not split its reduction runs on whichever of the two is modelled faster.  Small maps, widths off the segments and padded channels favour the
     // general kernel (no padding launch, tiles of any shape), large pooled or whole-chunk layers the direct one.  Both models
     // were fitted to 160 layers (batch 1 to 32, 16 to 512 channels, 7x7 to 880x764, pooled and not): 15 and 9 % rms; of the
     // 102 layers the rule moves none loses more than 3 %, the mean gain over all 160 is 1.24.  97 -> 33 channels, 64x53:
@@ -784,7 +795,11 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
     const MfmaLayout direct_ml = ml;
     const pp_conv_tuning_t direct_chosen = hp.chosen;
     double general_us = 0.0;
-    if (either) ml.direct = false;
+    if (either) {
+        ml.direct = false;
+        hp.chosen = pp_conv_tuning_t{};
+        hp.chosen.variant = 3;
+    }
     // The batch is one tall virtual image: image n's output row oy is virtual row n*po + oy, and the
     // matching input rows start at virtual input row n*po*S, so that a tile may straddle images; the
     // rows between images read as zeros (they are the padding) and their outputs are not stored.
@@ -899,7 +914,7 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
     if (either) {
         if (general_us == 0.0 || general_us >= 0.95 * direct_us) ml = direct_ml;
         else ml.ksplit = 1, ml.cpad = hp.c_in;
-        hp.chosen = direct_chosen;
+        if (ml.direct) hp.chosen = direct_chosen;
     }
 
     // weights: scatter the kept kernels into zero-filled operand fragments
@@ -929,6 +944,50 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
     return PP_OK;
 }
 
+namespace {
+
+// Calls put(place in fl.wpk, place in canon.wpacked) for every kept weight.
+template <typename F>
+void each_f32_weight(const HostPlan& hp, F&& put) {
+    const F32Layout& fl = hp.fl;
+    const Canonical& cn = hp.canon;
+    const int KK = hp.ks * hp.ks, last_pair = std::max(hp.c_in - 2, 0);
+    std::vector<std::vector<int>> taps(hp.num_patterns);
+    for (int p = 0; p < hp.num_patterns; ++p)
+        for (int tp = 0; tp < KK; ++tp)
+            if ((hp.masks[p] >> tp) & 1u) taps[p].push_back(tp);
+    for (int pos = 0; pos < hp.c_out; ++pos) {
+        const int co = cn.perm[pos], row = co % 32;
+        for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
+            const int ci = cn.kidx[e], g = ci / 8, p = ci % 8 / 2, half = ci - std::min(ci / 2 * 2, last_pair);
+            const size_t at = (size_t)(row + 32 * half) * 4 + p;
+            const std::vector<int>& tl = taps[cn.kpat[e]];
+            for (int j = 0; j < hp.taps; ++j)
+                put(((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at, (size_t)e * hp.taps + j);
+        }
+    }
+}
+
+// The same for ql.wpk.
+template <typename F>
+void each_quad_weight(const HostPlan& hp, F&& put) {
+    const Canonical& cn = hp.canon;
+    for (int pos = 0; pos < hp.c_out; ++pos) {
+        const int co = cn.perm[pos], q = co % 16 / 4, i = co % 4;
+        const size_t group = (size_t)(co / 16) * hp.c_in * 256 + i * 4;
+        size_t src = (size_t)hp.filt_off[pos] * hp.taps;
+        for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
+            const size_t at = group + (size_t)cn.kidx[e] * 256;
+            for (uint64_t mask = hp.masks[cn.kpat[e]]; mask; mask &= mask - 1) {
+                const int kr = 9 * q + __builtin_ctzll(mask);
+                put(at + kr % 16 * 16 + kr / 16, src++);
+            }
+        }
+    }
+}
+
+}  // namespace
+
 // Binary32 matrix-core operands: unit (tap, g) of a 32-filter tile multiplies channels 8 g .. 8 g + 7 at one tap with four
 // MFMAs, the p-th on the two channels from min(8 g + 2 p, c_in - 2) on.  A channel's weight sits in the first pair that holds
 // it; what the pairs past the end hold again is zero.
@@ -941,22 +1000,7 @@ void build_f32_layout(HostPlan& hp) {
     fl.wpk.assign(((size_t)fl.tiles * fl.units + kF32Pad) * 256, 0.0f);
     fl.bias_pad.assign((size_t)fl.tiles * 32, 0.0f);
     std::copy(hp.bias.begin(), hp.bias.end(), fl.bias_pad.begin());
-    const Canonical& cn = hp.canon;
-    const int last_pair = std::max(hp.c_in - 2, 0);
-    std::vector<std::vector<int>> taps(hp.num_patterns);
-    for (int p = 0; p < hp.num_patterns; ++p)
-        for (int tp = 0; tp < KK; ++tp)
-            if ((hp.masks[p] >> tp) & 1u) taps[p].push_back(tp);
-    for (int pos = 0; pos < hp.c_out; ++pos) {
-        const int co = cn.perm[pos], row = co % 32;
-        for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
-            const int ci = cn.kidx[e], g = ci / 8, p = ci % 8 / 2, half = ci - std::min(ci / 2 * 2, last_pair);
-            const size_t at = (size_t)(row + 32 * half) * 4 + p;
-            const std::vector<int>& tl = taps[cn.kpat[e]];
-            for (int j = 0; j < hp.taps; ++j)
-                fl.wpk[((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at] = cn.wpacked[(size_t)e * hp.taps + j];
-        }
-    }
+    each_f32_weight(hp, [&](size_t at, size_t src) { fl.wpk[at] = hp.canon.wpacked[src]; });
 }
 
 // Which taps any filter of a quad uses, per channel.
@@ -981,23 +1025,28 @@ void pack_quads(HostPlan& hp) {
     ql.wpk.assign((size_t)ql.groups * hp.c_in * 256, 0.0f);
     ql.bias_pad.assign((size_t)ql.groups * 16, 0.0f);
     std::copy(hp.bias.begin(), hp.bias.end(), ql.bias_pad.begin());
-    const Canonical& cn = hp.canon;
-    for (int pos = 0; pos < hp.c_out; ++pos) {
-        const int co = cn.perm[pos], q = co % 16 / 4, i = co % 4;
-        float* group = ql.wpk.data() + (size_t)(co / 16) * hp.c_in * 256 + i * 4;
-        const float* src = cn.wpacked.data() + hp.filt_off[pos] * hp.taps;
-        for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
-            float* dst = group + (size_t)cn.kidx[e] * 256;
-            for (uint64_t mask = hp.masks[cn.kpat[e]]; mask; mask &= mask - 1) {
-                const int kr = 9 * q + __builtin_ctzll(mask);
-                dst[kr % 16 * 16 + kr / 16] = *src++;
-            }
-        }
-    }
+    each_quad_weight(hp, [&](size_t at, size_t src) { ql.wpk[at] = hp.canon.wpacked[src]; });
+}
+
+// The weights out of the operands of a binary32 3x3 plan; what no kept weight put there has to be zero.
+static pp_status_t unpack_operands(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, float* w) {
+    const std::vector<float>& wpk = hp.quads ? hp.ql.wpk : hp.fl.wpk;
+    std::copy(hp.canon.kidx.begin(), hp.canon.kidx.end(), kidx);
+    std::copy(hp.canon.kpat.begin(), hp.canon.kpat.end(), kpat);
+    size_t kept = 0, all = 0;
+    auto take = [&](size_t at, size_t to) {
+        w[to] = wpk[at];
+        kept += wpk[at] != 0.0f ? 1 : 0;
+    };
+    if (hp.quads) each_quad_weight(hp, take);
+    else each_f32_weight(hp, take);
+    for (float v : wpk) all += v != 0.0f ? 1 : 0;
+    return kept == all ? PP_OK : PP_ERR_UNSUPPORTED;
 }
 
 pp_status_t unpack_stream(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, float* w) {
-    if (!hp.tiled || hp.taps != 4 || hp.tl.covered) return PP_ERR_UNSUPPORTED;
+    if (hp.chosen.variant != 2 || hp.taps != 4 || hp.tl.covered) return PP_ERR_UNSUPPORTED;
+    if (!hp.tiled) return unpack_operands(hp, kidx, kpat, w);
     const TiledLayout& tl = hp.tl;
     const int EW = tl.entry_words;
     // slot -> lowest pattern id carrying that mask

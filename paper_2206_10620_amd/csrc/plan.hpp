@@ -98,7 +98,7 @@ struct HostPlan {
     std::vector<float> bias;            // [c_out], zeros if absent
     Canonical canon;
     pp_conv_tuning_t chosen{};
-    bool tiled = false;
+    bool tiled = false;                 // the tiled vector kernel runs the plan
     TiledLayout tl;
     bool mfma = false;
     MfmaLayout ml;
@@ -126,7 +126,7 @@ void build_f32_layout(HostPlan& hp);
 // Pack the weights of a binary32 3x3, stride 1 layer for the small matrix instruction (hp.ql).
 void mark_quad_taps(HostPlan& hp);
 void pack_quads(HostPlan& hp);
-// Decode tl.stream back to canonical order.
+// Decode tl.stream, or the operands of a binary32 3x3 plan, back to canonical order.
 pp_status_t unpack_stream(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, float* w);
 
 // binary16 conversion used when packing weights (round to nearest even).

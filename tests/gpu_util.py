@@ -48,12 +48,29 @@ def reference_at(lay, x_np, wd, pts, relu_flag):
     return y4.reshape(-1, 4).max(axis=1), pre4, sc4.reshape(-1, 4).max(axis=1)
 
 
+def flat_tile_points(lay, n, px, per_tile, count=2000):
+    """The same for kernels whose tiles are runs of per_tile pieces of px pixels of a row, numbered through rows and images:
+    the outputs on both sides of tile boundaries (a seeded choice of them) and of the whole last tile."""
+    mc = -(-lay.out_w // px)
+    pieces = n * lay.out_h * mc
+    rs = np.random.RandomState(lay.seed)
+    bounds = np.arange(per_tile, pieces, per_tile)
+    if len(bounds) > count:
+        bounds = np.sort(rs.choice(bounds, size=count, replace=False))
+    j = np.concatenate([bounds - 1, bounds, np.arange((pieces - 1) // per_tile * per_tile, pieces), [0]])
+    x = np.minimum(j % mc * px + rs.randint(px, size=len(j)), lay.out_w - 1)
+    edge = sorted({0, lay.c_out - 1} | {c for b in range(16, lay.c_out, 16) for c in (b - 1, b)})
+    return np.stack([j // (mc * lay.out_h), np.asarray(edge)[rs.randint(len(edge), size=len(j))], j // mc % lay.out_h, x], axis=1).astype(np.int32)
+
+
 def tile_boundary_points(lay, n, chosen):
     """Stored-output coordinates on both sides of every tile boundary of the plan that ran (row bands of
     the batch as one tall image, column strips), on the first and last row of every image and over the
     whole last ragged tile: the places a sampled comparison of a large layer would otherwise only hit by
     luck.  The tile geometry is read from the plan's reported parameters."""
     pool = 2 if getattr(lay, "pool", False) else 1
+    if chosen["mfma_kind"] in (4, 5):
+        return flat_tile_points(lay, n, 4 if chosen["mfma_kind"] == 4 else 1, 64 if chosen["mfma_kind"] == 4 else 32 // (pool * pool))
     if chosen["variant"] == 3:
         band, strip = max(chosen["tile_rows"] // pool, 1), max(chosen["tile_cols"] // pool, 1)
         # rows per image of the tall image: the general kernel pads by the kernel's reach, the direct one by one row

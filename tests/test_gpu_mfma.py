@@ -150,8 +150,14 @@ def test_direct_forced_tile_geometries(waves, tile_cols):
 def test_direct_is_the_default_where_it_applies_and_matches_the_general_kernel():
     from gpu_util import run_layer
     foreign = np.array([0x00F, 0x1E0, 0x03A, 0x145], dtype=np.uint16)
+    large = synth.random_pruned_layer("dauto", 4, 16, 64, 112, 112, "f16", foreign, 0.7, 0.3, seed=1)
+    rep, _ = check_layer(large, label="mfma-direct-auto")
+    assert rep["chosen"]["variant"] == 3 and rep["chosen"]["mfma_kind"] == 2
+    # small and odd maps run on the general kernel unless the direct one is asked for
     lay = synth.random_pruned_layer("dauto", 2, 32, 40, 19, 33, "f16", foreign, 0.7, 0.3, seed=1)
-    rep, y = check_layer(lay, label="mfma-direct-auto")
+    rep, _ = check_layer(lay, label="mfma-small-auto")
+    assert rep["chosen"]["variant"] == 3 and rep["chosen"]["mfma_kind"] == 1
+    rep, y = check_layer(lay, tuning=TD(), label="mfma-direct-small")
     assert rep["chosen"]["variant"] == 3 and rep["chosen"]["mfma_kind"] == 2
     y1, chosen1 = run_layer(lay, lay.make_input(), tuning=pp.Tuning(variant=3, mfma_kind=1))
     assert chosen1["mfma_kind"] == 1
@@ -232,9 +238,12 @@ def test_direct_padded_channels_beyond_the_batch_hint_and_dense_first_layer():
     lay = synth.random_pruned_layer("dpad", 5, 3, 20, 11, 16, "f16", synth.PSET8, 1.0, 0.3, seed=6)
     rep, _ = check_layer(lay, tuning=TD(), n_hint=2, label="mfma-direct-pad-groups")
     assert rep["chosen"]["mfma_kind"] == 2
-    # an unpruned three-channel first layer (nine taps) takes the same path by default
+    # an unpruned three-channel first layer (nine taps): the same path, by default at its real size
     dense = synth.dense_layer("dfirst", 2, 3, 64, 24, 40, "f16", 0.3, seed=2)
-    rep, _ = check_layer(dense, label="mfma-direct-dense-first")
+    rep, _ = check_layer(dense, tuning=TD(), label="mfma-direct-dense-first")
+    assert rep["chosen"]["variant"] == 3 and rep["chosen"]["mfma_kind"] == 2
+    dense = synth.dense_layer("dfirst", 8, 3, 64, 224, 224, "f16", 0.3, seed=2)
+    rep, _ = check_layer(dense, label="mfma-direct-dense-first-default")
     assert rep["chosen"]["variant"] == 3 and rep["chosen"]["mfma_kind"] == 2
 
 
@@ -256,7 +265,7 @@ def test_direct_fused_pool(waves):
 
 
 def test_direct_fused_pool_default_and_refusals():
-    lay = synth.random_pruned_layer_k("dpool-auto", 8, 64, 64, 56, 56, "f16", 3, synth.PSET8, 0.28, 0.05, seed=2, pool=True)
+    lay = synth.random_pruned_layer_k("dpool-auto", 8, 64, 64, 112, 112, "f16", 3, synth.PSET8, 0.28, 0.05, seed=2, pool=True)
     rep, _ = check_layer(lay, label="mfma-direct-pool-auto")
     assert rep["chosen"]["variant"] == 3 and rep["chosen"]["mfma_kind"] == 2
     with pytest.raises(pp.PPError):

@@ -48,9 +48,11 @@ def test_the_rule_between_the_matrix_core_kernels(layer):
     n, c_in, c_out, h, w, pool, general = layer
     print(f"mfma auto {layer}", flush=True)
     lay = synth.random_pruned_layer_k("auto", n, c_in, c_out, h, w, "f16", 3, synth.PSET8, 0.5, 0.1, seed=n + c_in, pool=pool)
-    for hint in (n, 1):
-        rep, y = check_layer(lay, n_hint=hint, label=f"auto{layer}")
-        assert rep["chosen"]["mfma_kind"] == 2
-    _, y = check_layer(lay, label=f"auto{layer}")
-    same, _ = run_layer(lay, lay.make_input(), tuning=pp.Tuning(variant=3, mfma_kind=1 if general else 2))
-    assert np.array_equal(y, same)               # the kernel it is said to run: the two sum in different orders
+    rep, _ = check_layer(lay, n_hint=1, label=f"auto{layer}-hint")
+    assert rep["chosen"]["mfma_kind"] in (1, 2)
+    rep, y = check_layer(lay, label=f"auto{layer}")
+    assert rep["chosen"]["mfma_kind"] == (1 if general else 2)
+    same, chosen = run_layer(lay, lay.make_input(), tuning=pp.Tuning(**rep["chosen"]))
+    assert chosen == rep["chosen"] and np.array_equal(y, same)
+    other, _ = run_layer(lay, lay.make_input(), tuning=pp.Tuning(variant=3, mfma_kind=2 if general else 1))
+    assert n * c_out * h * w < 100 or not np.array_equal(y, other)      # the other kernel sums in another order: enough outputs round differently

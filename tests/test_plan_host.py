@@ -76,6 +76,45 @@ def test_foreign_pattern_table_runs_on_the_tiled_kernel_as_a_cover_of_its_own_pa
     p5.close()
 
 
+@pytest.mark.parametrize("layer", [("f32", 16, 64, 64, 28, 28), ("f32", 2, 24, 32, 28, 28), ("f16", 1, 97, 33, 64, 53), ("f16", 2, 64, 64, 224, 224), ("f16", 8, 512, 512, 14, 14)],
+                         ids=lambda v: "x".join(str(i) for i in v))
+def test_a_plan_reports_the_kernel_it_runs(layer):
+    """Automatic and named plans: different kernels report different parameters, and the reported ones make the same plan."""
+    dtype, n, c_in, c_out, h, w = layer
+    lay = synth.random_pruned_layer("rep", n, c_in, c_out, h, w, dtype, synth.PSET8, 0.3, 0.3, seed=5)
+
+    def chosen(**tune):
+        plan = pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(**tune) if tune else None)
+        try:
+            return plan.query()["chosen"]
+        finally:
+            plan.close()
+
+    named = [dict(variant=2), dict(variant=1)]
+    named += [dict(variant=2, mfma_kind=4), dict(variant=2, mfma_kind=5)] if dtype == "f32" else [dict(variant=3, mfma_kind=1), dict(variant=3, mfma_kind=2)]
+    got = [chosen(**t) for t in named]
+    assert len({tuple(sorted(g.items())) for g in got}) == len(named)
+    for t, g in zip(named, got):
+        assert all(g[k] == v for k, v in t.items())
+    auto = chosen()
+    assert auto["mfma_kind"] in ((4, 5) if dtype == "f32" else (1, 2))
+    for g in got + [auto]:
+        assert chosen(**g) == g
+    with pytest.raises(pp.PPError):
+        chosen(mfma_kind=4 if dtype == "f16" else 3)
+
+
+@pytest.mark.parametrize("kind", [0, 4, 5])
+@pytest.mark.parametrize("c_in,c_out", [(1, 1), (37, 29), (64, 33)])
+def test_binary32_operands_round_trip(c_in, c_out, kind):
+    lay = synth.random_pruned_layer("p", 2, c_in, c_out, 12, 20, "f32", synth.PSET16, 0.4 if c_in > 1 else 1.0, 0.1, 5)
+    plan, info = check_against_reference(lay, pp.Tuning(variant=2, mfma_kind=kind) if kind else None)
+    assert info["chosen"]["mfma_kind"] in ((kind,) if kind else (4, 5))
+    st, kidx, kpat, w = pp.pp_conv_plan_unpack(plan.handle, info["k_kept"])
+    assert st == pp.PP_OK
+    assert np.array_equal(kidx, info["kidx"]) and np.array_equal(kpat, info["kpat"]) and np.array_equal(w, info["wpacked"])
+
+
 def test_error_paths():
     lay = synth.config1()
     H = pp.PP_FLAG_HOST_ONLY
