@@ -6,6 +6,7 @@
 #include <new>
 #include <vector>
 
+#include "k0_generic.hpp"
 #include "k1_tiled.hpp"
 #include "k2_mfma.hpp"
 #include "k3_mfma_direct.hpp"
@@ -61,63 +62,6 @@ k1_launch_fn k1_lookup(int dtype, int np, int r, int f, int lw, bool direct) {
     if (np == 8) { PPC_PICK(f16, 8) }
     PPC_PICK(f16, 16)
 #undef PPC_PICK
-}
-
-// ---------------------------------------------------------------------------------------------
-// Generic kernel: any pattern table, kernel size, stride, with or without the fused 2x2 max-pool.
-// One lane per stored output, one filter per blockIdx.y; walks the filter's reordered kernel list
-// (same-pattern kernels consecutive) with wave-uniform indices and reads the input straight from
-// global memory with bounds checks.  It serves binary16 plans that ask for it and binary32 images
-// beyond the matrix-core kernel's 31-bit offsets.
-struct K0Args {
-    const void* x;
-    void* y;
-    const int32_t* filt_off;   // [c_out+1]
-    const int32_t* kidx;       // [k_kept]
-    const uint8_t* kpat;       // [k_kept]
-    const float* w;            // [k_kept*taps] (binary16-rounded values for an fp16 plan)
-    const int8_t* tap_dyx;     // [P*taps*2]
-    const int32_t* perm;       // [c_out]
-    const float* bias;         // [c_out] by original index
-    int32_t n, c_in, c_out, h, w_, taps, relu;
-    int32_t stride, ho, wo, out_h, out_w, pool;
-};
-
-template <typename T>
-__global__ __launch_bounds__(256) void k0_generic(const K0Args a) {
-    const int pos = blockIdx.y;
-    const int64_t pix = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t ohw = (int64_t)a.out_h * a.out_w;
-    if (pix >= (int64_t)a.n * ohw) return;
-    const int img = (int)(pix / ohw);
-    const int rem = (int)(pix - (int64_t)img * ohw);
-    const int sy = rem / a.out_w, sx = rem - sy * a.out_w;      // stored output
-    const int64_t hw = (int64_t)a.h * a.w_;
-    const T* __restrict__ x = static_cast<const T*>(a.x);
-    const int co = a.perm[pos];
-    const int beg = a.filt_off[pos], end = a.filt_off[pos + 1];
-    const int np = a.pool ? 2 : 1;
-    float best = 0.0f;
-    for (int py = 0; py < np; ++py)
-        for (int px = 0; px < np; ++px) {
-            const int oy = sy * np + py, ox = sx * np + px;     // the convolution's own output
-            float acc = 0.0f;
-            for (int e = beg; e < end; ++e) {
-                const int ci = a.kidx[e];
-                const int8_t* tp = a.tap_dyx + (int)a.kpat[e] * a.taps * 2;
-                const float* wv = a.w + (int64_t)e * a.taps;
-                const T* xc = x + ((int64_t)img * a.c_in + ci) * hw;
-                for (int j = 0; j < a.taps; ++j) {
-                    const int iy = oy * a.stride + tp[2 * j], ix = ox * a.stride + tp[2 * j + 1];
-                    if (iy >= 0 && iy < a.h && ix >= 0 && ix < a.w_) acc = __builtin_fmaf(wv[j], (float)xc[iy * a.w_ + ix], acc);
-                }
-            }
-            acc += a.bias[co];
-            if (a.relu) acc = acc > 0.0f ? acc : 0.0f;
-            const float v = (float)(T)acc;                      // pooling acts on stored values
-            best = (py == 0 && px == 0) ? v : (v > best ? v : best);
-        }
-    static_cast<T*>(a.y)[((int64_t)img * a.c_out + co) * ohw + rem] = (T)best;
 }
 
 template <typename T>
@@ -195,21 +139,14 @@ struct pp_conv_plan {
     float* d_ws3 = nullptr;                   // their workspace: [ksplit][n_hint][c_out][h][w] binary32
     pp_block_gemm_plan_t* pointwise = nullptr; // a 1x1 stride-1 layer in binary16 runs as a batch of matrix products (one per image)
     _Float16* d_xpad = nullptr;               // x with zero channels appended up to whole chunks of 16: [n_hint][cpad][h][w]
-    // binary32 matrix-core kernel
-    float* d_w32 = nullptr;
-    float* d_bias32 = nullptr;
-    // binary32 3x3 kernel on the small matrix instruction
-    float* d_wquad = nullptr;
-    uint32_t* d_used = nullptr;
-    float* d_bias_quad = nullptr;
+    // binary32 matrix-core kernels
+    const float* w32 = nullptr;
+    const float* bias32 = nullptr;
+    const uint32_t* used32 = nullptr;         // (small matrix instruction)
     // generic kernel
-    int32_t* d_filt_off = nullptr;
-    int32_t* d_kidx = nullptr;
-    uint8_t* d_kpat = nullptr;
-    float* d_w = nullptr;
-    int8_t* d_tap = nullptr;
-    int32_t* d_perm = nullptr;
-    float* d_bias = nullptr;
+    unsigned char* d_lists = nullptr;         // the binary32 operands, the tables `lists` points into and a copy of `lists`: one allocation
+    K0Args lists{};
+    const K0Args* lists_copy = nullptr;
 };
 
 namespace {
@@ -226,8 +163,7 @@ bool upload(T** dst, const void* src, size_t bytes) {
 }
 
 void free_device(pp_conv_plan_t* p) {
-    void* bufs[] = {p->d_wquad, p->d_used, p->d_bias_quad, p->d_w32, p->d_bias32, p->d_xpad, p->d_ws3, p->d_stream, p->d_wave_off, p->d_chan_map, p->d_ws, p->d_counters, p->d_perm_pad, p->d_bias_pad, p->d_wpk, p->d_bias_mfma, p->d_filt_off, p->d_kidx,
-                    p->d_kpat,   p->d_w,        p->d_tap,      p->d_perm,     p->d_bias};
+    void* bufs[] = {p->d_xpad, p->d_ws3, p->d_stream, p->d_wave_off, p->d_chan_map, p->d_ws, p->d_counters, p->d_perm_pad, p->d_bias_pad, p->d_wpk, p->d_bias_mfma, p->d_lists};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
 }
@@ -255,6 +191,53 @@ const char* pp_status_string(pp_status_t s) {
         case PP_ERR_SCRATCH: return "request exceeds the static scratch buffer";
     }
     return "unknown status";
+}
+
+// The operands of the binary32 matrix-core kernels, the reordered kernel lists (the generic kernel's, and theirs where x is not
+// finite) and everything else of a generic kernel's arguments but the buffers and n.
+static bool upload_lists(pp_conv_plan_t* p) {
+    const HostPlan& hp = p->hp;
+    const Canonical& cn = hp.canon;
+    std::vector<float> w = cn.wpacked;
+    if (hp.dtype == PP_F16)
+        for (float& v : w) v = f16_to_f32(f32_to_f16_rne(v));
+    std::vector<int32_t> place(cn.perm.size());
+    for (size_t pos = 0; pos < cn.perm.size(); ++pos) place[cn.perm[pos]] = (int32_t)pos;
+    std::vector<unsigned char> blob;
+    auto add = [&](const void* src, size_t bytes) {
+        const size_t at = blob.size();
+        blob.resize(at + (bytes + 15) / 16 * 16);
+        if (bytes) std::memcpy(blob.data() + at, src, bytes);
+        return at;
+    };
+    const size_t args = add(&p->lists, sizeof p->lists), filt_off = add(hp.filt_off.data(), hp.filt_off.size() * 4), kidx = add(cn.kidx.data(), cn.kidx.size() * 4), kpat = add(cn.kpat.data(), cn.kpat.size()),
+                 wv = add(w.data(), w.size() * 4), tap = add(hp.tap_dyx.data(), hp.tap_dyx.size()), perm = add(cn.perm.data(), cn.perm.size() * 4),
+                 pl = add(place.data(), place.size() * 4), bias = add(hp.bias.data(), hp.bias.size() * 4);
+    void* mem = nullptr;
+    static const std::vector<float> none;
+    const std::vector<float>& operands = hp.quads ? hp.ql.wpk : hp.dense32 ? hp.fl.wpk : none;
+    const std::vector<float>& bias_pad = hp.quads ? hp.ql.bias_pad : hp.dense32 ? hp.fl.bias_pad : none;
+    const size_t bias32 = add(bias_pad.data(), bias_pad.size() * 4), used32 = add(hp.ql.used.data(), hp.quads ? hp.ql.used.size() * 4 : 0);
+    const size_t op_bytes = operands.size() * 4;            // (a multiple of 1024)
+    if (hipMalloc(&mem, op_bytes + blob.size()) != hipSuccess) return false;
+    p->d_lists = static_cast<unsigned char*>(mem);
+    if (op_bytes && hipMemcpy(p->d_lists, operands.data(), op_bytes, hipMemcpyHostToDevice) != hipSuccess) return false;
+    const unsigned char* d = p->d_lists + op_bytes;
+    p->w32 = reinterpret_cast<const float*>(p->d_lists), p->bias32 = reinterpret_cast<const float*>(d + bias32), p->used32 = reinterpret_cast<const uint32_t*>(d + used32);
+    p->lists_copy = reinterpret_cast<const K0Args*>(d + args);
+    K0Args& a = p->lists;
+    a.filt_off = reinterpret_cast<const int32_t*>(d + filt_off), a.kidx = reinterpret_cast<const int32_t*>(d + kidx), a.kpat = d + kpat;
+    a.w = reinterpret_cast<const float*>(d + wv), a.tap_dyx = reinterpret_cast<const int8_t*>(d + tap), a.perm = reinterpret_cast<const int32_t*>(d + perm);
+    a.place = reinterpret_cast<const int32_t*>(d + pl), a.bias = reinterpret_cast<const float*>(d + bias);
+    a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w_ = hp.w, a.taps = hp.taps, a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
+    a.stride = hp.stride, a.ho = hp.ho, a.wo = hp.wo, a.out_h = hp.out_h, a.out_w = hp.out_w, a.pool = hp.pool ? 1 : 0;
+    std::memcpy(blob.data() + args, &a, sizeof a);
+    return hipMemcpy(p->d_lists + op_bytes, blob.data(), blob.size(), hipMemcpyHostToDevice) == hipSuccess;
+}
+static K0Args lists_of(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n) {
+    K0Args a = plan->lists;
+    a.x = x_dev, a.y = y_dev, a.n = n;
+    return a;
 }
 
 // pp_conv_plan with tuning.autotune = 1: the execution parameters that section 2.3.1 leaves to tuning are
@@ -446,11 +429,7 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
         return PP_OK;
     }
     bool ok = true;
-    if (hp.quads) {
-        ok = ok && upload(&p->d_wquad, hp.ql.wpk.data(), hp.ql.wpk.size() * 4);
-        ok = ok && upload(&p->d_used, hp.ql.used.data(), hp.ql.used.size() * 4);
-        ok = ok && upload(&p->d_bias_quad, hp.ql.bias_pad.data(), hp.ql.bias_pad.size() * 4);
-    } else if (hp.tiled) {
+    if (hp.tiled) {
         const TiledLayout& tl = hp.tl;
         ok = ok && upload(&p->d_stream, tl.stream.data(), tl.stream.size() * 4);
         ok = ok && upload(&p->d_wave_off, tl.wave_off.data(), tl.wave_off.size() * 4);
@@ -476,21 +455,12 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
                  hipMemset(p->d_xpad, 0, (size_t)std::max(1, hp.n_hint) * hp.ml.cpad * hp.h * hp.w * 2) == hipSuccess;
         if (hp.ml.direct && hp.ml.ksplit > 1)   // the shares' partial sums, for up to n_hint images
             ok = ok && upload(&p->d_ws3, nullptr, (size_t)hp.ml.ksplit * std::max(1, hp.n_hint) * hp.c_out * hp.h * hp.w * 4);
-    } else if (hp.dense32) {
-        ok = ok && upload(&p->d_w32, hp.fl.wpk.data(), hp.fl.wpk.size() * 4);
-        ok = ok && upload(&p->d_bias32, hp.fl.bias_pad.data(), hp.fl.bias_pad.size() * 4);
     } else {
-        const Canonical& cn = hp.canon;
-        std::vector<float> w = cn.wpacked;
-        if (hp.dtype == PP_F16)
-            for (float& v : w) v = f16_to_f32(f32_to_f16_rne(v));
-        ok = ok && upload(&p->d_filt_off, hp.filt_off.data(), hp.filt_off.size() * 4);
-        ok = ok && upload(&p->d_kidx, cn.kidx.data(), cn.kidx.size() * 4);
-        ok = ok && upload(&p->d_kpat, cn.kpat.data(), cn.kpat.size());
-        ok = ok && upload(&p->d_w, w.data(), w.size() * 4);
-        ok = ok && upload(&p->d_tap, hp.tap_dyx.data(), hp.tap_dyx.size());
-        ok = ok && upload(&p->d_perm, cn.perm.data(), cn.perm.size() * 4);
-        ok = ok && upload(&p->d_bias, hp.bias.data(), hp.bias.size() * 4);
+        try {
+            ok = upload_lists(p);
+        } catch (const std::bad_alloc&) {
+            ok = false;
+        }
     }
     if (!ok) {
         free_device(p);
@@ -589,8 +559,8 @@ static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, voi
     K5ConvArgs a{};
     a.x = static_cast<const float*>(x_dev);
     a.y = static_cast<float*>(y_dev);
-    a.wpk = plan->d_w32;
-    a.bias = plan->d_bias32;
+    a.wpk = plan->w32;
+    a.bias = plan->bias32;
     a.n = n, a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w = hp.w, a.ho = hp.ho, a.wo = hp.wo, a.out_h = hp.out_h, a.out_w = hp.out_w;
     a.ks = hp.ks, a.stride = hp.stride, a.pool = hp.pool ? 1 : 0, a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
     a.groups = fl.groups, a.units = fl.units;
@@ -604,6 +574,7 @@ static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, voi
     if (pix + per_wg >= ((int64_t)1 << 31) || ptiles * a.ftiles >= ((int64_t)1 << 28)) return PP_ERR_SHAPE;
     a.pix = (int32_t)pix, a.ptiles = (int32_t)ptiles, a.items = (int32_t)(ptiles * a.ftiles), a.per_xcd = (a.items + 7) / 8;
     a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 4;
+    a.lists = plan->lists_copy;
     const k5_conv_fn fn = k5_conv_lookup(sh);
     if (!fn) return PP_ERR_UNSUPPORTED;
     (void)hipGetLastError();
@@ -617,7 +588,7 @@ static pp_status_t launch_quads(const pp_conv_plan_t* plan, const void* x_dev, v
     K6Args a{};
     a.x = static_cast<const float*>(x_dev);
     a.y = static_cast<float*>(y_dev);
-    a.wpk = plan->d_wquad, a.used = plan->d_used, a.bias = plan->d_bias_quad;
+    a.wpk = plan->w32, a.used = plan->used32, a.bias = plan->bias32;
     a.n = n, a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w = hp.w, a.mc = (hp.w + 3) / 4;
     a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
     const int64_t pieces = (int64_t)n * hp.h * a.mc, ptiles = (pieces + 63) / 64;
@@ -627,6 +598,7 @@ static pp_status_t launch_quads(const pp_conv_plan_t* plan, const void* x_dev, v
     if (pieces + 64 >= ((int64_t)1 << 31) || ptiles * a.fgroups >= ((int64_t)1 << 28)) return PP_ERR_SHAPE;
     a.pieces = (int32_t)pieces, a.items = (int32_t)(ptiles * a.fgroups), a.per_xcd = (a.items + 7) / 8;
     a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 4;
+    a.lists = plan->lists_copy;
     const k6_fn fn = k6_lookup(wk, 64 % a.mc != 0, hp.w % 4 != 0);
     if (!fn) return PP_ERR_UNSUPPORTED;
     (void)hipGetLastError();
@@ -637,10 +609,7 @@ static pp_status_t launch_quads(const pp_conv_plan_t* plan, const void* x_dev, v
 static pp_status_t launch_generic(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream) {
     const HostPlan& hp = plan->hp;
     const int64_t ohw = (int64_t)hp.out_h * hp.out_w;
-    const int relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
-    K0Args a{x_dev, y_dev, plan->d_filt_off, plan->d_kidx, plan->d_kpat, plan->d_w, plan->d_tap, plan->d_perm,
-             plan->d_bias, n, hp.c_in, hp.c_out, hp.h, hp.w, hp.taps, relu,
-             hp.stride, hp.ho, hp.wo, hp.out_h, hp.out_w, hp.pool ? 1 : 0};
+    const K0Args a = lists_of(plan, x_dev, y_dev, n);
     const int64_t blocks = ((int64_t)n * ohw + 255) / 256;
     if (blocks >= ((int64_t)1 << 31)) return PP_ERR_SHAPE;
     dim3 grid((unsigned)blocks, (unsigned)hp.c_out);

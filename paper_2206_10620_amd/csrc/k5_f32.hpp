@@ -13,6 +13,9 @@
 // masks in the loop.  Reduction and pixels are dealt over the wavefronts of a workgroup: WK of them split the reduction
 // units (one unit = one tap x eight channels = four MFMAs per tile) and are summed through LDS in order, WP of them
 // take different pixels with the same weights.
+//
+// A pruned tap is a zero weight here, and 0 x Inf is NaN where the definition skips the tap.  Outputs whose dense sum is not
+// finite are therefore summed again from the kernel lists (k0_again); finite inputs pay one multiply-add per output for the test.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -20,6 +23,7 @@
 #include <cstdint>
 
 #include "f32_rules.hpp"
+#include "k0_generic.hpp"
 
 namespace ppc {
 
@@ -34,6 +38,7 @@ struct K5ConvArgs {
     int32_t pix;            // n * ho * wo convolution outputs
     int32_t ftiles, ptiles, items, per_xcd;
     int64_t x_bytes;
+    const K0Args* lists;    // in device memory; its x, y and n are not set
 };
 
 typedef float k5_f16 __attribute__((ext_vector_type(16)));
@@ -85,6 +90,15 @@ __device__ __forceinline__ void k5_reduce(const k5_f16& acc, float* red, int wk,
             out[i] = s;
         }
     }
+}
+
+// Whether any of the sums is infinite or NaN.
+template <int R>
+__device__ __forceinline__ bool k5_not_finite(const float (&v)[R]) {
+    float z = 0.0f;
+#pragma unroll
+    for (int i = 0; i < R; ++i) z = __builtin_fmaf(v[i], 0.0f, z);
+    return z != z;
 }
 
 template <int MT, int NT, int WK, int WP>
@@ -217,6 +231,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     constexpr int R = 16 / WK;
     float* red = red_all + wp * (WK * 16 * 64);
     const int oplane = a.out_h * a.out_w;
+    uint32_t again = 0;                                         // bit mt NT + nt: the lane's outputs of that tile
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -224,6 +239,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
             float v[R];
             k5_reduce<WK>(acc[mt][nt], red, wk, lane, v);
             const int co0 = (ft * MT + mt) * 32 + half * 4;
+            if (k5_not_finite(v)) again |= 1u << (mt * NT + nt);
             if (a.relu) {
 #pragma unroll
                 for (int i = 0; i < R; ++i) v[i] = v[i] > 0.0f ? v[i] : 0.0f;
@@ -243,6 +259,21 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
                 }
             }
         }
+    if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
+    if (a.pool) {                                               // any of a window's four
+        again |= (uint32_t)__shfl_xor((int)again, 1);
+        again |= (uint32_t)__shfl_xor((int)again, 2);
+        if (lane & 3) again = 0;
+    }
+#pragma unroll 1
+    for (int e = 0; e < MT * NT * R; ++e) {
+        const int tile = e / R, reg = wk * R + e % R;
+        const int j = j0 + tile % NT * 32 + col, co = (ft * MT + tile / NT) * 32 + half * 4 + (reg >> 2) * 8 + (reg & 3);
+        if (((again >> tile) & 1u) && j < a.pix && co < a.c_out) {
+            const int img = j / ohw, opix = a.pool ? (j - img * ohw) >> 2 : j - img * ohw, sy = opix / a.out_w;
+            k0_again(a.lists, a.x, a.y, img, co, sy, opix - sy * a.out_w);
+        }
+    }
 }
 
 // Block-pruned product, binary32: a 32-row tile of the weight matrix with its own compact column list.  The B operand

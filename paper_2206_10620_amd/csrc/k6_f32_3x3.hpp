@@ -42,6 +42,7 @@ struct K6Args {
     int32_t pieces;         // n * h * mc
     int32_t fgroups, items, per_xcd, relu;
     int64_t x_bytes;
+    const K0Args* lists;    // (in device memory) for outputs whose sum is not finite: a tap that only some of a quad's filters use is a zero weight of the others
 };
 
 typedef const __attribute__((address_space(4))) uint32_t* k6_const_u32;
@@ -179,6 +180,7 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(4))) vo
     constexpr int R = 16 / WK;                                      // sums a wavefront finishes per lane: values 4 i + p (filter i, pixel p) from wk R on
     const int64_t obase = (int64_t)img * a.c_out * hw + oy * a.w + 4 * col;
     const int left_px = a.w - 4 * col;                              // pixels of the piece inside the row: at least 1
+    uint32_t again = 0;                                             // bit q: the lane's outputs of that quad
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         __syncthreads();
@@ -191,8 +193,11 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(4))) vo
             float s = red[(wk * R + e) * 64 + lane];
 #pragma unroll
             for (int k = 1; k < WK; ++k) s += red[(k * 16 + wk * R + e) * 64 + lane];
-            v[e] = a.relu && !(s > 0.0f) ? 0.0f : s;
+            v[e] = s;
         }
+        if (k5_not_finite(v)) again |= 1u << q;
+#pragma unroll
+        for (int e = 0; e < R; ++e) v[e] = a.relu && !(v[e] > 0.0f) ? 0.0f : v[e];
         const int val = wk * R, co = fg * 16 + q * 4 + (val >> 2);
         if (!ok || co >= a.c_out) continue;
         float* dst = a.y + obase + (int64_t)co * hw + (val & 3);
@@ -205,6 +210,12 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(4))) vo
             for (int p = 0; p < R; ++p)
                 if ((val & 3) + p < left_px) dst[p] = v[p];
         }
+    }
+    if (__builtin_amdgcn_ballot_w64(again != 0) == 0) return;
+#pragma unroll 1
+    for (int e = 0; e < 4 * R; ++e) {
+        const int q = e / R, val = wk * R + e % R, co = fg * 16 + q * 4 + (val >> 2), px = val & 3;
+        if (((again >> q) & 1u) && ok && co < a.c_out && px < left_px) k0_again(a.lists, a.x, a.y, img, co, oy, 4 * col + px);
     }
 }
 
