@@ -58,16 +58,32 @@ inline K5Shape k5_pick_list(int rows32, int64_t cols, int units) { return k5_pic
 // (4, 8 or 16) on a tile's channels; that number in *wk.
 // A channel costs a SIMD 250 cycles and 33 per used (quad, tap); a wavefront with nobody to share the SIMD with takes about
 // 1500.  Fitted to eleven layers (batch 1 to 32, 16 to 512 channels, 7x7 to 224x224): within 12 % on all but the smallest.
+// They kept 0.3 to 0.5 of the kernels; with few used the taken branches weigh more, and the time is modelled with 550 and 21
+// (191 layers with 0.005 to 0.7 kept: 17 % rms), which is the same around six used taps.
 inline double k6_model(int fgroups, int64_t ptiles, int c_in, double taps_used, int* wk) {
-    double best = 1e300;
+    double best = 1e300, modelled = 0.0;
     for (int w : {4, 8, 16}) {
         const double share = (c_in + w - 1) / w;
         const double per_simd = (double)((fgroups * ptiles + 255) / 256) * w / 4.0;
-        const double together = per_simd * share * (250.0 + 33.0 * 4.0 * taps_used), alone = share * 1500.0;
-        const double us = 7.0 + (together > alone ? together : alone) / 2350.0;
-        if (us < best - 0.01) best = us, *wk = w;
+        const double together = per_simd * share, alone = share * 1500.0;
+        auto us = [&](double cycles) { return 7.0 + (cycles > alone ? cycles : alone) / 2350.0; };
+        const double split = us(together * (250.0 + 33.0 * 4.0 * taps_used));
+        if (split < best - 0.01) best = split, *wk = w, modelled = us(together * (550.0 + 85.0 * taps_used));
     }
-    return best;
+    return modelled;
+}
+
+// The tiled vector kernel in binary32: modelled microseconds of `tiles` tiles of 64 lanes (`lw` across, `r` rows each), for each of
+// which `blocks` workgroups stage c_in channels and `groups` groups of four filters, with `kernels` kept kernels each, walk them in
+// `ks` shares and `chunks` chunks.  Staging costs by the row and by the slot of 16 bytes (rows on 16-byte boundaries) or 4; a channel
+// and a kernel cost a SIMD 22 and 106 cycles a row; one wavefront alone waits for latencies.  Fitted to 491 layers, closest where
+// the kernel is near the fastest: 29 % rms.
+inline double k1_model(int64_t tiles, int lw, int r, bool slots16, int blocks, int groups, int ks, int c_in, double kernels, int chunks) {
+    const double rows = 64.0 * r / lw + 2.0, share = (double)c_in / ks, per_share = kernels / ks;
+    const double staging = (double)tiles * blocks * c_in * rows * (0.9 * lw * (slots16 ? 1 : 4) + 5.6) / 256.0;
+    const double walk = (double)tiles * groups * ks / 1024.0 * r * (share * 22.0 + per_share * 106.0);
+    const double alone = share * 240.0 + per_share * 610.0 + chunks * 2650.0;
+    return 13.0 + (staging + walk > alone ? staging + walk : alone) / 2350.0;
 }
 
 }  // namespace ppc

@@ -288,6 +288,17 @@ int64_t spatial_waves(int n, int h, int w, int lw, int r) {
 
 }  // namespace
 
+// The binary32 3x3 layer runs on the small matrix instruction (hp.quads) or as a dense product.
+static void take_f32_3x3(HostPlan& hp) {
+    hp.tiled = false;
+    hp.dense32 = !hp.quads;
+    hp.chosen = pp_conv_tuning_t{};
+    hp.chosen.variant = 2;
+    hp.chosen.mfma_kind = hp.quads ? 4 : 5;
+    if (hp.quads) pack_quads(hp);
+    else build_f32_layout(hp);
+}
+
 pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     pp_conv_tuning_t t{};
     if (d.tuning) t = *d.tuning;
@@ -349,35 +360,37 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     TiledLayout& tl = hp.tl;
     tl.covered = covered;
 
-    // A binary32 layer whose tuning is left to the library runs on the matrix cores: on the small instruction, which profits
-    // from the sparsity, or as a dense product where that is modelled to be faster (few pixels: it splits the work finer).
-    // Measured, tiled / dense / small instruction: 256 channels 56x56 batch 1 at 0.3: 41 / 39 / 28 us; 256 channels 14x14 batch
-    // 32 at 0.5: 78 / 73 / 56; 64 channels 56x56 batch 32: 56 / 76 / 50; 64 channels 56x56 batch 1: 26 / 7 / 12.
-    {
+    // A binary32 layer whose tuning is left to the library runs on the kernel that is modelled fastest: the small matrix
+    // instruction, which profits from the sparsity, the dense product where the work is little (it splits it finer), or the
+    // vector kernel where few kernels are kept of a large layer (the first costs a channel some 550 cycles however few of its
+    // taps are used).  Measured, vector / dense / small instruction: 256 channels 56x56 batch 1 at 0.3: 42 / 38 / 33 us; 256
+    // channels 14x14 batch 32 at 0.5: 83 / 73 / 71, at 0.05: 38 / 73 / 41; 64 channels 56x56 batch 32 at 0.5: 57 / 75 / 53, at
+    // 0.1: 26 / 75 / 34; 64 channels 56x56 batch 1: 26 / 6 / 13.  On 491 drawn layers (kept 0.005 to 0.7, 8 to 512 channels, 7x7
+    // to 224x224, batch 1 to 32) the choice is 2 % from the best of the three on average, 1.6 times at worst.  The vector kernel
+    // is looked at only where quads use few taps: with a quarter kept or more it was never the fastest by more than 3 %.
+    double other_us = 0.0;                                    // of the faster one of the matrix-core kernels; 0: they don't take the layer
+    if (hp.dtype == PP_F32) {
         const pp_conv_tuning_t none{};
         pp_conv_tuning_t asked = t;
         asked.autotune = 0;
         const bool left_to_us = std::memcmp(&asked, &none, sizeof none) == 0;
         const int mc = (hp.w + 3) / 4;
         const int64_t images = 64 / ((int64_t)hp.h * std::min(mc, hp.w)) + 2;         // that the 64 pieces or pixels of a wavefront can touch
-        if (hp.dtype == PP_F32 && (left_to_us || quads_asked || dense_asked)) {
-            if (images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31)) {
-                hp.quads = quads_asked;
-                if (!dense_asked) mark_quad_taps(hp);
-                if (left_to_us) {
-                    int wk = 0;
-                    const int64_t rows = (int64_t)hp.n_hint * hp.h;
-                    hp.quads = k6_model(hp.ql.groups, (rows * mc + 63) / 64, hp.c_in, hp.ql.taps_used, &wk) <
-                               k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 7) / 8));
-                }
-                hp.tiled = false;
-                hp.dense32 = !hp.quads;
-                hp.chosen.mfma_kind = hp.quads ? 4 : 5;
-                if (hp.quads) pack_quads(hp);
-                else build_f32_layout(hp);
-                return PP_OK;
-            }
-            if (!left_to_us) return PP_ERR_UNSUPPORTED;
+        const bool fits = images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31);
+        if ((quads_asked || dense_asked) && !fits) return PP_ERR_UNSUPPORTED;
+        if (quads_asked || (left_to_us && fits)) mark_quad_taps(hp);
+        if (left_to_us && fits) {
+            int wk = 0;
+            const int64_t rows = (int64_t)hp.n_hint * hp.h;
+            const double quads_us = k6_model(hp.ql.groups, (rows * mc + 63) / 64, hp.c_in, hp.ql.taps_used, &wk);
+            const double dense_us = k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 7) / 8));
+            hp.quads = quads_us < dense_us;
+            other_us = std::min(quads_us, dense_us);
+        }
+        if (quads_asked || dense_asked) {
+            hp.quads = quads_asked;
+            take_f32_3x3(hp);
+            return PP_OK;
         }
     }
     const int eb = hp.dtype == PP_F16 ? 2 : 4;
@@ -499,6 +512,14 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     hp.chosen.chunk_c = tl.cc;
     hp.chosen.staging = tl.mode ? tl.nbuf : 1;
     hp.chosen.split_wg = tl.sw;
+    if (other_us > 0.0) {
+        const double vector_us = k1_model(spatial_wgs, tl.lw, tl.r, tl.mode == 1, (groups_f + tl.wf - 1) / tl.wf, groups_f, tl.ks, hp.c_in, 4.0 * (double)hp.canon.k_kept / hp.c_out, tl.chunks);
+        if (hp.ql.taps_used > 3.5 || other_us < 1.1 * vector_us) {
+            take_f32_3x3(hp);
+            return PP_OK;
+        }
+        hp.quads = false;
+    }
 
     // ---- device layout: which filter sits in which wavefront slot, which channel in which chunk ----
     // The wavefronts of a workgroup meet at a barrier once per channel chunk, so what a chunk costs

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # others), batches whose images a wavefront straddles, filter counts around 16 and its quads, channels around the shares of
 # 4, 8 and 16 wavefronts; which kernel the library takes
 LAYERS = [(1, 1, 1, 1, 1, 1.0, 5), (2, 3, 5, 4, 3, 0.6, 5), (64, 16, 33, 7, 7, 0.5, 5), (40, 17, 16, 9, 13, 0.5, 5), (8, 31, 20, 16, 64, 0.5, 5), (4, 40, 50, 33, 62, 0.3, 5),
-          (16, 64, 64, 28, 28, 0.5, 4), (2, 256, 144, 30, 57, 0.3, 4), (3, 100, 77, 33, 45, 0.4, 5), (32, 130, 64, 14, 14, 0.5, 5), (1, 20, 16, 300, 261, 0.5, 4),
+          (16, 64, 64, 28, 28, 0.4, 4), (2, 256, 144, 30, 57, 0.3, 4), (3, 100, 77, 33, 45, 0.4, 5), (32, 130, 64, 14, 14, 0.5, 5), (1, 20, 16, 300, 261, 0.5, 4),
           (1, 256, 256, 56, 56, 0.3, 4)]
 
 
@@ -74,3 +74,12 @@ def test_tuners_time_every_kernel_and_what_they_report_runs_again(dtype, shape):
         chosen["autotune"] = 0
         again, same = run_layer(lay, x, tuning=pp.Tuning(**chosen))
         assert same == chosen and np.array_equal(again, y), chosen
+
+
+@pytest.mark.parametrize("n,c_in,c_out,h,w,keep", [(32, 64, 64, 56, 56, 0.1), (19, 77, 500, 43, 32, 0.008), (4, 64, 64, 224, 224, 0.2)])
+def test_large_layers_with_few_kernels_left_run_on_the_vector_kernel(n, c_in, c_out, h, w, keep):
+    lay = synth.random_pruned_layer("few", n, c_in, c_out, h, w, "f32", synth.PSET16, keep, 0.3, seed=3)
+    rep, y = check_layer(lay, label=f"few{(n, c_in, c_out, h, w)}")
+    assert rep["chosen"]["variant"] == 2 and rep["chosen"]["mfma_kind"] == 0 and rep["chosen"]["filters_per_wave"] > 0
+    again, chosen = run_layer(lay, lay.make_input(), tuning=pp.Tuning(**rep["chosen"]))
+    assert chosen == rep["chosen"] and np.array_equal(again, y)
