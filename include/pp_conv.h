@@ -68,7 +68,8 @@ enum {
  * section 2.3.1).  A zero field means "let the library choose". */
 typedef struct {
     int32_t variant;        /* 0 auto; 1 generic (any layer: binary32 as a dense product on the binary32 matrix
-                               cores (mfma_kind 5), otherwise one lane per output); 2 the 3x3, stride 1 kernels without a
+                               cores (mfma_kind 5) unless it is very sparse, otherwise one lane per output (for binary32
+                               mfma_kind 6)); 2 the 3x3, stride 1 kernels without a
                                fused pool that profit from the patterns: by itself the tiled pattern-specialised vector kernel
                                (masks outside its sixteen run as covers of those with zero weights), with mfma_kind 4 or 5
                                the binary32 matrix cores (an automatic binary32 plan reports 2 and one of these); 3 matrix-core kernel (binary16 storage only: the pruned
@@ -113,7 +114,7 @@ typedef struct {
                                wavefronts holds 2 * wg_waves or 4 * wg_waves; tile_rows = that count divided by
                                the segments per row, tile_cols / 30 or tile_cols / 14); for binary32 storage: 4 the 3x3, stride 1 one on the small
                                matrix instruction, which skips taps that no filter of four uses, 5 the dense product
-                               (variant 2 or 1) */
+                               (variant 2 or 1), 6 none: one lane per output (variant 1) */
     int32_t split_k;        /* direct-load matrix-core kernel only: workgroups that share one output tile, each on its
                                own run of channel chunks (0 auto, 1 none, 2, 4 or 8; must divide the number of
                                16-channel chunks and leave each share at least 2).  Layers with few tiles fill the

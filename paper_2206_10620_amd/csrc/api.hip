@@ -268,10 +268,14 @@ static pp_status_t plan_autotuned(const pp_conv_desc_t* desc, pp_conv_plan_t** o
                 add([&](pp_conv_tuning_t& t) { t.variant = 3, t.mfma_kind = 2, t.split_k = k; });
         if (base.mfma_kind == 0) add([&](pp_conv_tuning_t& t) { t.variant = 3, t.mfma_kind = 1; });
     }
+    if (!f16 && !base.mfma_kind && base.variant < 2) {
+        add([&](pp_conv_tuning_t& t) { t.variant = 1, t.mfma_kind = 6; });
+        if (base.variant == 1) add([&](pp_conv_tuning_t& t) { t.mfma_kind = 5; });
+    }
     if (base.variant == 0 || base.variant == 2) {
         if (base.variant == 0) add([&](pp_conv_tuning_t& t) { t.variant = 2; });
         if (!f16 && !base.mfma_kind)
-            for (int kind : {4, 5}) add([&](pp_conv_tuning_t& t) { t.variant = 2, t.mfma_kind = kind; });
+            for (int kind : {4, 5}) add([&](pp_conv_tuning_t& t) { t.mfma_kind = kind; });
         if (!f16 || base.variant == 2)
             for (int r : {1, 2})
                 for (int ks : {1, 2, 4})

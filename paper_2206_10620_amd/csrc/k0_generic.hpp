@@ -64,8 +64,8 @@ __device__ __forceinline__ void k0_again(const K0Args* lists, const float* x, fl
 }
 
 // Generic kernel: any pattern table, kernel size, stride, with or without the fused 2x2 max-pool.  One lane per stored output,
-// one filter per blockIdx.y, so that the lists are walked with wave-uniform indices.  It serves binary16 plans that ask for it
-// and binary32 images beyond the matrix-core kernel's 31-bit offsets.
+// one filter per blockIdx.y, so that the lists are walked with wave-uniform indices.  It serves binary16 plans that ask for it,
+// very sparse binary32 layers, and binary32 images beyond the matrix-core kernel's 31-bit offsets.
 template <typename T>
 __global__ __launch_bounds__(256) void k0_generic(const K0Args a) {
     const int pos = blockIdx.y;

@@ -103,7 +103,7 @@ int main() {
         // tuning requests, some of them impossible: they must be refused, not crash
         tun.variant = rng.below(4);
         if (c % 3 == 0) tun.rows_per_lane = rng.below(3), tun.split_c = rng.below(5), tun.waves_f = rng.below(9), tun.filters_per_wave = 4 * rng.below(3);
-        if (c % 4 == 1) tun.tile_cols = 14 * rng.below(5), tun.wg_waves = 4 * rng.below(3), tun.mfma_kind = rng.below(6);
+        if (c % 4 == 1) tun.tile_cols = 14 * rng.below(5), tun.wg_waves = 4 * rng.below(3), tun.mfma_kind = rng.below(7);
         if (c % 5 == 2) tun.tile_rows = rng.below(20), tun.tile_cols = rng.below(80), tun.tiles_per_wave = 2 * rng.below(3);
         if (c % 6 == 3) tun.staging = rng.below(9), tun.split_wg = rng.below(4), tun.chunk_c = rng.below(40), tun.lanes_x = rng.below(17);
         d.tuning = (c % 2) ? &tun : nullptr;

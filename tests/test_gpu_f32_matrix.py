@@ -27,6 +27,9 @@ def test_conv(layer):
     pset = synth.random_pattern_set(ksize, {1: 1, 3: 4, 5: 6, 7: 9}[ksize], 1 if ksize == 1 else 5, seed=2)
     lay = synth.random_pruned_layer_k("f32mc", n, c_in, c_out, h, w, "f32", ksize, pset, 0.6, 0.3, seed=n + c_in, stride=stride, pool=pool)
     for relu in (True, False):
+        for kind in (5, 6):                  # the dense product and the kernel lists
+            rep, _ = check_layer(lay, tuning=pp.Tuning(variant=1, mfma_kind=kind), relu=relu, label=f"f32mc{layer}-{kind}")
+            assert rep["chosen"] == pp.Tuning(variant=1, mfma_kind=kind).as_dict()
         check_layer(lay, relu=relu, label=f"f32mc{layer}")
 
 

@@ -76,6 +76,18 @@ def test_foreign_pattern_table_runs_on_the_tiled_kernel_as_a_cover_of_its_own_pa
     p5.close()
 
 
+@pytest.mark.parametrize("layer,keep,kind", [((2, 512, 512, 14, 14, 7), 0.5, 5), ((2, 512, 512, 14, 14, 7), 0.01, 6), ((8, 64, 64, 56, 56, 5), 0.5, 5),
+                                             ((8, 64, 64, 56, 56, 5), 0.01, 6), ((8, 256, 512, 28, 28, 1), 0.1, 5), ((8, 256, 512, 28, 28, 1), 0.001, 6)])
+def test_very_sparse_binary32_layers_stay_on_the_kernel_lists(layer, keep, kind):
+    n, c_in, c_out, h, w, ksize = layer
+    pset = synth.random_pattern_set(ksize, 1 if ksize == 1 else 4, 1 if ksize == 1 else 6, 1)
+    lay = synth.random_pruned_layer_k("sp", n, c_in, c_out, h, w, "f32", ksize, pset, keep, 0.1, 0)
+    for tuning in (None, pp.Tuning(variant=1), pp.Tuning(variant=1, mfma_kind=kind)):
+        plan = pp.plan_from_layer(lay, host_only=True, tuning=tuning)
+        assert plan.query()["chosen"] == pp.Tuning(variant=1, mfma_kind=kind).as_dict()
+        plan.close()
+
+
 @pytest.mark.parametrize("layer", [("f32", 16, 64, 64, 28, 28), ("f32", 2, 24, 32, 28, 28), ("f16", 1, 97, 33, 64, 53), ("f16", 2, 64, 64, 224, 224), ("f16", 8, 512, 512, 14, 14)],
                          ids=lambda v: "x".join(str(i) for i in v))
 def test_a_plan_reports_the_kernel_it_runs(layer):
