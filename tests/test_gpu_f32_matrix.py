@@ -38,6 +38,23 @@ def test_conv_batches_beyond_the_hint():
     check_layer(lay, n_hint=1, label="f32mc-hint")
 
 
+def test_the_largest_batch_a_call_takes():
+    # 2^31 - 2 pixels of one channel: no room behind them in 32 bits for the rest of a tile
+    n, h, w = 42966, 151, 331
+    plan_args = dict(c_in=1, c_out=1, h=h, w=w, pattern_masks=np.array([1], dtype=np.uint16), pattern_id=np.zeros(1, np.int32), conn_mask=None,
+                     weights=np.array([2.0], np.float32), bias=np.array([1.0], np.float32), kernel_size=1, n_hint=n, tuning=pp.Tuning(variant=1, mfma_kind=5))
+    st, handle = pp.pp_conv_plan(**plan_args)
+    assert st == pp.PP_OK
+    x = torch.empty(n * h * w, device="cuda")
+    for i in range(0, x.numel(), 1 << 28):
+        x[i:i + (1 << 28)] = torch.arange(i % 8191, i % 8191 + min(1 << 28, x.numel() - i), device="cuda").remainder_(8191)
+    y = torch.full_like(x, float("nan"))
+    assert pp.pp_conv_run(handle, x.data_ptr(), y.data_ptr(), n, torch.cuda.current_stream().cuda_stream) == pp.PP_OK
+    for i in range(0, x.numel(), 1 << 28):
+        assert torch.equal(y[i:i + (1 << 28)], 2 * x[i:i + (1 << 28)] + 1)
+    pp.pp_conv_destroy(handle)
+
+
 # m, k, n, block, row keep, column keep
 PRODUCTS = [(1, 1, 1, 1, 1.0, 1.0), (31, 7, 31, 8, 1.0, 1.0), (32, 8, 32, 16, 1.0, 1.0), (33, 9, 33, 16, 0.6, 0.6), (100, 200, 65, 16, 0.5, 0.5),
             (64, 64, 40, 32, 0.0, 0.5), (200, 1000, 1, 64, 0.5, 0.5), (300, 520, 197, 50, 0.5, 0.5), (1000, 600, 700, 16, 0.5, 0.5)]
