@@ -6,18 +6,23 @@
 A step is one forward pass of the whole hot path (input staging, multiply-accumulates, fused
 bias+ReLU epilogue) over one batch of seeded synthetic input that is already resident in HBM.
 The plan (filter kernel reorder + weight packing) is built once, before the timed region.
-Prints ONE JSON line.
+Prints ONE JSON line, the last one of the output: short enough for a reader that keeps the last 2000 characters, floats to
+six digits.  The other workloads come before it: their records one per line behind "# other ", then all their microseconds
+per step in one line behind "# others_us".
 
 metric   : effective GMAC/s = non-zero multiply-accumulates (4 per kept kernel per output pixel) per second
 workload : by default the largest single-GPU configuration, the 1080p image-enhancement layer (its
            tensors exceed the 256 MB last-level cache, so it streams HBM); every other benchmark layer and
-           the VGG-shaped stack run as one chain of launches are timed too and reported under `others`.
+           the VGG-shaped stack run as one chain of launches are timed too.
 roofline : the dominant kernel of the timed workload against the roofline that binds it:
-           * the tiled pattern-specialised kernel (variant 2) is bound by the FP32 vector ALUs:
+           * the tiled pattern-specialised kernel (k1_tiled) is bound by the FP32 vector ALUs:
              256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2 (packed) x 2.4 GHz = 157.3 TFLOP/s; the library is
              built with packed-FP32 formation disabled, so `peak_unpacked` = 78.6 TFLOP/s is the reachable
              ceiling.  `achieved` counts 2 flop per effective MAC.
-           * the matrix-core kernels (variant 3, zero-filled dense weights in binary16) do 9/(4*keep) times
+           * the binary32 matrix-core kernels are bound by the binary32 MFMA rate, 157.3 TFLOP/s: `achieved`
+             counts 2 flop per dense MAC for k5_conv_f32, which multiplies the zeros too, and per effective
+             MAC for k6_f32_3x3, which skips most of them.
+           * the binary16 matrix-core kernels (variant 3, zero-filled dense weights in binary16) do 9/(4*keep) times
              the multiply-accumulates at matrix-core rate.  By algorithmic counts the 1080p layer then
              needs 66 us of HBM time (531 MB at 8 TB/s) against 61 us of matrix-core time (153 GFLOP at
              2.5 PFLOP/s): HBM is the binding roofline, and `achieved` = algorithmic bytes (x once, y
@@ -50,15 +55,54 @@ PEAK_HBM_GBS = 8000.0
 
 # HBM-side traffic of one launch (bytes), from rocprofv3 FETCH_SIZE / WRITE_SIZE scaled by a copy
 # kernel of known size; see profiles/.  Valid only for the kernel revision it was measured on:
-# reported as null for any other.  Keyed by (workload, variant).
+# reported as null for any other.  Keyed by (workload, variant): k1_tiled for variant 2, k3_mfma for 3.
 MEASURED_TRAFFIC = {
-    ("cfg5_enhance_1080p", 3): ("lib-2026-11-28-i", 606.92e6),
-    ("cfg4_vgg_L6", 3): ("lib-2026-11-28-i", 38.16e6),
-    ("cfg4_vgg_L9", 3): ("lib-2026-11-28-i", 53.92e6),
-    ("cfg2_vgg_mid", 2): ("lib-2026-11-28-i", 20.43e6),
+    ("cfg5_enhance_1080p", 3): ("lib-2026-12-04-a", 609.51e6),
+    ("cfg4_vgg_L6", 3): ("lib-2026-12-04-a", 38.16e6),
+    ("cfg4_vgg_L9", 3): ("lib-2026-12-04-a", 53.92e6),
+    ("cfg2_vgg_mid", 2): ("lib-2026-12-04-a", 20.43e6),
+}
+
+# The same for the binary32 matrix-core kernels, keyed by (workload, kernel).
+MEASURED_TRAFFIC_F32 = {
+    ("cfg2_vgg_mid", "k6_f32_3x3"): ("lib-2026-12-04-a", 44.64e6),
 }
 
 DEFAULT_WORKLOAD = "cfg5_enhance_1080p"
+
+
+def kernel_of(chosen):
+    """The kernel a plan with these reported parameters runs on."""
+    variant, kind = chosen["variant"], chosen["mfma_kind"]
+    if variant == 3:
+        return {2: "k3_mfma", 3: "k4 block product"}.get(kind, "k2_mfma")
+    return {4: "k6_f32_3x3", 5: "k5_conv_f32"}.get(kind, "k1_tiled" if variant == 2 else "k0_generic")
+
+
+def traffic_of(workload, chosen, revision):
+    kernel = kernel_of(chosen)
+    rev, nbytes = MEASURED_TRAFFIC_F32.get((workload, kernel), (None, None))
+    if kernel in ("k1_tiled", "k3_mfma"):
+        rev, nbytes = MEASURED_TRAFFIC.get((workload, chosen["variant"]), (None, None))
+    return nbytes if rev == revision else None
+
+
+def short(v):
+    """Floats to six digits, all the way down."""
+    if isinstance(v, float):
+        return float(f"{v:.6g}")
+    if isinstance(v, dict):
+        return {k: short(w) for k, w in v.items()}
+    return [short(w) for w in v] if isinstance(v, (list, tuple)) else v
+
+
+def output_lines(out, others):
+    """What is printed: the other workloads, then the JSON line."""
+    out = dict(out, config={k: ({p: w for p, w in v.items() if w} if k == "params" else v) for k, v in out["config"].items()})
+    lines = ["# other " + json.dumps(short(o)) for o in others or ()]
+    if others:
+        lines.append("# others_us " + " ".join(f"{o['workload']}={o['us_per_step']:.1f}" for o in others))
+    return lines + [json.dumps(short(out), separators=(",", ":"))]
 
 
 def workloads():
@@ -177,8 +221,7 @@ def time_copy_reference(x, y, layer_us):
     ev1.record()
     torch.cuda.synchronize()
     us = ev0.elapsed_time(ev1) * 1e3 / steps
-    return {"what": "torch device copy reading and writing as many bytes as the layer's input and output hold",
-            "bytes_moved": 2 * (nbytes // 4) * 4, "us": us, "gb_per_s": 2 * (nbytes // 4) * 4 / us / 1e3,
+    return {"bytes_moved": 2 * (nbytes // 4) * 4, "us": us, "gb_per_s": 2 * (nbytes // 4) * 4 / us / 1e3,
             "layer_us_over_copy_us": layer_us / us}
 
 
@@ -195,13 +238,14 @@ def summarize(lay, t):
                 eff_gmac_per_s=lay.eff_macs / sec / 1e9, alg_gb_per_s=lay.alg_bytes / sec / 1e9,
                 frac_fp32_valu=2 * lay.eff_macs / sec / 1e12 / PEAK_FP32_TFLOPS,
                 frac_fp32_valu_unpacked=2 * lay.eff_macs / sec / 1e12 / PEAK_FP32_UNPACKED_TFLOPS,
-                frac_mfma_dense=2 * dense_macs(lay) / sec / 1e12 / PEAK_MFMA_F16_TFLOPS,
+                kernel=kernel_of(t["chosen"]),
+                frac_mfma_dense=2 * dense_macs(lay) / sec / 1e12 / (PEAK_MFMA_F16_TFLOPS if lay.dtype == "f16" else PEAK_FP32_TFLOPS),
                 frac_hbm=lay.alg_bytes / sec / 1e9 / PEAK_HBM_GBS, params=t["chosen"])
 
 
 BLOCK_WORKLOAD = "block_ffn_4096"
 # HBM-side bytes of one launch of the block-pruned product, measured as above (profiles/k4_block_gemm_block_ffn_4096.md)
-MEASURED_TRAFFIC_BLOCK = ("k4-2026-11-28-b", 184.45e6)
+MEASURED_TRAFFIC_BLOCK = ("k4-2026-12-04-a", 184.46e6)
 
 
 def time_block_gemm(steps, warmup, check=True, npts=2000):
@@ -231,7 +275,7 @@ def time_block_gemm(steps, warmup, check=True, npts=2000):
     plan.close()
     executed_flop = 2.0 * q["executed_weights"] * lay.n
     res = dict(workload=lay.name, dtype=lay.dtype, m=lay.m, k=lay.k, n=lay.n, block=[lay.bm, lay.bk],
-               kept_weights=int(q["kept_weights"]), executed_weights=int(q["executed_weights"]), kernel="k4_block_gemm" if q["variant"] == 2 else "k4_generic",
+               kept_weights=int(q["kept_weights"]), executed_weights=int(q["executed_weights"]), kernel="k4_block_gemm",      # (binary16, thousands of columns: the 512-column tile)
                eff_gmacs=lay.eff_macs / 1e9, alg_mb=lay.alg_bytes / 1e6, us_per_step=sec * 1e6, wall_us_per_step=wall * 1e6,
                eff_gmac_per_s=lay.eff_macs / sec / 1e9, alg_gb_per_s=lay.alg_bytes / sec / 1e9,
                executed_tflops=executed_flop / sec / 1e12, frac_mfma_executed=executed_flop / sec / 1e12 / PEAK_MFMA_F16_TFLOPS,
@@ -308,7 +352,7 @@ def reuse_main(args):
            "vs_baseline": None, "dtype": "f32", "data": "synthetic",
            "config": {k: r[k] for k in ("workload", "n", "k", "m", "seg_len", "hash_bits", "neuron_vectors", "clusters")},
            "roofline": {"bound": "hbm", "achieved": r["alg_gb_per_s"], "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": r["frac_hbm"],
-                        "traffic": None, "kernel": "reuse_hash + reuse_products + reuse_gather", "kernel_us": sec * 1e6}}
+                        "traffic": None, "kernel": "reuse_clear + reuse_hash_tiled + reuse_products_packed + reuse_gather_packed", "kernel_us": sec * 1e6}}
     if "max_rel_err" in r:
         import oracle
         out["cpu_baseline"] = {"value": lay.dense_macs / r["cpu_seconds"] / 1e9, "unit": "GMAC/s", "cores": 1, "kind": "oracle",
@@ -436,17 +480,19 @@ def time_vgg_stack(steps, warmup):
 def roofline_of(lay, t, traffic):
     """The roofline that binds the kernel the plan chose."""
     sec = t["event_ms_per_step"] * 1e-3
-    variant = t["chosen"]["variant"]
-    if variant == 3:
+    kernel = kernel_of(t["chosen"])
+    if t["chosen"]["variant"] == 3:
         return {"bound": "hbm", "achieved": lay.alg_bytes / sec / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": lay.alg_bytes / sec / 1e9 / PEAK_HBM_GBS, "traffic": traffic,
-                "kernel": {2: "k3_mfma", 3: "k4_block_gemm"}.get(t["chosen"].get("mfma_kind"), "k2_mfma"),
-                "kernel_us": t["event_ms_per_step"] * 1e3,
+                "kernel": kernel, "kernel_us": t["event_ms_per_step"] * 1e3,
                 "frac_mfma": 2 * dense_macs(lay) / sec / 1e12 / PEAK_MFMA_F16_TFLOPS,
                 "peak_mfma_tflops": PEAK_MFMA_F16_TFLOPS}
-    ach = 2 * lay.eff_macs / sec / 1e12
+    ach = 2 * (dense_macs(lay) if kernel == "k5_conv_f32" else lay.eff_macs) / sec / 1e12
+    if kernel in ("k5_conv_f32", "k6_f32_3x3"):
+        return {"bound": "mfma", "achieved": ach, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_FP32_TFLOPS,
+                "traffic": traffic, "kernel": kernel, "kernel_us": t["event_ms_per_step"] * 1e3}
     return {"bound": "alu", "achieved": ach, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_FP32_TFLOPS,
-            "traffic": traffic, "kernel": "k1_tiled" if variant == 2 else "k0_generic",
+            "traffic": traffic, "kernel": kernel,
             "kernel_us": t["event_ms_per_step"] * 1e3,
             "peak_unpacked": PEAK_FP32_UNPACKED_TFLOPS, "frac_unpacked": ach / PEAK_FP32_UNPACKED_TFLOPS}
 
@@ -509,8 +555,7 @@ def main():
     s = summarize(lay, t)
     sec_wall = t["wall_ms_per_step"] * 1e-3
 
-    rev, tbytes = MEASURED_TRAFFIC.get((args.workload, t["chosen"]["variant"]), (None, None))
-    traffic = tbytes if (rev == pp.KERNEL_REVISION and not args.tuning and not args.mfma_tile and not args.autotune) else None
+    traffic = None if args.tuning or args.mfma_tile or args.autotune else traffic_of(args.workload, t["chosen"], pp.KERNEL_REVISION)
 
     out = {
         "metric": "effective GMAC/s (nonzero MACs), pattern-pruned 3x3 conv",
@@ -562,6 +607,7 @@ def main():
     del t
     torch.cuda.empty_cache()
 
+    others = None
     if not args.no_others:
         others = []
         for name, make in table.items():
@@ -580,9 +626,9 @@ def main():
         torch.cuda.empty_cache()
         reu = time_deep_reuse(steps=20, warmup=5, check=not args.no_cpu)
         others.append({k: v for k, v in reu.items() if not k.startswith("_")})
-        out["others"] = others
 
-    print(json.dumps(out))
+    for line in output_lines(out, others):
+        print(line)
 
 
 if __name__ == "__main__":

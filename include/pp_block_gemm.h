@@ -77,7 +77,9 @@ typedef struct {
     int32_t row_tile;           /* rows per tile (64) */
     int32_t row_tiles;          /* ceil(m / row_tile) */
     int64_t kept_weights;       /* number of (m, k) with Wd structurally kept */
-    int64_t executed_weights;   /* row_tile * sum over tiles of the padded list length: what the matrix cores multiply */
+    int64_t executed_weights;   /* row_tile * sum over tiles of the padded list length: what the matrix cores multiply in a
+                                   PP_F16 plan of variant 2 (the other kernels walk lists of their own, one per 32 rows, which
+                                   hold at most these columns) */
     const int32_t *tile_off;    /* [row_tiles + 1] */
     const int32_t *tile_cols;   /* [tile_off[row_tiles]] */
     const int32_t *tile_len;    /* [row_tiles] list length before padding */

@@ -281,8 +281,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // A product with few columns has few 64 x 512 tiles, each a long serial walk: 4096 x 4096 on one column is 64 of them.  Here
 // a workgroup owns 64 rows x 32 NT columns and its WK wavefronts take consecutive shares of the list; each stages its own
 // chunks (a ring in its own part of LDS, so the loop has no barrier) and the shares are summed through LDS in order.
-// Bound by the latency of its loads (0.3 us per chunk and wavefront); 4096 x 4096 in 64 x 64 blocks at 0.41: one column 2834 us
-// (one lane per output) -> 9 us, 8 columns 44.7 (the 512-column tile) -> 7.5, 512 columns 57 -> 19, 1024 columns 59 -> 30.
+// Bound by the latency of its loads (0.3 us per chunk and wavefront); 4096 x 4096 in 64 x 64 blocks at 0.41: one column 3314 us
+// (one lane per output) -> 9.9 us; repeated on one input 2834 -> 9, 8 columns 44.7 (the 512-column tile) -> 7.5, 512 columns
+// 57 -> 19, 1024 columns 59 -> 30.
 // A row of x in the stage is 64 NT bytes, so one direct load moves 16 / NT rows: lane i of load q brings list entry
 // (i / (4 NT)) NT + q, whose columns sit at slot piece ^ (q << 1) of LDS row q (16 / NT) + i / (4 NT) -- the exchange puts
 // the four rows a transposing read touches into different banks.

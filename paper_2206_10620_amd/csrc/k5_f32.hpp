@@ -335,7 +335,6 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 1
             xv[set][nt][p] = k5_load(xr, ro[p] + jb[nt], 0u);
         }
     };
-    auto next_unit = [&]() {};
     auto load = [&](int set, int u) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) load_slot(set, u, i);
@@ -367,7 +366,6 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 1
                 for (int i = q * NL / NM; i < (q + 1) * NL / NM; ++i) load_slot((d + D - 1) % D, u + d + D - 1, i);
                 __builtin_amdgcn_sched_barrier(0);
             });
-            next_unit();
         }
     }
 #pragma unroll

@@ -31,6 +31,48 @@ def test_measured_traffic_belongs_to_the_current_kernel_revision():
         assert m and abs(float(m.group(1)) * 1e6 - nbytes) <= 0.02e6 + 1e-3 * nbytes
 
 
+def test_binary32_traffic_belongs_to_the_kernel_that_runs():
+    sys.path.insert(0, ROOT)
+    import bench
+    for (wl, kernel), (rev, nbytes) in bench.MEASURED_TRAFFIC_F32.items():
+        plan = pp.plan_from_layer(bench.workloads()[wl](), host_only=True)
+        chosen = plan.query()["chosen"]
+        plan.close()
+        assert bench.kernel_of(chosen) == kernel and rev == pp.KERNEL_REVISION
+        assert bench.traffic_of(wl, chosen, pp.KERNEL_REVISION) == nbytes and bench.traffic_of(wl, chosen, "another") is None
+        text = open(os.path.join(ROOT, "profiles", f"{kernel}_{wl}.md")).read()
+        assert pp.KERNEL_REVISION in text
+        m = re.search(r"= ([0-9.]+) MB, against", text)
+        assert m and abs(float(m.group(1)) * 1e6 - nbytes) <= 0.02e6 + 1e-3 * nbytes
+    # a kernel that runs by name only has its own figures, or none
+    named = pp.Tuning(variant=2, mfma_kind=5).as_dict()
+    assert bench.traffic_of("cfg2_vgg_mid", named, pp.KERNEL_REVISION) is None
+
+
+def test_the_json_line_is_last_and_short():
+    """A reader that keeps the last 2000 characters of the output has to find the whole line."""
+    import json
+    sys.path.insert(0, ROOT)
+    import bench
+    x = 12345.67890123456789
+    names = [n for n in bench.workloads()] + ["cfg4_vgg_stack_chained", bench.BLOCK_WORKLOAD, bench.REUSE_WORKLOAD]
+    out = {"metric": "effective GMAC/s (nonzero MACs), pattern-pruned 3x3 conv", "value": x, "unit": "GMAC/s", "n_gpus": 1, "steps": 100, "warmup": 20, "ms_per_step": x,
+           "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "tuned": False, "dtype": "f16", "data": "synthetic",
+           "config": {"workload": "cfg5_enhance_1080p", "n": 1, "c_in": 64, "c_out": 64, "h": 1080, "w": 1920, "patterns": 16, "k_kept": 1638, "keep": x, "fused": "bias+relu",
+                      "params": pp.Tuning(variant=3, tile_rows=16, tile_cols=60, tiles_per_wave=2, wg_waves=8, mfma_kind=2, split_k=1).as_dict()},
+           "alg_gb_per_s": x, "frac_hbm": x, "frac_fp32_valu": x, "frac_fp32_valu_unpacked": x,
+           "roofline": {"bound": "hbm", "achieved": x, "peak": x, "unit": "GB/s", "frac": x, "traffic": x, "kernel": "k3_mfma", "kernel_us": x, "frac_mfma": x, "peak_mfma_tflops": x},
+           "copy_reference": {"bytes_moved": 530841600, "us": x, "gb_per_s": x, "layer_us_over_copy_us": x},
+           "cpu_baseline": {"value": x, "unit": "GMAC/s", "cores": 16, "kind": "oracle", "sample": "3472222 sampled outputs (2.616% of the layer)", "seconds": x}, "max_rel_err": x}
+    lines = bench.output_lines(out, [dict(workload=n, us_per_step=412.34567, note="y" * 500) for n in names])
+    assert len(lines) == len(names) + 2 and all(l.startswith("# other {") for l in lines[:-2])
+    assert dict(o.split("=") for o in lines[-2].split()[2:]) == {n: "412.3" for n in names}
+    assert all("\n" not in l for l in lines) and len(lines[-1]) <= 1600          # (what the runtime prints to stderr comes behind it)
+    back = json.loads(lines[-1])
+    assert set(out) == set(back) and back["config"]["params"]["wg_waves"] == 8
+    assert json.loads(bench.output_lines(out, None)[-1])["value"] == 12345.7
+
+
 def test_block_product_traffic_belongs_to_the_current_kernel_revision():
     sys.path.insert(0, ROOT)
     import bench
