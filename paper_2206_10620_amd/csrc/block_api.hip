@@ -63,10 +63,12 @@ template <int NT, int WK> void launch_split(const K4Args& a, int blocks, hipStre
 }
 
 // Which tile a launch runs with: the smallest modelled time.  A workgroup of the split kernel walks chunks / wk chunks per
-// wavefront, each worth 0.3 us of load latency or, with several wavefronts on a compute unit, nt + 2 KB through the vector
-// cache (0.012 us per KB); the 512-column tile takes 0.4 us per chunk alone on a compute unit and 0.52 with a neighbour.
-// Measured on 27 products (1 to 4096 columns, 4 to 64 row tiles, 8 to 106 chunks) the pick is 1.4 % from the best shape on
-// average, 16 % at worst; 4096 x 4096 at 0.41: at 2048 columns 4 x 4 takes 57 us against the wide tile's 61, at 3000 87 against 72.
+// wavefront, each worth 0.14 us of latency and, for every wavefront on the compute unit, nt + 2 KB through the vector cache
+// (0.012 us per KB), and a round of them 2.1 us and its stores; the 512-column tile takes 3.65 us and, two to a compute unit,
+// 0.74 us per chunk, 0.28 where few run, and 2.6 us more where pieces straddle rows.  Fitted to 370 products timed with every
+// tile (1 to 8192 columns, 8 to 4096 rows, 4 to 4096 columns of weights, 1- to 64-wide blocks): the pick is 1.2 % from the best
+// on average, 1.28 times at worst.  4096 x 4096 at 0.41 on 4096 columns: 512-column tile 63 us, 4 x 4 104 modelled; 1775 x 23 on
+// 181 columns: 1 x 8 4.6 us, 512-column tile 9.8.
 K4Shape k4_pick(const BlockHostPlan& hp, int n, int batch) {
     struct Split { int nt, wk, resident; K4Shape shape; };
     static const Split kSplits[] = {{1, 4, 4, {32, launch_split<1, 4>}}, {1, 8, 2, {32, launch_split<1, 8>}}, {2, 4, 3, {64, launch_split<2, 4>}},
@@ -74,14 +76,14 @@ K4Shape k4_pick(const BlockHostPlan& hp, int n, int batch) {
     const K4Shape wide{kBlockColTile, launch_wide};
     if (hp.k >= (1 << 24) || n >= (1 << 23)) return wide;       // the split kernel multiplies in 24 bits
     const double chunks = (double)hp.tile_cols.size() / kBlockChunk / hp.row_tiles;
-    auto per_cu = [&](int cols) { return ((int64_t)hp.row_tiles * ((n + cols - 1) / cols) * batch + 255) / 256; };
-    const int64_t pw = per_cu(kBlockColTile);
+    auto wgs = [&](int cols) { return (int64_t)hp.row_tiles * ((n + cols - 1) / cols) * batch; };
+    const int64_t full = wgs(kBlockColTile) / 512, rest = wgs(kBlockColTile) % 512;
     K4Shape best = wide;
-    double best_t = chunks * ((double)(pw / 2) * 0.52 + (double)(pw % 2) * 0.4);
+    double best_t = (double)full * (3.65 + chunks * 0.737) + (rest ? 3.65 + chunks * (0.276 + 0.0009 * (double)rest) : 0.0) + (n % 8 ? 2.6 : 0.0);
     for (const Split& s : kSplits) {
         const double share = chunks / s.wk > 1.0 ? chunks / s.wk : 1.0;
-        auto round = [&](int64_t k) { return k == 0 ? 0.0 : std::max(share * 0.3, (double)k * s.wk * share * (s.nt + 2) * 0.012) + 0.7 * s.nt; };
-        const int64_t p = per_cu(s.shape.cols);
+        auto round = [&](int64_t k) { return k == 0 ? 0.0 : share * 0.137 + (double)k * s.wk * share * (s.nt + 2) * 0.012 + 0.72 * s.nt * (0.25 + 0.75 * (double)k) + 2.1; };
+        const int64_t p = (wgs(s.shape.cols) + 255) / 256;
         const double t = (double)(p / s.resident) * round(s.resident) + round(p % s.resident);
         if (t < best_t) best_t = t, best = s.shape;
     }
