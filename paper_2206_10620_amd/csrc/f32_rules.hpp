@@ -49,13 +49,16 @@ inline double k5_model_conv(int rows32, int64_t cols, int units) {
     (void)k5_pick(kK5Conv, rows32, cols, units, &cycles);
     return 5.0 + 1.1 * cycles / 2350.0;
 }
-// The generic kernel, one lane per output walking its filter's kernel list: modelled microseconds for `pixels` stored outputs per
-// filter, `kept` kernels of `taps` taps, at most `longest` in a filter.  Fitted to 209 layers (1x1 to 7x7, stride 1 and 2, pooled or
-// not, 0.005 to 0.7 kept): 26 % rms where it is within a factor of three of the dense product.
-inline double lists_model(int64_t pixels, int64_t kept, int taps, int64_t longest, bool pool) {
-    const double windows = pool ? 4.0 : 1.0;
-    const double together = (double)((pixels + 255) / 256 * 4) * (double)kept * windows * 1e-6 * (82.0 + 72.0 * taps), alone = (double)longest * windows * (0.05 + 0.22 * taps);
-    return 3.7 + (together > alone ? together : alone);
+// The generic kernel, one lane per output walking its filter's kernel list: modelled microseconds for n images of c_in channels of
+// in_px pixels and c_out filters with out_px stored outputs each, `kept` kernels of `taps` taps, at most `longest` in a filter.
+// The walk costs up to 1.4 times as much where an image is larger than an L2 (4 MB); reading and writing is 0.27 us per MB.  Fitted
+// to 209 layers (1x1 to 7x7, stride 1 and 2, pooled or not, 0.005 to 0.7 kept): 19 % rms, closest where it is near the dense product.
+inline double lists_model(int n, int c_in, int64_t in_px, int c_out, int64_t out_px, int64_t kept, int taps, int64_t longest, bool pool) {
+    const double windows = pool ? 4.0 : 1.0, waves = (double)(((int64_t)n * out_px + 255) / 256 * 4);
+    const double image = (double)c_in * (double)in_px * 4e-6, over = image / 4.0 - 1.0, read = kept < c_in ? (double)kept / c_in : 1.0;
+    const double far = 1.0 + 0.385 * (over < 0.0 ? 0.0 : over > 1.0 ? 1.0 : over);
+    const double together = waves * (double)kept * windows * 1e-6 * (36.0 + 65.0 * taps) * far, alone = (double)longest * windows * (0.075 + 0.224 * taps);
+    return 3.05 + (together > alone ? together : alone) + 0.27 * n * (image * read + (double)c_out * (double)out_px * 4e-6);
 }
 // The shape for a layer (or block-pruned product) of `rows32` 32-row tiles, `cols` pixels or columns and `units` reduction units per tile.
 inline K5Shape k5_pick_conv(int rows32, int64_t cols, int units) { return k5_pick(kK5Conv, rows32, cols, units); }

@@ -350,10 +350,10 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
         // The binary32 layers the tiled kernel has no code for run as dense products on the binary32 matrix cores: a
         // bottleneck block (1x1, strided 3x3, 1x1; 256-128-512 channels, 56x56 maps, batch 8) took 1574 us with one lane per output.
         // That kernel stays for binary16 storage on request, for images that a 31-bit byte offset does not span, and for layers
-        // so sparse that it is modelled 1.4 times as fast (the dense product takes its time whatever is kept).  Measured, dense /
+        // so sparse that it is modelled faster (the dense product takes its time whatever is kept).  Measured, dense /
         // lists: 7x7, four taps, 512 channels, 14x14, batch 2: 116 / 86 us at 0.1 kept, 116 / 16 at 0.01; 5x5, 64 channels, 56x56,
         // batch 8: 53 / 55 and 53 / 9; 1x1, 256 -> 512, 28x28, batch 8: 23 / 175 and 23 / 24.  On 209 drawn layers the choice is
-        // 3 % from the better one on average, 1.64 times at worst; dense everywhere was 2.4 times, 38 at worst.
+        // 1 % from the better one on average, 1.44 times at worst; dense everywhere was 2.4 times, 38 at worst.
         if (hp.dtype != PP_F32) return PP_OK;
         const int64_t images = 64 / ((int64_t)hp.ho * hp.wo) + 2;       // that the 64 pixels of a wavefront can touch
         const bool fits = images * hp.c_in * hp.h * hp.w * 4 < ((int64_t)1 << 31);
@@ -362,9 +362,9 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
         if (hp.dense32 && !dense_asked) {
             const int KK = hp.ks * hp.ks, rows32 = (hp.c_out + 31) / 32, units = KK * ((hp.c_in + 7) / 8);
             const int64_t longest = hp.canon.kcount.empty() ? 0 : hp.canon.kcount[0];      // filters are in descending order of it
-            const double lists_us = lists_model((int64_t)hp.n_hint * hp.out_h * hp.out_w, hp.canon.k_kept, hp.taps, longest, hp.pool);
+            const double lists_us = lists_model(hp.n_hint, hp.c_in, (int64_t)hp.h * hp.w, hp.c_out, (int64_t)hp.out_h * hp.out_w, hp.canon.k_kept, hp.taps, longest, hp.pool);
             // (the operands of the very largest layers would not fit a host's memory)
-            hp.dense32 = 1.4 * lists_us > k5_model_conv(rows32, (int64_t)hp.n_hint * hp.ho * hp.wo, units) && (int64_t)rows32 * units * 1024 < ((int64_t)1 << 33);
+            hp.dense32 = 1.05 * lists_us > k5_model_conv(rows32, (int64_t)hp.n_hint * hp.ho * hp.wo, units) && (int64_t)rows32 * units * 1024 < ((int64_t)1 << 33);
         }
         hp.chosen.mfma_kind = hp.dense32 ? 5 : 6;
         if (hp.dense32) build_f32_layout(hp);
