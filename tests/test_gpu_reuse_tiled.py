@@ -43,7 +43,7 @@ def test_runs_of_different_lengths_in_turn():
     lay = synth.random_reuse_layer("t", 5000, 96, 32, 8, 10, seed=6, prototypes=40)
     plan = pp.reuse_plan_from_layer(lay)
     try:
-        for n in (5000, 70, 2049, 5000):          # each run finds the tables as the one before left them
+        for n in (5000, 70, 513, 2048, 2049, 5000, 2048):      # each run finds the tables as the one before left them
             x = lay.make_input(n)
             y = plan.run(torch.from_numpy(x).cuda())
             torch.cuda.synchronize()
