@@ -36,12 +36,12 @@ def test_block_product(m, k, n):
     compare(y, wd @ x.astype(np.float64) + (0.0 if lay.bias is None else lay.bias.astype(np.float64)[:, None]))
 
 
-@pytest.mark.parametrize("tuning", [dict(variant=2), dict(variant=3, mfma_kind=1), dict(variant=3, mfma_kind=2), dict(variant=3, mfma_kind=2, split_k=2)],
-                         ids=lambda t: "-".join(f"{k}{v}" for k, v in t.items()))
-@pytest.mark.parametrize("pool", [False, True])
+KERNELS = [(dict(variant=2), False), (dict(variant=3, mfma_kind=1), False), (dict(variant=3, mfma_kind=1), True), (dict(variant=3, mfma_kind=2), False),
+           (dict(variant=3, mfma_kind=2), True), (dict(variant=3, mfma_kind=2, split_k=2), False)]
+
+
+@pytest.mark.parametrize("tuning,pool", KERNELS, ids=lambda t: "-".join(f"{k}{v}" for k, v in t.items()) if isinstance(t, dict) else f"pool{int(t)}")
 def test_convolution(tuning, pool):
-    if pool and (tuning["variant"] == 2 or "split_k" in tuning):
-        pytest.skip("no fused pool there")
     lay = synth.random_pruned_layer_k("big", 2, 64, 40, 14, 20, "f16", 3, synth.PSET8, 0.5, 0.3, seed=3, pool=pool)
     lay.weights = lay.weights * np.float32(600.0)
     x = (lay.make_input().astype(np.float32) * 300.0).astype(np.float16)

@@ -32,7 +32,9 @@ def T(**kw):
 def test_config1_small_layer(seed, relu):
     lay = synth.config1(seed)
     say(f"config1 seed={seed} relu={relu}")
-    rep, _ = check_layer(lay, relu=relu, label="cfg1")
+    for tuning in (None, T(variant=2)):                       # the library's choice, and the tiled vector kernel
+        rep, _ = check_layer(lay, tuning=tuning, relu=relu, label="cfg1")
+    assert rep["chosen"]["mfma_kind"] == 0
     say(f"  E={rep['E']:.2e} {rep['chosen']}")
 
 
@@ -183,39 +185,48 @@ def test_degenerate_sparsity():
     # empty mask: bias only
     lay = copy.copy(base)
     lay.conn_mask = np.zeros_like(base.conn_mask)
-    _, y = check_layer(lay, relu=False, label="empty")
-    assert np.array_equal(y, np.broadcast_to(base.bias[None, :, None, None], y.shape))
+    both = (None, T(variant=2))                               # the library's choice, and the tiled vector kernel
+    for tuning in both:
+        _, y = check_layer(lay, tuning=tuning, relu=False, label="empty")
+        assert np.array_equal(y, np.broadcast_to(base.bias[None, :, None, None], y.shape))
     # some empty filters, one full filter
     lay = copy.copy(base)
     m = base.conn_mask.copy().reshape(20, 12)
     m[[0, 7, 19]] = 0
     m[4] = 1
     lay.conn_mask = m.reshape(-1)
-    check_layer(lay, label="empty-filters")
+    for tuning in both:
+        check_layer(lay, tuning=tuning, label="empty-filters")
     # a single pattern everywhere; and every pattern present in one filter
     lay = copy.copy(base)
     lay.pattern_id = np.full_like(base.pattern_id, 5)
-    check_layer(lay, label="single-pattern")
+    for tuning in both:
+        check_layer(lay, tuning=tuning, label="single-pattern")
     lay = copy.copy(base)
     lay.conn_mask = np.ones_like(base.conn_mask)
     lay.pattern_id = (np.arange(base.pattern_id.size) % 8).astype(np.int32)
-    check_layer(lay, label="all-kept")
+    for tuning in both:
+        check_layer(lay, tuning=tuning, label="all-kept")
     # no bias
     lay = copy.copy(base)
     lay.bias = None
-    check_layer(lay, label="no-bias")
+    for tuning in both:
+        check_layer(lay, tuning=tuning, label="no-bias")
 
 
 def test_foreign_patterns_and_dense_layer():
     lay = synth.random_pruned_layer("foreign", 2, 6, 10, 9, 11, "f32", np.array([0x00F, 0x1E0, 0x03A, 0x145], dtype=np.uint16),
                                     0.7, 0.3, seed=1)
     rep, _ = check_layer(lay, label="foreign")
-    assert rep["chosen"]["variant"] == 2                       # runs as a cover of the kernel's own patterns
+    assert rep["chosen"]["variant"] == 2
+    rep, _ = check_layer(lay, tuning=T(variant=2), label="foreign-cover")
+    assert rep["chosen"]["variant"] == 2 and rep["chosen"]["mfma_kind"] == 0      # runs as a cover of the kernel's own patterns
     rep, _ = check_layer(lay, tuning=T(variant=1), label="foreign-generic")
     assert rep["chosen"]["variant"] == 1
     for dtype in ("f32", "f16"):
         lay = synth.dense_layer("dense", 2, 3, 16, 12, 20, dtype, 0.3, seed=2)
-        rep, _ = check_layer(lay, label="dense")
+        for tuning in (None, T(variant=2)):
+            rep, _ = check_layer(lay, tuning=tuning, label="dense")
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
@@ -245,6 +256,10 @@ def test_filter_reordering_invariance_and_determinism():
     lay2.pattern_id, lay2.conn_mask, lay2.weights, lay2.bias = lay.pattern_id[rows], lay.conn_mask[rows], lay.weights[rows], lay.bias[perm]
     y3, _ = run_layer(lay2, x)
     assert np.array_equal(y3, y1[:, perm])                     # same per-filter summation order: bit-identical
+    v1, _ = run_layer(lay, x, tuning=T(variant=2))
+    v2, _ = run_layer(lay, x, tuning=T(variant=2))
+    v3, _ = run_layer(lay2, x, tuning=T(variant=2))
+    assert np.array_equal(v1, v2) and np.array_equal(v3, v1[:, perm])      # the same on the tiled vector kernel
     # With channels in natural order, waves per workgroup and filters per wave do not change any
     # output's summation order either; the load-balanced channel order depends on which filters share
     # a workgroup, so there results agree to rounding only.
@@ -272,7 +287,8 @@ def test_config2_full_size():
     lay = synth.config2()
     say("config2")
     for relu in (True, False):
-        rep, _ = check_layer(lay, relu=relu, label="cfg2")
+        for tuning in (T(variant=2), None):
+            rep, _ = check_layer(lay, tuning=tuning, relu=relu, label="cfg2")
     say(f"  E={rep['E']:.2e} E_scale={rep['E_scale']:.2e} {rep['chosen']}")
 
 
@@ -281,7 +297,8 @@ def test_config3_resnet_shapes(batch):
     for lay in synth.config3(batch):
         say(lay.name)
         for relu in (True, False):
-            rep, _ = check_layer(lay, relu=relu, label="cfg3")
+            for tuning in (T(variant=2), None):
+                rep, _ = check_layer(lay, tuning=tuning, relu=relu, label="cfg3")
         say(f"  E={rep['E']:.2e} E_scale={rep['E_scale']:.2e} {rep['chosen']}")
 
 

@@ -65,7 +65,10 @@ def test_foreign_pattern_table_runs_on_the_tiled_kernel_as_a_cover_of_its_own_pa
     assert info["chosen"]["variant"] == 2
     st, *_ = pp.pp_conv_plan_unpack(plan.handle, info["k_kept"])
     assert st == pp.PP_ERR_UNSUPPORTED                     # several stream entries per kernel: no round trip
-    pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(variant=2)).close()
+    tiled = pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(variant=2))
+    assert tiled.query()["chosen"]["mfma_kind"] == 0
+    assert pp.pp_conv_plan_unpack(tiled.handle, info["k_kept"])[0] == pp.PP_ERR_UNSUPPORTED
+    tiled.close()
     gen = pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(variant=1))
     assert gen.query()["chosen"]["variant"] == 1           # the generic kernel stays available by name
     gen.close()
