@@ -1,5 +1,5 @@
 """Binary32 3x3 layers on the kernel of the small matrix instruction (mfma_kind 4) and as dense products (5), each by name and
-left to the library's choice, against the CPU checker with the binary32 gate of 1e-5 (a sum of K products in any order errs by about sqrt(K) *
+left to the library's choice, against the oracle with the binary32 gate of 1e-5 (a sum of K products in any order errs by about sqrt(K) *
 2^-24 of its rms: 3e-6 for the 2304 longest one here)."""
 import numpy as np
 import pytest

@@ -1,5 +1,5 @@
 """Infinities and NaN in the input of binary32 layers: a pruned tap is skipped, so they reach the outputs whose kept taps read
-them and no other, on every kernel; against the checker's gather evaluation, which walks the masks' bits."""
+them and no other, on every kernel; against the oracle's gather evaluation, which walks the masks' bits."""
 import numpy as np
 import pytest
 
