@@ -464,13 +464,14 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
             ok = upload_lists(p);
         } catch (const std::bad_alloc&) {
             ok = false;
+            st = PP_ERR_ALLOC;
         }
     }
     if (!ok) {
         free_device(p);
         delete p;
         (void)hipGetLastError();
-        return PP_ERR_DEVICE;
+        return st == PP_OK ? PP_ERR_DEVICE : st;
     }
     {   // set-up is the place to look up this device's copy of the static scratch array
         void* unused = nullptr;

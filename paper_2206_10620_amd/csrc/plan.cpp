@@ -532,6 +532,7 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
             return PP_OK;
         }
         hp.quads = false;
+        hp.ql = QuadLayout{};
     }
 
     // ---- device layout: which filter sits in which wavefront slot, which channel in which chunk ----
