@@ -33,10 +33,10 @@ def test_layers(layer):
 
 
 @pytest.mark.parametrize("w", [4, 12, 13, 16, 64, 67])
-@pytest.mark.parametrize("n,c_in,c_out,h", [(1, 3, 16, 5), (3, 9, 70, 7), (40, 33, 64, 20), (3, 200, 64, 40)])
-def test_every_instantiation(n, c_in, c_out, h, w):
+@pytest.mark.parametrize("n,c_in,c_out,h,keep", [(1, 3, 16, 5, 0.5), (3, 9, 70, 7, 0.5), (40, 33, 64, 20, 0.5), (3, 200, 64, 40, 0.5), (1, 250, 40, 9, 0.2)])
+def test_every_instantiation(n, c_in, c_out, h, keep, w):
     # pieces that divide 64 and others, whole pieces and not, with 4, 8 and 16 wavefronts on a tile's channels
-    lay = synth.random_pruned_layer("quads", n, c_in, c_out, h, w, "f32", synth.PSET16, 0.5, 0.3, seed=c_in + w)
+    lay = synth.random_pruned_layer("quads", n, c_in, c_out, h, w, "f32", synth.PSET16, keep, 0.3, seed=c_in + w)
     check_layer(lay, tuning=pp.Tuning(variant=2, mfma_kind=4), label=f"quads{(n, c_in, c_out, h, w)}")
 
 
