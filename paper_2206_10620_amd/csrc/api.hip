@@ -140,7 +140,7 @@ struct pp_conv_plan {
     pp_block_gemm_plan_t* pointwise = nullptr; // a 1x1 stride-1 layer in binary16 runs as a batch of matrix products (one per image)
     _Float16* d_xpad = nullptr;               // x with zero channels appended up to whole chunks of 16: [n_hint][cpad][h][w]
     // binary32 matrix-core kernels
-    const float* w32 = nullptr;
+    const void* w32 = nullptr;
     const float* bias32 = nullptr;
     const uint32_t* used32 = nullptr;         // (small matrix instruction)
     // generic kernel
@@ -215,15 +215,15 @@ static bool upload_lists(pp_conv_plan_t* p) {
                  pl = add(place.data(), place.size() * 4), bias = add(hp.bias.data(), hp.bias.size() * 4);
     void* mem = nullptr;
     static const std::vector<float> none;
-    const std::vector<float>& operands = hp.quads ? hp.ql.wpk : hp.dense32 ? hp.fl.wpk : none;
+    const void* operands = hp.quads ? (const void*)hp.ql.wpk.data() : hp.dense32 ? (hp.fl.narrow ? (const void*)hp.fl.wpk_narrow.data() : (const void*)hp.fl.wpk.data()) : nullptr;
     const std::vector<float>& bias_pad = hp.quads ? hp.ql.bias_pad : hp.dense32 ? hp.fl.bias_pad : none;
     const size_t bias32 = add(bias_pad.data(), bias_pad.size() * 4), used32 = add(hp.ql.used.data(), hp.quads ? hp.ql.used.size() * 4 : 0);
-    const size_t op_bytes = operands.size() * 4;            // (a multiple of 1024)
+    const size_t op_bytes = hp.quads ? hp.ql.wpk.size() * 4 : hp.dense32 ? hp.fl.wpk.size() * 2 + hp.fl.wpk_narrow.size() * 4 : 0;            // (a multiple of 1024)
     if (hipMalloc(&mem, op_bytes + blob.size()) != hipSuccess) return false;
     p->d_lists = static_cast<unsigned char*>(mem);
-    if (op_bytes && hipMemcpy(p->d_lists, operands.data(), op_bytes, hipMemcpyHostToDevice) != hipSuccess) return false;
+    if (op_bytes && hipMemcpy(p->d_lists, operands, op_bytes, hipMemcpyHostToDevice) != hipSuccess) return false;
     const unsigned char* d = p->d_lists + op_bytes;
-    p->w32 = reinterpret_cast<const float*>(p->d_lists), p->bias32 = reinterpret_cast<const float*>(d + bias32), p->used32 = reinterpret_cast<const uint32_t*>(d + used32);
+    p->w32 = p->d_lists, p->bias32 = reinterpret_cast<const float*>(d + bias32), p->used32 = reinterpret_cast<const uint32_t*>(d + used32);
     p->lists_copy = reinterpret_cast<const K0Args*>(d + args);
     K0Args& a = p->lists;
     a.filt_off = reinterpret_cast<const int32_t*>(d + filt_off), a.kidx = reinterpret_cast<const int32_t*>(d + kidx), a.kpat = d + kpat;
@@ -576,22 +576,25 @@ static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, voi
     a.bias = plan->bias32;
     a.n = n, a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w = hp.w, a.ho = hp.ho, a.wo = hp.wo, a.out_h = hp.out_h, a.out_w = hp.out_w;
     a.ks = hp.ks, a.stride = hp.stride, a.pool = hp.pool ? 1 : 0, a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
-    a.groups = fl.groups, a.units = fl.units;
+    a.units = fl.units, a.groups = fl.groups;
     const int64_t pix = (int64_t)n * hp.ho * hp.wo;
     const int rows32 = (hp.c_out + 31) / 32;
-    const K5Shape sh = k5_pick_conv(rows32, pix, fl.units);
-    const int64_t per_wg = (int64_t)32 * sh.nt * sh.wp;
+    static constexpr K5ConvShape narrow{};
+    const K5ConvShape& sh = fl.narrow ? narrow : k5_pick_conv(rows32, pix, fl.units);
+    const int64_t per_wg = (int64_t)32 * sh.wp;
     const int64_t ptiles = (pix + per_wg - 1) / per_wg;
     a.ftiles = (rows32 + sh.mt - 1) / sh.mt;
     // pixel indices past the last one are formed in 32 bits
     if (pix + per_wg >= ((int64_t)1 << 31) || ptiles * a.ftiles >= ((int64_t)1 << 28)) return PP_ERR_SHAPE;
     a.pix = (int32_t)pix, a.ptiles = (int32_t)ptiles, a.items = (int32_t)(ptiles * a.ftiles), a.per_xcd = (a.items + 7) / 8;
     a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 4;
+    // The operand that every XCD reads is the smaller one.
+    a.pixels_inner = (int64_t)fl.tiles * fl.units * (fl.narrow ? 1024 : 3072) > a.x_bytes ? 1 : 0;
     a.lists = plan->lists_copy;
-    const k5_conv_fn fn = k5_conv_lookup(sh);
+    const k5_conv_fn fn = fl.narrow ? k5_narrow_lookup(k5_pick_narrow(rows32, pix, fl.units)) : k5_conv_lookup(sh);
     if (!fn) return PP_ERR_UNSUPPORTED;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(fn, dim3((unsigned)(a.per_xcd * 8)), dim3((unsigned)(64 * sh.wk * sh.wp)), 0, stream, a);
+    fn(a, a.per_xcd * 8, stream);
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
@@ -601,7 +604,7 @@ static pp_status_t launch_quads(const pp_conv_plan_t* plan, const void* x_dev, v
     K6Args a{};
     a.x = static_cast<const float*>(x_dev);
     a.y = static_cast<float*>(y_dev);
-    a.wpk = plan->w32, a.used = plan->used32, a.bias = plan->bias32;
+    a.wpk = static_cast<const float*>(plan->w32), a.used = plan->used32, a.bias = plan->bias32;
     a.n = n, a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w = hp.w, a.mc = (hp.w + 3) / 4;
     a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
     const int64_t pieces = (int64_t)n * hp.h * a.mc, ptiles = (pieces + 63) / 64;

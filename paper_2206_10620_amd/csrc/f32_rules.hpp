@@ -7,48 +7,88 @@
 
 namespace ppc {
 
-// The dense kernel: wavefront tiles of 32 mt filters x 32 nt pixels (columns), wk wavefronts of a workgroup on one tile's
-// reduction, wp on different pixels.
-struct K5Shape {
-    int mt = 1, nt = 1, wk = 1, wp = 1;
+// The dense convolution: workgroups of wp x wk wavefronts of 32 mt filters x 32 pixels each, wk of them on one tile's reduction, wp on
+// different pixels with the same weights.  Modelled microseconds of a launch: start, and per workgroup on a compute unit (the mean of
+// their number and that number rounded up) `wg`, and per reduction unit of a wavefront `alone` or, where more, `wg_unit` per workgroup.
+// Fitted to 64 layers (1x1 to 7x7, stride 1 and 2, 3 to 478 channels, 7x7 to 199 wide, batch 1 to 32): 7 to 19 % rms; the shape it
+// picks is 3 % from the best of seventeen tried on average, 1.4 times at worst.  The shapes left out were never better by more than
+// a percent or two.  Examples: 256 channels, 14x14, 3x3, batch 32: 4 2 4 takes 41 us, 2 2 2 53, 4 4 1 58; 256 to 128 channels, 1x1, 56x56,
+// batch 8: 4 4 2 takes 17.0 us, 4 4 1 18.2, 2 2 2 20.
+struct K5ConvShape {
+    int mt = 1, wp = 1, wk = 1;
+    double wg = 0.0, alone = 0.0, wg_unit = 0.0;
 };
+inline constexpr K5ConvShape kK5Conv[] = {{4, 4, 1, 1.97, 0.351, 0.521}, {4, 4, 2, 4.11, 0.046, 0.763}, {4, 2, 4, 3.70, 0.750, 0.844}, {2, 4, 1, 0.88, 0.393, 0.326},
+                                          {2, 2, 2, 0.84, 0.386, 0.336}, {2, 2, 4, 2.46, 0.485, 0.583}, {2, 1, 4, 1.13, 0.300, 0.372}, {1, 4, 1, 0.45, 0.305, 0.231}};
 
-// Modelled time of a launch in cycles: the larger of the matrix-core time on the fullest compute unit (its wavefronts per
-// SIMD times 4 mt nt MFMAs of 64 cycles per unit) and the time the operands take to come out of L2 (1 KB per unit for each
-// of mt weight and nt pixel operands, 16 bytes per clock and compute unit; wavefronts that share weights find most of them
-// in the vector cache).  Fitted to 11 shapes on 13 layers and 7 on 9 products: the shape it picks is within 1 % of the best
-// one tried on average, 3 % at worst.  Examples: 128 channels, 56x56 to 28x28, 3x3, batch 8: 2 2 4 1 takes 23.5 us, 1 1 4 1
-// 30.2, 2 2 1 4 72.8; 256 to 128 channels, 1x1, 56x56, batch 8: 1 2 1 4 22.5 us, 2 2 8 1 32.6.
-inline double k5_cycles(int64_t wgs, int waves, int64_t units_per_wave, int mt, int nt, int wp) {
-    const double per_simd = (double)((wgs + 255) / 256) * waves / 4.0;
-    const double mfma = (per_simd < 1.0 ? 1.0 : per_simd) * (double)units_per_wave * 4 * mt * nt * 64;
-    const double traffic = (double)wgs * waves * (double)units_per_wave * (mt * (wp > 1 ? 0.3 : 1.0) + nt) * 1024 / (256 * 16.0);
-    return mfma > traffic ? mfma : traffic;
+// The shape for a layer of `rows32` 32-filter tiles, `cols` pixels and `units` reduction units; its modelled microseconds in *us.
+inline const K5ConvShape& k5_pick_conv(int rows32, int64_t cols, int units, double* us = nullptr) {
+    const K5ConvShape* best = nullptr;
+    double best_t = 1e300;
+    for (const K5ConvShape& o : kK5Conv) {
+        const int64_t wgs = (int64_t)((rows32 + o.mt - 1) / o.mt) * ((cols + 32 * o.wp - 1) / (32 * o.wp));
+        const double even = wgs < 256 ? 1.0 : (double)wgs / 256.0, load = 0.5 * (even + (double)((wgs + 255) / 256));
+        const double unit = load * o.wg_unit > o.alone ? load * o.wg_unit : o.alone;
+        const double t = 5.8 + load * o.wg + (double)((units + o.wk - 1) / o.wk) * unit;
+        if (t < best_t) best_t = t, best = &o;
+    }
+    if (us) *us = best_t;
+    return *best;
+}
+// The kernel of the binary32 instruction: how many wavefronts share the reduction of a 32 x 32 tile; modelled microseconds in *us.  It is
+// the faster one where there are few tiles, one to a compute unit: the bound is what a compute unit can read, and its weights are four
+// bytes, not six.  Units of eight channels here, in cycles of four instructions; rounds of workgroups cost 0.4 us beyond the first.  Between
+// the two kernels the models are 0.6 % from the faster one on 90 layers (1x1 to 5x5, 3 to 500 channels, 56 to 200000 pixels).
+inline int k5_pick_narrow(int rows32, int64_t cols, int units, double* us = nullptr) {
+    const int64_t wgs = (int64_t)rows32 * ((cols + 31) / 32), rounds = (wgs + 255) / 256;
+    int best = 0;
+    int64_t best_t = 0;
+    for (int wk : {4, 8, 16}) {
+        if (wk > 4 && units < 2 * wk) continue;              // shares of less than two units only cost their reduction
+        const int64_t t = rounds * (wk / 4) * ((units + wk - 1) / wk);
+        if (!best || t < best_t) best_t = t, best = wk;
+    }
+    if (us) *us = 5.8 + 1.1 * 256.0 / 2350.0 * (double)best_t + 0.4 * (double)(rounds - 1);
+    return best;
+}
+// The faster one's microseconds; `units` are the reduction units of sixteen channels, `narrow_units` those of eight.
+inline double k5_model_conv(int rows32, int64_t cols, int units, int narrow_units, bool* narrow = nullptr) {
+    double us = 0.0, narrow_us = 0.0;
+    (void)k5_pick_conv(rows32, cols, units, &us);
+    (void)k5_pick_narrow(rows32, cols, narrow_units, &narrow_us);
+    if (narrow) *narrow = narrow_us < us;
+    return narrow_us < us ? narrow_us : us;
 }
 
-inline constexpr K5Shape kK5Conv[] = {{2, 2, 1, 4}, {2, 2, 2, 2}, {2, 2, 4, 1}, {2, 2, 8, 1}, {1, 2, 1, 4}, {1, 2, 4, 1}, {1, 2, 8, 1}, {1, 1, 4, 1}, {1, 1, 8, 1}, {1, 1, 16, 1}};
-inline constexpr K5Shape kK5List[] = {{1, 2, 4, 1}, {1, 2, 8, 1}, {1, 1, 4, 1}, {1, 1, 8, 1}, {1, 1, 16, 1}};
+// The block-pruned product: wavefront tiles of 32 rows x 32 nt columns, wk wavefronts of a workgroup on one tile's reduction.
+struct K5Shape {
+    int nt = 1, wk = 1;
+};
 
-template <int N>
-inline K5Shape k5_pick(const K5Shape (&opts)[N], int rows32, int64_t cols, int units, double* cycles = nullptr) {
+// Modelled time of a launch in cycles: the larger of the matrix-core time on the fullest compute unit (its wavefronts per SIMD times
+// 4 nt MFMAs of 64 cycles per unit) and the time the operands take to come out of L2 (1 KB per unit for the weight and each of nt
+// column operands, 16 bytes per clock and compute unit).  Fitted to 7 shapes on 9 products: the shape it picks is within 3 % of the
+// best one tried.
+inline double k5_cycles(int64_t wgs, int waves, int64_t units_per_wave, int nt) {
+    const double per_simd = (double)((wgs + 255) / 256) * waves / 4.0;
+    const double mfma = (per_simd < 1.0 ? 1.0 : per_simd) * (double)units_per_wave * 4 * nt * 64;
+    const double traffic = (double)wgs * waves * (double)units_per_wave * (1 + nt) * 1024 / (256 * 16.0);
+    return mfma > traffic ? mfma : traffic;
+}
+inline constexpr K5Shape kK5List[] = {{2, 4}, {2, 8}, {1, 4}, {1, 8}, {1, 16}};
+// The shape for a product of `rows32` 32-row tiles, `cols` columns and `units` reduction units per tile.
+inline K5Shape k5_pick_list(int rows32, int64_t cols, int units) {
     K5Shape best;
     double best_t = 1e300;
-    for (const K5Shape& o : opts) {
+    for (const K5Shape& o : kK5List) {
         if (o.wk > 4 && units < 2 * o.wk) continue;          // shares of less than two units only cost their reduction
-        const int64_t wgs = (int64_t)((rows32 + o.mt - 1) / o.mt) * ((cols + 32 * o.nt * o.wp - 1) / (32 * o.nt * o.wp));
-        const double t = k5_cycles(wgs, o.wk * o.wp, (units + o.wk - 1) / o.wk, o.mt, o.nt, o.wp);
+        const int64_t wgs = (int64_t)rows32 * ((cols + 32 * o.nt - 1) / (32 * o.nt));
+        const double t = k5_cycles(wgs, o.wk, (units + o.wk - 1) / o.wk, o.nt);
         if (t < best_t) best_t = t, best = o;
     }
-    if (cycles) *cycles = best_t;
     return best;
 }
 
-// Its modelled microseconds.
-inline double k5_model_conv(int rows32, int64_t cols, int units) {
-    double cycles = 0.0;
-    (void)k5_pick(kK5Conv, rows32, cols, units, &cycles);
-    return 5.0 + 1.1 * cycles / 2350.0;
-}
 // The generic kernel, one lane per output walking its filter's kernel list: modelled microseconds for n images of c_in channels of
 // in_px pixels and c_out filters with out_px stored outputs each, `kept` kernels of `taps` taps, at most `longest` in a filter.
 // The walk costs up to 1.4 times as much where an image is larger than an L2 (4 MB); reading and writing is 0.27 us per MB.  Fitted
@@ -60,10 +100,6 @@ inline double lists_model(int n, int c_in, int64_t in_px, int c_out, int64_t out
     const double together = waves * (double)kept * windows * 1e-6 * (36.0 + 65.0 * taps) * far, alone = (double)longest * windows * (0.075 + 0.224 * taps);
     return 3.05 + (together > alone ? together : alone) + 0.27 * n * (image * read + (double)c_out * (double)out_px * 4e-6);
 }
-// The shape for a layer (or block-pruned product) of `rows32` 32-row tiles, `cols` pixels or columns and `units` reduction units per tile.
-inline K5Shape k5_pick_conv(int rows32, int64_t cols, int units) { return k5_pick(kK5Conv, rows32, cols, units); }
-inline K5Shape k5_pick_list(int rows32, int64_t cols, int units) { return k5_pick(kK5List, rows32, cols, units); }
-
 // The 3x3 kernel on the small instruction: modelled microseconds of a layer of `fgroups` 16-filter groups, `ptiles` 256-pixel
 // tiles and c_in channels of which a quad of filters uses `taps_used` taps on average, with the best number of wavefronts
 // (4, 8 or 16) on a tile's channels; that number in *wk.

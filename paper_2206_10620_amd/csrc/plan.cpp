@@ -96,6 +96,28 @@ uint16_t f32_to_f16_rne(float v) {
     return (uint16_t)(sign | out);
 }
 
+float bf16_to_f32(uint16_t b) {
+    const uint32_t u = (uint32_t)b << 16;
+    float v;
+    std::memcpy(&v, &u, 4);
+    return v;
+}
+
+void split_bf16(float v, uint16_t (&part)[3]) {
+    for (int i = 0; i < 3; ++i) {
+        uint32_t u;
+        std::memcpy(&u, &v, 4);
+        const uint32_t rounded = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+        if ((u & 0x7FFFFFFFu) >= 0x7F800000u) {                     // infinite or NaN, and stays so
+            part[i] = (uint16_t)(u >> 16 | ((u & 0x7FFFFFu) != 0 ? 0x40u : 0u));
+            for (++i; i < 3; ++i) part[i] = 0;
+            return;
+        }
+        part[i] = (uint16_t)((rounded & 0x7F80u) == 0x7F80u ? u >> 16 : rounded);
+        v -= bf16_to_f32(part[i]);
+    }
+}
+
 float f16_to_f32(uint16_t b) {
     const uint32_t sign = (uint32_t)(b & 0x8000u) << 16, e = (b >> 10) & 31u, m = b & 1023u;
     uint32_t u;
@@ -360,11 +382,11 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
         if (dense_asked && !fits) return PP_ERR_UNSUPPORTED;
         hp.dense32 = fits && !lists_asked;
         if (hp.dense32 && !dense_asked) {
-            const int KK = hp.ks * hp.ks, rows32 = (hp.c_out + 31) / 32, units = KK * ((hp.c_in + 7) / 8);
+            const int KK = hp.ks * hp.ks, rows32 = (hp.c_out + 31) / 32, units = KK * ((hp.c_in + 15) / 16);
             const int64_t longest = hp.canon.kcount.empty() ? 0 : hp.canon.kcount[0];      // filters are in descending order of it
             const double lists_us = lists_model(hp.n_hint, hp.c_in, (int64_t)hp.h * hp.w, hp.c_out, (int64_t)hp.out_h * hp.out_w, hp.canon.k_kept, hp.taps, longest, hp.pool);
             // (the operands of the very largest layers would not fit a host's memory)
-            hp.dense32 = 1.05 * lists_us > k5_model_conv(rows32, (int64_t)hp.n_hint * hp.ho * hp.wo, units) && (int64_t)rows32 * units * 1024 < ((int64_t)1 << 33);
+            hp.dense32 = 1.05 * lists_us > k5_model_conv(rows32, (int64_t)hp.n_hint * hp.ho * hp.wo, units, KK * ((hp.c_in + 7) / 8)) && (int64_t)rows32 * units * 3072 < ((int64_t)1 << 33);
         }
         hp.chosen.mfma_kind = hp.dense32 ? 5 : 6;
         if (hp.dense32) build_f32_layout(hp);
@@ -373,14 +395,15 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     TiledLayout& tl = hp.tl;
     tl.covered = covered;
 
-    // A binary32 layer whose tuning is left to the library runs on the kernel that is modelled fastest: the small matrix
-    // instruction, which profits from the sparsity, the dense product where the work is little (it splits it finer), or the
-    // vector kernel where few kernels are kept of a large layer (the first costs a channel some 550 cycles however few of its
-    // taps are used).  Measured, vector / dense / small instruction: 256 channels 56x56 batch 1 at 0.3: 42 / 38 / 33 us; 256
-    // channels 14x14 batch 32 at 0.5: 83 / 73 / 71, at 0.05: 38 / 73 / 41; 64 channels 56x56 batch 32 at 0.5: 57 / 75 / 53, at
-    // 0.1: 26 / 75 / 34; 64 channels 56x56 batch 1: 26 / 6 / 13.  On 491 drawn layers (kept 0.005 to 0.7, 8 to 512 channels, 7x7
-    // to 224x224, batch 1 to 32) the choice is 2 % from the best of the three on average, 1.6 times at worst.  The vector kernel
-    // is looked at only where quads use few taps: with a quarter kept or more it was never the fastest by more than 3 %.
+    // A binary32 layer whose tuning is left to the library runs on the kernel that is modelled fastest: the dense product, the small
+    // matrix instruction, which profits from the sparsity, or the vector kernel where few kernels are kept of a large layer.  Measured
+    // at half the kernels kept, dense / small instruction: 256 channels 14x14 batch 32: 41 / 68 us; 512 channels 14x14 batch 1: 24 / 66;
+    // 64 channels 56x56 batch 1: 7.0 / 12.8; 17 to 394 channels 46x49 batch 24: 101 / 64.  Between 0.9 of the small instruction's modelled
+    // time and all of it the two are about as fast (256 channels, 56x56, batch 1, 0.3 kept: 28 / 29; 64 channels, 56x56, batch 32: 50 / 51) and
+    // the layer stays with the small instruction; below 10 us both are mostly launch and the dense product is the faster one.  On 36 drawn
+    // layers (3 to 512 channels, 7x7 to 98x80, batch 1 to 32) the choice is 1.4 % from the better one on average, 1.23 times at worst.
+    // The vector kernel is looked at only where quads use few taps: with a quarter kept or more it was never the fastest by more than
+    // 3 %; at 0.05 kept, 256 channels 14x14 batch 32, it takes 38 us, at 0.1 kept, 64 channels 56x56 batch 32, 26.
     double other_us = 0.0;                                    // of the faster one of the matrix-core kernels; 0: they don't take the layer
     if (hp.dtype == PP_F32) {
         const pp_conv_tuning_t none{};
@@ -396,9 +419,9 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
             int wk = 0;
             const int64_t rows = (int64_t)hp.n_hint * hp.h;
             const double quads_us = k6_model(hp.ql.groups, (rows * mc + 63) / 64, hp.c_in, hp.ql.taps_used, &wk);
-            const double dense_us = k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 7) / 8));
-            hp.quads = quads_us < dense_us;
-            other_us = std::min(quads_us, dense_us);
+            const double dense_us = k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 15) / 16), 9 * ((hp.c_in + 7) / 8));
+            hp.quads = dense_us >= 10.0 && dense_us >= 0.9 * quads_us;
+            other_us = hp.quads ? quads_us : dense_us;
         }
         if (quads_asked || dense_asked) {
             hp.quads = quads_asked;
@@ -981,7 +1004,8 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
 
 namespace {
 
-// Calls put(place in fl.wpk, place in canon.wpacked) for every kept weight.
+// Calls put(place, place in canon.wpacked) for every kept weight: its place in fl.wpk_narrow, or that of its leading part in fl.wpk (the
+// other parts are 512 and 1024 places on).
 template <typename F>
 void each_f32_weight(const HostPlan& hp, F&& put) {
     const F32Layout& fl = hp.fl;
@@ -994,11 +1018,16 @@ void each_f32_weight(const HostPlan& hp, F&& put) {
     for (int pos = 0; pos < hp.c_out; ++pos) {
         const int co = cn.perm[pos], row = co % 32;
         for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
-            const int ci = cn.kidx[e], g = ci / 8, p = ci % 8 / 2, half = ci - std::min(ci / 2 * 2, last_pair);
-            const size_t at = (size_t)(row + 32 * half) * 4 + p;
+            const int ci = cn.kidx[e];
             const std::vector<int>& tl = taps[cn.kpat[e]];
-            for (int j = 0; j < hp.taps; ++j)
-                put(((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at, (size_t)e * hp.taps + j);
+            if (fl.narrow) {
+                const int g = ci / 8, p = ci % 8 / 2, half = ci - std::min(ci / 2 * 2, last_pair);
+                const size_t at = (size_t)(row + 32 * half) * 4 + p;
+                for (int j = 0; j < hp.taps; ++j) put(((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at, (size_t)e * hp.taps + j);
+            } else {
+                const size_t at = (size_t)(row + 32 * (ci % 16 / 8)) * 8 + ci % 8;
+                for (int j = 0; j < hp.taps; ++j) put(((size_t)(co / 32) * fl.units + (size_t)(ci / 16) * KK + tl[j]) * 1536 + at, (size_t)e * hp.taps + j);
+            }
         }
     }
 }
@@ -1023,19 +1052,29 @@ void each_quad_weight(const HostPlan& hp, F&& put) {
 
 }  // namespace
 
-// Binary32 matrix-core operands: unit (tap, g) of a 32-filter tile multiplies channels 8 g .. 8 g + 7 at one tap with four
-// MFMAs, the p-th on the two channels from min(8 g + 2 p, c_in - 2) on.  A channel's weight sits in the first pair that holds
-// it; what the pairs past the end hold again is zero.
+// Binary32 matrix-core operands: unit (g, tap) of a 32-filter tile multiplies channels 16 g .. 16 g + 15 at one tap.  The kernel of the
+// binary32 instruction has units (tap, g) of channels 8 g .. 8 g + 7 with four MFMAs, the p-th on the two channels from
+// min(8 g + 2 p, c_in - 2) on.  A channel's weight sits in the first pair that holds it; what the pairs past the end hold again is zero.
 void build_f32_layout(HostPlan& hp) {
     F32Layout& fl = hp.fl;
     const int KK = hp.ks * hp.ks;
-    fl.groups = (hp.c_in + 7) / 8;
+    (void)k5_model_conv((hp.c_out + 31) / 32, (int64_t)hp.n_hint * hp.ho * hp.wo, KK * ((hp.c_in + 15) / 16), KK * ((hp.c_in + 7) / 8), &fl.narrow);
+    fl.groups = fl.narrow ? (hp.c_in + 7) / 8 : (hp.c_in + 15) / 16;
     fl.units = KK * fl.groups;
-    fl.tiles = (hp.c_out + 63) / 64 * 2;
-    fl.wpk.assign(((size_t)fl.tiles * fl.units + kF32Pad) * 256, 0.0f);
+    fl.tiles = (hp.c_out + 127) / 128 * 4;
     fl.bias_pad.assign((size_t)fl.tiles * 32, 0.0f);
     std::copy(hp.bias.begin(), hp.bias.end(), fl.bias_pad.begin());
-    each_f32_weight(hp, [&](size_t at, size_t src) { fl.wpk[at] = hp.canon.wpacked[src]; });
+    if (fl.narrow) {
+        fl.wpk_narrow.assign(((size_t)fl.tiles * fl.units + kF32Pad) * 256, 0.0f);
+        each_f32_weight(hp, [&](size_t at, size_t src) { fl.wpk_narrow[at] = hp.canon.wpacked[src]; });
+        return;
+    }
+    fl.wpk.assign((size_t)fl.tiles * fl.units * 1536, 0);
+    each_f32_weight(hp, [&](size_t at, size_t src) {
+        uint16_t part[3];
+        split_bf16(hp.canon.wpacked[src], part);
+        for (int i = 0; i < 3; ++i) fl.wpk[at + 512 * i] = part[i];
+    });
 }
 
 // Which taps any filter of a quad uses, per channel.
@@ -1065,17 +1104,26 @@ void pack_quads(HostPlan& hp) {
 
 // The weights out of the operands of a binary32 3x3 plan; what no kept weight put there has to be zero.
 static pp_status_t unpack_operands(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, float* w) {
-    const std::vector<float>& wpk = hp.quads ? hp.ql.wpk : hp.fl.wpk;
     std::copy(hp.canon.kidx.begin(), hp.canon.kidx.end(), kidx);
     std::copy(hp.canon.kpat.begin(), hp.canon.kpat.end(), kpat);
     size_t kept = 0, all = 0;
-    auto take = [&](size_t at, size_t to) {
-        w[to] = wpk[at];
-        kept += wpk[at] != 0.0f ? 1 : 0;
-    };
-    if (hp.quads) each_quad_weight(hp, take);
-    else each_f32_weight(hp, take);
-    for (float v : wpk) all += v != 0.0f ? 1 : 0;
+    if (hp.quads || hp.fl.narrow) {
+        const std::vector<float>& wpk = hp.quads ? hp.ql.wpk : hp.fl.wpk_narrow;
+        auto take = [&](size_t at, size_t to) {
+            w[to] = wpk[at];
+            kept += wpk[at] != 0.0f ? 1 : 0;
+        };
+        if (hp.quads) each_quad_weight(hp, take);
+        else each_f32_weight(hp, take);
+        for (float v : wpk) all += v != 0.0f ? 1 : 0;
+    } else {
+        const std::vector<uint16_t>& wpk = hp.fl.wpk;
+        each_f32_weight(hp, [&](size_t at, size_t to) {
+            w[to] = (bf16_to_f32(wpk[at + 1024]) + bf16_to_f32(wpk[at + 512])) + bf16_to_f32(wpk[at]);
+            for (int i = 0; i < 3; ++i) kept += (wpk[at + 512 * i] & 0x7FFFu) != 0 ? 1 : 0;
+        });
+        for (uint16_t v : wpk) all += (v & 0x7FFFu) != 0 ? 1 : 0;
+    }
     return kept == all ? PP_OK : PP_ERR_UNSUPPORTED;
 }
 

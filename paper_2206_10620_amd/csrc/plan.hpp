@@ -69,11 +69,13 @@ struct MfmaLayout {
     std::vector<float> bias_pad;      // [fb*64]
 };
 
-constexpr int kF32Pad = 4;                  // units the kernel may load past the end
-// Binary32 matrix-core kernel: the zero-filled dense weights in operand order.
+constexpr int kF32Pad = 4;                  // units the kernels of the binary32 instruction may load past the end
+// Binary32 matrix-core kernels: the zero-filled dense weights in operand order, as they are or each in three bfloat16 parts.
 struct F32Layout {
-    int groups = 0, units = 0, tiles = 0;   // groups of eight channels, ks * ks * groups, 32-filter tiles (rounded up to an even number)
-    std::vector<float> wpk;                 // [tiles][units][64][4], and kF32Pad units of zeros behind them
+    bool narrow = false;                    // as they are, for the kernel of the binary32 instruction
+    int groups = 0, units = 0, tiles = 0;   // groups of sixteen channels (eight), ks * ks * groups, 32-filter tiles (rounded up to a multiple of four)
+    std::vector<uint16_t> wpk;              // [tiles][units][3][64][8]
+    std::vector<float> wpk_narrow;          // [tiles][units][64][4], and kF32Pad units of zeros behind them
     std::vector<float> bias_pad;            // [tiles * 32]
 };
 
@@ -131,6 +133,9 @@ pp_status_t unpack_stream(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, floa
 
 // binary16 conversion used when packing weights (round to nearest even).
 uint16_t f32_to_f16_rne(float v);
+// A binary32 value as the sum of three bfloat16 ones (round to nearest even, each what the ones before it leave).
+void split_bf16(float v, uint16_t (&part)[3]);
+float bf16_to_f32(uint16_t b);
 float f16_to_f32(uint16_t b);
 
 }  // namespace ppc

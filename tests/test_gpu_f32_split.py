@@ -1,0 +1,36 @@
+"""The dense binary32 convolution as bfloat16 parts: every workgroup shape, with each remainder of its loop over four reduction
+units and shares shorter than that loop, partial filter and pixel tiles, 1x1 to 5x5, stride 1 and 2, against the oracle."""
+import math
+
+import pytest
+
+import synth
+import paper_2206_10620_amd as pp
+from gpu_util import check_layer
+
+pytestmark = pytest.mark.gpu
+
+# n, c_in, c_out, h, w, ksize, stride; the workgroup (filter tiles, pixel tiles, reduction shares; none: too few tiles, the kernel of the
+# binary32 instruction); reduction units of a share
+LAYERS = [((1, 3, 3, 7, 7, 1, 2), None, 1), ((1, 64, 3, 5, 7, 1, 2), None, 1), ((1, 77, 3, 7, 5, 3, 2), None, 6), ((1, 17, 3, 5, 7, 5, 2), None, 7), ((4, 33, 3, 64, 33, 1, 1), None, 1),
+          ((32, 3, 3, 9, 57, 1, 1), (1, 4, 1), 1), ((32, 17, 3, 57, 9, 1, 1), (1, 4, 1), 2), ((32, 33, 3, 9, 57, 1, 1), (1, 4, 1), 3), ((16, 64, 3, 57, 28, 1, 1), (1, 4, 1), 4),
+          ((2, 64, 33, 33, 64, 3, 1), (2, 1, 4), 9), ((32, 48, 33, 15, 33, 3, 2), (2, 1, 4), 7), ((8, 77, 33, 9, 57, 3, 1), (2, 1, 4), 12),
+          ((1, 17, 300, 57, 57, 1, 1), (2, 2, 2), 1), ((32, 200, 33, 57, 7, 1, 1), (2, 2, 2), 7), ((32, 33, 33, 28, 14, 3, 1), (2, 2, 2), 14),
+          ((16, 17, 33, 28, 28, 5, 1), (2, 2, 4), 13), ((16, 33, 33, 28, 28, 5, 1), (2, 2, 4), 19), ((8, 3, 33, 64, 57, 1, 1), (2, 4, 1), 1), ((32, 100, 33, 14, 57, 1, 1), (2, 4, 1), 7),
+          ((16, 33, 77, 15, 57, 3, 1), (4, 2, 4), 7), ((16, 300, 77, 33, 28, 1, 1), (4, 2, 4), 5), ((32, 17, 200, 57, 33, 1, 2), (4, 4, 1), 2), ((16, 3, 77, 28, 57, 3, 1), (4, 4, 1), 9),
+          ((32, 256, 77, 14, 57, 1, 1), (4, 4, 2), 8), ((16, 33, 130, 57, 57, 3, 2), (4, 4, 2), 14)]
+
+
+@pytest.mark.parametrize("layer,shape,share", LAYERS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_shapes_and_remainders(layer, shape, share):
+    n, c_in, c_out, h, w, ks, stride = layer
+    print(f"split layer {layer}", flush=True)
+    lay = synth.random_pruned_layer_k("split", n, c_in, c_out, h, w, "f32", ks, synth.random_pattern_set(ks, 1 if ks == 1 else 4, 1 if ks == 1 else 6, seed=2), 0.8, 0.3,
+                                      seed=c_in + w, stride=stride)
+    # A sum is rounded once per 16 products, in binary32, in each of two accumulators and once per share: a walk of `units` steps of 2^-24 of
+    # the sum, of which four deviations cover 10^5 outputs, and the operands' three parts leave nothing out above 2^-24.
+    units = ks * ks * ((c_in + 15) // 16)
+    tol = 4 * 2.0 ** -24 * (2 * math.sqrt(units if shape else 8 * units) + 2)
+    rep, _ = check_layer(lay, tuning=pp.Tuning(variant=2 if ks == 3 and stride == 1 else 1, mfma_kind=5), tol=tol, label=f"split{layer}")
+    assert rep["chosen"]["mfma_kind"] == 5
+    assert share * (shape[2] if shape else 8) >= units
