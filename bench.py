@@ -75,7 +75,8 @@ def kernel_of(chosen):
     """The kernel a plan with these reported parameters runs on."""
     variant, kind = chosen["variant"], chosen["mfma_kind"]
     if variant == 3:
-        return {2: "k3_mfma", 3: "k4 block product"}.get(kind, "k2_mfma")
+        rows = kind == 2 and chosen["tile_cols"] in (16, 32, 64)
+        return "k7_rows" if rows else {2: "k3_mfma", 3: "k4 block product"}.get(kind, "k2_mfma")
     return {4: "k6_f32_3x3", 5: "k5_conv_f32"}.get(kind, "k1_tiled" if variant == 2 else "k0_generic")
 
 

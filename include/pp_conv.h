@@ -67,7 +67,7 @@ enum {
 /* Execution parameters (the part of the layer-wise representation that the paper leaves to tuning,
  * section 2.3.1).  A zero field means "let the library choose". */
 typedef struct {
-    int32_t variant;        /* 0 auto; 1 generic (any layer: binary32 as a dense product on the binary32 matrix
+    int32_t variant;        /* 0 auto; 1 generic (any layer: binary32 as a dense product on the matrix
                                cores (mfma_kind 5) unless it is very sparse, otherwise one lane per output (for binary32
                                mfma_kind 6)); 2 the 3x3, stride 1 kernels without a
                                fused pool that profit from the patterns: by itself the tiled pattern-specialised vector kernel
@@ -112,7 +112,10 @@ typedef struct {
                                memory-to-LDS as they are and transposed by the LDS read; tile_cols is then a multiple
                                of 30 or of 14: segments of 30 or 14 outputs, of which a workgroup of wg_waves
                                wavefronts holds 2 * wg_waves or 4 * wg_waves; tile_rows = that count divided by
-                               the segments per row, tile_cols / 30 or tile_cols / 14); for binary32 storage: 4 the 3x3, stride 1 one on the small
+                               the segments per row, tile_cols / 30 or tile_cols / 14), or, with tile_cols 16, 32 or 64, the row-stacked one (even
+                               widths, no copy of the input; tiles_per_wave 2 or 4 rows of a wavefront, tile_rows =
+                               128 * tiles_per_wave / tile_cols, wg_waves 8: two groups of four share a tile's
+                               channels, an even number of sixteens); for binary32 storage: 4 the 3x3, stride 1 one on the small
                                matrix instruction, which skips taps that no filter of four uses, 5 the dense product
                                (variant 2 or 1), 6 none: one lane per output (variant 1) */
     int32_t split_k;        /* direct-load matrix-core kernel only: workgroups that share one output tile, each on its

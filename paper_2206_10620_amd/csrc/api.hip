@@ -12,6 +12,7 @@
 #include "k3_mfma_direct.hpp"
 #include "k5_f32.hpp"
 #include "k6_f32_3x3.hpp"
+#include "k7_rows.hpp"
 #include "block_plan.hpp"
 #include "plan.hpp"
 #include "pp_block_gemm.h"
@@ -43,6 +44,20 @@ k2_launch_fn k2_lookup(int ks, int stride, int ntw, int waves, int units, bool p
         case 3: return k2_lookup_k3(stride, ntw, waves, units, pairs);
         case 5: return k2_lookup_k5(stride, ntw, waves, units, pairs);
         case 7: return k2_lookup_k7(stride, ntw, waves, units, pairs);
+        default: return nullptr;
+    }
+}
+
+k7_launch_fn k7_lookup_t2_c16(int groups, bool ragged, bool pool);
+k7_launch_fn k7_lookup_t2_c32(int groups, bool ragged, bool pool);
+k7_launch_fn k7_lookup_t2_c64(int groups, bool ragged, bool pool);
+k7_launch_fn k7_lookup_t4_c64(int groups, bool ragged, bool pool);
+k7_launch_fn k7_lookup(int rows, int cols, int groups, bool ragged, bool pool) {
+    switch (rows * 100 + cols) {
+        case 216: return k7_lookup_t2_c16(groups, ragged, pool);
+        case 232: return k7_lookup_t2_c32(groups, ragged, pool);
+        case 264: return k7_lookup_t2_c64(groups, ragged, pool);
+        case 464: return k7_lookup_t4_c64(groups, ragged, pool);
         default: return nullptr;
     }
 }
@@ -136,6 +151,7 @@ struct pp_conv_plan {
     k2_launch_fn launch2 = nullptr;
     k3_launch_fn launch3 = nullptr;
     k3_launch_fn launch3_split = nullptr;     // the same kernel storing partial sums of a share of the chunks
+    k7_launch_fn launch7 = nullptr;
     float* d_ws3 = nullptr;                   // their workspace: [ksplit][n_hint][c_out][h][w] binary32
     pp_block_gemm_plan_t* pointwise = nullptr; // a 1x1 stride-1 layer in binary16 runs as a batch of matrix products (one per image)
     _Float16* d_xpad = nullptr;               // x with zero channels appended up to whole chunks of 16: [n_hint][cpad][h][w]
@@ -387,12 +403,14 @@ pp_status_t pp_conv_plan(const pp_conv_desc_t* desc, pp_conv_plan_t** out_plan) 
             return PP_ERR_UNSUPPORTED;
         }
     } else if (hp.mfma) {
-        if (hp.ml.direct) {
+        if (hp.ml.rows) {
+            p->launch7 = k7_lookup(hp.ml.ntw, hp.ml.tc, hp.ml.waves / 4, hp.w % 8 != 0, hp.pool);
+        } else if (hp.ml.direct) {
             p->launch3 = k3_lookup(hp.ml.g3.sw, hp.ml.g3.waves, false, hp.pool);
             if (hp.ml.ksplit > 1) p->launch3_split = k3_lookup(hp.ml.g3.sw, hp.ml.g3.waves, true, false);
         }
         else p->launch2 = k2_lookup(hp.ks, hp.stride, hp.ml.ntw, hp.ml.waves, hp.ml.units, hp.ml.pairs);
-        if (!p->launch2 && !p->launch3) {
+        if (!p->launch2 && !p->launch3 && !p->launch7) {
             delete p;
             return PP_ERR_UNSUPPORTED;
         }
@@ -745,12 +763,38 @@ static pp_status_t launch_mfma_direct(const pp_conv_plan_t* plan, const void* x_
     return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
+static pp_status_t launch_rows(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream) {
+    const HostPlan& hp = plan->hp;
+    const MfmaLayout& ml = hp.ml;
+    K7Args a{};
+    a.x = x_dev, a.y = y_dev, a.wpk = plan->d_wpk, a.bias = plan->d_bias_mfma;
+    a.n = n, a.c_in = hp.c_in, a.c_out = hp.c_out, a.h = hp.h, a.w = hp.w, a.out_h = hp.out_h, a.out_w = hp.out_w;
+    a.po = ml.po;
+    a.tiles_x = (hp.w + ml.tc - 1) / ml.tc;
+    a.tiles_v = ((n - 1) * ml.po + hp.h + ml.tr - 1) / ml.tr;
+    a.fb = ml.fb, a.q = ml.q;
+    a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 2;
+    const int64_t items = (int64_t)a.tiles_x * a.tiles_v * ml.fb;
+    if (items >= ((int64_t)1 << 30)) return PP_ERR_SHAPE;
+    a.work_items = (int)items;
+    a.blocks_per_xcd = (int)((items + 7) / 8);
+    a.magic_po = ml.po <= 1 ? 0u : (uint32_t)((((uint64_t)1) << 32) / (uint64_t)ml.po + 1u);
+    a.relu = (hp.flags & PP_FLAG_RELU) ? 1 : 0;
+    const int kg = ml.waves / 4;
+    // persistent workgroups, two to a compute unit; those of eight wavefronts take one tile each
+    const int grid = kg == 1 ? std::min(a.blocks_per_xcd * 8, 512) : a.blocks_per_xcd * 8;
+    (void)hipGetLastError();
+    plan->launch7(a, grid, k7_lds(ml.ntw, ml.tc, kg), stream);
+    return hipGetLastError() == hipSuccess ? PP_OK : PP_ERR_DEVICE;
+}
+
 // One launch of the matrix-core kernel on n images.
 static pp_status_t launch_mfma(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream, bool may_split = true) {
     const HostPlan& hp = plan->hp;
     const MfmaLayout& ml = hp.ml;
     if (plan->pointwise)
         return pp_block_gemm_launch_batched(plan->pointwise, x_dev, y_dev, hp.h * hp.w, n, (int64_t)hp.c_in * hp.h * hp.w, (int64_t)hp.c_out * hp.h * hp.w, stream);
+    if (ml.rows) return launch_rows(plan, x_dev, y_dev, n, stream);
     if (ml.direct) return launch_mfma_direct(plan, x_dev, y_dev, n, stream, may_split);
     K2Args a{};
     a.x = x_dev;

@@ -4,6 +4,7 @@
 #include "plan.hpp"
 
 #include "f32_rules.hpp"
+#include "k7_geom.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -840,7 +841,31 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         if (ml.cpad != hp.c_in) direct_us += 1.5 + 2e-6 * hp.n_hint * hp.c_in * hp.h * hp.w * (ragged ? 1.1 : 0.5);
         return true;
     };
-    ml.direct = direct_ok && t.mfma_kind != 1 && t.mfma_kind != 3 && direct_layout();
+    // The row-stacked kernel: the shape asked for or the one modelled fastest; even widths only (x is loaded four bytes at least).
+    double rows_us = 0.0;
+    const MfmaLayout fresh_ml = ml;
+    auto rows_layout = [&]() -> bool {
+        const int po = hp.h + (hp.pool ? 2 : 1);
+        const K7Shape* best = nullptr;
+        for (const K7Shape& s : kK7Shapes) {
+            const int tr = k7_geom(s.t, s.tc).tr;
+            if ((t.tile_cols && t.tile_cols != s.tc) || (t.tile_rows && t.tile_rows != tr) || (t.tiles_per_wave && t.tiles_per_wave != s.t) || (t.wg_waves && t.wg_waves != 4 * s.kg)) continue;
+            if (hp.w % 2 != 0 || (s.tc == 16 && hp.w > 16) || ml.q % s.kg != 0) continue;
+            if (po + tr + 2 >= 65536 || ((int64_t)(tr + 2) / po + 2) * hp.c_in * hp.h * hp.w * 2 >= ((int64_t)1 << 31)) continue;      // 16-bit divisions; offsets within a tile's buffer
+            const int64_t items = (int64_t)((hp.w + s.tc - 1) / s.tc) * (((int64_t)(hp.n_hint - 1) * po + hp.h + tr - 1) / tr) * ml.fb;
+            if (s.kg == 2 && items > 512 && !t.wg_waves) continue;
+            const double us = k7_model(s, items, ml.q, hp.w % 8 != 0);
+            if (!best || us < rows_us) best = &s, rows_us = us;
+        }
+        if (!best || t.split_k > 1) return false;
+        ml = fresh_ml;
+        ml.direct = ml.rows = true;
+        ml.po = po, ml.tr = k7_geom(best->t, best->tc).tr, ml.tc = best->tc, ml.ntw = best->t, ml.waves = 4 * best->kg, ml.ksplit = 1, ml.cpad = hp.c_in;
+        hp.chosen.wg_waves = ml.waves, hp.chosen.tile_rows = ml.tr, hp.chosen.tile_cols = ml.tc, hp.chosen.tiles_per_wave = ml.ntw, hp.chosen.mfma_kind = 2, hp.chosen.split_k = 1;
+        return true;
+    };
+    const bool rows_asked = t.mfma_kind == 2 && (t.tile_cols == 16 || t.tile_cols == 32 || t.tile_cols == 64);      // widths that the direct-load kernel doesn't have
+    ml.direct = direct_ok && t.mfma_kind != 1 && t.mfma_kind != 3 && (rows_asked ? rows_layout() : direct_layout());
     if (t.mfma_kind == 2 && !ml.direct) return PP_ERR_UNSUPPORTED;
     if (t.split_k > 1 && !ml.direct) return PP_ERR_UNSUPPORTED;      // only the direct-load kernel splits the reduction
     // A layer left to the library that does not split its reduction runs on whichever of the two is modelled faster.  Small maps, widths off the segments and padded channels favour the
@@ -973,6 +998,17 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         if (general_us == 0.0 || general_us >= 0.95 * direct_us) ml = direct_ml;
         else ml.ksplit = 1, ml.cpad = hp.c_in;
         if (ml.direct) hp.chosen = direct_chosen;
+    }
+    // The row-stacked kernel where it is modelled faster than that by more than a tenth, about what the models are off by: on 53 of 70
+    // drawn layers, 1.33 times as fast there on average (64 channels, 1080x1920: 203 -> 187 us; 3 to 64, 224x224, batch 8: 28 -> 18; 67 to 140, 84x90,
+    // batch 2: 26 -> 12).  A layer whose reduction is split stays (512 channels, 14x14, batch 8: 26, 33 us there).
+    if (left_to_us && direct_ok && hp.h < 65000 && !(ml.direct && ml.ksplit > 1)) {
+        const MfmaLayout other_ml = ml;
+        const pp_conv_tuning_t other_chosen = hp.chosen;
+        const double other_us = ml.direct ? direct_us : general_us;
+        hp.chosen = pp_conv_tuning_t{};
+        hp.chosen.variant = 3;
+        if (!rows_layout() || rows_us >= 0.9 * other_us) ml = other_ml, hp.chosen = other_chosen;
     }
 
     // weights: scatter the kept kernels into zero-filled operand fragments

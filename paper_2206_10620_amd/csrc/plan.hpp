@@ -55,6 +55,7 @@ struct MfmaLayout {
     bool direct = false;              // the direct-load kernel (3x3, stride 1, whole chunks of 16 channels) runs this plan
     K3Geom g3;                        // ... with this geometry
     int cpad = 0;                     // ... on this many input channels: c_in rounded up to whole chunks (a larger value than c_in means x is copied into a zero-padded buffer first)
+    bool rows = false;                // of the 3x3, stride 1 kernels the row-stacked one runs this plan, not the direct-load one
     int ksplit = 1;                   // ... and this many workgroups sharing a tile's reduction (partial sums to a workspace)
     bool pairs = true;                // images more than one pixel wide: input loaded as 32-bit pixel pairs
     int units = 0;                    // staging units (16 pixel pairs x 8 channels) of a wavefront
