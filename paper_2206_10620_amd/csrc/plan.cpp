@@ -999,16 +999,18 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
         else ml.ksplit = 1, ml.cpad = hp.c_in;
         if (ml.direct) hp.chosen = direct_chosen;
     }
-    // The row-stacked kernel where it is modelled faster than that by more than a tenth, about what the models are off by: on 53 of 70
-    // drawn layers, 1.33 times as fast there on average (64 channels, 1080x1920: 203 -> 187 us; 3 to 64, 224x224, batch 8: 28 -> 18; 67 to 140, 84x90,
-    // batch 2: 26 -> 12).  A layer whose reduction is split stays (512 channels, 14x14, batch 8: 26, 33 us there).
+    // The row-stacked kernel instead of the direct-load one unless it is modelled much slower: on all 34 of 70 drawn layers that ran on
+    // that it was the faster one, by 1.04 to 2.4 times, where the direct-load kernel's model gives 0.7 to 1.2 of what is measured (64 channels,
+    // 1080x1920: 203 -> 187 us; 3 to 64, 224x224, batch 8: 28 -> 18; 256 channels, 56x56, batch 8: 36.9 -> 35.6, modelled 27.6 and 34.3).  Instead
+    // of the general kernel where it is modelled faster: on 22 of the 36 others, 1.3 times as fast there, none slower (6 x 147 to 90, 197x242: 148 ->
+    // 95).  A layer whose reduction is split stays (512 channels, 14x14, batch 8: 26, 33 us there).
     if (left_to_us && direct_ok && hp.h < 65000 && !(ml.direct && ml.ksplit > 1)) {
         const MfmaLayout other_ml = ml;
         const pp_conv_tuning_t other_chosen = hp.chosen;
         const double other_us = ml.direct ? direct_us : general_us;
         hp.chosen = pp_conv_tuning_t{};
         hp.chosen.variant = 3;
-        if (!rows_layout() || rows_us >= 0.9 * other_us) ml = other_ml, hp.chosen = other_chosen;
+        if (!rows_layout() || rows_us >= (other_ml.direct ? 1.3 : 0.95) * other_us) ml = other_ml, hp.chosen = other_chosen;
     }
 
     // weights: scatter the kept kernels into zero-filled operand fragments
