@@ -63,8 +63,10 @@ MEASURED_TRAFFIC = {
     ("cfg2_vgg_mid", 2): ("lib-2026-12-04-a", 20.43e6),
 }
 
-# The same for the binary32 matrix-core kernels, keyed by (workload, kernel).
+# The same for the binary32 matrix-core kernels and the row-stacked one, keyed by (workload, kernel).
 MEASURED_TRAFFIC_F32 = {
+    ("cfg5_enhance_1080p", "k7_rows"): ("lib-2026-12-04-a", 646.33e6),
+    ("cfg4_vgg_L9", "k7_rows"): ("lib-2026-12-04-a", 53.79e6),
     ("cfg2_vgg_mid", "k6_f32_3x3"): ("lib-2026-12-04-a", 44.64e6),
 }
 
