@@ -7,6 +7,22 @@
 
 namespace ppc {
 
+// The sixteen channels that reduction group g of the dense convolution in parts loads: from channel k5_group_first on, the upper half of
+// a wavefront k5_half_channels further, the j-th of a lane's eight at k5_step j.  All of them are channels of the layer: x ends behind the
+// last one of the last image, and of the sum that is a load's address the hardware need not check the part that names the channel.  The
+// last group therefore begins early, and what it holds again of the one before it meets zero weights.
+constexpr int k5_group_first(int c_in, int g) { return 16 * g <= c_in - 16 ? 16 * g : c_in > 16 ? c_in - 16 : 0; }
+constexpr int k5_half_channels(int c_in) { return c_in >= 16 ? 8 : c_in > 8 ? c_in - 8 : 0; }
+constexpr int k5_step(int c_in, int j) { return j < c_in ? j : c_in - 1; }
+// Where a channel's weight stands: its group, half and place.
+struct K5Slot {
+    int g, half, j;
+};
+constexpr K5Slot k5_slot(int c_in, int ci) {
+    const int g = ci / 16, o = ci - k5_group_first(c_in, g), half = o >= 8 ? 1 : 0;
+    return K5Slot{g, half, o - half * k5_half_channels(c_in)};
+}
+
 // The dense convolution: workgroups of wp x wk wavefronts of 32 mt filters x 32 pixels each, wk of them on one tile's reduction, wp on
 // different pixels with the same weights.  Modelled microseconds of a launch: start, and per workgroup on a compute unit (the mean of
 // their number and that number rounded up) `wg`, and per reduction unit of a wavefront `alone` or, where more, `wg_unit` per workgroup.

@@ -34,7 +34,7 @@ namespace ppc {
 
 struct K5ConvArgs {
     const float* x;
-    const void* wpk;        // [32-filter tile][unit][3 parts][64 lanes][8] bfloat16: lane l, value i: filter l % 32, channel 16 g + 8 (l / 32) + i of unit (g, tap)
+    const void* wpk;        // [32-filter tile][unit][3 parts][64 lanes][8] bfloat16: lane l, value i: filter l % 32, the channel at (g, l / 32, i) (k5_slot) of unit (g, tap)
     const float* bias;      // [tiles * 32]
     float* y;
     int32_t n, c_in, c_out, h, w, ho, wo, out_h, out_w;
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     const int64_t img_elems = (int64_t)a.c_in * hw;
     const __amdgpu_buffer_rsrc_t xr = k5_buffer(a.x + img0 * img_elems, a.x_bytes - img0 * img_elems * 4);
 
-    const K5Pixel px = k5_pixel(a, j0 + col, img0, half * 8 * hw);
+    const K5Pixel px = k5_pixel(a, j0 + col, img0, half * k5_half_channels(a.c_in) * hw);
     // The products of the leading parts have an accumulator of their own, those of the others another: the first is rounded
     // once per unit, at the size of the sum, the second at a 256th of it.
     k5_f16 acc[MT], low[MT];                                    // the first reduction share starts from the bias
@@ -264,15 +264,17 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
         const uint32_t at = (px.base + (uint32_t)(tr * a.w + tc)) * 4u;
         const bool in = (lu < own) & ((unsigned)(px.iy0 + tr) < (unsigned)a.h) & ((unsigned)(px.ix0 + tc) < (unsigned)a.w);
         voff = in ? at : kK5Outside;
-        xsoff = (uint32_t)(16 * g) * plane;
+        xsoff = (uint32_t)k5_group_first(a.c_in, g) * plane;
         ++lu;
         const int row = tc + 1 == a.ks ? 1 : 0, group = row & (tr + 1 == a.ks ? 1 : 0);
         tc = row ? 0 : tc + 1;
         tr = group ? 0 : tr + row;
         g += group;
     };
-    // (channels past the last one are the next image's or outside the buffer: their weights are zeros)
-    auto load_x = [&](auto set_tag, int j) __attribute__((always_inline)) { xv[decltype(set_tag)::value][j] = k5_load(xr, voff, xsoff + (uint32_t)j * plane); };
+    uint32_t step_bytes[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) step_bytes[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)k5_step(a.c_in, j) * plane));
+    auto load_x = [&](auto set_tag, int j) __attribute__((always_inline)) { xv[decltype(set_tag)::value][j] = k5_load(xr, voff, xsoff + step_bytes[j]); };
     const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)(k5_lds_ptr)k5_smem) + (uint32_t)(wk * FR * 1024);
     int wu = 0;
     uint32_t wbuf = 0;

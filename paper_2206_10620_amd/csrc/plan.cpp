@@ -1063,8 +1063,9 @@ void each_f32_weight(const HostPlan& hp, F&& put) {
                 const size_t at = (size_t)(row + 32 * half) * 4 + p;
                 for (int j = 0; j < hp.taps; ++j) put(((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at, (size_t)e * hp.taps + j);
             } else {
-                const size_t at = (size_t)(row + 32 * (ci % 16 / 8)) * 8 + ci % 8;
-                for (int j = 0; j < hp.taps; ++j) put(((size_t)(co / 32) * fl.units + (size_t)(ci / 16) * KK + tl[j]) * 1536 + at, (size_t)e * hp.taps + j);
+                const K5Slot s = k5_slot(hp.c_in, ci);
+                const size_t at = (size_t)(row + 32 * s.half) * 8 + s.j;
+                for (int j = 0; j < hp.taps; ++j) put(((size_t)(co / 32) * fl.units + (size_t)s.g * KK + tl[j]) * 1536 + at, (size_t)e * hp.taps + j);
             }
         }
     }
@@ -1090,7 +1091,7 @@ void each_quad_weight(const HostPlan& hp, F&& put) {
 
 }  // namespace
 
-// Binary32 matrix-core operands: unit (g, tap) of a 32-filter tile multiplies channels 16 g .. 16 g + 15 at one tap.  The kernel of the
+// Binary32 matrix-core operands: unit (g, tap) of a 32-filter tile multiplies the sixteen channels of group g (k5_slot) at one tap.  The kernel of the
 // binary32 instruction has units (tap, g) of channels 8 g .. 8 g + 7 with four MFMAs, the p-th on the two channels from
 // min(8 g + 2 p, c_in - 2) on.  A channel's weight sits in the first pair that holds it; what the pairs past the end hold again is zero.
 void build_f32_layout(HostPlan& hp) {

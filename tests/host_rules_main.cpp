@@ -1,8 +1,10 @@
 // The launch rules that keep the kernels' loads inside their buffers, walked exhaustively on the CPU.
 #include <algorithm>
 #include <cstdio>
+#include <vector>
 
 #include "block_rules.hpp"
+#include "f32_rules.hpp"
 #include "reuse_rules.hpp"
 
 using namespace ppc;
@@ -43,8 +45,30 @@ static int gather_rows() {
     return 0;
 }
 
+// Every channel that a reduction group of the binary32 convolution in parts loads, also those asked for past a share's end, is one of
+// the layer's, and every channel has a place of its own that is loaded from it.
+static int group_channels() {
+    for (int c = 1; c <= 600; ++c) {
+        const int groups = (c + 15) / 16;
+        for (int g = 0; g <= 2 * groups + 2; ++g)
+            for (int half = 0; half < 2; ++half)
+                for (int j = 0; j < 8; ++j) {
+                    const int ch = k5_group_first(c, g) + half * k5_half_channels(c) + k5_step(c, j);
+                    if (ch < 0 || ch >= c) return fail("group loads a channel behind x", c, g, ch);
+                }
+        std::vector<char> taken((size_t)groups * 16, 0);
+        for (int ci = 0; ci < c; ++ci) {
+            const K5Slot s = k5_slot(c, ci);
+            if (s.g < 0 || s.g >= groups || s.half < 0 || s.half > 1 || s.j < 0 || s.j > 7) return fail("no place for a channel", c, ci, s.g);
+            if (k5_group_first(c, s.g) + s.half * k5_half_channels(c) + k5_step(c, s.j) != ci) return fail("a channel's place loads another one", c, ci, s.g);
+            if (taken[(size_t)(s.g * 2 + s.half) * 8 + s.j]++) return fail("two channels in one place", c, ci, s.g);
+        }
+    }
+    return 0;
+}
+
 int main() {
-    if (block_pieces() || gather_rows()) return 1;
+    if (block_pieces() || gather_rows() || group_channels()) return 1;
     std::printf("ok\n");
     return 0;
 }
