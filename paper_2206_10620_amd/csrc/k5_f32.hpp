@@ -27,6 +27,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "buffer_rules.hpp"
 #include "f32_rules.hpp"
 #include "k0_generic.hpp"
 
@@ -59,8 +60,7 @@ constexpr int kK5Ahead = 3;                        // reduction units whose load
 constexpr uint32_t kK5Outside = 0x80000000u;      // a byte offset no buffer of these kernels reaches: the load returns 0
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t k5_buffer(const void* base, int64_t bytes) {
-    const uint32_t num = bytes > 0x7FFFFFFF ? 0x7FFFFFFFu : (uint32_t)bytes;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)num, 0x00027000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)buffer_records(bytes), 0x00027000);
 }
 __device__ __forceinline__ float k5_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0));

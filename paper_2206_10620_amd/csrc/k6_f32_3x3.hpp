@@ -47,6 +47,10 @@ struct K6Args {
 
 typedef const __attribute__((address_space(4))) uint32_t* k6_const_u32;
 
+// the buffer from a channel on, which a row's last load, past the row's end, needs
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t k6_channel(const void* base, uint32_t records) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)records, 0x00027000);
+}
 __device__ __forceinline__ k5_f4 k6_load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     return __builtin_bit_cast(k5_f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
 }
@@ -81,6 +85,7 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(4))) vo
     const bool ok = j < a.pieces;
     const int64_t img_elems = (int64_t)a.c_in * hw;
     const __amdgpu_buffer_rsrc_t xr = k5_buffer(a.x + img0 * img_elems, a.x_bytes - img0 * img_elems * 4);
+    const uint32_t records = buffer_records(a.x_bytes - img0 * img_elems * 4);
     uint32_t voff[RW], voff_l[BOUND ? RW : 1], voff_r[BOUND ? RW : 1];
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
@@ -117,6 +122,7 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(4))) vo
     auto load_slot = [&](Chan& k, int c, int i) {                   // c beyond the share: the last channel again (its masks are cleared)
         const int cc = c < a.c_in ? c : a.c_in - 1;
         if (i == 0) k.w = *reinterpret_cast<const k5_f4*>(wbase + (int64_t)cc * 256);
+        else if (RAGGED && i <= RW) k.mid[i - 1] = k6_load4(k6_channel(a.x + img0 * img_elems + (int64_t)cc * hw, buffer_records_from(records, (uint32_t)cc * plane)), voff[i - 1], 0u);
         else if (i <= RW) k.mid[i - 1] = k6_load4(xr, voff[i - 1], (uint32_t)cc * plane);
         else if (BOUND && i <= 2 * RW) k.el[i - 1 - RW] = k5_load(xr, voff_l[BOUND ? i - 1 - RW : 0], (uint32_t)cc * plane);
         else if (BOUND && i <= 3 * RW) k.er[i - 1 - 2 * RW] = k5_load(xr, voff_r[BOUND ? i - 1 - 2 * RW : 0], (uint32_t)cc * plane);

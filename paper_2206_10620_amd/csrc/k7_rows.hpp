@@ -16,6 +16,7 @@
 
 #include <type_traits>
 
+#include "buffer_rules.hpp"
 #include "k7_geom.hpp"
 #include "mfma_geom.hpp"
 
@@ -167,6 +168,8 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
     uint32_t voff[SR], mask[RAGGED ? SR : 1][4];
     k7_u4 xreg[D < 2 ? 2 : D][SR][4];
     __amdgpu_buffer_rsrc_t xr;
+    const unsigned char* xbase = nullptr;           // (RAGGED) what xr begins with, and its size
+    uint32_t records = 0u;
     const int q0 = kg * QN;                         // first chunk of this group
     int xq = 0, xk = 0;                             // the chunk to load next: of tile xk, chunk xq of the group's
     const int64_t img_bytes = (int64_t)a.c_in * hw * 2;
@@ -175,9 +178,9 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int u0 = t.v0 - 1;                    // tall row of staged row 0
         const int img0 = (u0 + a.po) / a.po - 1, iy0 = u0 - img0 * a.po;
         const int ib = img0 > 0 ? img0 : 0;
-        const int64_t room = a.x_bytes - ib * img_bytes;
-        xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(static_cast<const unsigned char*>(a.x) + ib * img_bytes), 0,
-                                               (int)(room > 0x7FFFFFFC ? 0x7FFFFFFC : room), 0x00027000);
+        xbase = static_cast<const unsigned char*>(a.x) + ib * img_bytes;
+        records = buffer_records(a.x_bytes - ib * img_bytes);
+        xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(xbase), 0, (int)records, 0x00027000);
 #pragma unroll
         for (int r = 0; r < SR; ++r) {
             const int task = r * 64 + lane, srow = task / G.gpr, sg = task - srow * G.gpr + (TC == 16 ? 1 : 0);       // group 0 and TC / 8 + 1 lie beside the tile
@@ -199,8 +202,15 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int ch = (q0 + xq) * kMfmaChunk + wave * 4 + j, chc = ch < a.c_in ? ch : a.c_in - 1;    // past the last channel: its values again, for zero weights
+            const uint32_t at = (uint32_t)(chc * hw * 2);
+            if constexpr (RAGGED) {                 // a row's last load may run past the row: the buffer begins at the channel, so that it ends with x
+                const __amdgpu_buffer_rsrc_t cr = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(xbase + at), 0, (int)buffer_records_from(records, at), 0x00027000);
 #pragma unroll
-            for (int r = 0; r < SR; ++r) xreg[set][r][j] = __builtin_bit_cast(k7_u4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)voff[r], chc * hw * 2, 0));
+                for (int r = 0; r < SR; ++r) xreg[set][r][j] = __builtin_bit_cast(k7_u4, __builtin_amdgcn_raw_buffer_load_b128(cr, (int)voff[r], 0, 0));
+            } else {
+#pragma unroll
+                for (int r = 0; r < SR; ++r) xreg[set][r][j] = __builtin_bit_cast(k7_u4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)voff[r], (int)at, 0));
+            }
         }
         if (++xq == QN) xq = 0, ++xk;
     };

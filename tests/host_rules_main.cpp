@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "block_rules.hpp"
+#include "buffer_rules.hpp"
 #include "f32_rules.hpp"
 #include "reuse_rules.hpp"
 
@@ -67,8 +68,33 @@ static int group_channels() {
     return 0;
 }
 
+// The 16-byte loads of a row's last pixels, with elements of eb bytes: what of them lies inside the buffer of their channel lies inside x, and
+// every pixel of the row inside the buffer.
+static int row_ends() {
+    for (int eb : {2, 4})
+        for (int n = 1; n <= 3; ++n)
+            for (int c = 1; c <= 4; ++c)
+                for (int h = 1; h <= 3; ++h)
+                    for (int w = eb == 2 ? 2 : 1; w <= 40; w += eb == 2 ? 2 : 1) {
+                        const int64_t plane = (int64_t)h * w * eb, img = plane * c, x_bytes = img * n;
+                        for (int ib = 0; ib < n; ++ib)
+                            for (int i = ib; i < n; ++i)
+                                for (int ch = 0; ch < c; ++ch)
+                                    for (int px = 0; px < w; px += 16 / eb) {
+                                        const uint32_t records = buffer_records_from(buffer_records(x_bytes - ib * img), (uint32_t)(ch * plane));
+                                        const int64_t off = (i - ib) * img + (int64_t)((h - 1) * w + px) * eb, base = ib * img + ch * plane;
+                                        for (int e = 0; e < 4; ++e) {
+                                            const bool in = off + 4 * e + 4 <= (int64_t)records;
+                                            if (in && base + off + 4 * e + 4 > x_bytes) return fail("a row's load ends behind x", c, w, off + 4 * e);
+                                            if (!in && px + 4 * e / eb < w) return fail("a pixel outside the buffer", c, w, off + 4 * e);
+                                        }
+                                    }
+                    }
+    return 0;
+}
+
 int main() {
-    if (block_pieces() || gather_rows() || group_channels()) return 1;
+    if (block_pieces() || gather_rows() || group_channels() || row_ends()) return 1;
     std::printf("ok\n");
     return 0;
 }
