@@ -67,14 +67,20 @@ inline int k5_pick_narrow(int rows32, int64_t cols, int units, double* us = null
     if (us) *us = 5.8 + 1.1 * 256.0 / 2350.0 * (double)best_t + 0.4 * (double)(rounds - 1);
     return best;
 }
-// The faster one's microseconds; `units` are the reduction units of sixteen channels, `narrow_units` those of eight.
-inline double k5_model_conv(int rows32, int64_t cols, int units, int narrow_units, bool* narrow = nullptr) {
+// The faster one's microseconds, or those of the kernel of the binary32 instruction where the other is not allowed; `units` are the
+// reduction units of sixteen channels, `narrow_units` those of eight.
+inline double k5_model_conv(int rows32, int64_t cols, int units, int narrow_units, bool parts_allowed, bool* narrow = nullptr) {
     double us = 0.0, narrow_us = 0.0;
     (void)k5_pick_conv(rows32, cols, units, &us);
     (void)k5_pick_narrow(rows32, cols, narrow_units, &narrow_us);
-    if (narrow) *narrow = narrow_us < us;
-    return narrow_us < us ? narrow_us : us;
+    const bool take = !parts_allowed || narrow_us < us;
+    if (narrow) *narrow = take;
+    return take ? narrow_us : us;
 }
+// Whether a layer's sums are as near in parts as on the binary32 instruction: they are from eight products on (k5_f32.hpp has the
+// errors); a window that overlaps the border has down to half its taps.  `fewest` is the kept taps of the filter that three quarters of the
+// filters with any have at least as many as.
+constexpr bool k5_parts_near(int64_t fewest, int ks) { return fewest >= (ks > 1 ? 16 : 8); }
 
 // The block-pruned product: wavefront tiles of 32 rows x 32 nt columns, wk wavefronts of a workgroup on one tile's reduction.
 struct K5Shape {

@@ -3,11 +3,15 @@
 //
 // Convolution (k5_conv_f32): the pruned weights are zero-filled to a dense matrix (a 32-filter tile uses every (channel, tap) pair at
 // the densities that pattern pruning leaves) and multiplied on the bfloat16 matrix instruction, which is sixteen times as fast as the
-// binary32 one (32 x 32 x 16 in 32 cycles).  Every value is the sum of three bfloat16 parts, x1 + x2 + x3, exactly; of the nine products
-// of parts the six down to 2^-16 are taken: what the other three leave out is a relative 2^-24.  x1 w1 has an accumulator of its own,
-// rounded once per sixteen products, the small ones another at a 256th of its size: against 64 bits the sums are nearer than those
-// of the binary32 instruction (relative error 1.06e-7 against 2.85e-7 over 2304 terms, 2.9e-8 against 5.4e-8 over 64; all six in
-// one accumulator would be 5.1e-7).  256 channels, 14x14, 3x3, batch 32: 73 us on the binary32 instruction, 41 now.
+// binary32 one (32 x 32 x 16 in 32 cycles).  Every value is the sum of three bfloat16 parts, x1 + x2 + x3, exactly, if its last bit is not
+// below bfloat16's smallest value, 2^-133: x is therefore scaled by 2^16 (sums from 2^112 on overflow and are summed again from the kernel lists), and layers
+// with a weight that is not the sum of its parts (one below 2^-109 may not be) run on the binary32 instruction.  Of the nine products
+// of parts the six down to 2^-16 are taken: what the other three leave out is at most a relative 2^-24.  x1 w1 has an accumulator of its own,
+// rounded once per sixteen products, the small ones another at a 256th of its size: against 64 bits sums of eight or more products are
+// as near as those of the binary32 instruction or nearer (relative error 1.06e-7 against 2.85e-7 over 2304 terms, 2.9e-8 against 5.4e-8
+// over 64, 4.2e-8 against 4.3e-8 over 8 with a bias; all six in one accumulator would be 5.1e-7 over 2304).  Below that they are not (4.0e-8
+// against 2.5e-8 for one product and a bias): such layers stay on the binary32 instruction (k5_parts_near).
+// 256 channels, 14x14, 3x3, batch 32: 73 us on the binary32 instruction, 41 now.
 //
 // Per lane and unit (one tap x sixteen channels) the operand of x is eight values of one output pixel: plain loads, a lane's offset
 // changing with the tap only; the channel is the scalar offset of a buffer load, and a tap that falls outside the image gives the lane
@@ -56,6 +60,7 @@ typedef __bf16 k5_b8 __attribute__((ext_vector_type(8)));
 typedef uint32_t k5_u4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) unsigned char* k5_lds_ptr;
 
+constexpr float kK5Scale = 65536.0f;               // of x ahead of its splitting
 constexpr int kK5Ahead = 3;                        // reduction units whose loads are in flight behind the one being multiplied
 constexpr uint32_t kK5Outside = 0x80000000u;      // a byte offset no buffer of these kernels reaches: the load returns 0
 
@@ -134,7 +139,7 @@ __device__ __forceinline__ void k5_for(F&& f) {
 }
 
 // Two binary32 values as three pairs of bfloat16 parts, each part the rounding of what the parts before it leave: together they are
-// the values themselves.  In five slices, to be issued between matrix instructions.
+// the values themselves.  In five slices, behind that of the scaling, to be issued between matrix instructions.
 template <int SLICE>
 __device__ __forceinline__ void k5_split_slice(float& a, float& b, uint32_t (&part)[3]) {
     if constexpr (SLICE % 2 == 0) {
@@ -243,7 +248,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     k5_f16 acc[MT], low[MT];                                    // the first reduction share starts from the bias
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        acc[mt] = k5_bias(a.bias + (ft * MT + mt) * 32 + half * 4, wk == 0);
+        acc[mt] = k5_bias(a.bias + (ft * MT + mt) * 32 + half * 4, wk == 0) * kK5Scale;
         low[mt] = k5_f16(0.0f);
     }
 
@@ -295,11 +300,11 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     k5_u4 xf[2][3];                                             // the parts of this unit's pixels and of the next one's
     float sa[4], sb[4];
     uint32_t part[4][3];
-    auto slice = [&](auto from_tag, auto to_tag, auto k_tag) __attribute__((always_inline)) {     // slice k % 5 of pair k / 5
-        constexpr int from = decltype(from_tag)::value, to = decltype(to_tag)::value, k = decltype(k_tag)::value, j = k / 5;
-        if constexpr (k % 5 == 0) sa[j] = xv[from][2 * j], sb[j] = xv[from][2 * j + 1];
-        k5_split_slice<k % 5>(sa[j], sb[j], part[j]);
-        if constexpr (k % 5 == 4) {
+    auto slice = [&](auto from_tag, auto to_tag, auto k_tag) __attribute__((always_inline)) {     // slice k % 6 of pair k / 6
+        constexpr int from = decltype(from_tag)::value, to = decltype(to_tag)::value, k = decltype(k_tag)::value, j = k / 6;
+        if constexpr (k % 6 == 0) sa[j] = xv[from][2 * j] * kK5Scale, sb[j] = xv[from][2 * j + 1] * kK5Scale;
+        else k5_split_slice<k % 6 - 1>(sa[j], sb[j], part[j]);
+        if constexpr (k % 6 == 5) {
 #pragma unroll
             for (int i = 0; i < 3; ++i) xf[to][i][j] = part[j][i];
         }
@@ -325,7 +330,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     fill_x(I2{});
     fill_w();
     fill_x(I3{});
-    k5_for<20>([&](auto k) __attribute__((always_inline)) { slice(I0{}, I0{}, k); });
+    k5_for<24>([&](auto k) __attribute__((always_inline)) { slice(I0{}, I0{}, k); });
     // At most YOUNGER of this wavefront's loads are on their way; past the barrier every wavefront's are there that it had waited for, and
     // the buffer of the unit before is free.
     auto arrive = [&](auto younger) __attribute__((always_inline)) {
@@ -372,8 +377,8 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
             k5_for<8>([&](auto j) __attribute__((always_inline)) {
                 if constexpr (loads && decltype(j)::value * (NM / 2) / 8 == m) load_x(u_tag, decltype(j)::value);
             });
-            k5_for<20>([&](auto k) __attribute__((always_inline)) {
-                if constexpr (more && decltype(k)::value * NM / 20 == m) slice(From{}, To{}, k);
+            k5_for<24>([&](auto k) __attribute__((always_inline)) {
+                if constexpr (more && decltype(k)::value * NM / 24 == m) slice(From{}, To{}, k);
             });
             if constexpr (more && m == NM / 2 - 1) {
                 arrive(std::integral_constant<int, younger>{});
@@ -417,6 +422,8 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
         float v[R];
         k5_reduce<WK>(acc[mt] + low[mt], red, wk, lane, v);
         if (k5_not_finite(v)) again |= 1u << mt;
+#pragma unroll
+        for (int i = 0; i < R; ++i) v[i] *= 1.0f / kK5Scale;
         k5_store<R>(a, v, (ft * MT + mt) * 32 + half * 4, wk * R, px.obase, lane);
     }
     k5_redo<R>(a, again, MT, ft * MT, j0 + col, wk * R, half, lane);

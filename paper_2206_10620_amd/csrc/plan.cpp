@@ -311,6 +311,31 @@ int64_t spatial_waves(int n, int h, int w, int lw, int r) {
 
 }  // namespace
 
+// A weight as the sum of its three bfloat16 parts, smallest first: the weight itself, if none of its bits lies below 2^-133.
+static float sum_of_parts(const uint16_t* lead, size_t stride) { return (bf16_to_f32(lead[2 * stride]) + bf16_to_f32(lead[stride])) + bf16_to_f32(lead[0]); }
+
+// Whether the dense product of a binary32 layer may run in parts: without loss.
+static bool parts_allowed(const HostPlan& hp) {
+    const std::vector<int32_t>& kcount = hp.canon.kcount;       // in descending order
+    const size_t any = (size_t)(std::find(kcount.begin(), kcount.end(), 0) - kcount.begin());
+    if (any && !k5_parts_near((int64_t)kcount[3 * (any - 1) / 4] * hp.taps, hp.ks)) return false;
+    for (float v : hp.canon.wpacked) {
+        uint32_t u;
+        std::memcpy(&u, &v, 4);
+        if (((u >> 23) & 255u) - 18u <= 253u - 18u) continue;   // from 2^-109 on, and below 2^127: 24 bits at or above 2^-132
+        uint16_t part[3];
+        split_bf16(v, part);
+        if (!(sum_of_parts(part, 1) == v)) return false;
+    }
+    return true;
+}
+
+// Modelled microseconds of the dense product at the batch size the plan is for; hp.fl.narrow is the kernel that takes them.
+static double model_dense32(HostPlan& hp) {
+    const int KK = hp.ks * hp.ks;
+    return k5_model_conv((hp.c_out + 31) / 32, (int64_t)hp.n_hint * hp.ho * hp.wo, KK * ((hp.c_in + 15) / 16), KK * ((hp.c_in + 7) / 8), parts_allowed(hp), &hp.fl.narrow);
+}
+
 // The binary32 3x3 layer runs on the small matrix instruction (hp.quads) or as a dense product.
 static void take_f32_3x3(HostPlan& hp) {
     hp.tiled = false;
@@ -387,7 +412,7 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
             const int64_t longest = hp.canon.kcount.empty() ? 0 : hp.canon.kcount[0];      // filters are in descending order of it
             const double lists_us = lists_model(hp.n_hint, hp.c_in, (int64_t)hp.h * hp.w, hp.c_out, (int64_t)hp.out_h * hp.out_w, hp.canon.k_kept, hp.taps, longest, hp.pool);
             // (the operands of the very largest layers would not fit a host's memory)
-            hp.dense32 = 1.05 * lists_us > k5_model_conv(rows32, (int64_t)hp.n_hint * hp.ho * hp.wo, units, KK * ((hp.c_in + 7) / 8)) && (int64_t)rows32 * units * 3072 < ((int64_t)1 << 33);
+            hp.dense32 = 1.05 * lists_us > model_dense32(hp) && (int64_t)rows32 * units * 3072 < ((int64_t)1 << 33);
         }
         hp.chosen.mfma_kind = hp.dense32 ? 5 : 6;
         if (hp.dense32) build_f32_layout(hp);
@@ -420,7 +445,7 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
             int wk = 0;
             const int64_t rows = (int64_t)hp.n_hint * hp.h;
             const double quads_us = k6_model(hp.ql.groups, (rows * mc + 63) / 64, hp.c_in, hp.ql.taps_used, &wk);
-            const double dense_us = k5_model_conv((hp.c_out + 31) / 32, rows * hp.w, 9 * ((hp.c_in + 15) / 16), 9 * ((hp.c_in + 7) / 8));
+            const double dense_us = model_dense32(hp);
             hp.quads = dense_us >= 10.0 && dense_us >= 0.9 * quads_us;
             other_us = hp.quads ? quads_us : dense_us;
         }
@@ -1097,7 +1122,7 @@ void each_quad_weight(const HostPlan& hp, F&& put) {
 void build_f32_layout(HostPlan& hp) {
     F32Layout& fl = hp.fl;
     const int KK = hp.ks * hp.ks;
-    (void)k5_model_conv((hp.c_out + 31) / 32, (int64_t)hp.n_hint * hp.ho * hp.wo, KK * ((hp.c_in + 15) / 16), KK * ((hp.c_in + 7) / 8), &fl.narrow);
+    (void)model_dense32(hp);
     fl.groups = fl.narrow ? (hp.c_in + 7) / 8 : (hp.c_in + 15) / 16;
     fl.units = KK * fl.groups;
     fl.tiles = (hp.c_out + 127) / 128 * 4;
@@ -1158,7 +1183,7 @@ static pp_status_t unpack_operands(const HostPlan& hp, int32_t* kidx, uint8_t* k
     } else {
         const std::vector<uint16_t>& wpk = hp.fl.wpk;
         each_f32_weight(hp, [&](size_t at, size_t to) {
-            w[to] = (bf16_to_f32(wpk[at + 1024]) + bf16_to_f32(wpk[at + 512])) + bf16_to_f32(wpk[at]);
+            w[to] = sum_of_parts(&wpk[at], 512);
             for (int i = 0; i < 3; ++i) kept += (wpk[at + 512 * i] & 0x7FFFu) != 0 ? 1 : 0;
         });
         for (uint16_t v : wpk) all += (v & 0x7FFFu) != 0 ? 1 : 0;

@@ -134,7 +134,8 @@ pp_status_t unpack_stream(const HostPlan& hp, int32_t* kidx, uint8_t* kpat, floa
 
 // binary16 conversion used when packing weights (round to nearest even).
 uint16_t f32_to_f16_rne(float v);
-// A binary32 value as the sum of three bfloat16 ones (round to nearest even, each what the ones before it leave).
+// A binary32 value as the sum of three bfloat16 ones (round to nearest even, each what the ones before it leave); bits below 2^-133 are
+// left out.
 void split_bf16(float v, uint16_t (&part)[3]);
 float bf16_to_f32(uint16_t b);
 float f16_to_f32(uint16_t b);

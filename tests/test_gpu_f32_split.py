@@ -1,12 +1,15 @@
 """The dense binary32 convolution as bfloat16 parts: every workgroup shape, with each remainder of its loop over four reduction
-units and shares shorter than that loop, partial filter and pixel tiles, 1x1 to 5x5, stride 1 and 2, against the oracle."""
+units and shares shorter than that loop, partial filter and pixel tiles, 1x1 to 5x5, stride 1 and 2, and inputs of
+every size, against the oracle."""
 import math
 
+import numpy as np
 import pytest
 
+import oracle
 import synth
 import paper_2206_10620_amd as pp
-from gpu_util import check_layer
+from gpu_util import check_layer, run_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +37,19 @@ def test_shapes_and_remainders(layer, shape, share):
     rep, _ = check_layer(lay, tuning=pp.Tuning(variant=2 if ks == 3 and stride == 1 else 1, mfma_kind=5), tol=tol, label=f"split{layer}")
     assert rep["chosen"]["mfma_kind"] == 5
     assert share * (shape[2] if shape else 8) >= units
+
+
+@pytest.mark.parametrize("layer", [(2, 64, 33, 33, 64, 3, 1), (32, 256, 77, 14, 57, 1, 1)], ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("scale", [0, 100, -100, -112, -126, -140, -145])
+def test_inputs_of_every_size(layer, scale):
+    # 64 bits say what a sum is; each of its K roundings in binary32 is 2^-24 of it or half the smallest subnormal
+    n, c_in, c_out, h, w, ks, stride = layer
+    lay = synth.random_pruned_layer_k("size", n, c_in, c_out, h, w, "f32", ks, synth.PSET8 if ks == 3 else np.array([1], np.uint16), 0.8, 0.3, seed=3, stride=stride)
+    lay.bias = None
+    x = np.ldexp(lay.make_input().astype(np.float64), scale).astype(np.float32)
+    y, chosen = run_layer(lay, x, tuning=pp.Tuning(variant=2 if ks == 3 else 1, mfma_kind=5), relu=False)
+    pts = np.stack([np.random.RandomState(1).randint(m, size=4096) for m in y.shape], axis=1).astype(np.int32)
+    conv_at = oracle.conv_at if ks == 3 else lambda x, w, p, b, r: oracle.conv_k_at(x, w, p, stride, b, r)
+    ref, _, sc = conv_at(x, oracle.layer_dense_weights(lay), pts, None, False)
+    err = np.abs(y[tuple(pts.T)].astype(np.float64) - ref)
+    assert chosen["mfma_kind"] == 5 and np.all(err <= 4 * math.sqrt(ks * ks * c_in) * (2.0 ** -24 * sc + 2.0 ** -150))

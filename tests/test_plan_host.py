@@ -130,6 +130,18 @@ def test_binary32_operands_round_trip(c_in, c_out, kind):
     assert np.array_equal(kidx, info["kidx"]) and np.array_equal(kpat, info["kpat"]) and np.array_equal(w, info["wpacked"])
 
 
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -100, 2.0 ** -112, 1e-34, 2.0 ** -126, 2.0 ** -140, 2.0 ** 124])
+def test_binary32_operands_keep_weights_of_every_size(scale):
+    # a batch for which the dense product in bfloat16 parts is the faster one, with weights that the parts hold and with some they do not
+    lay = synth.random_pruned_layer("p", 32, 64, 64, 14, 14, "f32", synth.PSET8, 0.5, 0.1, 5)
+    lay.weights = (lay.weights.astype(np.float64) * scale).astype(np.float32)
+    plan = pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(variant=2, mfma_kind=5))
+    info = plan.query()
+    st, _, _, w = pp.pp_conv_plan_unpack(plan.handle, info["k_kept"])
+    plan.close()
+    assert st == pp.PP_OK and np.array_equal(w, info["wpacked"])
+
+
 def test_error_paths():
     lay = synth.config1()
     H = pp.PP_FLAG_HOST_ONLY
