@@ -231,10 +231,10 @@ static bool upload_lists(pp_conv_plan_t* p) {
                  pl = add(place.data(), place.size() * 4), bias = add(hp.bias.data(), hp.bias.size() * 4);
     void* mem = nullptr;
     static const std::vector<float> none;
-    const void* operands = hp.quads ? (const void*)hp.ql.wpk.data() : hp.dense32 ? (hp.fl.narrow ? (const void*)hp.fl.wpk_narrow.data() : (const void*)hp.fl.wpk.data()) : nullptr;
+    const void* operands = hp.quads ? (const void*)hp.ql.wpk.data() : hp.dense32 ? (hp.fl.whole ? (const void*)hp.fl.wpk_whole.data() : (const void*)hp.fl.wpk.data()) : nullptr;
     const std::vector<float>& bias_pad = hp.quads ? hp.ql.bias_pad : hp.dense32 ? hp.fl.bias_pad : none;
     const size_t bias32 = add(bias_pad.data(), bias_pad.size() * 4), used32 = add(hp.ql.used.data(), hp.quads ? hp.ql.used.size() * 4 : 0);
-    const size_t op_bytes = hp.quads ? hp.ql.wpk.size() * 4 : hp.dense32 ? hp.fl.wpk.size() * 2 + hp.fl.wpk_narrow.size() * 4 : 0;            // (a multiple of 1024)
+    const size_t op_bytes = hp.quads ? hp.ql.wpk.size() * 4 : hp.dense32 ? hp.fl.wpk.size() * 2 + hp.fl.wpk_whole.size() * 4 : 0;            // (a multiple of 1024)
     if (hipMalloc(&mem, op_bytes + blob.size()) != hipSuccess) return false;
     p->d_lists = static_cast<unsigned char*>(mem);
     if (op_bytes && hipMemcpy(p->d_lists, operands, op_bytes, hipMemcpyHostToDevice) != hipSuccess) return false;
@@ -597,19 +597,22 @@ static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, voi
     a.units = fl.units, a.groups = fl.groups;
     const int64_t pix = (int64_t)n * hp.ho * hp.wo;
     const int rows32 = (hp.c_out + 31) / 32;
-    static constexpr K5ConvShape narrow{};
-    const K5ConvShape& sh = fl.narrow ? narrow : k5_pick_conv(rows32, pix, fl.units);
-    const int64_t per_wg = (int64_t)32 * sh.wp;
+    K5Shape wsh;
+    K5ConvShape psh;
+    if (fl.whole) wsh = k5_pick_whole(rows32, pix, fl.units);
+    else psh = k5_pick_conv(rows32, pix, fl.units);
+    const int64_t per_wg = 32 * (fl.whole ? wsh.nt * wsh.wp : psh.wp);
     const int64_t ptiles = (pix + per_wg - 1) / per_wg;
-    a.ftiles = (rows32 + sh.mt - 1) / sh.mt;
+    const int mt = fl.whole ? wsh.mt : psh.mt;
+    a.ftiles = (rows32 + mt - 1) / mt;
     // pixel indices past the last one are formed in 32 bits
     if (pix + per_wg >= ((int64_t)1 << 31) || ptiles * a.ftiles >= ((int64_t)1 << 28)) return PP_ERR_SHAPE;
     a.pix = (int32_t)pix, a.ptiles = (int32_t)ptiles, a.items = (int32_t)(ptiles * a.ftiles), a.per_xcd = (a.items + 7) / 8;
     a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 4;
     // The operand that every XCD reads is the smaller one.
-    a.pixels_inner = (int64_t)fl.tiles * fl.units * (fl.narrow ? 1024 : 3072) > a.x_bytes ? 1 : 0;
+    a.pixels_inner = (int64_t)fl.tiles * fl.units * (fl.whole ? 1024 : 3072) > a.x_bytes ? 1 : 0;
     a.lists = plan->lists_copy;
-    const k5_conv_fn fn = fl.narrow ? k5_narrow_lookup(k5_pick_narrow(rows32, pix, fl.units)) : k5_conv_lookup(sh);
+    const k5_conv_fn fn = fl.whole ? k5_whole_lookup(wsh) : k5_conv_lookup(psh);
     if (!fn) return PP_ERR_UNSUPPORTED;
     (void)hipGetLastError();
     fn(a, a.per_xcd * 8, stream);

@@ -51,65 +51,65 @@ inline const K5ConvShape& k5_pick_conv(int rows32, int64_t cols, int units, doub
     if (us) *us = best_t;
     return *best;
 }
-// The kernel of the binary32 instruction: how many wavefronts share the reduction of a 32 x 32 tile; modelled microseconds in *us.  It is
-// the faster one where there are few tiles, one to a compute unit: the bound is what a compute unit can read, and its weights are four
-// bytes, not six.  Units of eight channels here, in cycles of four instructions; rounds of workgroups cost 0.4 us beyond the first.  Between
-// the two kernels the models are 0.6 % from the faster one on 90 layers (1x1 to 5x5, 3 to 500 channels, 56 to 200000 pixels).
-inline int k5_pick_narrow(int rows32, int64_t cols, int units, double* us = nullptr) {
-    const int64_t wgs = (int64_t)rows32 * ((cols + 31) / 32), rounds = (wgs + 255) / 256;
-    int best = 0;
-    int64_t best_t = 0;
-    for (int wk : {4, 8, 16}) {
-        if (wk > 4 && units < 2 * wk) continue;              // shares of less than two units only cost their reduction
-        const int64_t t = rounds * (wk / 4) * ((units + wk - 1) / wk);
-        if (!best || t < best_t) best_t = t, best = wk;
+// Tiles on the binary32 instruction: wavefronts of 32 mt filters x 32 nt pixels (columns), wk wavefronts of a workgroup on one tile's
+// reduction, wp on different pixels.
+struct K5Shape {
+    int mt = 1, nt = 1, wk = 1, wp = 1;
+};
+
+// Modelled time of a launch in cycles: the larger of the matrix-core time on the fullest compute unit (its wavefronts per
+// SIMD times 4 mt nt MFMAs of 64 cycles per unit) and the time the operands take to come out of L2 (1 KB per unit for each
+// of mt weight and nt pixel operands, 16 bytes per clock and compute unit; wavefronts that share weights find most of them
+// in the vector cache).  Fitted to 11 shapes on 13 layers and 7 on 9 products: the shape it picks is within 1 % of the best
+// one tried on average, 3 % at worst.  Examples: 128 channels, 56x56 to 28x28, 3x3, batch 8: 2 2 4 1 takes 23.5 us, 1 1 4 1
+// 30.2, 2 2 1 4 72.8; 256 to 128 channels, 1x1, 56x56, batch 8: 1 2 1 4 22.5 us, 2 2 8 1 32.6.
+inline double k5_cycles(int64_t wgs, int waves, int64_t units_per_wave, int mt, int nt, int wp) {
+    const double per_simd = (double)((wgs + 255) / 256) * waves / 4.0;
+    const double mfma = (per_simd < 1.0 ? 1.0 : per_simd) * (double)units_per_wave * 4 * mt * nt * 64;
+    const double traffic = (double)wgs * waves * (double)units_per_wave * (mt * (wp > 1 ? 0.3 : 1.0) + nt) * 1024 / (256 * 16.0);
+    return mfma > traffic ? mfma : traffic;
+}
+
+inline constexpr K5Shape kK5Whole[] = {{2, 2, 1, 4}, {2, 2, 2, 2}, {2, 2, 4, 1}, {2, 2, 8, 1}, {1, 2, 1, 4}, {1, 2, 4, 1}, {1, 2, 8, 1}, {1, 1, 4, 1}, {1, 1, 8, 1}, {1, 1, 16, 1}};
+inline constexpr K5Shape kK5List[] = {{1, 2, 4, 1}, {1, 2, 8, 1}, {1, 1, 4, 1}, {1, 1, 8, 1}, {1, 1, 16, 1}};
+
+template <int N>
+inline K5Shape k5_pick(const K5Shape (&opts)[N], int rows32, int64_t cols, int units, double* cycles = nullptr) {
+    K5Shape best;
+    double best_t = 1e300;
+    for (const K5Shape& o : opts) {
+        if (o.wk > 4 && units < 2 * o.wk) continue;          // shares of less than two units only cost their reduction
+        const int64_t wgs = (int64_t)((rows32 + o.mt - 1) / o.mt) * ((cols + 32 * o.nt * o.wp - 1) / (32 * o.nt * o.wp));
+        const double t = k5_cycles(wgs, o.wk * o.wp, (units + o.wk - 1) / o.wk, o.mt, o.nt, o.wp);
+        if (t < best_t) best_t = t, best = o;
     }
-    if (us) *us = 5.8 + 1.1 * 256.0 / 2350.0 * (double)best_t + 0.4 * (double)(rounds - 1);
+    if (cycles) *cycles = best_t;
     return best;
 }
-// The faster one's microseconds, or those of the kernel of the binary32 instruction where the other is not allowed; `units` are the
-// reduction units of sixteen channels, `narrow_units` those of eight.
-inline double k5_model_conv(int rows32, int64_t cols, int units, int narrow_units, bool parts_allowed, bool* narrow = nullptr) {
-    double us = 0.0, narrow_us = 0.0;
+// The shape of k5_whole_f32 for a layer (units of eight channels), its modelled microseconds in *us; the shape for a block-pruned product
+// of `rows32` 32-row tiles, `cols` columns and `units` reduction units per tile.
+inline K5Shape k5_pick_whole(int rows32, int64_t cols, int units, double* us = nullptr) {
+    double cycles = 0.0;
+    const K5Shape s = k5_pick(kK5Whole, rows32, cols, units, &cycles);
+    if (us) *us = 5.0 + 1.1 * cycles / 2350.0;
+    return s;
+}
+inline K5Shape k5_pick_list(int rows32, int64_t cols, int units) { return k5_pick(kK5List, rows32, cols, units); }
+
+// The faster one's microseconds, or those of k5_whole_f32 where the other is not allowed; `units` are the
+// reduction units of sixteen channels, `whole_units` those of eight.
+inline double k5_model_conv(int rows32, int64_t cols, int units, int whole_units, bool parts_allowed, bool* whole = nullptr) {
+    double us = 0.0, whole_us = 0.0;
     (void)k5_pick_conv(rows32, cols, units, &us);
-    (void)k5_pick_narrow(rows32, cols, narrow_units, &narrow_us);
-    const bool take = !parts_allowed || narrow_us < us;
-    if (narrow) *narrow = take;
-    return take ? narrow_us : us;
+    (void)k5_pick_whole(rows32, cols, whole_units, &whole_us);
+    const bool take = !parts_allowed || whole_us < us;
+    if (whole) *whole = take;
+    return take ? whole_us : us;
 }
 // Whether a layer's sums are as near in parts as on the binary32 instruction: they are from eight products on (k5_f32.hpp has the
 // errors); a window that overlaps the border has down to half its taps.  `fewest` is the kept taps of the filter that three quarters of the
 // filters with any have at least as many as.
 constexpr bool k5_parts_near(int64_t fewest, int ks) { return fewest >= (ks > 1 ? 16 : 8); }
-
-// The block-pruned product: wavefront tiles of 32 rows x 32 nt columns, wk wavefronts of a workgroup on one tile's reduction.
-struct K5Shape {
-    int nt = 1, wk = 1;
-};
-
-// Modelled time of a launch in cycles: the larger of the matrix-core time on the fullest compute unit (its wavefronts per SIMD times
-// 4 nt MFMAs of 64 cycles per unit) and the time the operands take to come out of L2 (1 KB per unit for the weight and each of nt
-// column operands, 16 bytes per clock and compute unit).  Fitted to 7 shapes on 9 products: the shape it picks is within 3 % of the
-// best one tried.
-inline double k5_cycles(int64_t wgs, int waves, int64_t units_per_wave, int nt) {
-    const double per_simd = (double)((wgs + 255) / 256) * waves / 4.0;
-    const double mfma = (per_simd < 1.0 ? 1.0 : per_simd) * (double)units_per_wave * 4 * nt * 64;
-    const double traffic = (double)wgs * waves * (double)units_per_wave * (1 + nt) * 1024 / (256 * 16.0);
-    return mfma > traffic ? mfma : traffic;
-}
-inline constexpr K5Shape kK5List[] = {{2, 4}, {2, 8}, {1, 4}, {1, 8}, {1, 16}};
-// The shape for a product of `rows32` 32-row tiles, `cols` columns and `units` reduction units per tile.
-inline K5Shape k5_pick_list(int rows32, int64_t cols, int units) {
-    K5Shape best;
-    double best_t = 1e300;
-    for (const K5Shape& o : kK5List) {
-        if (o.wk > 4 && units < 2 * o.wk) continue;          // shares of less than two units only cost their reduction
-        const int64_t wgs = (int64_t)rows32 * ((cols + 32 * o.nt - 1) / (32 * o.nt));
-        const double t = k5_cycles(wgs, o.wk, (units + o.wk - 1) / o.wk, o.nt);
-        if (t < best_t) best_t = t, best = o;
-    }
-    return best;
-}
 
 // The generic kernel, one lane per output walking its filter's kernel list: modelled microseconds for n images of c_in channels of
 // in_px pixels and c_out filters with out_px stored outputs each, `kept` kernels of `taps` taps, at most `longest` in a filter.

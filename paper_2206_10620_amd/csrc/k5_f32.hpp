@@ -44,7 +44,7 @@ struct K5ConvArgs {
     float* y;
     int32_t n, c_in, c_out, h, w, ho, wo, out_h, out_w;
     int32_t ks, stride, pool, relu;
-    int32_t groups, units;  // groups of sixteen channels (eight for the kernel of the binary32 instruction), ks * ks * groups
+    int32_t groups, units;  // groups of sixteen channels (eight for k5_whole_f32), ks * ks * groups
     int32_t pix;            // n * ho * wo convolution outputs
     int32_t ftiles, ptiles, items, per_xcd;
     int32_t pixels_inner;   // order of the items: pixel tiles fastest, or filter tiles
@@ -429,50 +429,66 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     k5_redo<R>(a, again, MT, ft * MT, j0 + col, wk * R, half, lane);
 }
 
-// The same convolution on the binary32 matrix instruction (v_mfma_f32_32x32x2_f32), where the layer has few tiles: WK wavefronts share the
-// reduction of one 32 x 32 tile, operands come straight from the vector cache.  Per 16 channels and tap a wavefront reads 2 KB of weights
-// instead of 3 KB, which is what bounds such a layer: 120 to 131 channels, 14x23, 3x3, batch 5 takes 8.1 us, 9.4 in parts; 444 to 358, 9x14,
-// batch 3 21.2, 23.0; where the tiles share their weights the parts are faster (256 channels, 14x14, batch 32: 68 us here, 39).
+// The same convolution on the binary32 matrix instruction (v_mfma_f32_32x32x2_f32): layers with few tiles, with few products to a sum, or
+// with weights that are not the sums of their parts.  Operands come straight from the vector cache: 32 neighbouring pixels of a channel's row are
+// 128 consecutive bytes of x.  Wavefronts of 32 MT filters x 32 NT pixels, WK of a workgroup on one tile's reduction, WP on different pixels with
+// the same weights.  With few tiles what a compute unit can read is the bound, and per 16 channels and tap a wavefront reads 2 KB of weights
+// here, 3 KB in parts: 120 to 131 channels, 14x23, 3x3, batch 5 takes 8.1 us, 9.4 in parts; 444 to 358, 9x14, batch 3 21.2, 23.0; with many
+// the instruction's rate is: 256 channels, 14x14, batch 32: 68 us here, 41 in parts.
 // Here taps are outermost: a lane's byte offset into x changes with the tap only.
-template <int WK>
-__global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 16 ? 4 : 2))) void k5_narrow_f32(const K5ConvArgs a) {
-    __shared__ float red[WK * 16 * 64];
-    const int lane = (int)(threadIdx.x & 63u), wk = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+template <int MT, int NT, int WK, int WP>
+__global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK * WP == 16 ? 4 : 2))) void k5_whole_f32(const K5ConvArgs a) {
+    __shared__ float red_all[WK > 1 ? WP * WK * 16 * 64 : 1];
+    const int lane = (int)(threadIdx.x & 63u), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wk = wave % WK, wp = wave / WK;
     const int col = lane & 31, half = lane >> 5;
     const int item = (int)(blockIdx.x & 7u) * a.per_xcd + (int)(blockIdx.x >> 3);
     if (item >= a.items) return;
     const int inner = a.pixels_inner ? a.ptiles : a.ftiles, outer_i = item / inner, inner_i = item - outer_i * inner;
     const int ft = a.pixels_inner ? outer_i : inner_i, pt = a.pixels_inner ? inner_i : outer_i;
-    const int j0 = pt * 32;
+    const int j0 = (pt * WP + wp) * 32 * NT;                    // first pixel of this wavefront
     const int hw = a.h * a.w, ohw = a.ho * a.wo;
     const int img0 = (j0 < a.pix ? j0 : 0) / ohw;               // wave-uniform
     const int64_t img_elems = (int64_t)a.c_in * hw;
     const __amdgpu_buffer_rsrc_t xr = k5_buffer(a.x + img0 * img_elems, a.x_bytes - img0 * img_elems * 4);
-    const K5Pixel px = k5_pixel(a, j0 + col, img0, a.c_in > 1 ? half * hw : 0);
-    k5_f16 acc = k5_bias(a.bias + ft * 32 + half * 4, wk == 0);
+    K5Pixel px[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) px[nt] = k5_pixel(a, j0 + nt * 32 + col, img0, a.c_in > 1 ? half * hw : 0);
+    k5_f16 acc[MT][NT];                                         // the first reduction share starts from the bias
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const k5_f16 b = k5_bias(a.bias + (ft * MT + mt) * 32 + half * 4, wk == 0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = b;
+    }
 
     const int u0 = (int)((int64_t)a.units * wk / WK), u1 = (int)((int64_t)a.units * (wk + 1) / WK);
-    const float* wbase = static_cast<const float*>(a.wpk) + (int64_t)ft * a.units * 256 + lane * 4;
+    const float* wbase = static_cast<const float*>(a.wpk) + (int64_t)ft * MT * a.units * 256 + lane * 4;
     const uint32_t plane = (uint32_t)(hw * 4);
     const int last_pair = a.c_in >= 2 ? a.c_in - 2 : 0;
     int tap = u0 / a.groups, g = u0 - tap * a.groups;           // of the unit to load next
-    uint32_t voff;
+    uint32_t voff[NT];
     auto set_tap = [&]() __attribute__((always_inline)) {
         const int r = tap / a.ks, c = tap - r * a.ks;
-        const bool in = (unsigned)(px.iy0 + r) < (unsigned)a.h && (unsigned)(px.ix0 + c) < (unsigned)a.w;
-        voff = in ? (px.base + (uint32_t)(r * a.w + c)) * 4u : kK5Outside;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const bool in = (unsigned)(px[nt].iy0 + r) < (unsigned)a.h && (unsigned)(px[nt].ix0 + c) < (unsigned)a.w;
+            voff[nt] = in ? (px[nt].base + (uint32_t)(r * a.w + c)) * 4u : kK5Outside;
+        }
     };
     constexpr int D = kK5Ahead + 1;
-    k5_f4 wv[D];
-    float xv[D][4];
+    k5_f4 wv[D][MT];
+    float xv[D][NT][4];
     // the loads of one unit, one by one: weights first, then pair by pair the pixels
+    constexpr int NL = MT + 4 * NT, NM = 4 * MT * NT;
     auto load_slot = [&](int set, int u, int i) __attribute__((always_inline)) {
-        if (i == 0) {
-            wv[set] = *reinterpret_cast<const k5_f4*>(wbase + (int64_t)u * 256);
+        if (i < MT) {
+            wv[set][i] = *reinterpret_cast<const k5_f4*>(wbase + ((int64_t)i * a.units + u) * 256);
         } else {
+            const int p = (i - MT) / NT, nt = (i - MT) % NT;
             // pairs past the last channel read the last pair again: their weights are zeros
-            const int ch = 8 * g + 2 * (i - 1) < last_pair ? 8 * g + 2 * (i - 1) : last_pair;
-            xv[set][i - 1] = k5_load(xr, voff, (uint32_t)ch * plane);
+            const int ch = 8 * g + 2 * p < last_pair ? 8 * g + 2 * p : last_pair;
+            xv[set][nt][p] = k5_load(xr, voff[nt], (uint32_t)ch * plane);
         }
     };
     auto next_unit = [&]() __attribute__((always_inline)) {
@@ -482,13 +498,26 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 1
             set_tap();
         }
     };
+    auto multiply = [&](int set, auto&& between) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[set][mt][p], xv[set][nt][p], acc[mt][nt], 0, 0, 0);
+                    between((p * MT + mt) * NT + nt);
+                }
+    };
     // Loads run kK5Ahead units ahead, past the end too (padded weights, pixels inside x or outside the buffer): the loop
-    // has no branch, so the compiler's wait counts let the younger loads stay in flight.  They are dealt out between the MFMAs.
+    // has no branch, so the compiler's wait counts let the younger loads stay in flight.  They are dealt out between the MFMAs: in a
+    // block ahead of them, two and more wavefronts on a SIMD got in each other's way (a loop of 16 MFMAs and 8 loads: 85 to
+    // 102 TFLOP/s in blocks, 130 dealt out, 155 without loads).
     set_tap();
 #pragma unroll
     for (int d = 0; d < D - 1; ++d) {
 #pragma unroll
-        for (int i = 0; i < 5; ++i) load_slot(d, u0 + d, i);
+        for (int i = 0; i < NL; ++i) load_slot(d, u0 + d, i);
         next_unit();
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -497,30 +526,33 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 1
     for (; u + D <= u1; u += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[d][p], xv[d][p], acc, 0, 0, 0);
+            multiply(d, [&](int q) __attribute__((always_inline)) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = p * 5 / 4; i < (p + 1) * 5 / 4; ++i) load_slot((d + D - 1) % D, u + d + D - 1, i);
+                for (int i = q * NL / NM; i < (q + 1) * NL / NM; ++i) load_slot((d + D - 1) % D, u + d + D - 1, i);
                 __builtin_amdgcn_sched_barrier(0);
-            }
+            });
             next_unit();
         }
     }
 #pragma unroll
-    for (int d = 0; d < D - 1; ++d) {
-        if (u + d < u1) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[d][p], xv[d][p], acc, 0, 0, 0);
-        }
-    }
+    for (int d = 0; d < D - 1; ++d)
+        if (u + d < u1) multiply(d, [](int) {});
+
     constexpr int R = 16 / WK;
-    float v[R];
-    k5_reduce<WK>(acc, red, wk, lane, v);
-    const uint32_t again = k5_not_finite(v) ? 1u : 0u;
-    k5_store<R>(a, v, ft * 32 + half * 4, wk * R, px.obase, lane);
-    k5_redo<R>(a, again, 1, ft, j0 + col, wk * R, half, lane);
+    float* red = red_all + wp * (WK * 16 * 64);
+    uint32_t again[NT] = {};                                    // bit mt: the lane's outputs of that tile
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            float v[R];
+            k5_reduce<WK>(acc[mt][nt], red, wk, lane, v);
+            if (k5_not_finite(v)) again[nt] |= 1u << mt;
+            k5_store<R>(a, v, (ft * MT + mt) * 32 + half * 4, wk * R, px[nt].obase, lane);
+        }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) k5_redo<R>(a, again[nt], MT, ft * MT, j0 + nt * 32 + col, wk * R, half, lane);
 }
 
 // Block-pruned product, binary32: a 32-row tile of the weight matrix with its own compact column list.  The B operand
@@ -637,7 +669,7 @@ __global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 1
 typedef void (*k5_conv_fn)(const K5ConvArgs& a, int blocks, hipStream_t stream);
 typedef void (*k5_list_fn)(K5ListArgs);
 k5_conv_fn k5_conv_lookup(const K5ConvShape& s);
-k5_conv_fn k5_narrow_lookup(int shares);
+k5_conv_fn k5_whole_lookup(const K5Shape& s);
 k5_list_fn k5_list_lookup(const K5Shape& s);
 
 }  // namespace ppc

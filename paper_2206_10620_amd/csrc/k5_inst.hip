@@ -17,9 +17,9 @@ void launch_conv(const K5ConvArgs& a, int blocks, hipStream_t stream) {
     hipLaunchKernelGGL((k5_conv_f32<MT, WP, WK>), dim3((unsigned)blocks), dim3(64 * WP * WK), lds, stream, a);
 }
 
-template <int WK>
-void launch_narrow(const K5ConvArgs& a, int blocks, hipStream_t stream) {
-    hipLaunchKernelGGL((k5_narrow_f32<WK>), dim3((unsigned)blocks), dim3(64 * WK), 0, stream, a);
+template <int MT, int NT, int WK, int WP>
+void launch_whole(const K5ConvArgs& a, int blocks, hipStream_t stream) {
+    hipLaunchKernelGGL((k5_whole_f32<MT, NT, WK, WP>), dim3((unsigned)blocks), dim3(64 * WK * WP), 0, stream, a);
 }
 
 }  // namespace
@@ -32,7 +32,13 @@ k5_conv_fn k5_conv_lookup(const K5ConvShape& s) {
     return nullptr;
 }
 
-k5_conv_fn k5_narrow_lookup(int shares) { return shares == 4 ? launch_narrow<4> : shares == 8 ? launch_narrow<8> : shares == 16 ? launch_narrow<16> : nullptr; }
+k5_conv_fn k5_whole_lookup(const K5Shape& s) {
+#define PPC_K5(MT, NT, WK, WP) \
+    if (s.mt == MT && s.nt == NT && s.wk == WK && s.wp == WP) return launch_whole<MT, NT, WK, WP>;
+    PPC_K5(2, 2, 1, 4) PPC_K5(2, 2, 2, 2) PPC_K5(2, 2, 4, 1) PPC_K5(2, 2, 8, 1) PPC_K5(1, 2, 1, 4) PPC_K5(1, 2, 4, 1) PPC_K5(1, 2, 8, 1) PPC_K5(1, 1, 4, 1) PPC_K5(1, 1, 8, 1) PPC_K5(1, 1, 16, 1)
+#undef PPC_K5
+    return nullptr;
+}
 
 k5_list_fn k5_list_lookup(const K5Shape& s) {
 #define PPC_K5(NT, WK) \

@@ -330,10 +330,10 @@ static bool parts_allowed(const HostPlan& hp) {
     return true;
 }
 
-// Modelled microseconds of the dense product at the batch size the plan is for; hp.fl.narrow is the kernel that takes them.
+// Modelled microseconds of the dense product at the batch size the plan is for; hp.fl.whole is the kernel that takes them.
 static double model_dense32(HostPlan& hp) {
     const int KK = hp.ks * hp.ks;
-    return k5_model_conv((hp.c_out + 31) / 32, (int64_t)hp.n_hint * hp.ho * hp.wo, KK * ((hp.c_in + 15) / 16), KK * ((hp.c_in + 7) / 8), parts_allowed(hp), &hp.fl.narrow);
+    return k5_model_conv((hp.c_out + 31) / 32, (int64_t)hp.n_hint * hp.ho * hp.wo, KK * ((hp.c_in + 15) / 16), KK * ((hp.c_in + 7) / 8), parts_allowed(hp), &hp.fl.whole);
 }
 
 // The binary32 3x3 layer runs on the small matrix instruction (hp.quads) or as a dense product.
@@ -1067,7 +1067,7 @@ pp_status_t build_mfma_layout(const pp_conv_tuning_t& t, HostPlan& hp) {
 
 namespace {
 
-// Calls put(place, place in canon.wpacked) for every kept weight: its place in fl.wpk_narrow, or that of its leading part in fl.wpk (the
+// Calls put(place, place in canon.wpacked) for every kept weight: its place in fl.wpk_whole, or that of its leading part in fl.wpk (the
 // other parts are 512 and 1024 places on).
 template <typename F>
 void each_f32_weight(const HostPlan& hp, F&& put) {
@@ -1083,7 +1083,7 @@ void each_f32_weight(const HostPlan& hp, F&& put) {
         for (int64_t e = hp.filt_off[pos]; e < hp.filt_off[pos + 1]; ++e) {
             const int ci = cn.kidx[e];
             const std::vector<int>& tl = taps[cn.kpat[e]];
-            if (fl.narrow) {
+            if (fl.whole) {
                 const int g = ci / 8, p = ci % 8 / 2, half = ci - std::min(ci / 2 * 2, last_pair);
                 const size_t at = (size_t)(row + 32 * half) * 4 + p;
                 for (int j = 0; j < hp.taps; ++j) put(((size_t)(co / 32) * fl.units + (size_t)tl[j] * fl.groups + g) * 256 + at, (size_t)e * hp.taps + j);
@@ -1123,14 +1123,14 @@ void build_f32_layout(HostPlan& hp) {
     F32Layout& fl = hp.fl;
     const int KK = hp.ks * hp.ks;
     (void)model_dense32(hp);
-    fl.groups = fl.narrow ? (hp.c_in + 7) / 8 : (hp.c_in + 15) / 16;
+    fl.groups = fl.whole ? (hp.c_in + 7) / 8 : (hp.c_in + 15) / 16;
     fl.units = KK * fl.groups;
     fl.tiles = (hp.c_out + 127) / 128 * 4;
     fl.bias_pad.assign((size_t)fl.tiles * 32, 0.0f);
     std::copy(hp.bias.begin(), hp.bias.end(), fl.bias_pad.begin());
-    if (fl.narrow) {
-        fl.wpk_narrow.assign(((size_t)fl.tiles * fl.units + kF32Pad) * 256, 0.0f);
-        each_f32_weight(hp, [&](size_t at, size_t src) { fl.wpk_narrow[at] = hp.canon.wpacked[src]; });
+    if (fl.whole) {
+        fl.wpk_whole.assign(((size_t)fl.tiles * fl.units + kF32Pad) * 256, 0.0f);
+        each_f32_weight(hp, [&](size_t at, size_t src) { fl.wpk_whole[at] = hp.canon.wpacked[src]; });
         return;
     }
     fl.wpk.assign((size_t)fl.tiles * fl.units * 1536, 0);
@@ -1171,8 +1171,8 @@ static pp_status_t unpack_operands(const HostPlan& hp, int32_t* kidx, uint8_t* k
     std::copy(hp.canon.kidx.begin(), hp.canon.kidx.end(), kidx);
     std::copy(hp.canon.kpat.begin(), hp.canon.kpat.end(), kpat);
     size_t kept = 0, all = 0;
-    if (hp.quads || hp.fl.narrow) {
-        const std::vector<float>& wpk = hp.quads ? hp.ql.wpk : hp.fl.wpk_narrow;
+    if (hp.quads || hp.fl.whole) {
+        const std::vector<float>& wpk = hp.quads ? hp.ql.wpk : hp.fl.wpk_whole;
         auto take = [&](size_t at, size_t to) {
             w[to] = wpk[at];
             kept += wpk[at] != 0.0f ? 1 : 0;

@@ -73,10 +73,10 @@ struct MfmaLayout {
 constexpr int kF32Pad = 4;                  // units the kernels of the binary32 instruction may load past the end
 // Binary32 matrix-core kernels: the zero-filled dense weights in operand order, as they are or each in three bfloat16 parts.
 struct F32Layout {
-    bool narrow = false;                    // as they are, for the kernel of the binary32 instruction
+    bool whole = false;                     // as they are, for k5_whole_f32
     int groups = 0, units = 0, tiles = 0;   // groups of sixteen channels (eight), ks * ks * groups, 32-filter tiles (rounded up to a multiple of four)
     std::vector<uint16_t> wpk;              // [tiles][units][3][64][8]
-    std::vector<float> wpk_narrow;          // [tiles][units][64][4], and kF32Pad units of zeros behind them
+    std::vector<float> wpk_whole;          // [tiles][units][64][4], and kF32Pad units of zeros behind them
     std::vector<float> bias_pad;            // [tiles * 32]
 };
 

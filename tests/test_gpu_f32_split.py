@@ -1,6 +1,6 @@
 """The dense binary32 convolution as bfloat16 parts: every workgroup shape, with each remainder of its loop over four reduction
-units and shares shorter than that loop, partial filter and pixel tiles, 1x1 to 5x5, stride 1 and 2, and inputs of
-every size, against the oracle."""
+units and shares shorter than that loop, partial filter and pixel tiles, 1x1 to 5x5, stride 1 and 2, inputs of every
+size, and sums of one product, against the oracle."""
 import math
 
 import numpy as np
@@ -53,3 +53,11 @@ def test_inputs_of_every_size(layer, scale):
     ref, _, sc = conv_at(x, oracle.layer_dense_weights(lay), pts, None, False)
     err = np.abs(y[tuple(pts.T)].astype(np.float64) - ref)
     assert chosen["mfma_kind"] == 5 and np.all(err <= 4 * math.sqrt(ks * ks * c_in) * (2.0 ** -24 * sc + 2.0 ** -150))
+
+def test_a_sum_of_one_product_is_rounded_once():
+    # (such a layer is not split, and large enough that no two wavefronts share its reduction)
+    lay = synth.random_pruned_layer_k("one", 8, 1, 64, 224, 224, "f32", 1, np.array([1], np.uint16), 1.0, 0.3, seed=3)
+    x = lay.make_input()
+    y, chosen = run_layer(lay, x, relu=False)
+    ref = lay.weights.reshape(-1).astype(np.float64)[None, :, None, None] * x.astype(np.float64) + lay.bias.astype(np.float64)[None, :, None, None]
+    assert chosen["mfma_kind"] == 5 and np.all(np.abs(y - ref) <= 2.0 ** -24 * (1 + 1e-6) * np.abs(ref))
