@@ -83,7 +83,11 @@ typedef struct {
     int32_t chunk_c;        /* CC: input channels staged in LDS at a time (multiple of split_c) */
     int32_t staging;        /* how input tiles reach LDS: 1 through registers, one buffer; 2..8 direct global-to-LDS
                                loads into a ring of that many buffers of chunk_c channels (needs rows that start on
-                               4-byte boundaries: any fp32 width, even fp16 widths) */
+                               4-byte boundaries: any fp32 width, even fp16 widths); with mfma_kind 5 which of its two
+                               kernels (pp_conv_plan_kernel names the one that runs): 0 the faster one of those that keep the
+                               precision, 1 the one on the binary32 matrix instruction, whose operands go straight to registers,
+                               3 the one in bfloat16 parts, whose weights go through a ring of three buffers (refused if a
+                               weight is not the sum of its parts: some below 2^-109) */
     int32_t split_wg;       /* SW: workgroups that share one output tile, each on its own contiguous range of channel
                                chunks (1..64, at most the number of chunks); the last to finish adds the partial
                                sums up in range order, so results do not depend on who that is */
@@ -117,7 +121,10 @@ typedef struct {
                                128 * tiles_per_wave / tile_cols, wg_waves 8: two groups of four share a tile's
                                channels, an even number of sixteens); for binary32 storage: 4 the 3x3, stride 1 one on the small
                                matrix instruction, which skips taps that no filter of four uses, 5 the dense product
-                               (variant 2 or 1), 6 none: one lane per output (variant 1) */
+                               (variant 2 or 1), every operand as the sum of three bfloat16 values (six of the nine products,
+                               two binary32 accumulators; against 64 bits sums of eight and more products are as near as on the
+                               binary32 instruction or nearer, and others run there unless staging asks otherwise) or on the binary32
+                               instruction, 6 none: one lane per output (variant 1) */
     int32_t split_k;        /* direct-load matrix-core kernel only: workgroups that share one output tile, each on its
                                own run of channel chunks (0 auto, 1 none, 2, 4 or 8; must divide the number of
                                16-channel chunks and leave each share at least 2).  Layers with few tiles fill the
@@ -211,6 +218,10 @@ typedef struct {
                                 these as its tuning runs the same */
 } pp_plan_info_t;
 pp_status_t pp_conv_plan_query(const pp_conv_plan_t *plan, pp_plan_info_t *out);
+
+/* The name of the kernel that pp_conv_run launches for this plan (a constant; NULL for a NULL plan): k0_generic, k1_tiled, k2_mfma,
+ * k3_mfma, k4_block_gemm, k5_conv_f32 (in bfloat16 parts), k5_whole_f32 (on the binary32 instruction), k6_f32_3x3 or k7_rows. */
+const char *pp_conv_plan_kernel(const pp_conv_plan_t *plan);
 
 /* Decode the device-format weight stream of a tiled plan, or the packed operands of a binary32 3x3 plan, back into the
  * canonical order (a round-trip check of the packing).  kidx_out/kpat_out [k_kept], w_out [k_kept*4] (fp32; for

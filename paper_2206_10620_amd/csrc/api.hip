@@ -288,6 +288,8 @@ static pp_status_t plan_autotuned(const pp_conv_desc_t* desc, pp_conv_plan_t** o
         add([&](pp_conv_tuning_t& t) { t.variant = 1, t.mfma_kind = 6; });
         if (base.variant == 1) add([&](pp_conv_tuning_t& t) { t.mfma_kind = 5; });
     }
+    if (!f16 && !base.mfma_kind && !base.staging && base.variant < 3)
+        for (int staging : {1, 3}) add([&](pp_conv_tuning_t& t) { t.mfma_kind = 5, t.staging = staging; });
     if (base.variant == 0 || base.variant == 2) {
         if (base.variant == 0) add([&](pp_conv_tuning_t& t) { t.variant = 2; });
         if (!f16 && !base.mfma_kind)
@@ -934,6 +936,14 @@ pp_status_t pp_conv_plan_query(const pp_conv_plan_t* plan, pp_plan_info_t* out) 
     out->wpacked = hp.canon.wpacked.data();
     out->chosen = hp.chosen;
     return PP_OK;
+}
+
+const char* pp_conv_plan_kernel(const pp_conv_plan_t* plan) {
+    if (!plan) return nullptr;
+    const HostPlan& hp = plan->hp;
+    if (hp.mfma) return hp.chosen.mfma_kind == 3 ? "k4_block_gemm" : hp.ml.rows ? "k7_rows" : hp.ml.direct ? "k3_mfma" : "k2_mfma";
+    if (hp.dense32) return hp.fl.whole ? "k5_whole_f32" : "k5_conv_f32";
+    return hp.quads ? "k6_f32_3x3" : hp.tiled ? "k1_tiled" : "k0_generic";
 }
 
 pp_status_t pp_conv_plan_unpack(const pp_conv_plan_t* plan, int32_t* kidx_out, uint8_t* kpat_out, float* w_out) {

@@ -314,11 +314,8 @@ int64_t spatial_waves(int n, int h, int w, int lw, int r) {
 // A weight as the sum of its three bfloat16 parts, smallest first: the weight itself, if none of its bits lies below 2^-133.
 static float sum_of_parts(const uint16_t* lead, size_t stride) { return (bf16_to_f32(lead[2 * stride]) + bf16_to_f32(lead[stride])) + bf16_to_f32(lead[0]); }
 
-// Whether the dense product of a binary32 layer may run in parts: without loss.
-static bool parts_allowed(const HostPlan& hp) {
-    const std::vector<int32_t>& kcount = hp.canon.kcount;       // in descending order
-    const size_t any = (size_t)(std::find(kcount.begin(), kcount.end(), 0) - kcount.begin());
-    if (any && !k5_parts_near((int64_t)kcount[3 * (any - 1) / 4] * hp.taps, hp.ks)) return false;
+// Whether every weight of a binary32 layer is the sum of its parts.
+static bool parts_hold(const HostPlan& hp) {
     for (float v : hp.canon.wpacked) {
         uint32_t u;
         std::memcpy(&u, &v, 4);
@@ -330,10 +327,23 @@ static bool parts_allowed(const HostPlan& hp) {
     return true;
 }
 
+// Whether its dense product may run in parts without being asked to: without loss.
+static bool parts_allowed(const HostPlan& hp) {
+    const std::vector<int32_t>& kcount = hp.canon.kcount;       // in descending order
+    const size_t any = (size_t)(std::find(kcount.begin(), kcount.end(), 0) - kcount.begin());
+    return (!any || k5_parts_near((int64_t)kcount[3 * (any - 1) / 4] * hp.taps, hp.ks)) && parts_hold(hp);
+}
+
 // Modelled microseconds of the dense product at the batch size the plan is for; hp.fl.whole is the kernel that takes them.
 static double model_dense32(HostPlan& hp) {
-    const int KK = hp.ks * hp.ks;
-    return k5_model_conv((hp.c_out + 31) / 32, (int64_t)hp.n_hint * hp.ho * hp.wo, KK * ((hp.c_in + 15) / 16), KK * ((hp.c_in + 7) / 8), parts_allowed(hp), &hp.fl.whole);
+    const int KK = hp.ks * hp.ks, rows32 = (hp.c_out + 31) / 32, units = KK * ((hp.c_in + 15) / 16), whole_units = KK * ((hp.c_in + 7) / 8);
+    const int64_t cols = (int64_t)hp.n_hint * hp.ho * hp.wo;
+    if (!hp.fl.asked) return k5_model_conv(rows32, cols, units, whole_units, parts_allowed(hp), &hp.fl.whole);
+    hp.fl.whole = hp.fl.asked == 1;
+    double us = 0.0;
+    if (hp.fl.whole) (void)k5_pick_whole(rows32, cols, whole_units, &us);
+    else (void)k5_pick_conv(rows32, cols, units, &us);
+    return us;
 }
 
 // The binary32 3x3 layer runs on the small matrix instruction (hp.quads) or as a dense product.
@@ -343,6 +353,7 @@ static void take_f32_3x3(HostPlan& hp) {
     hp.chosen = pp_conv_tuning_t{};
     hp.chosen.variant = 2;
     hp.chosen.mfma_kind = hp.quads ? 4 : 5;
+    hp.chosen.staging = hp.quads ? 0 : hp.fl.asked;
     if (hp.quads) pack_quads(hp);
     else build_f32_layout(hp);
 }
@@ -388,6 +399,9 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
     const bool quads_asked = t.mfma_kind == 4, dense_asked = t.mfma_kind == 5, lists_asked = t.mfma_kind == 6;      // the binary32 kernels by name
     if ((quads_asked || dense_asked || lists_asked) && hp.dtype != PP_F32) return PP_ERR_UNSUPPORTED;
     if ((quads_asked && variant != 2) || (lists_asked && variant != 1)) return PP_ERR_UNSUPPORTED;
+    // which kernel of the dense product, by name (other values of the field are the tiled kernel's)
+    if (dense_asked && (t.staging == 1 || t.staging == 3)) hp.fl.asked = t.staging;
+    if (hp.fl.asked == 3 && !parts_hold(hp)) return PP_ERR_UNSUPPORTED;
     hp.tiled = variant == 2;
     hp.mfma = variant == 3;
     hp.chosen = pp_conv_tuning_t{};
@@ -415,6 +429,7 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
             hp.dense32 = 1.05 * lists_us > model_dense32(hp) && (int64_t)rows32 * units * 3072 < ((int64_t)1 << 33);
         }
         hp.chosen.mfma_kind = hp.dense32 ? 5 : 6;
+        if (hp.dense32) hp.chosen.staging = hp.fl.asked;
         if (hp.dense32) build_f32_layout(hp);
         return PP_OK;
     }

@@ -80,6 +80,8 @@ def lib() -> C.CDLL:
         L.pp_conv_destroy.restype = C.c_int
         L.pp_conv_plan_query.argtypes = [vp, C.POINTER(_Info)]
         L.pp_conv_plan_query.restype = C.c_int
+        L.pp_conv_plan_kernel.argtypes = [vp]
+        L.pp_conv_plan_kernel.restype = C.c_char_p
         L.pp_conv_plan_unpack.argtypes = [vp, vp, vp, vp]
         L.pp_conv_plan_unpack.restype = C.c_int
         L.pp_maxpool2x2_run.argtypes = [vp, vp, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, vp]
@@ -163,6 +165,10 @@ def pp_conv_plan_query(plan):
                     chosen=info.chosen.as_dict())
 
 
+def pp_conv_plan_kernel(plan) -> str:
+    return lib().pp_conv_plan_kernel(plan).decode()
+
+
 def pp_conv_plan_unpack(plan, k_kept: int):
     kidx = np.empty(k_kept, np.int32)
     kpat = np.empty(k_kept, np.uint8)
@@ -189,6 +195,11 @@ class Plan:
         if st != PP_OK:
             raise PPError(st, "pp_conv_plan_query")
         return info
+
+    @property
+    def kernel(self) -> str:
+        """The name of the kernel that run() launches."""
+        return pp_conv_plan_kernel(self.handle)
 
     def run(self, x, y=None, stream: Optional[int] = None, static: bool = False):
         """static=True goes through pp_conv_run_static (y must then be given: that entry point is for

@@ -130,6 +130,49 @@ def test_binary32_operands_round_trip(c_in, c_out, kind):
     assert np.array_equal(kidx, info["kidx"]) and np.array_equal(kpat, info["kpat"]) and np.array_equal(w, info["wpacked"])
 
 
+@pytest.mark.parametrize("shape,pool,taps", [((2, 64, 64, 28, 28), False, 4), ((32, 256, 256, 14, 14), False, 4), ((1, 1, 5, 6, 8), False, 1), ((8, 64, 256, 28, 28), True, 4)])
+def test_the_two_kernels_of_the_dense_product(shape, pool, taps):
+    """Each can be asked for, is reported, makes the same plan again and gives back its weights; a weight that is not the sum of its parts
+    rules out the one in parts."""
+    ks = 1 if taps == 1 else 3
+    lay = synth.random_pruned_layer_k("two", *shape, "f32", ks, synth.PSET8 if ks == 3 else np.array([1], np.uint16), 1.0 if taps == 1 else 0.5, 0.3, seed=5, pool=pool)
+    variant = 2 if ks == 3 and not pool else 1
+
+    def plan(staging, **over):
+        return pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(variant=variant, mfma_kind=5, staging=staging), **over)
+
+    for staging, name in ((1, "k5_whole_f32"), (3, "k5_conv_f32")):
+        p = plan(staging)
+        info = p.query()
+        assert p.kernel == name and info["chosen"] == pp.Tuning(variant=variant, mfma_kind=5, staging=staging).as_dict()
+        again = pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(**info["chosen"]))
+        assert again.kernel == name and again.query()["chosen"] == info["chosen"]
+        if variant == 2:                                       # (the operands of 3x3, stride 1 plans can be unpacked)
+            st, kidx, kpat, w = pp.pp_conv_plan_unpack(p.handle, info["k_kept"])
+            assert st == pp.PP_OK and np.array_equal(w, info["wpacked"]) and np.array_equal(kidx, info["kidx"])
+    p = plan(0)
+    assert p.kernel in ("k5_whole_f32", "k5_conv_f32") and p.query()["chosen"]["staging"] == 0
+    lay.weights = lay.weights.copy()
+    lay.weights.reshape(-1)[np.flatnonzero(np.repeat(lay.conn_mask != 0, taps))[0]] = np.float32(2.0 ** -120 * (1 + 2.0 ** -23))
+    assert plan(0).kernel == plan(1).kernel == "k5_whole_f32"
+    with pytest.raises(pp.PPError):
+        plan(3)
+
+
+def test_plans_name_their_kernel():
+    def kernel(lay, **tune):
+        return pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(**tune) if tune else None).kernel
+
+    f32 = synth.random_pruned_layer("name", 2, 64, 64, 28, 28, "f32", synth.PSET8, 0.5, 0.3, seed=5)
+    f16 = synth.random_pruned_layer("name", 2, 64, 64, 28, 28, "f16", synth.PSET8, 0.5, 0.3, seed=5)
+    one = synth.random_pruned_layer_k("name", 2, 64, 64, 28, 28, "f16", 1, np.array([1], np.uint16), 0.5, 0.3, seed=5)
+    assert [kernel(f32, variant=1, mfma_kind=6), kernel(f32, variant=2), kernel(f32, variant=2, mfma_kind=4)] == ["k0_generic", "k1_tiled", "k6_f32_3x3"]
+    assert [kernel(f16, variant=1), kernel(f16, variant=2), kernel(f16, variant=3, mfma_kind=1)] == ["k0_generic", "k1_tiled", "k2_mfma"]
+    assert [kernel(f16, variant=3, mfma_kind=2), kernel(f16, variant=3, mfma_kind=2, tile_cols=32)] == ["k3_mfma", "k7_rows"]
+    assert [kernel(one), kernel(one, variant=3, mfma_kind=1)] == ["k4_block_gemm", "k2_mfma"]
+    assert pp.lib().pp_conv_plan_kernel(None) is None
+
+
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -100, 2.0 ** -112, 1e-34, 2.0 ** -126, 2.0 ** -140, 2.0 ** 124])
 def test_binary32_operands_keep_weights_of_every_size(scale):
     # a batch for which the dense product in bfloat16 parts is the faster one, with weights that the parts hold and with some they do not
