@@ -338,7 +338,7 @@ static bool parts_allowed(const HostPlan& hp) {
 static double model_dense32(HostPlan& hp) {
     const int KK = hp.ks * hp.ks, rows32 = (hp.c_out + 31) / 32, units = KK * ((hp.c_in + 15) / 16), whole_units = KK * ((hp.c_in + 7) / 8);
     const int64_t cols = (int64_t)hp.n_hint * hp.ho * hp.wo;
-    if (!hp.fl.asked) return k5_model_conv(rows32, cols, units, whole_units, parts_allowed(hp), &hp.fl.whole);
+    if (!hp.fl.asked) return k5_model_conv(rows32, cols, units, whole_units, parts_allowed(hp), (double)cols * hp.c_out * 4e-6, &hp.fl.whole);
     hp.fl.whole = hp.fl.asked == 1;
     double us = 0.0;
     if (hp.fl.whole) (void)k5_pick_whole(rows32, cols, whole_units, &us);
