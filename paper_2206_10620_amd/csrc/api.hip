@@ -578,11 +578,11 @@ static pp_status_t check_run_args(const pp_conv_plan_t* plan, const void* x_dev,
 }
 
 // The binary32 matrix-core kernel: one launch, or more where the pixels of the batch do not fit 32-bit numbers with those of
-// a last tile behind them.
+// a last tile behind them, or their lanes a launch: it holds fewer than 2^32, at two to a pixel.
 static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t n, hipStream_t stream) {
     const HostPlan& hp = plan->hp;
     const F32Layout& fl = hp.fl;
-    if (n > 1 && (int64_t)n * hp.ho * hp.wo >= ((int64_t)1 << 31) - 512) {      // (one image of these plans is far smaller)
+    if (n > 1 && (int64_t)n * hp.ho * hp.wo >= ((int64_t)1 << 30)) {      // (one image of these plans is far smaller)
         const int32_t half = n / 2;
         const pp_status_t st = launch_f32(plan, x_dev, y_dev, half, stream);
         if (st != PP_OK) return st;

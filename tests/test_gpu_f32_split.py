@@ -5,6 +5,7 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import synth
@@ -61,3 +62,18 @@ def test_a_sum_of_one_product_is_rounded_once():
     y, chosen = run_layer(lay, x, relu=False)
     ref = lay.weights.reshape(-1).astype(np.float64)[None, :, None, None] * x.astype(np.float64) + lay.bias.astype(np.float64)[None, :, None, None]
     assert chosen["mfma_kind"] == 5 and np.all(np.abs(y - ref) <= 2.0 ** -24 * (1 + 1e-6) * np.abs(ref))
+
+
+@pytest.mark.parametrize("staging", [0, 3])
+def test_a_batch_just_below_two_to_the_31_pixels(staging):
+    # 128 pixels to 256 lanes: a single launch would be of 2^32 lanes
+    n, h, w = 7613, 51, 5531
+    st, handle = pp.pp_conv_plan(c_in=1, c_out=1, h=h, w=w, pattern_masks=np.array([1], np.uint16), pattern_id=np.zeros(1, np.int32), conn_mask=None, weights=np.array([2.0], np.float32),
+                                 bias=np.array([1.0], np.float32), kernel_size=1, n_hint=n, tuning=pp.Tuning(variant=1, mfma_kind=5, staging=staging))
+    assert st == pp.PP_OK
+    x = torch.full((n * h * w,), 3.0, device="cuda")
+    y = torch.full_like(x, float("nan"))
+    assert pp.pp_conv_run(handle, x.data_ptr(), y.data_ptr(), n, torch.cuda.current_stream().cuda_stream) == pp.PP_OK
+    for i in range(0, x.numel(), 1 << 28):
+        assert bool((y[i:i + (1 << 28)] == 7.0).all())
+    pp.pp_conv_destroy(handle)
