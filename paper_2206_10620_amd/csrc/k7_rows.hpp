@@ -414,7 +414,8 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
         const Tile t = decode(k);
         const int oimg0 = t.v0 / a.po, oy0 = t.v0 - oimg0 * a.po;
         const int plane_out = a.out_h * a.out_w;
-        const _Float16 floor16 = a.relu ? (_Float16)0.0f : -(_Float16)__builtin_inff();
+        // ReLU, or nothing: the larger of a value and a NaN is the value, and a NaN stays one
+        const _Float16 floor16 = a.relu ? (_Float16)0.0f : (_Float16)__builtin_nanf("");
         // An accumulator holds one filter per lane, two rows of 32 columns: lower and upper lanes four columns each in turn.  They
         // exchange halves, so that the lower lanes hold the first row, the upper ones the second; then four neighbouring lanes
         // exchange pieces of 16 bytes, so that they store 64 bytes of one filter at a time: a store of 64 lanes to 32 filters

@@ -1,6 +1,6 @@
 """The row-stacked matrix-core kernel of 3x3 binary16 layers: every shape, by request and replayed from what the plan reports, on images smaller than
 a tile, widths that end inside a group of eight pixels and inside a tile, channels that fill no chunk, one chunk, several tiles for
-each workgroup with a number of chunks that doesn't divide the kernel's unrolling, with and without a fused pool."""
+each workgroup with a number of chunks that doesn't divide the kernel's unrolling, with and without a fused pool; and a NaN."""
 import numpy as np
 import pytest
 
@@ -33,3 +33,19 @@ def test_shapes(layer, shape):
         assert (chosen["mfma_kind"], chosen["tiles_per_wave"], chosen["tile_cols"], chosen["tile_rows"], chosen["wg_waves"]) == (2, t, tc, 128 * t // tc, 4 * groups)
         same, again = run_layer(lay, lay.make_input(), tuning=pp.Tuning(**chosen), relu=pool)
         assert again == chosen and np.array_equal(y, same)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda v: "x".join(map(str, v)))
+def test_a_nan_without_relu_stays_one(shape):
+    # the general kernel, which ran such layers before, stores it too; the product is dense, so it reaches every filter of its window
+    t, tc, groups = shape
+    lay = synth.random_pruned_layer_k("nan", 2, 32, 70, 14, 14 if tc == 16 else 38, "f16", 3, synth.PSET8, 0.5, 0.1, seed=9)
+    x = lay.make_input()
+    clean, _ = run_layer(lay, x, tuning=pp.Tuning(variant=3, mfma_kind=2, tiles_per_wave=t, tile_cols=tc, wg_waves=4 * groups), relu=False)
+    x[1, 17, 6, 9] = np.nan
+    for kind in (dict(mfma_kind=1), dict(mfma_kind=2, tiles_per_wave=t, tile_cols=tc, wg_waves=4 * groups)):
+        y, _ = run_layer(lay, x, tuning=pp.Tuning(variant=3, **kind), relu=False)
+        nan = np.zeros(y.shape, bool)
+        nan[1, :, 5:8, 8:11] = True
+        assert np.array_equal(np.isnan(y), nan)
+    assert np.array_equal(y[~nan], clean[~nan])
