@@ -70,15 +70,15 @@ inline double k5_cycles(int64_t wgs, int waves, int64_t units_per_wave, int mt, 
     return mfma > traffic ? mfma : traffic;
 }
 
-inline constexpr K5Shape kK5Whole[] = {{2, 2, 1, 4}, {2, 2, 2, 2}, {2, 2, 4, 1}, {2, 2, 8, 1}, {1, 2, 1, 4}, {1, 2, 4, 1}, {1, 2, 8, 1}, {1, 1, 4, 1}, {1, 1, 8, 1}, {1, 1, 16, 1}};
-inline constexpr K5Shape kK5List[] = {{1, 2, 4, 1}, {1, 2, 8, 1}, {1, 1, 4, 1}, {1, 1, 8, 1}, {1, 1, 16, 1}};
+// (More than four shares are never modelled faster than four: the same matrix-core time and more to sum.)
+inline constexpr K5Shape kK5Whole[] = {{2, 2, 1, 4}, {2, 2, 2, 2}, {2, 2, 4, 1}, {1, 2, 1, 4}, {1, 2, 4, 1}, {1, 1, 4, 1}};
+inline constexpr K5Shape kK5List[] = {{1, 2, 4, 1}, {1, 1, 4, 1}};
 
 template <int N>
 inline K5Shape k5_pick(const K5Shape (&opts)[N], int rows32, int64_t cols, int units, double* cycles = nullptr) {
     K5Shape best;
     double best_t = 1e300;
     for (const K5Shape& o : opts) {
-        if (o.wk > 4 && units < 2 * o.wk) continue;          // shares of less than two units only cost their reduction
         const int64_t wgs = (int64_t)((rows32 + o.mt - 1) / o.mt) * ((cols + 32 * o.nt * o.wp - 1) / (32 * o.nt * o.wp));
         const double t = k5_cycles(wgs, o.wk * o.wp, (units + o.wk - 1) / o.wk, o.mt, o.nt, o.wp);
         if (t < best_t) best_t = t, best = o;

@@ -437,7 +437,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
 // the instruction's rate is: 256 channels, 14x14, batch 32: 68 us here, 41 in parts.
 // Here taps are outermost: a lane's byte offset into x changes with the tap only.
 template <int MT, int NT, int WK, int WP>
-__global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK * WP == 16 ? 4 : 2))) void k5_whole_f32(const K5ConvArgs a) {
+__global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(2))) void k5_whole_f32(const K5ConvArgs a) {
     __shared__ float red_all[WK > 1 ? WP * WK * 16 * 64 : 1];
     const int lane = (int)(threadIdx.x & 63u), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wk = wave % WK, wp = wave / WK;
@@ -572,7 +572,7 @@ struct K5ListArgs {
 };
 
 template <int NT, int WK>
-__global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(WK == 16 ? 4 : 2))) void k5_list_f32(const K5ListArgs a) {
+__global__ __launch_bounds__(64 * WK) __attribute__((amdgpu_waves_per_eu(2))) void k5_list_f32(const K5ListArgs a) {
     __shared__ float red[WK > 1 ? WK * 16 * 64 : 1];
     const int lane = (int)(threadIdx.x & 63u), wk = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int col = lane & 31, half = lane >> 5;

@@ -35,7 +35,7 @@ k5_conv_fn k5_conv_lookup(const K5ConvShape& s) {
 k5_conv_fn k5_whole_lookup(const K5Shape& s) {
 #define PPC_K5(MT, NT, WK, WP) \
     if (s.mt == MT && s.nt == NT && s.wk == WK && s.wp == WP) return launch_whole<MT, NT, WK, WP>;
-    PPC_K5(2, 2, 1, 4) PPC_K5(2, 2, 2, 2) PPC_K5(2, 2, 4, 1) PPC_K5(2, 2, 8, 1) PPC_K5(1, 2, 1, 4) PPC_K5(1, 2, 4, 1) PPC_K5(1, 2, 8, 1) PPC_K5(1, 1, 4, 1) PPC_K5(1, 1, 8, 1) PPC_K5(1, 1, 16, 1)
+    PPC_K5(2, 2, 1, 4) PPC_K5(2, 2, 2, 2) PPC_K5(2, 2, 4, 1) PPC_K5(1, 2, 1, 4) PPC_K5(1, 2, 4, 1) PPC_K5(1, 1, 4, 1)
 #undef PPC_K5
     return nullptr;
 }
@@ -43,7 +43,7 @@ k5_conv_fn k5_whole_lookup(const K5Shape& s) {
 k5_list_fn k5_list_lookup(const K5Shape& s) {
 #define PPC_K5(NT, WK) \
     if (s.nt == NT && s.wk == WK) return k5_list_f32<NT, WK>;
-    PPC_K5(2, 4) PPC_K5(2, 8) PPC_K5(1, 4) PPC_K5(1, 8) PPC_K5(1, 16)
+    PPC_K5(2, 4) PPC_K5(1, 4)
 #undef PPC_K5
     return nullptr;
 }
