@@ -1,6 +1,8 @@
-// The launch rules that keep the kernels' loads inside their buffers, walked exhaustively on the CPU.
+// The launch rules that keep the kernels' loads inside their buffers, walked exhaustively on the CPU; with arguments, the shapes they pick.
 #include <algorithm>
 #include <cstdio>
+#include <cstdlib>
+#include <iterator>
 #include <vector>
 
 #include "block_rules.hpp"
@@ -93,7 +95,22 @@ static int row_ends() {
     return 0;
 }
 
-int main() {
+// The shapes of the two kernels of the binary32 dense product for (32-filter tiles, pixels, units of sixteen channels, of eight), and how many
+// shapes each has.
+static int shapes(int argc, char** argv) {
+    for (int i = 1; i + 3 < argc; i += 4) {
+        const int rows32 = std::atoi(argv[i]), units = std::atoi(argv[i + 2]), whole_units = std::atoi(argv[i + 3]);
+        const int64_t cols = std::atoll(argv[i + 1]);
+        const K5ConvShape p = k5_pick_conv(rows32, cols, units);
+        const K5Shape w = k5_pick_whole(rows32, cols, whole_units);
+        std::printf("%d %d %d %d %d %d %d %d\n", p.mt, p.wp, p.wk, (units + p.wk - 1) / p.wk, w.mt, w.nt, w.wk, w.wp);
+    }
+    std::printf("%zu %zu\n", std::size(kK5Conv), std::size(kK5Whole));
+    return 0;
+}
+
+int main(int argc, char** argv) {
+    if (argc > 1) return shapes(argc, argv);
     if (block_pieces() || gather_rows() || group_channels() || row_ends()) return 1;
     std::printf("ok\n");
     return 0;

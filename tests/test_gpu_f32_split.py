@@ -1,6 +1,6 @@
-"""The dense binary32 convolution as bfloat16 parts: every workgroup shape, with each remainder of its loop over four reduction
-units and shares shorter than that loop, partial filter and pixel tiles, 1x1 to 5x5, stride 1 and 2, inputs of every
-size, and sums of one product, against the oracle."""
+"""The dense binary32 convolution in bfloat16 parts and on the binary32 instruction: every workgroup shape, in parts with each remainder of
+its loop over four reduction units and shares shorter than that loop, partial filter and pixel tiles, 1x1 to 5x5, stride 1 and 2, a fused
+pool; inputs of every size, and sums of one product, against the oracle."""
 import math
 
 import numpy as np
@@ -14,41 +14,55 @@ from gpu_util import check_layer, run_layer
 
 pytestmark = pytest.mark.gpu
 
-# n, c_in, c_out, h, w, ksize, stride; the workgroup (filter tiles, pixel tiles, reduction shares; none: too few tiles, the kernel of the
-# binary32 instruction); reduction units of a share
-LAYERS = [((1, 3, 3, 7, 7, 1, 2), None, 1), ((1, 64, 3, 5, 7, 1, 2), None, 1), ((1, 77, 3, 7, 5, 3, 2), None, 6), ((1, 17, 3, 5, 7, 5, 2), None, 7), ((4, 33, 3, 64, 33, 1, 1), None, 1),
-          ((32, 3, 3, 9, 57, 1, 1), (1, 4, 1), 1), ((32, 17, 3, 57, 9, 1, 1), (1, 4, 1), 2), ((32, 33, 3, 9, 57, 1, 1), (1, 4, 1), 3), ((16, 64, 3, 57, 28, 1, 1), (1, 4, 1), 4),
-          ((2, 64, 33, 33, 64, 3, 1), (2, 1, 4), 9), ((32, 48, 33, 15, 33, 3, 2), (2, 1, 4), 7), ((8, 77, 33, 9, 57, 3, 1), (2, 1, 4), 12),
-          ((1, 17, 300, 57, 57, 1, 1), (2, 2, 2), 1), ((32, 200, 33, 57, 7, 1, 1), (2, 2, 2), 7), ((32, 33, 33, 28, 14, 3, 1), (2, 2, 2), 14),
-          ((16, 17, 33, 28, 28, 5, 1), (2, 2, 4), 13), ((16, 33, 33, 28, 28, 5, 1), (2, 2, 4), 19), ((8, 3, 33, 64, 57, 1, 1), (2, 4, 1), 1), ((32, 100, 33, 14, 57, 1, 1), (2, 4, 1), 7),
-          ((16, 33, 77, 15, 57, 3, 1), (4, 2, 4), 7), ((16, 300, 77, 33, 28, 1, 1), (4, 2, 4), 5), ((32, 17, 200, 57, 33, 1, 2), (4, 4, 1), 2), ((16, 3, 77, 28, 57, 3, 1), (4, 4, 1), 9),
-          ((32, 256, 77, 14, 57, 1, 1), (4, 4, 2), 8), ((16, 33, 130, 57, 57, 3, 2), (4, 4, 2), 14)]
+# n, c_in, c_out, h, w, ksize, stride, pool; in parts the workgroup (filter tiles, pixel tiles, reduction shares) and the reduction units of a
+# share; on the binary32 instruction the workgroup (filter tiles, pixel tiles, shares, wavefronts on different pixels).  test_host_rules.py holds the
+# rules to these.
+LAYERS = [((1, 3, 3, 7, 7, 1, 2, False), (1, 4, 1), 1, (1, 1, 4, 1)), ((1, 64, 3, 5, 7, 1, 2, False), (2, 1, 4), 1, (1, 1, 4, 1)), ((1, 77, 3, 7, 5, 3, 2, False), (2, 1, 4), 12, (1, 1, 4, 1)),
+          ((1, 17, 3, 5, 7, 5, 2, False), (2, 1, 4), 13, (1, 1, 4, 1)), ((4, 33, 3, 64, 33, 1, 1, False), (1, 4, 1), 3, (1, 2, 4, 1)),
+          ((32, 3, 3, 9, 57, 1, 1, False), (1, 4, 1), 1, (1, 2, 1, 4)), ((32, 17, 3, 57, 9, 1, 1, False), (1, 4, 1), 2, (1, 2, 4, 1)), ((32, 33, 3, 9, 57, 1, 1, False), (1, 4, 1), 3, (1, 2, 4, 1)),
+          ((16, 64, 3, 57, 28, 1, 1, False), (1, 4, 1), 4, (1, 2, 4, 1)), ((16, 64, 3, 58, 28, 1, 1, True), (1, 4, 1), 4, (1, 2, 4, 1)),
+          ((2, 64, 33, 33, 64, 3, 1, False), (2, 1, 4), 9, (1, 2, 4, 1)), ((2, 64, 33, 34, 64, 3, 1, True), (2, 1, 4), 9, (1, 2, 4, 1)), ((32, 48, 33, 15, 33, 3, 2, False), (2, 1, 4), 7, (1, 2, 4, 1)),
+          ((8, 77, 33, 9, 57, 3, 1, False), (2, 1, 4), 12, (1, 2, 4, 1)),
+          ((1, 17, 300, 57, 57, 1, 1, False), (2, 2, 2), 1, (2, 2, 4, 1)), ((32, 200, 33, 57, 7, 1, 1, False), (2, 2, 2), 7, (2, 2, 4, 1)), ((32, 33, 33, 28, 14, 3, 1, False), (2, 2, 2), 14, (2, 2, 4, 1)),
+          ((32, 33, 33, 28, 14, 3, 1, True), (2, 2, 2), 14, (2, 2, 4, 1)),
+          ((16, 17, 33, 28, 28, 5, 1, False), (2, 2, 4), 13, (2, 2, 4, 1)), ((16, 33, 33, 28, 28, 5, 1, False), (2, 2, 4), 19, (2, 2, 4, 1)), ((16, 17, 33, 28, 28, 5, 1, True), (2, 2, 4), 13, (2, 2, 4, 1)),
+          ((8, 3, 33, 64, 57, 1, 1, False), (2, 4, 1), 1, (1, 2, 1, 4)), ((32, 100, 33, 14, 57, 1, 1, False), (2, 4, 1), 7, (1, 2, 1, 4)), ((32, 100, 33, 14, 58, 1, 1, True), (2, 4, 1), 7, (1, 2, 1, 4)),
+          ((16, 33, 77, 15, 57, 3, 1, False), (4, 2, 4), 7, (1, 2, 1, 4)), ((16, 300, 77, 33, 28, 1, 1, False), (4, 2, 4), 5, (2, 2, 2, 2)), ((16, 300, 77, 34, 28, 1, 1, True), (4, 2, 4), 5, (2, 2, 2, 2)),
+          ((32, 17, 200, 57, 33, 1, 2, False), (4, 4, 1), 2, (2, 2, 1, 4)), ((16, 3, 77, 28, 57, 3, 1, False), (4, 4, 1), 9, (2, 2, 1, 4)), ((16, 3, 77, 28, 58, 3, 1, True), (4, 4, 1), 9, (2, 2, 1, 4)),
+          ((32, 256, 77, 14, 57, 1, 1, False), (4, 4, 2), 8, (1, 2, 4, 1)), ((16, 33, 130, 57, 57, 3, 2, False), (4, 4, 2), 14, (2, 2, 4, 1)), ((32, 256, 77, 14, 58, 1, 1, True), (4, 4, 2), 8, (1, 2, 4, 1))]
 
 
-@pytest.mark.parametrize("layer,shape,share", LAYERS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
-def test_shapes_and_remainders(layer, shape, share):
-    n, c_in, c_out, h, w, ks, stride = layer
-    print(f"split layer {layer}", flush=True)
+def dense(layer, staging):
+    """The tuning that asks for a kernel of the dense product by name: 1 the binary32 instruction, 3 parts."""
+    return pp.Tuning(variant=2 if layer[5] == 3 and layer[6] == 1 and not layer[7] else 1, mfma_kind=5, staging=staging)
+
+
+@pytest.mark.parametrize("staging", [1, 3])
+@pytest.mark.parametrize("layer", [row[0] for row in LAYERS], ids=lambda v: "x".join(str(int(i)) for i in v))
+def test_shapes_and_remainders(layer, staging):
+    n, c_in, c_out, h, w, ks, stride, pool = layer
+    print(f"split layer {layer} {staging}", flush=True)
     lay = synth.random_pruned_layer_k("split", n, c_in, c_out, h, w, "f32", ks, synth.random_pattern_set(ks, 1 if ks == 1 else 4, 1 if ks == 1 else 6, seed=2), 0.8, 0.3,
-                                      seed=c_in + w, stride=stride)
-    # A sum is rounded once per 16 products, in binary32, in each of two accumulators and once per share: a walk of `units` steps of 2^-24 of
-    # the sum, of which four deviations cover 10^5 outputs, and the operands' three parts leave nothing out above 2^-24.
+                                      seed=c_in + w, stride=stride, pool=pool)
+    # A sum is rounded once per 16 products, in binary32, in each of two accumulators and once per share (on the binary32 instruction once per two
+    # products): a walk of `units` steps of 2^-24 of the sum, of which four deviations cover 10^5 outputs, and the operands' three parts leave
+    # nothing out above 2^-24.
     units = ks * ks * ((c_in + 15) // 16)
-    tol = 4 * 2.0 ** -24 * (2 * math.sqrt(units if shape else 8 * units) + 2)
-    rep, _ = check_layer(lay, tuning=pp.Tuning(variant=2 if ks == 3 and stride == 1 else 1, mfma_kind=5), tol=tol, label=f"split{layer}")
-    assert rep["chosen"]["mfma_kind"] == 5
-    assert share * (shape[2] if shape else 8) >= units
+    tol = 4 * 2.0 ** -24 * (2 * math.sqrt(units if staging == 3 else 8 * units) + 2)
+    rep, _ = check_layer(lay, tuning=dense(layer, staging), tol=tol, label=f"split{layer}")
+    assert rep["chosen"] == dense(layer, staging).as_dict()
 
 
 @pytest.mark.parametrize("layer", [(2, 64, 33, 33, 64, 3, 1), (32, 256, 77, 14, 57, 1, 1)], ids=lambda v: "x".join(map(str, v)))
 @pytest.mark.parametrize("scale", [0, 100, -100, -112, -126, -140, -145])
-def test_inputs_of_every_size(layer, scale):
+@pytest.mark.parametrize("staging", [1, 3])
+def test_inputs_of_every_size(layer, staging, scale):
     # 64 bits say what a sum is; each of its K roundings in binary32 is 2^-24 of it or half the smallest subnormal
     n, c_in, c_out, h, w, ks, stride = layer
     lay = synth.random_pruned_layer_k("size", n, c_in, c_out, h, w, "f32", ks, synth.PSET8 if ks == 3 else np.array([1], np.uint16), 0.8, 0.3, seed=3, stride=stride)
     lay.bias = None
     x = np.ldexp(lay.make_input().astype(np.float64), scale).astype(np.float32)
-    y, chosen = run_layer(lay, x, tuning=pp.Tuning(variant=2 if ks == 3 else 1, mfma_kind=5), relu=False)
+    y, chosen = run_layer(lay, x, tuning=pp.Tuning(variant=2 if ks == 3 else 1, mfma_kind=5, staging=staging), relu=False)
     pts = np.stack([np.random.RandomState(1).randint(m, size=4096) for m in y.shape], axis=1).astype(np.int32)
     conv_at = oracle.conv_at if ks == 3 else lambda x, w, p, b, r: oracle.conv_k_at(x, w, p, stride, b, r)
     ref, _, sc = conv_at(x, oracle.layer_dense_weights(lay), pts, None, False)
