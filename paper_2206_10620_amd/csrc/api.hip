@@ -612,7 +612,7 @@ static pp_status_t launch_f32(const pp_conv_plan_t* plan, const void* x_dev, voi
     a.pix = (int32_t)pix, a.ptiles = (int32_t)ptiles, a.items = (int32_t)(ptiles * a.ftiles), a.per_xcd = (a.items + 7) / 8;
     a.x_bytes = (int64_t)n * hp.c_in * hp.h * hp.w * 4;
     // The operand that every XCD reads is the smaller one.
-    a.pixels_inner = (int64_t)fl.tiles * fl.units * (fl.whole ? 1024 : 3072) > a.x_bytes ? 1 : 0;
+    a.pixels_inner = (int64_t)rows32 * fl.units * (fl.whole ? 1024 : 3072) > a.x_bytes ? 1 : 0;
     a.lists = plan->lists_copy;
     const k5_conv_fn fn = fl.whole ? k5_whole_lookup(wsh) : k5_conv_lookup(psh);
     if (!fn) return PP_ERR_UNSUPPORTED;
