@@ -34,6 +34,7 @@
 #include "buffer_rules.hpp"
 #include "f32_rules.hpp"
 #include "k0_generic.hpp"
+#include "lds_loads.hpp"
 
 namespace ppc {
 
@@ -69,19 +70,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t k5_buffer(const void* base, in
 }
 __device__ __forceinline__ float k5_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0));
-}
-
-// s_waitcnt's operand for vmcnt(n) alone
-constexpr int k5_vmcnt(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
-// a wave-uniform address, in scalar registers
-__device__ __forceinline__ const void* k5_uniform(const void* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return (const void*)(((uint64_t)hi << 32) | lo);
-}
-// 64 lanes x 16 bytes from base + off to the 1 KB of LDS at lds_dst (wave-uniform)
-__device__ __forceinline__ void k5_direct16(uint32_t off, const void* base, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_dst) : "memory", "m0");
 }
 
 // Register i of a 32 x 32 tile holds row 8 (i / 4) + 4 (lane / 32) + i % 4, column lane % 32: the bias in that order.
@@ -295,7 +283,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     constexpr int ND = (FR + WP - 1) / WP;                      // fragments that a wavefront brings
     auto load_w = [&](int i) __attribute__((always_inline)) {
         const int f = wp + WP * i;
-        if (FR % WP == 0 || f < FR) k5_direct16((uint32_t)lane * 16u, k5_uniform(wsrc + (int64_t)(f / 3) * a.units * 3072 + f % 3 * 1024), wdst + (uint32_t)f * 1024u);
+        if (FR % WP == 0 || f < FR) load_lds16((uint32_t)lane * 16u, uniform_address(wsrc + (int64_t)(f / 3) * a.units * 3072 + f % 3 * 1024), wdst + (uint32_t)f * 1024u);
     };
     k5_u4 xf[2][3];                                             // the parts of this unit's pixels and of the next one's
     float sa[4], sb[4];
@@ -335,7 +323,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
     // the buffer of the unit before is free.
     auto arrive = [&](auto younger) __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);                      // (a load moved behind the wait would be counted as one ahead of it)
-        __builtin_amdgcn_s_waitcnt(k5_vmcnt(decltype(younger)::value));
+        __builtin_amdgcn_s_waitcnt(wait_vmcnt(decltype(younger)::value));
         if constexpr (WP > 1) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
             __builtin_amdgcn_s_barrier();

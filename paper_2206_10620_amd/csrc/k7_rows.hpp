@@ -18,6 +18,7 @@
 
 #include "buffer_rules.hpp"
 #include "k7_geom.hpp"
+#include "lds_loads.hpp"
 #include "mfma_geom.hpp"
 
 namespace ppc {
@@ -54,24 +55,6 @@ constexpr uint32_t kK7Outside = 0x80000000u;      // a byte offset that no tile'
 // n / d for n < 65536 and 1 <= d < 65536 with magic = floor(2^32 / d) + 1 (0 stands for d = 1)
 __device__ __forceinline__ int k7_div(int n, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)n, magic) : n; }
 
-// 64 lanes x 16 bytes from base + off to the 1 KB of LDS at lds_dst (wave-uniform)
-__device__ __forceinline__ void k7_direct16(uint32_t off, const void* base, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_dst) : "memory", "m0");
-}
-
-// a wave-uniform address, in scalar registers
-__device__ __forceinline__ const void* k7_uniform(const void* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return (const void*)(((uint64_t)hi << 32) | lo);
-}
-// ... 4 bytes, to 256 bytes
-__device__ __forceinline__ void k7_direct4(uint32_t off, const void* base, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_dst) : "memory", "m0");
-}
-
-// s_waitcnt's operand for vmcnt(n) alone
-constexpr int k7_vmcnt(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 // A barrier for LDS traffic only: loads from memory stay in flight over it.
 __device__ __forceinline__ void k7_lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -283,14 +266,14 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
         if (wq == 0) {
             const Tile t = decode(wk);
             wptr = static_cast<const unsigned char*>(a.wpk) + ((int64_t)t.fbi * a.q + q0) * kK7WeightBytes;
-            if (kg == 0 && wave == 3) k7_direct4((uint32_t)lane * 4u, k7_uniform(a.bias + t.fbi * kMfmaFilters), lds0 + tail + (uint32_t)(wk & 3) * 256u);
+            if (kg == 0 && wave == 3) load_lds4((uint32_t)lane * 4u, uniform_address(a.bias + t.fbi * kMfmaFilters), lds0 + tail + (uint32_t)(wk & 3) * 256u);
         }
-        const unsigned char* base = static_cast<const unsigned char*>(k7_uniform(wptr));
+        const unsigned char* base = static_cast<const unsigned char*>(uniform_address(wptr));
         const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)group0 + 2 * G.xbuf + buf * kK7WeightBytes));
 #pragma unroll
         for (int i = 0; i < 5; ++i) {
             const int f = wave + 4 * i;
-            if (f < 18) k7_direct16(w_off, base + f * 1024, lds + (uint32_t)f * 1024u);
+            if (f < 18) load_lds16(w_off, base + f * 1024, lds + (uint32_t)f * 1024u);
         }
         wptr += kK7WeightBytes;
         if (++wq == QN) wq = 0, ++wk;
@@ -368,9 +351,9 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
                 if constexpr (WR == 2) read_w(u_tag, 8);
                 // All of this wavefront's reads of chunk s have left LDS.  Younger than its part of the weights of chunk s + 1 are the
                 // loads of one chunk of x, or with three buffers of two and, if there are any, the weights of chunk s + 2.
-                if constexpr (WB == 2) __builtin_amdgcn_s_waitcnt(k7_vmcnt(4 * SR));
-                else if (s + 2 < steps) __builtin_amdgcn_s_waitcnt(k7_vmcnt(8 * SR + 4));
-                else __builtin_amdgcn_s_waitcnt(k7_vmcnt(8 * SR));
+                if constexpr (WB == 2) __builtin_amdgcn_s_waitcnt(wait_vmcnt(4 * SR));
+                else if (s + 2 < steps) __builtin_amdgcn_s_waitcnt(wait_vmcnt(8 * SR + 4));
+                else __builtin_amdgcn_s_waitcnt(wait_vmcnt(8 * SR));
                 k7_lds_barrier();
             }
 #pragma unroll
