@@ -19,13 +19,15 @@ from .pp_conv import PPError, Tuning, plan_from_layer
 
 def default_candidates() -> List[dict]:
     """The automatic choice first; then, for the tiled vector kernel, rows per lane x (split inside, split
-    across workgroups); then the matrix-core kernels: three for binary32 layers (and the generic kernel), two and both wavefront tile counts for
-    binary16 ones."""
+    across workgroups); then the matrix-core kernels: three for binary32 layers (and the generic kernel), two, the shapes of the
+    row-stacked one and both wavefront tile counts for binary16 ones."""
     cands: List[dict] = [dict()]
     for r, (ks, sw) in itertools.product((1, 2), ((1, 1), (2, 1), (4, 1), (1, 2), (2, 2))):
         cands.append(dict(variant=2, filters_per_wave=4, rows_per_lane=r, split_c=ks, split_wg=sw))
     cands += [dict(mfma_kind=v) for v in (4, 5)] + [dict(mfma_kind=5, staging=v) for v in (1, 3)]
     cands += [dict(variant=1, mfma_kind=6), dict(variant=3, mfma_kind=1), dict(variant=3, mfma_kind=2)]
+    cands += [dict(variant=3, mfma_kind=2, tile_cols=c, wg_waves=w) for c in (16, 32, 64) for w in (4, 8)]
+    cands += [dict(variant=3, mfma_kind=2, tile_cols=64, tiles_per_wave=t) for t in (2, 4)]
     cands.append(dict(variant=3, tiles_per_wave=2))
     cands.append(dict(variant=3, tiles_per_wave=4))
     return cands

@@ -275,7 +275,7 @@ static pp_status_t plan_autotuned(const pp_conv_desc_t* desc, pp_conv_plan_t** o
     if (f16 && (base.variant == 0 || base.variant == 3)) {
         if (base.mfma_kind != 1) {
             for (int waves : {4, 8})
-                for (int cols : {0, 60, 28})
+                for (int cols : {0, 60, 28, 16, 32, 64})            // of the direct-load kernel, of the row-stacked one
                     if (!base.wg_waves && !base.tile_cols && !base.tile_rows)
                         add([&](pp_conv_tuning_t& t) { t.variant = 3, t.mfma_kind = 2, t.wg_waves = waves, t.tile_cols = cols; });
         }

@@ -6,7 +6,7 @@ import pytest
 
 import synth
 import paper_2206_10620_amd as pp
-from gpu_util import check_layer, run_layer
+from gpu_util import check_layer, run_layer, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,11 @@ def test_a_nan_without_relu_stays_one(shape):
         nan[1, :, 5:8, 8:11] = True
         assert np.array_equal(np.isnan(y), nan)
     assert np.array_equal(y[~nan], clean[~nan])
+
+
+def test_the_tuner_times_every_shape():
+    lay = synth.random_pruned_layer("tune", 4, 32, 64, 14, 14, "f16", synth.PSET8, 0.5, 0.3, seed=5)
+    x = lay.make_input()
+    _, report = pp.autotune(lay, to_device(x), to_device(np.zeros((4, 64, 14, 14), np.float16)), steps=2, rounds=1)
+    timed = {(c["tiles_per_wave"], c["tile_cols"], c["wg_waves"] // 4) for _, c, _ in report if c["mfma_kind"] == 2}
+    assert set(SHAPES) <= timed
