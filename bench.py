@@ -19,9 +19,10 @@ roofline : the dominant kernel of the timed workload against the roofline that b
              256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2 (packed) x 2.4 GHz = 157.3 TFLOP/s; the library is
              built with packed-FP32 formation disabled, so `peak_unpacked` = 78.6 TFLOP/s is the reachable
              ceiling.  `achieved` counts 2 flop per effective MAC.
-           * the binary32 matrix-core kernels are bound by the binary32 MFMA rate, 157.3 TFLOP/s: `achieved`
-             counts 2 flop per dense MAC for k5_conv_f32, which multiplies the zeros too, and per effective
-             MAC for k6_f32_3x3, which skips most of them.
+           * the binary32 matrix-core kernels are bound by an MFMA rate: k5_whole_f32 and k6_f32_3x3 by the binary32
+             one, 157.3 TFLOP/s, k5_conv_f32 by a sixth of the 16-bit one, 416.7, since it takes six bfloat16 products
+             for each of its own.  `achieved` counts 2 flop per dense MAC for the first and the last, which multiply
+             the zeros too, and per effective MAC for k6_f32_3x3, which skips most of them.
            * the binary16 matrix-core kernels (variant 3, zero-filled dense weights in binary16) do 9/(4*keep) times
              the multiply-accumulates at matrix-core rate.  By algorithmic counts the 1080p layer then
              needs 66 us of HBM time (531 MB at 8 TB/s) against 61 us of matrix-core time (153 GFLOP at
@@ -51,6 +52,7 @@ import numpy as np
 PEAK_FP32_TFLOPS = 157.3
 PEAK_FP32_UNPACKED_TFLOPS = 78.6
 PEAK_MFMA_F16_TFLOPS = 2500.0
+PEAK_PARTS_TFLOPS = PEAK_MFMA_F16_TFLOPS / 6
 PEAK_HBM_GBS = 8000.0
 
 # HBM-side traffic of one launch (bytes), from rocprofv3 FETCH_SIZE / WRITE_SIZE scaled by a copy
@@ -74,12 +76,20 @@ DEFAULT_WORKLOAD = "cfg5_enhance_1080p"
 
 
 def kernel_of(chosen):
-    """The kernel a plan with these reported parameters runs on."""
+    """The kernel a plan with these reported parameters runs on (of the two that may run under mfma_kind 5 the usual one: a plan's
+    own `kernel` says which it is)."""
     variant, kind = chosen["variant"], chosen["mfma_kind"]
     if variant == 3:
         rows = kind == 2 and chosen["tile_cols"] in (16, 32, 64)
         return "k7_rows" if rows else {2: "k3_mfma", 3: "k4 block product"}.get(kind, "k2_mfma")
-    return {4: "k6_f32_3x3", 5: "k5_conv_f32"}.get(kind, "k1_tiled" if variant == 2 else "k0_generic")
+    if kind == 5:
+        return "k5_whole_f32" if chosen["staging"] == 1 else "k5_conv_f32"
+    return "k6_f32_3x3" if kind == 4 else "k1_tiled" if variant == 2 else "k0_generic"
+
+
+def mfma_peak(kernel, dtype):
+    """Dense TFLOP/s of the matrix instruction that a kernel (or the layer's type) works with."""
+    return PEAK_MFMA_F16_TFLOPS if dtype == "f16" else PEAK_PARTS_TFLOPS if kernel == "k5_conv_f32" else PEAK_FP32_TFLOPS
 
 
 def traffic_of(workload, chosen, revision):
@@ -202,7 +212,7 @@ def time_layer(lay, steps, warmup, tuning=None, autotune=False):
     wall = time.perf_counter() - t0
     ev_ms = ev0.elapsed_time(ev1)
     res = dict(wall_ms_per_step=wall * 1e3 / steps, event_ms_per_step=ev_ms / steps, chosen=plan.query()["chosen"],
-               x=x, y=y)
+               kernel=plan.kernel, x=x, y=y)
     plan.close()
     return res
 
@@ -241,8 +251,8 @@ def summarize(lay, t):
                 eff_gmac_per_s=lay.eff_macs / sec / 1e9, alg_gb_per_s=lay.alg_bytes / sec / 1e9,
                 frac_fp32_valu=2 * lay.eff_macs / sec / 1e12 / PEAK_FP32_TFLOPS,
                 frac_fp32_valu_unpacked=2 * lay.eff_macs / sec / 1e12 / PEAK_FP32_UNPACKED_TFLOPS,
-                kernel=kernel_of(t["chosen"]),
-                frac_mfma_dense=2 * dense_macs(lay) / sec / 1e12 / (PEAK_MFMA_F16_TFLOPS if lay.dtype == "f16" else PEAK_FP32_TFLOPS),
+                kernel=t["kernel"],
+                frac_mfma_dense=2 * dense_macs(lay) / sec / 1e12 / mfma_peak(t["kernel"], lay.dtype),
                 frac_hbm=lay.alg_bytes / sec / 1e9 / PEAK_HBM_GBS, params=t["chosen"])
 
 
@@ -483,16 +493,17 @@ def time_vgg_stack(steps, warmup):
 def roofline_of(lay, t, traffic):
     """The roofline that binds the kernel the plan chose."""
     sec = t["event_ms_per_step"] * 1e-3
-    kernel = kernel_of(t["chosen"])
+    kernel = t["kernel"]
     if t["chosen"]["variant"] == 3:
         return {"bound": "hbm", "achieved": lay.alg_bytes / sec / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": lay.alg_bytes / sec / 1e9 / PEAK_HBM_GBS, "traffic": traffic,
                 "kernel": kernel, "kernel_us": t["event_ms_per_step"] * 1e3,
                 "frac_mfma": 2 * dense_macs(lay) / sec / 1e12 / PEAK_MFMA_F16_TFLOPS,
                 "peak_mfma_tflops": PEAK_MFMA_F16_TFLOPS}
-    ach = 2 * (dense_macs(lay) if kernel == "k5_conv_f32" else lay.eff_macs) / sec / 1e12
-    if kernel in ("k5_conv_f32", "k6_f32_3x3"):
-        return {"bound": "mfma", "achieved": ach, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_FP32_TFLOPS,
+    ach = 2 * (dense_macs(lay) if kernel in ("k5_conv_f32", "k5_whole_f32") else lay.eff_macs) / sec / 1e12
+    if kernel in ("k5_conv_f32", "k5_whole_f32", "k6_f32_3x3"):
+        peak = mfma_peak(kernel, lay.dtype)
+        return {"bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
                 "traffic": traffic, "kernel": kernel, "kernel_us": t["event_ms_per_step"] * 1e3}
     return {"bound": "alu", "achieved": ach, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_FP32_TFLOPS,
             "traffic": traffic, "kernel": kernel,

@@ -49,6 +49,22 @@ def test_binary32_traffic_belongs_to_the_kernel_that_runs():
     assert bench.traffic_of("cfg2_vgg_mid", named, pp.KERNEL_REVISION) is None
 
 
+def test_a_binary32_kernel_is_held_to_the_rate_of_its_own_instruction():
+    sys.path.insert(0, ROOT)
+    import bench
+    lay = bench.workloads()["cfg3_resnet_c256_n32"]()
+    chosen = pp.Tuning(variant=2, mfma_kind=5).as_dict()
+    for kernel, us, peak in (("k5_conv_f32", 41.0, 2500.0 / 6), ("k5_whole_f32", 80.0, 157.3), ("k6_f32_3x3", 68.0, 157.3)):
+        t = dict(event_ms_per_step=us * 1e-3, wall_ms_per_step=us * 1e-3, chosen=chosen, kernel=kernel)
+        roof, line = bench.roofline_of(lay, t, None), bench.summarize(lay, t)
+        assert roof["kernel"] == line["kernel"] == kernel and roof["peak"] == peak and 0.1 < roof["frac"] < 1
+        assert abs(line["frac_mfma_dense"] - 2 * bench.dense_macs(lay) / us / 1e6 / peak) < 1e-9
+    for staging, kernel in ((1, "k5_whole_f32"), (3, "k5_conv_f32")):
+        plan = pp.plan_from_layer(lay, host_only=True, tuning=pp.Tuning(variant=2, mfma_kind=5, staging=staging))
+        assert plan.kernel == bench.kernel_of(plan.query()["chosen"]) == kernel
+        plan.close()
+
+
 def test_the_json_line_is_last_and_short():
     """A reader that keeps the last 2000 characters of the output has to find the whole line."""
     import json
