@@ -59,17 +59,17 @@ PEAK_HBM_GBS = 8000.0
 # kernel of known size; see profiles/.  Valid only for the kernel revision it was measured on:
 # reported as null for any other.  Keyed by (workload, variant): k1_tiled for variant 2, k3_mfma for 3.
 MEASURED_TRAFFIC = {
-    ("cfg5_enhance_1080p", 3): ("lib-2026-12-04-a", 609.51e6),
-    ("cfg4_vgg_L6", 3): ("lib-2026-12-04-a", 38.16e6),
-    ("cfg4_vgg_L9", 3): ("lib-2026-12-04-a", 53.92e6),
-    ("cfg2_vgg_mid", 2): ("lib-2026-12-04-a", 20.43e6),
+    ("cfg5_enhance_1080p", 3): ("lib-2026-12-04-b", 606.52e6),
+    ("cfg4_vgg_L6", 3): ("lib-2026-12-04-b", 38.16e6),
+    ("cfg4_vgg_L9", 3): ("lib-2026-12-04-b", 53.92e6),
+    ("cfg2_vgg_mid", 2): ("lib-2026-12-04-b", 20.43e6),
 }
 
 # The same for the binary32 matrix-core kernels and the row-stacked one, keyed by (workload, kernel).
 MEASURED_TRAFFIC_F32 = {
-    ("cfg5_enhance_1080p", "k7_rows"): ("lib-2026-12-04-a", 646.33e6),
-    ("cfg4_vgg_L9", "k7_rows"): ("lib-2026-12-04-a", 53.79e6),
-    ("cfg2_vgg_mid", "k6_f32_3x3"): ("lib-2026-12-04-a", 44.64e6),
+    ("cfg5_enhance_1080p", "k7_rows"): ("lib-2026-12-04-b", 646.85e6),
+    ("cfg4_vgg_L9", "k7_rows"): ("lib-2026-12-04-b", 53.80e6),
+    ("cfg2_vgg_mid", "k6_f32_3x3"): ("lib-2026-12-04-b", 44.70e6),
 }
 
 DEFAULT_WORKLOAD = "cfg5_enhance_1080p"

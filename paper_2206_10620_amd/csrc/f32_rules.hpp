@@ -100,7 +100,7 @@ inline K5Shape k5_pick_list(int rows32, int64_t cols, int units) { return k5_pic
 // reduction units of sixteen channels, `whole_units` those of eight; out_mb is what the convolution stores, in MB, which costs k5_whole_f32 more.  On 420 layers (1x1 to 7x7, stride 1 and 2, 1 to 512 channels, 100 to
 // 8 million pixels) the choice is 1.8 % from the faster one on average, 1.39 times at worst; parts everywhere would be 11 %.  Parts lose
 // where there is little to share or few channels to a group of sixteen: 3 to 64 channels, 7x7, stride 2, 1080x1920: 267 us against
-// 232; 3 to 32, 5x5, 2160x3840: 1253 against 984; 256 channels, 14x14, batch 32: 41 against 80.
+// 232; 3 to 32, 5x5, 2160x3840: 1253 against 984; 256 channels, 14x14, batch 32: 42 against 75.
 inline double k5_model_conv(int rows32, int64_t cols, int units, int whole_units, bool parts_allowed, double out_mb, bool* whole = nullptr) {
     double us = 0.0, whole_us = 0.0;
     (void)k5_pick_conv(rows32, cols, units, &us);

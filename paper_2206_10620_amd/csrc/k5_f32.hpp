@@ -3,7 +3,7 @@
 //
 // Convolution (k5_conv_f32): the pruned weights are zero-filled to a dense matrix (a 32-filter tile uses every (channel, tap) pair at
 // the densities that pattern pruning leaves) and multiplied on the bfloat16 matrix instruction, which is sixteen times as fast as the
-// binary32 one (32 x 32 x 16 in 32 cycles).  Every value is the sum of three bfloat16 parts, x1 + x2 + x3, exactly, if its last bit is not
+// binary32 one (32 x 32 x 16 in 32 cycles; the method is that of Henry, Tang and Heinecke, arXiv:1904.06376).  Every value is the sum of three bfloat16 parts, x1 + x2 + x3, exactly, if its last bit is not
 // below bfloat16's smallest value, 2^-133: x is therefore scaled by 2^16 (sums from 2^112 on overflow and are summed again from the kernel lists), and layers
 // with a weight that is not the sum of its parts (one below 2^-109 may not be) run on the binary32 instruction.  Of the nine products
 // of parts the six down to 2^-16 are taken: what the other three leave out is at most a relative 2^-24.  x1 w1 has an accumulator of its own,
@@ -11,11 +11,11 @@
 // as near as those of the binary32 instruction or nearer (relative error 1.06e-7 against 2.85e-7 over 2304 terms, 2.9e-8 against 5.4e-8
 // over 64, 4.2e-8 against 4.3e-8 over 8 with a bias; all six in one accumulator would be 5.1e-7 over 2304).  Below that they are not (4.0e-8
 // against 2.5e-8 for one product and a bias): such layers stay on the binary32 instruction (k5_parts_near).
-// 256 channels, 14x14, 3x3, batch 32: 73 us on the binary32 instruction, 41 now.
+// 256 channels, 14x14, 3x3, batch 32: 75 us on the binary32 instruction, 42 in parts, where the scaling costs half a microsecond.
 //
 // Per lane and unit (one tap x sixteen channels) the operand of x is eight values of one output pixel: plain loads, a lane's offset
 // changing with the tap only; the channel is the scalar offset of a buffer load, and a tap that falls outside the image gives the lane
-// an offset beyond the buffer, which loads as zero.  The wavefront splits them (11 vector instructions for two values) and uses each
+// an offset beyond the buffer, which loads as zero.  The wavefront scales and splits them (13 vector instructions for two values) and uses each
 // part for 32 mt filters.  Weights come as ready operands, 3 KB per tile and unit, through a ring of three buffers in LDS by direct
 // loads, shared by the WP wavefronts of a reduction share; WK shares are summed through LDS in order.  What bounds it is that vector
 // and matrix instructions of a wavefront overlap only when dealt out among each other: with loads, splitting and weight reads in
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(WK
 // 128 consecutive bytes of x.  Wavefronts of 32 MT filters x 32 NT pixels, WK of a workgroup on one tile's reduction, WP on different pixels with
 // the same weights.  With few tiles what a compute unit can read is the bound, and per 16 channels and tap a wavefront reads 2 KB of weights
 // here, 3 KB in parts: 120 to 131 channels, 14x23, 3x3, batch 5 takes 8.1 us, 9.4 in parts; 444 to 358, 9x14, batch 3 21.2, 23.0; with many
-// the instruction's rate is: 256 channels, 14x14, batch 32: 68 us here, 41 in parts.
+// the instruction's rate is: 256 channels, 14x14, batch 32: 75 us here, 42 in parts.
 // Here taps are outermost: a lane's byte offset into x changes with the tap only.
 template <int MT, int NT, int WK, int WP>
 __global__ __launch_bounds__(64 * WK * WP) __attribute__((amdgpu_waves_per_eu(2))) void k5_whole_f32(const K5ConvArgs a) {

@@ -4,11 +4,12 @@
 // vector cache for each matrix instruction, so here a wavefront works on T rows of 32 columns and 64 filters: an x fragment (32 pixels
 // x 16 channels) of one staged row and column shift serves up to three rows of outputs, 3 (T + 2) fragments for 18 T instructions.
 // Pixels are the rows of the instruction's first operand: LDS holds a plane of words for each pair of channels, a pixel a word, so that a
-// shift by a column is an address and a fragment four reads without conflicts.  x comes by 16-byte loads of eight pixels of a
+// shift by a column is an address and a fragment four reads, without conflicts where planes are
+// multiples of 256 bytes (two rows: none counted on 512 channels, 28x28; four rows: 12 % of LDS cycles on the 1080p layer).  x comes by 16-byte loads of eight pixels of a
 // channel, D chunks ahead in registers, and is interleaved by pairs of channels on its way to LDS; weights lie in memory as in LDS and come by
 // direct loads, at half the vector cache's time for them.  One barrier a chunk, in its last but one step.
 // Measured (direct-load kernel before): 64 channels, 1080x1920: 203 -> 187 us; 3 to 64, 224x224, batch 8: 28 -> 17.7; 64 to 64 pooled:
-// 39 -> 31; 512 channels, 28x28, batch 8: 50 -> 36 (980 TFLOP/s); 67 to 140, 84x90, batch 2 (general kernel before): 26 -> 12.
+// 39 -> 31; 512 channels, 28x28, batch 8: 50 -> 36 (822 TFLOP/s); 67 to 140, 84x90, batch 2 (general kernel before): 26 -> 12.
 #pragma once
 
 #include <hip/hip_runtime.h>
