@@ -37,11 +37,15 @@ struct K5ConvShape {
 inline constexpr K5ConvShape kK5Conv[] = {{4, 4, 1, 1.97, 0.351, 0.521}, {4, 4, 2, 4.11, 0.046, 0.763}, {4, 2, 4, 3.70, 0.750, 0.844}, {2, 4, 1, 0.88, 0.393, 0.326},
                                           {2, 2, 2, 0.84, 0.386, 0.336}, {2, 2, 4, 2.46, 0.485, 0.583}, {2, 1, 4, 1.13, 0.300, 0.372}, {1, 4, 1, 0.45, 0.305, 0.231}};
 
+// How many 32-filter tiles of operands there are for the rows32 of a layer: a wavefront takes up to four, of layers that have no more up to two.
+constexpr int k5_padded_tiles(int rows32) { return rows32 <= 2 ? 2 : (rows32 + 3) / 4 * 4; }
+
 // The shape for a layer of `rows32` 32-filter tiles, `cols` pixels and `units` reduction units; its modelled microseconds in *us.
 inline const K5ConvShape& k5_pick_conv(int rows32, int64_t cols, int units, double* us = nullptr) {
     const K5ConvShape* best = nullptr;
     double best_t = 1e300;
     for (const K5ConvShape& o : kK5Conv) {
+        if (o.mt > k5_padded_tiles(rows32)) continue;        // (never modelled fastest there)
         const int64_t wgs = (int64_t)((rows32 + o.mt - 1) / o.mt) * ((cols + 32 * o.wp - 1) / (32 * o.wp));
         const double even = wgs < 256 ? 1.0 : (double)wgs / 256.0, load = 0.5 * (even + (double)((wgs + 255) / 256));
         const double unit = load * o.wg_unit > o.alone ? load * o.wg_unit : o.alone;

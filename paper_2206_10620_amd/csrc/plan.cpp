@@ -426,7 +426,7 @@ pp_status_t build_layouts(const pp_conv_desc_t& d, HostPlan& hp) {
             const int64_t longest = hp.canon.kcount.empty() ? 0 : hp.canon.kcount[0];      // filters are in descending order of it
             const double lists_us = lists_model(hp.n_hint, hp.c_in, (int64_t)hp.h * hp.w, hp.c_out, (int64_t)hp.out_h * hp.out_w, hp.canon.k_kept, hp.taps, longest, hp.pool);
             // (the operands of the very largest layers would not fit a host's memory)
-            hp.dense32 = 1.05 * lists_us > model_dense32(hp) && (int64_t)(rows32 + 3) / 4 * 4 * units * 3072 < ((int64_t)1 << 33);
+            hp.dense32 = 1.05 * lists_us > model_dense32(hp) && (int64_t)k5_padded_tiles(rows32) * units * 3072 < ((int64_t)1 << 33);
         }
         hp.chosen.mfma_kind = hp.dense32 ? 5 : 6;
         if (hp.dense32) hp.chosen.staging = hp.fl.asked;
@@ -1140,7 +1140,7 @@ void build_f32_layout(HostPlan& hp) {
     (void)model_dense32(hp);
     fl.groups = fl.whole ? (hp.c_in + 7) / 8 : (hp.c_in + 15) / 16;
     fl.units = KK * fl.groups;
-    fl.tiles = fl.whole ? (hp.c_out + 63) / 64 * 2 : (hp.c_out + 127) / 128 * 4;
+    fl.tiles = fl.whole ? (hp.c_out + 63) / 64 * 2 : k5_padded_tiles((hp.c_out + 31) / 32);
     fl.bias_pad.assign((size_t)fl.tiles * 32, 0.0f);
     std::copy(hp.bias.begin(), hp.bias.end(), fl.bias_pad.begin());
     if (fl.whole) {

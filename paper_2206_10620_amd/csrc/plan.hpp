@@ -75,7 +75,7 @@ constexpr int kF32Pad = 4;                  // units the kernels of the binary32
 struct F32Layout {
     bool whole = false;                     // as they are, for k5_whole_f32
     int asked = 0;                          // by the tuning: 1 for k5_whole_f32, 3 for k5_conv_f32
-    int groups = 0, units = 0, tiles = 0;   // groups of sixteen channels (eight), ks * ks * groups, 32-filter tiles (rounded up to what a wavefront takes: a multiple of four, of two)
+    int groups = 0, units = 0, tiles = 0;   // groups of sixteen channels (eight), ks * ks * groups, 32-filter tiles (rounded up to what a wavefront takes: k5_padded_tiles, or a multiple of two)
     std::vector<uint16_t> wpk;              // [tiles][units][3][64][8]
     std::vector<float> wpk_whole;          // [tiles][units][64][4], and kF32Pad units of zeros behind them
     std::vector<float> bias_pad;            // [tiles * 32]

@@ -95,6 +95,18 @@ static int row_ends() {
     return 0;
 }
 
+// Every 32-filter tile of weights that a wavefront of the binary32 dense product reads is there, whatever the batch.
+static int weight_tiles() {
+    for (int rows32 = 1; rows32 <= 40; ++rows32)
+        for (int units = 1; units < 700; units += 1 + units / 20)
+            for (int64_t cols = 1; cols < 40000000; cols = cols * 5 / 4 + 1) {
+                const int mt = k5_pick_conv(rows32, cols, units).mt, whole_mt = k5_pick_whole(rows32, cols, units).mt;
+                if ((rows32 + mt - 1) / mt * mt > k5_padded_tiles(rows32)) return fail("parts read a tile that is not there", rows32, units, mt);
+                if ((rows32 + whole_mt - 1) / whole_mt * whole_mt > (rows32 + 1) / 2 * 2) return fail("a tile that is not there", rows32, units, whole_mt);
+            }
+    return 0;
+}
+
 // The shapes of the two kernels of the binary32 dense product for (32-filter tiles, pixels, units of sixteen channels, of eight), and how many
 // shapes each has.
 static int shapes(int argc, char** argv) {
@@ -111,7 +123,7 @@ static int shapes(int argc, char** argv) {
 
 int main(int argc, char** argv) {
     if (argc > 1) return shapes(argc, argv);
-    if (block_pieces() || gather_rows() || group_channels() || row_ends()) return 1;
+    if (block_pieces() || gather_rows() || group_channels() || row_ends() || weight_tiles()) return 1;
     std::printf("ok\n");
     return 0;
 }
